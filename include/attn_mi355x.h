@@ -32,7 +32,8 @@
  *     d in {64, 128, 256} (block masks: block == 128; fused, nothing n x n leaves the chip) and
  *     for d in {512, 1024} without block mask and n <= 32768 (four-phase path through the
  *     workspace; d = 1024 is supported there only); every other supported case, ATTN_F32 always,
- *     runs fp32 FMA kernels.
+ *     runs in fp32 arithmetic: on the matrix cores for d <= 128 (ATTN_F32) or d <= 256 (ATTN_BF16) and
+ *     mask blocks that are a multiple of 16, on fp32 FMA kernels beyond.
  */
 #ifndef ATTN_MI355X_H
 #define ATTN_MI355X_H

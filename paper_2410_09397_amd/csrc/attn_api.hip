@@ -157,6 +157,9 @@ GenericParams generic_params(const attn_desc* d, const attn_blockmask* m) {
     p.d = d->d;
     p.scale = d->scale;
     p.causal = d->causal;
+    const double c = (double)d->scale * 1.4426950408889634;
+    p.c_hi = (float)c;
+    p.c_lo = (float)(c - (double)p.c_hi);
     p.block = 1;
     if (m) {
         p.csr_ptr = m->row_ptr;

@@ -254,6 +254,7 @@ static hipError_t run_generic(const GenericParams& p, bool backward, hipStream_t
 
 hipError_t launch_generic(bool is_bf16, bool backward, const GenericParams& p, hipStream_t stream) {
     if (p.d > kMaxD) return hipErrorInvalidValue;
+    if (exact_takes(is_bf16, p)) return launch_exact(is_bf16, backward, p, stream);
     return is_bf16 ? run_generic<__bf16>(p, backward, stream) : run_generic<float>(p, backward, stream);
 }
 

@@ -1,0 +1,56 @@
+"""The fp32-arithmetic matrix-core kernels (fp32 tensors, bf16 tensors of any head dimension, block masks of any edge
+that is a multiple of 16) at the edges of their tiles: head dimensions on both sides of every padded width, including
+those that are no multiple of 4 (fp32), and lengths around 16- and 32-row steps and the four waves' turns.
+
+Bounds: fp32 arithmetic on both storage types, so the error is that of sums of at most n + d terms in fp32, about
+sqrt(n + d) 2^-24 = 1.5e-6 of the largest value at the sizes here (fp32 storage: the regression bound of tests/helpers, 3e-6); with
+bf16 storage one rounding of the result comes on top: 8 significant bits, half a unit in the last place of a value just
+above a power of two, 2^-8 of it at most."""
+import numpy as np
+import pytest
+
+from paper_2410_09397_amd import synth
+from tests.helpers import LSE_TOL, check, oracle_reference, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+BF16_BOUND = 2.0 ** -8 + 1e-5
+
+
+def W(b, h, n, d, dtype, **kw):
+    name = "exact_%s_d%d_n%d%s%s" % (dtype, d, n, "_causal" if kw.get("causal") else "", "_b%d" % kw["block"] if kw.get("sparse") else "")
+    return synth.Workload(name, 500 + d, b, h, n, d, dtype, **kw)
+
+
+CASES = (
+    [W(1, 2, n, d, "f32", causal=c) for d, n in ((1, 17), (3, 64), (31, 65), (32, 16), (33, 127), (64, 33), (66, 129), (95, 200),
+                                                (96, 1), (97, 63), (126, 130), (128, 257)) for c in (False, True)]
+    + [W(1, 2, n, d, "bf16", causal=c) for d, n in ((8, 31), (32, 33), (40, 128), (56, 129), (72, 64), (96, 257), (120, 1),
+                                                   (136, 95), (192, 130), (200, 65), (248, 127)) for c in (False, True)]
+    + [W(1, 2, 300, 64, "bf16", sparse=True, block=64, extra_frac=0.4), W(2, 2, 500, 128, "bf16", sparse=True, block=16, extra_frac=0.2, causal=True),
+       W(1, 2, 333, 256, "bf16", sparse=True, block=48, extra_frac=0.3), W(1, 3, 777, 80, "f32", sparse=True, block=32, extra_frac=0.2, causal=True,
+                                                                        per_head_masks=True),
+       W(1, 1, 400, 128, "f32", sparse=True, block=80, extra_frac=0.5)])
+
+
+@pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)
+def test_fp32_arithmetic_at_tile_edges(w):
+    from paper_2410_09397_amd import attn
+    print("case", w, flush=True)
+    inp = synth.make_inputs(w)
+    ref = oracle_reference(w, inp)
+    tol = 3e-6 if w.dtype == "f32" else BF16_BOUND
+    Q, K, V, dO = (to_dev(inp[t], w.dtype) for t in ("Q", "K", "V", "dO"))
+    mask = attn.BlockMask(inp["keep"], w.block, w.n) if w.sparse else None
+    O, LSE = attn.attn_fwd(Q, K, V, w.scale, causal=w.causal, mask=mask)
+    check(w.name, "O", to_np(O), ref["O"], w.dtype, tol=tol)
+    assert np.abs(to_np(LSE) - ref["LSE"]).max() <= LSE_TOL["f32"] * max(1.0, np.abs(ref["LSE"]).max())
+    O_in, LSE_in = to_dev(ref["O_in"], w.dtype), to_dev(ref["LSE_in"], "f32")
+    if mask is not None:
+        grads = attn.attn_bwd_blocksparse(Q, K, V, O_in, dO, LSE_in, w.scale, mask, causal=w.causal)
+    else:
+        grads = attn.attn_bwd(Q, K, V, O_in, dO, LSE_in, w.scale, causal=w.causal)
+    for name, g, r in zip(("dQ", "dK", "dV"), grads, ref["iso"]):
+        if np.abs(r).max() > 0:  # a single row has dQ = dK = 0 up to rounding
+            den = max(np.abs(r).max(), 1e-3)
+            assert np.abs(to_np(g) - r).max() <= tol * den, (w.name, name, np.abs(to_np(g) - r).max() / den)
