@@ -238,6 +238,12 @@ __global__ void __launch_bounds__(kThreads) generic_dkdv_kernel(GenericParams p)
     }
 }
 
+void launch_generic_delta(bool is_bf16, const GenericParams& p, hipStream_t stream) {
+    const dim3 grid((unsigned)(((long)p.batch * p.heads * p.n + 3) / 4));
+    if (is_bf16) hipLaunchKernelGGL(generic_delta_kernel<__bf16>, grid, dim3(kThreads), 0, stream, p);
+    else hipLaunchKernelGGL(generic_delta_kernel<float>, grid, dim3(kThreads), 0, stream, p);
+}
+
 template <typename T>
 static hipError_t run_generic(const GenericParams& p, bool backward, hipStream_t stream) {
     const long rows = (long)p.batch * p.heads * p.n;
@@ -245,7 +251,7 @@ static hipError_t run_generic(const GenericParams& p, bool backward, hipStream_t
     if (!backward) {
         hipLaunchKernelGGL(generic_fwd_kernel<T>, grid, block, 0, stream, p);
     } else {
-        hipLaunchKernelGGL(generic_delta_kernel<T>, grid, block, 0, stream, p);
+        launch_generic_delta(sizeof(T) == 2, p, stream);
         hipLaunchKernelGGL(generic_dq_kernel<T>, grid, block, 0, stream, p);
         hipLaunchKernelGGL(generic_dkdv_kernel<T>, grid, block, 0, stream, p);
     }
@@ -254,7 +260,7 @@ static hipError_t run_generic(const GenericParams& p, bool backward, hipStream_t
 
 hipError_t launch_generic(bool is_bf16, bool backward, const GenericParams& p, hipStream_t stream) {
     if (p.d > kMaxD) return hipErrorInvalidValue;
-    if (exact_takes(is_bf16, p)) return launch_exact(is_bf16, backward, p, stream);
+    if (stream_takes(is_bf16, p)) return launch_stream(is_bf16, backward, p, stream);
     return is_bf16 ? run_generic<__bf16>(p, backward, stream) : run_generic<float>(p, backward, stream);
 }
 

@@ -1,0 +1,1056 @@
+// Attention for short sequences and for fp32 arithmetic on the matrix cores.
+//
+// A workgroup owns 16 XG rows (queries for O and dQ, keys for dK and dV).  Its four or eight waves take the 16- or 32-row
+// steps of the other sequence in turn, so that short sequences still fill the chip, and their partial results are
+// summed through LDS in a fixed order.  Each wave stages its own steps in LDS (global_load_lds, whole rows, swizzled) and
+// waits for its own copies only: there is no barrier before the final sum.  Both uses of a staged tensor, as rows in
+// the first products and as columns in the second, read the one copy.
+//
+// Kinds of arithmetic:
+//   kF32   fp32 tensors of any d <= 128: every product is v_mfma_f32_16x16x4_f32 (an fp32 multiply-add chain)
+//   kBf3   bf16 tensors of any d <= 256, nothing rounded below fp32 on the way: S = Q K^T and dP = dO V^T have bf16
+//          operands, whose products are exact in fp32 (v_mfma_f32_16x16x32_bf16); f and p stay fp32, each written as
+//          the sum of three bf16 numbers (8 significant bits each, together the 24 of an fp32 number), and the
+//          second products run once per part
+// Formulas: A, l, f, O, q, p of App. B.4 with the scale, mask and log-sum-exp readings.
+//
+// Forward and backward together, against the row-per-wave FMA kernels of attn_generic.hip (1 TFLOP/s: both operands of
+// every multiply-add come from memory): fp32 b1 h1 n256 d64 347 -> 24.5 us, b2 h6 n777 d80 causal 4250 -> 89 us;
+// bf16 b1 h8 n1500 d96 causal 11650 -> 62 us.  What bounds them now: the fp32 matrix rate (154 TFLOP/s), half of which the
+// backward reaches on the long blocks; for bf16 the vector instructions that split f and p (5.5 per value) and the
+// latency of a step; the shortest calls, launches.  Reading the row operands straight from global memory in MFMA order,
+// without LDS, costs one L1 access per lane (64 per KB instead of 16) and measured 135 and 90 us on the last two.
+#include "attn_common.hpp"
+#include "attn_internal.hpp"
+
+namespace attn {
+
+namespace {
+
+enum Kind { kF32 = 0, kBf3 = 3 };
+
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int KIND>
+struct Traits {  // bf16
+    typedef __bf16 T;
+    typedef bf16x8 Row;                            // one lane's share of a 64-byte piece of 16 rows
+    static constexpr int kChunk = 32, kG = 2;      // columns per piece; 16-row groups per step
+};
+template <>
+struct Traits<kF32> {
+    typedef float T;
+    typedef f32x4 Row;
+    static constexpr int kChunk = 16, kG = 1;
+};
+
+__device__ __forceinline__ f32x4 mma_rows(f32x4 a, f32x4 b, f32x4 c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+    return c;
+}
+__device__ __forceinline__ f32x4 mma_rows(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+    const unsigned long long a = reinterpret_cast<unsigned long long>(p);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    return reinterpret_cast<const char*>(((unsigned long long)hi << 32) | lo);
+}
+
+// ------------------------------------------------------------------------------ staged steps
+// Lane l of a wave: r16 = l % 16, h4 = l / 16.
+//
+// One tensor of one step in LDS: 16 kG rows of DP columns (P bytes), 16-byte chunks XOR-swizzled by row so that 8 lanes
+// that read one chunk column of 8 rows, and 16 lanes that read 2 chunks of 4 rows, hit every bank at most once.
+template <int P>
+__device__ __forceinline__ constexpr int stage_swz(int r) {
+    constexpr int g = P / 64;  // a row is g quarters of the 64 banks
+    if (g % 2 == 1) return (r >> 2) & 3;
+    if (g % 4 == 2) return (((r >> 1) & 1) << 1) | ((r >> 2) & 1);
+    return ((r & 3) << 2) | ((r >> 2) & 3);
+}
+
+// Copies one tensor's step into LDS, one instruction per KB: the lane at LDS position (row, chunk) fetches the chunk
+// that the swizzle puts there.  Rows at or past n repeat the last row; columns at or past d (only the last 32 of the
+// padded width can be) repeat columns of the same row: the zeros of the owned rows cancel them in the first products, and in
+// the second they only reach output columns that are not stored.  QUAD: rows are whole 16-byte pieces; else 4 bytes
+// at a time.
+template <int KIND, bool QUAD, int DP>
+struct StageLoader {
+    static constexpr int kEs = sizeof(typename Traits<KIND>::T), G = Traits<KIND>::kG;
+    static constexpr int P = DP * kEs, kGroupBytes = 16 * P, kBytes = kGroupBytes * G;
+    static constexpr int kPiece = QUAD ? 1024 : 256, kLane = QUAD ? 16 : 4;
+    static constexpr int kInst = kGroupBytes / kPiece;  // per 16-row group
+    static constexpr int kCopies = kInst * G;           // per step
+    unsigned voff[kInst];
+    static __device__ __forceinline__ void where(int u, int lane, int d, int& row, unsigned& col_bytes) {
+        const int b = u * kPiece + lane * kLane;  // byte position inside the group
+        row = b / P;
+        const int c = (((b % P) >> 4) ^ stage_swz<P>(row)) * 16 + (b & 15);
+        col_bytes = c < d * kEs ? c : 0;
+    }
+    __device__ __forceinline__ void init(int lane, unsigned ldb, int d) {
+#pragma unroll
+        for (int u = 0; u < kInst; ++u) {
+            int row;
+            unsigned cb;
+            where(u, lane, d, row, cb);
+            voff[u] = (unsigned)row * ldb + cb;
+        }
+    }
+    // start[g]: first row of group g (n: nothing there, the last row is repeated); lds: byte address of the stage
+    __device__ __forceinline__ void load(const char* base, const int (&start)[G], int n, unsigned ldb, int d, unsigned lds, int lane) const {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            // the counter of outstanding copies holds 63: whole rows in 16-byte pieces stay below it by the size of LDS
+            if constexpr (!QUAD) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(62 - kInst) : "memory");
+            const unsigned dst = lds + g * kGroupBytes;
+            if (start[g] + 16 <= n) {
+                const char* first = uniform_ptr(base + (size_t)start[g] * ldb);
+#pragma unroll
+                for (int u = 0; u < kInst; ++u) issue(dst + u * kPiece, voff[u], first);
+            } else {
+                const char* first = uniform_ptr(base);
+                int l = lane;
+                asm volatile("" : "+v"(l));  // positions are formed here, not kept in registers for this rare case
+#pragma unroll
+                for (int u = 0; u < kInst; ++u) {
+                    int row;
+                    unsigned cb;
+                    where(u, l, d, row, cb);
+                    issue(dst + u * kPiece, (unsigned)min(start[g] + row, n - 1) * ldb + cb, first);
+                }
+            }
+        }
+    }
+    static __device__ __forceinline__ void issue(unsigned lds_in, unsigned off, const char* first) {
+        const unsigned lds = __builtin_amdgcn_readfirstlane(lds_in);
+        if constexpr (QUAD)
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(first) : "memory", "m0");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds), "v"(off), "s"(first) : "memory", "m0");
+    }
+};
+
+// Waits until at most N of this wave's copies are outstanding (they complete in order; no other vector memory
+// instruction is in flight in the loops that use this).
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N < 63 ? N : 63) : "memory");
+}
+// This wave's LDS reads have returned: what they read may be overwritten.
+__device__ __forceinline__ void wait_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Reads of a staged step at byte `imm` of the wave's part of LDS.
+//   row      operand of the first products: lane <-> row r16 of group g, 16 bytes at 16 h4 of the 64-byte piece s
+//   block16  column operand of 16 output columns nb, bf16: transposing reads; element t <-> row 16 (t / 4) + 4 h4 + t % 4
+//   block4   fp32: columns 64 B + 4 r16 .. + 3 of row 4 h4 + i, i.e. four operands; used as A operand number b, output row m
+//            <-> column 64 B + 4 m + b
+//   block2   fp32, the last 32 columns of an odd width: columns 2 r16, 2 r16 + 1
+template <int KIND, int DP>
+struct StageReader {
+    static constexpr int P = DP * (int)sizeof(typename Traits<KIND>::T), kGroupBytes = 16 * P, kN4 = DP / 64;
+    typedef typename Traits<KIND>::Row Row;
+    int rb[4], cb[KIND == kF32 ? 4 : 8], c2[KIND == kF32 ? 4 : 1];
+    __device__ __forceinline__ void init(int lane, int wave_off) {
+        const int r16 = lane & 15, h4 = lane >> 4;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) rb[q] = wave_off + r16 * P + (((4 * q + h4) ^ stage_swz<P>(r16)) << 4);
+        if constexpr (KIND == kF32) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = 4 * h4 + i;
+                cb[i] = wave_off + row * P + ((r16 ^ stage_swz<P>(row)) << 4);
+                c2[i] = wave_off + row * P + 256 * kN4 + (((r16 >> 1) ^ stage_swz<P>(row)) << 4) + 8 * (r16 & 1);
+            }
+        } else {
+            const int row = 4 * h4 + (r16 >> 2);
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                cb[q] = wave_off + row * P + (((2 * q + ((r16 >> 1) & 1)) ^ stage_swz<P>(row)) << 4) + 8 * (r16 & 1);
+        }
+    }
+    __device__ __forceinline__ Row row(const char* smem, int imm, int g, int s) const {
+        return *reinterpret_cast<const Row*>(smem + rb[s & 3] + (imm + 256 * (s >> 2) + g * kGroupBytes));
+    }
+    __device__ __forceinline__ bf16x8 block16(const char* smem, int imm, int nb) const {
+        const char* a = smem + cb[nb & 7] + (imm + 256 * (nb >> 3));
+        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 ATTN_LDS*)a);
+        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 ATTN_LDS*)(a + kGroupBytes));
+        typedef short i16x8 __attribute__((ext_vector_type(8)));
+        const i16x8 r = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        return __builtin_bit_cast(bf16x8, r);
+    }
+    __device__ __forceinline__ f32x4 block4(const char* smem, int imm, int B, int i) const {
+        return *reinterpret_cast<const f32x4*>(smem + cb[i] + (imm + 256 * B));
+    }
+    __device__ __forceinline__ f32x2 block2(const char* smem, int imm, int i) const {
+        return *reinterpret_cast<const f32x2*>(smem + c2[i] + imm);
+    }
+};
+
+// An owned row (lane <-> row r16) straight from memory in MFMA order, zero at and past column d.  row: its first byte.
+template <int KIND, bool QUAD, int DP>
+__device__ __forceinline__ void load_owned(const char* row, int h4, int d, typename Traits<KIND>::Row (&out)[DP / Traits<KIND>::kChunk]) {
+    typedef typename Traits<KIND>::T T;
+    constexpr int kPer = 16 / sizeof(T);
+#pragma unroll
+    for (int s = 0; s < DP / Traits<KIND>::kChunk; ++s) {
+        const int col = Traits<KIND>::kChunk * s + kPer * h4;
+        if constexpr (KIND != kF32) {
+            const bf16x8 v = *reinterpret_cast<const bf16x8*>(row + (col < d ? 2 * col : 0));
+            const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+            out[s] = col < d ? v : zero;
+        } else if constexpr (QUAD) {
+            const f32x4 v = *reinterpret_cast<const f32x4_u*>(row + (col < d ? 4 * col : 0));
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            out[s] = col < d ? v : zero;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = *reinterpret_cast<const float*>(row + (col + e < d ? 4 * (col + e) : 0));
+                out[s][e] = col + e < d ? v : 0.f;
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------ second products
+// A 16 kG x 16 block of f or p (lane <-> owned row) as the B operand of the second products.
+template <int KIND>
+struct Weights {
+    bf16x8 part[KIND];  // kBf3: v = part[0] + part[1] + part[2], exactly
+    __device__ __forceinline__ void set(const f32x4 (&v)[2]) {
+        u32x4 w[KIND];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float a = v[j >> 1][2 * (j & 1)], b = v[j >> 1][2 * (j & 1) + 1];
+#pragma unroll
+            for (int k = 0; k < KIND; ++k) {
+                w[k][j] = pack_bf16(a, b);
+                a -= __builtin_bit_cast(float, w[k][j] << 16);
+                b -= __builtin_bit_cast(float, w[k][j] & 0xffff0000u);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < KIND; ++k) part[k] = __builtin_bit_cast(bf16x8, w[k]);
+    }
+};
+template <>
+struct Weights<kF32> {
+    f32x4 w;
+    __device__ __forceinline__ void set(const f32x4 (&v)[1]) { w = v[0]; }
+};
+
+// acc[x][nb] += columns^T weights[x]: every column operand read from LDS feeds XG products (per part)
+template <int KIND, int DP, int XG>
+__device__ __forceinline__ void accumulate(f32x4 (&acc)[XG][DP / 16], const StageReader<KIND, DP>& rd, const char* smem, int imm,
+                                           const Weights<KIND> (&w)[XG]) {
+    if constexpr (KIND != kF32) {
+#pragma unroll
+        for (int nb = 0; nb < DP / 16; ++nb) {
+            const bf16x8 a = rd.block16(smem, imm, nb);
+#pragma unroll
+            for (int k = KIND - 1; k >= 0; --k)
+#pragma unroll
+                for (int x = 0; x < XG; ++x) acc[x][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w[x].part[k], acc[x][nb], 0, 0, 0);
+        }
+    } else {
+#pragma unroll
+        for (int B = 0; B < DP / 64; ++B)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f32x4 a = rd.block4(smem, imm, B, i);
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int x = 0; x < XG; ++x)
+                        acc[x][4 * B + b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b], w[x].w[i], acc[x][4 * B + b], 0, 0, 0);
+            }
+        if constexpr (DP % 64 != 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f32x2 a = rd.block2(smem, imm, i);
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int x = 0; x < XG; ++x)
+                        acc[x][DP / 16 - 2 + b] =
+                            __builtin_amdgcn_mfma_f32_16x16x4f32(a[b], w[x].w[i], acc[x][DP / 16 - 2 + b], 0, 0, 0);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------ which steps
+// The 16-row groups of the other sequence that a workgroup visits: dense (group g starts at row 16 g) or the kept blocks
+// of a block list (edge a multiple of 16), trimmed at group granularity by the causal rule.
+struct Groups {
+    const int32_t* idx;
+    int first, per, block, count, n;
+    __device__ __forceinline__ int start(int g) const {  // n (nothing there) past the end
+        if (g >= count) return n;
+        const int f = first + g;
+        if (!idx) return 16 * f;
+        // through the constant address space: a scalar load (the lists are never written by these kernels)
+        typedef const int32_t __attribute__((address_space(4))) * const_i32_ptr;
+        return ((const_i32_ptr)(unsigned long long)idx)[__builtin_amdgcn_readfirstlane(f / per)] * block + (f % per) * 16;
+    }
+};
+// rows_after: the owned rows are keys and see queries at or after them; else queries that see keys up to them
+__device__ __forceinline__ Groups make_groups(const GenericParams& p, int bh, bool rows_after, int r0, int r_last) {
+    Groups g;
+    g.n = p.n;
+    g.block = p.block;
+    const int32_t* ptr = rows_after ? p.csc_ptr : p.csr_ptr;
+    if (!ptr) {
+        g.idx = nullptr;
+        g.per = 1;
+        const int all = (p.n + 15) / 16;
+        g.first = p.causal && rows_after ? r0 / 16 : 0;
+        g.count = (p.causal && !rows_after ? min(all, r_last / 16 + 1) : all) - g.first;
+        return g;
+    }
+    ptr += (long)bh * p.mask_stride;
+    g.idx = rows_after ? p.csc_idx : p.csr_idx;
+    g.per = p.block / 16;
+    int e0 = ptr[r0 / p.block], e1 = ptr[r0 / p.block + 1];
+    int skip = 0;
+    if (p.causal) {
+        if (rows_after) {
+            while (e0 < e1 && (g.idx[e0] + 1) * p.block <= r0) ++e0;
+            if (e0 < e1 && g.idx[e0] * p.block <= r0) skip = (r0 - g.idx[e0] * p.block) / 16;
+        } else {
+            while (e0 < e1 && g.idx[e1 - 1] * p.block > r_last) --e1;
+        }
+    }
+    g.first = e0 * g.per + skip;
+    g.count = (e1 - e0) * g.per - skip;
+    return g;
+}
+
+// ------------------------------------------------------------------------------ sum over the waves
+// `factor(w, row)` scales the part of wave w.  red: [NW][16 XG][DP + 4] floats, over the stages.
+template <int KIND, bool QUAD, int DP, int XG, int NW, typename F>
+__device__ __forceinline__ void combine_store(const f32x4 (&acc)[XG][DP / 16], float* red, int w, int lane, char* out, unsigned ldb,
+                                              int row0, int n, int d, F factor) {
+    constexpr int kPitch = DP + 4;
+    typedef typename Traits<KIND>::T T;
+    const int r16 = lane & 15, h4 = lane >> 4;
+    __syncthreads();  // every wave is past its last step (or past the previous sum)
+#pragma unroll
+    for (int x = 0; x < XG; ++x) {
+        float* row = red + (w * 16 * XG + 16 * x + r16) * kPitch;
+        if constexpr (KIND != kF32) {
+#pragma unroll
+            for (int nb = 0; nb < DP / 16; ++nb) *reinterpret_cast<f32x4*>(row + 16 * nb + 4 * h4) = acc[x][nb];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                for (int B = 0; B < DP / 64; ++B)
+                    *reinterpret_cast<f32x4*>(row + 64 * B + 16 * h4 + 4 * i) =
+                        f32x4{acc[x][4 * B][i], acc[x][4 * B + 1][i], acc[x][4 * B + 2][i], acc[x][4 * B + 3][i]};
+                if constexpr (DP % 64 != 0)
+                    *reinterpret_cast<f32x2*>(row + 64 * (DP / 64) + 8 * h4 + 2 * i) = f32x2{acc[x][DP / 16 - 2][i], acc[x][DP / 16 - 1][i]};
+            }
+        }
+    }
+    __syncthreads();
+    constexpr int kQuads = DP / 4;
+    for (int t = w * 64 + lane; t < 16 * XG * kQuads; t += NW * 64) {
+        const int r = t / kQuads, c = (t % kQuads) * 4;
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(red + (k * 16 * XG + r) * kPitch + c);
+            const float f = factor(k, r);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] = fmaf(v[e], f, s[e]);
+        }
+        if (row0 + r >= n || c >= d) continue;
+        char* o = out + (size_t)(row0 + r) * ldb + c * sizeof(T);
+        if constexpr (KIND != kF32) {
+            *reinterpret_cast<u32x2*>(o) = u32x2{pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3])};
+        } else if constexpr (QUAD) {
+            *reinterpret_cast<f32x4_u*>(o) = s;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (c + e < d) reinterpret_cast<float*>(o)[e] = s[e];
+        }
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ const char* head_base(const void* ptr, long base) {
+    return reinterpret_cast<const char*>(static_cast<const T*>(ptr) + base);
+}
+
+// s * scale * log2(e) - m with the constant in two parts (its rounding alone would shift every f of a row by
+// |s| 2^-24 relative)
+__device__ __forceinline__ float scaled(float s, float hi, float lo, float m) { return fmaf(s, lo, fmaf(s, hi, -m)); }
+
+// log2 form of a row's LSE in two parts; a row with nothing visible (LSE = -inf) gives f = 0
+struct Lse2 {
+    float hi, lo;
+    __device__ __forceinline__ void set(float lse) {
+        constexpr float kLog2eLo = 1.92596299e-8f;  // log2(e) - (float)log2(e)
+        hi = lse * kLog2e;
+        lo = fmaf(lse, kLog2e, -hi) + lse * kLog2eLo;
+        if (lse == -__builtin_inff()) {
+            hi = __builtin_inff();
+            lo = 0.f;
+        }
+    }
+};
+
+__device__ __forceinline__ float dot_pair(f32x4 a, f32x4 b, float c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = fmaf(a[e], b[e], c);
+    return c;
+}
+__device__ __forceinline__ float dot_pair(bf16x8 a, bf16x8 b, float c) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) c = fmaf((float)a[e], (float)b[e], c);
+    return c;
+}
+
+// Owned 16-row groups per workgroup: bf16 operands of 16 x 32 feed one 16-cycle MFMA each, which is twice the LDS rate,
+// so there each feeds two; fp32 operands feed 32 cycles per 256 bytes.
+template <int KIND, int DP>
+constexpr int kOwned = KIND != kF32 && DP <= 128 ? 2 : 1;
+// Whether the key owners form v = rowsum(dO o O) of the streamed queries themselves (then the backward is one launch) or
+// read it (where the stages of Q, dO and O do not fit LDS together).
+template <int KIND, int DP>
+constexpr bool kOwnDelta = DP <= 192;
+
+// One step's stage of a wave: K, V forward; Q, dO, O (or v) and LSE backward.
+template <int KIND, bool QUAD, int DP>
+__host__ __device__ constexpr int stage_lds(bool backward) {
+    typedef StageLoader<KIND, QUAD, DP> L;
+    return L::kBytes * (backward && kOwnDelta<KIND, DP> ? 3 : 2) + (backward ? 512 : 0);
+}
+// Whether a workgroup can have eight waves (their stages fit LDS) instead of four; which it has is decided at launch.
+template <int KIND, bool QUAD, int DP>
+__host__ __device__ constexpr bool eight_waves(bool backward) {
+    return 8 * stage_lds<KIND, QUAD, DP>(backward) <= 156 * 1024;
+}
+
+// Which (batch, head), block and role (0: queries, 1: keys) a workgroup has.  Dense lists of equal length: all of one
+// head on one XCD.  Under the causal rule a block's work grows with its distance from one end, and which workgroups share
+// a CU decides the run time: workgroup L lands on CU L mod 256 while there is room, so ranks (longest first over all heads)
+// are laid out in rounds of 256, every second one reversed, and each CU gets a long, a short, a long ... one.  (In
+// head order some CUs had twice the average work.)
+__device__ __forceinline__ void balanced_block(int linear, int blocks, int bh_total, int roles, int causal, int& bh, int& rank, int& role) {
+    const int per = bh_total * roles;
+    if (!causal) {
+        decode_block(linear, blocks * roles, bh_total, bh, rank);
+        role = rank % roles;
+        rank /= roles;
+        return;
+    }
+    const int round = linear >> 8, in = linear & 255;
+    int r = linear;
+    if ((round & 1) && (round + 1) * 256 <= blocks * per) r = round * 256 + (31 - (in >> 3)) * 8 + (in & 7);
+    rank = r / per;
+    const int rest = r % per;
+    bh = rest / roles;
+    role = rest % roles;
+}
+
+// ------------------------------------------------------------------------------------ forward
+template <int KIND, bool QUAD, int DP, int XG, int NW>
+__global__ void __launch_bounds__(NW * 64, 2) stream_fwd_kernel(GenericParams p) {
+    typedef Traits<KIND> TR;
+    typedef typename TR::T T;
+    typedef StageLoader<KIND, QUAD, DP> Loader;
+    constexpr int G = TR::kG, NS = DP / TR::kChunk, kV = Loader::kBytes;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    __shared__ float st_m[NW][16 * XG], st_l[NW][16 * XG];
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, h4 = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int blocks = (p.n + 16 * XG - 1) / (16 * XG);
+    int bh, blk, role;
+    balanced_block(blockIdx.x, blocks, p.batch * p.heads, 1, p.causal, bh, blk, role);
+    if (p.causal) blk = blocks - 1 - blk;  // longest rows first
+    const int i0 = blk * 16 * XG;
+    const long base = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
+    const unsigned ldb = (unsigned)p.stride_n * sizeof(T);
+    const char *Q = head_base<T>(p.Q, base), *K = head_base<T>(p.K, base), *V = head_base<T>(p.V, base);
+    const Groups groups = make_groups(p, bh, false, i0, min(p.n, i0 + 16 * XG) - 1);
+
+    constexpr int C = Loader::kCopies;
+    const int wave_off = w * stage_lds<KIND, QUAD, DP>(false);
+    const unsigned lds = (unsigned)(size_t)(ATTN_LDS char*)smem + wave_off;
+    Loader ld;
+    ld.init(lane, ldb, p.d);
+    StageReader<KIND, DP> rd;
+    rd.init(lane, wave_off);
+    int kb[G], kb_next[G];
+    auto next_step = [&](int g0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) kb_next[g] = groups.start(g0 + g);
+    };
+
+    // The place of K is free as soon as the first products have read it, that of V after the second ones: the copies of
+    // the next step go out there, each with the other half of a step to arrive in.  The first step is requested in front
+    // of the owned rows, so that the latencies overlap.
+    if (w * G < groups.count) {
+        next_step(w * G);
+        ld.load(K, kb_next, p.n, ldb, p.d, lds, lane);
+        ld.load(V, kb_next, p.n, ldb, p.d, lds + kV, lane);
+    }
+
+    typename TR::Row qf[XG][NS];
+    int lim[XG];
+#pragma unroll
+    for (int x = 0; x < XG; ++x) {
+        const int q = i0 + 16 * x + r16;
+        load_owned<KIND, QUAD, DP>(Q + (size_t)min(q, p.n - 1) * ldb, h4, p.d, qf[x]);
+        lim[x] = p.causal ? min(q + 1, p.n) : p.n;
+    }
+    // a negative scale moves into Q, a zero one becomes a tiny positive one (masked scores must stay -inf)
+    float chi = p.c_hi, clo = p.c_lo;
+    if (p.scale < 0.f) {
+        chi = -chi;
+        clo = -clo;
+#pragma unroll
+        for (int x = 0; x < XG; ++x)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) qf[x][s] = -qf[x][s];
+    }
+    chi = fmaxf(chi, 1.17549435e-38f);
+#pragma unroll
+    for (int x = 0; x < XG; ++x)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) settle(qf[x][s]);
+    const int lim_all = p.causal ? min(i0 + 1, p.n) : p.n;  // rows below it are visible to every query here
+
+    f32x4 acc[XG][DP / 16];
+    float m_run[XG], l_run[XG];
+#pragma unroll
+    for (int x = 0; x < XG; ++x) {
+        m_run[x] = -__builtin_inff();
+        l_run[x] = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < DP / 16; ++nb) acc[x][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int g0 = w * G; g0 < groups.count; g0 += NW * G) {
+        const bool more = g0 + NW * G < groups.count;
+        bool full = true;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            kb[g] = kb_next[g];
+            full = full && kb[g] + 16 <= lim_all;
+        }
+        wait_copies<C>();  // K is there; V, requested after it, may be on its way
+        f32x4 st[XG][G];
+#pragma unroll
+        for (int x = 0; x < XG; ++x)
+#pragma unroll
+            for (int g = 0; g < G; ++g) st[x][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const typename TR::Row kf = rd.row(smem, 0, g, s);
+#pragma unroll
+                for (int x = 0; x < XG; ++x) st[x][g] = mma_rows(kf, qf[x][s], st[x][g]);
+            }
+        wait_reads();
+        // the scores are taken out of the matrix pipe before the branch: read behind it, the compiler (ROCm 7.2) left out the
+        // wait that an MFMA result needs on the path around the copies
+#pragma unroll
+        for (int x = 0; x < XG; ++x)
+#pragma unroll
+            for (int g = 0; g < G; ++g) asm volatile("" : "+v"(st[x][g]));
+        if (more) {
+            next_step(g0 + NW * G);
+            ld.load(K, kb_next, p.n, ldb, p.d, lds, lane);
+        }
+        Weights<KIND> wt[XG];
+#pragma unroll
+        for (int x = 0; x < XG; ++x) {
+            if (!full) {
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        st[x][g][i] = kb[g] + 4 * h4 + i < lim[x] ? st[x][g][i] : -__builtin_inff();
+            }
+            float mx = st[x][0][0];
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mx = __builtin_elementwise_maximum(mx, st[x][g][i]);
+            // The reference point of the exponentials follows the row maximum with a slack of 2^8 (see the tile kernels).
+            // Whether it has to move is seen from each lane's own scores; the maximum over the lanes of a row is formed
+            // only then (two cross-lane reads, some 250 cycles).
+            if (__builtin_amdgcn_ballot_w64(mx * chi > m_run[x] + 8.f) != 0) {
+                mx = __builtin_elementwise_maximum(mx, __shfl_xor(mx, 16, 64));
+                mx = __builtin_elementwise_maximum(mx, __shfl_xor(mx, 32, 64));
+                const float cand = mx * chi;
+                const float m_new = cand > m_run[x] + 8.f ? cand : m_run[x];
+                const float alpha = __builtin_amdgcn_exp2f(m_run[x] - (m_new == -__builtin_inff() ? 0.f : m_new));
+                l_run[x] *= alpha;
+#pragma unroll
+                for (int nb = 0; nb < DP / 16; ++nb) acc[x][nb] *= alpha;
+                m_run[x] = m_new;
+            }
+            const float m_use = m_run[x] == -__builtin_inff() ? 0.f : m_run[x];  // nothing visible yet
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float v = __builtin_amdgcn_exp2f(scaled(st[x][g][i], chi, clo, m_use));
+                    // (with a two-part constant -inf - (-inf) can appear at a masked score)
+                    if (!full) v = kb[g] + 4 * h4 + i < lim[x] ? v : 0.f;
+                    st[x][g][i] = v;
+                    l_run[x] += v;
+                }
+            wt[x].set(st[x]);
+        }
+        if (more) wait_copies<C>();
+        else wait_copies<0>();
+        accumulate<KIND, DP, XG>(acc, rd, smem, kV, wt);
+        if (more) {
+            wait_reads();
+            ld.load(V, kb_next, p.n, ldb, p.d, lds + kV, lane);
+        }
+    }
+    // the waves' partial rows: a common reference point per row, then O = sum of parts / l
+#pragma unroll
+    for (int x = 0; x < XG; ++x) {
+        float l = l_run[x];
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (h4 == 0) {
+            st_m[w][16 * x + r16] = m_run[x];
+            st_l[w][16 * x + r16] = l;
+        }
+    }
+    __syncthreads();
+    if (tid < 16 * XG) {
+        float M = -__builtin_inff(), L = 0.f;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) M = fmaxf(M, st_m[k][tid]);
+        const float M_use = M == -__builtin_inff() ? 0.f : M;
+        float f[NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            f[k] = __builtin_amdgcn_exp2f(st_m[k][tid] - M_use);
+            L = fmaf(st_l[k][tid], f[k], L);
+        }
+        const float inv = L > 0.f ? 1.f / L : 0.f;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) st_l[k][tid] = f[k] * inv;
+        if (i0 + tid < p.n)
+            p.LSE_out[(long)bh * p.n + i0 + tid] =
+                L > 0.f ? fmaf(M, kLn2, fmaf(M, -1.90465421e-9f, __builtin_amdgcn_logf(L) * kLn2)) : -__builtin_inff();  // (ln 2 in two parts)
+    }
+    combine_store<KIND, QUAD, DP, XG, NW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.O, base)), ldb, i0,
+                                      p.n, p.d, [&](int k, int r) { return st_l[k][r]; });
+}
+
+// ----------------------------------------------------------------------------------- backward
+// dQ of 16 XG queries
+template <int KIND, bool QUAD, int DP, int XG, int NW>
+__device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, int bh, int blk) {
+    typedef Traits<KIND> TR;
+    typedef typename TR::T T;
+    typedef StageLoader<KIND, QUAD, DP> Loader;
+    constexpr int G = TR::kG, NS = DP / TR::kChunk, kV = Loader::kBytes;
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, h4 = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i0 = blk * 16 * XG;
+    const long base = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
+    const unsigned ldb = (unsigned)p.stride_n * sizeof(T);
+    const char *Q = head_base<T>(p.Q, base), *K = head_base<T>(p.K, base), *V = head_base<T>(p.V, base);
+    const char *dO = head_base<T>(p.dO, base), *O = head_base<T>(p.O_in, base);
+    const Groups groups = make_groups(p, bh, false, i0, min(p.n, i0 + 16 * XG) - 1);
+
+    constexpr int C = Loader::kCopies;
+    const int wave_off = w * stage_lds<KIND, QUAD, DP>(true);
+    const unsigned lds = (unsigned)(size_t)(ATTN_LDS char*)smem + wave_off;
+    Loader ld;
+    ld.init(lane, ldb, p.d);
+    StageReader<KIND, DP> rd;
+    rd.init(lane, wave_off);
+    int kb[G], kb_next[G];
+    auto next_step = [&](int g0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) kb_next[g] = groups.start(g0 + g);
+    };
+
+    if (w * G < groups.count) {
+        next_step(w * G);
+        ld.load(V, kb_next, p.n, ldb, p.d, lds + kV, lane);
+        ld.load(K, kb_next, p.n, ldb, p.d, lds, lane);
+    }
+
+    typename TR::Row qf[XG][NS], gf[XG][NS];
+    int lim[XG];
+    Lse2 lse[XG];
+    float delta[XG];
+#pragma unroll
+    for (int x = 0; x < XG; ++x) {
+        const int q = i0 + 16 * x + r16, qc = min(q, p.n - 1);
+        typename TR::Row of[NS];
+        load_owned<KIND, QUAD, DP>(O + (size_t)qc * ldb, h4, p.d, of);
+        load_owned<KIND, QUAD, DP>(dO + (size_t)qc * ldb, h4, p.d, gf[x]);
+        load_owned<KIND, QUAD, DP>(Q + (size_t)qc * ldb, h4, p.d, qf[x]);
+        lim[x] = p.causal ? min(q + 1, p.n) : p.n;
+        lse[x].set(p.LSE_in[(long)bh * p.n + qc]);
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) s = dot_pair(of[k], gf[x][k], s);
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        delta[x] = s;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            settle(qf[x][k]);
+            settle(gf[x][k]);
+        }
+        settle(lse[x].hi);
+    }
+    const int lim_all = p.causal ? min(i0 + 1, p.n) : p.n;
+
+    f32x4 acc[XG][DP / 16];
+#pragma unroll
+    for (int x = 0; x < XG; ++x)
+#pragma unroll
+        for (int nb = 0; nb < DP / 16; ++nb) acc[x][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int g0 = w * G; g0 < groups.count; g0 += NW * G) {
+        const bool more = g0 + NW * G < groups.count;
+        bool full = true;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            kb[g] = kb_next[g];
+            full = full && kb[g] + 16 <= lim_all;
+        }
+        f32x4 st[XG][G], dp[XG][G];
+#pragma unroll
+        for (int x = 0; x < XG; ++x)
+#pragma unroll
+            for (int g = 0; g < G; ++g) st[x][g] = dp[x][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+        wait_copies<C>();  // V is there; K, requested after it, may be on its way
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const typename TR::Row vf = rd.row(smem, kV, g, s);
+#pragma unroll
+                for (int x = 0; x < XG; ++x) dp[x][g] = mma_rows(vf, gf[x][s], dp[x][g]);
+            }
+        wait_copies<0>();
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const typename TR::Row kf = rd.row(smem, 0, g, s);
+#pragma unroll
+                for (int x = 0; x < XG; ++x) st[x][g] = mma_rows(kf, qf[x][s], st[x][g]);
+            }
+        wait_reads();
+        // the scores are taken out of the matrix pipe before the branch: read behind it, the compiler (ROCm 7.2) left out the
+        // wait that an MFMA result needs on the path around the copies
+#pragma unroll
+        for (int x = 0; x < XG; ++x)
+#pragma unroll
+            for (int g = 0; g < G; ++g) asm volatile("" : "+v"(st[x][g]));
+        if (more) {
+            next_step(g0 + NW * G);
+            ld.load(V, kb_next, p.n, ldb, p.d, lds + kV, lane);
+        }
+        Weights<KIND> wt[XG];
+#pragma unroll
+        for (int x = 0; x < XG; ++x) {
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float f = __builtin_amdgcn_exp2f(scaled(st[x][g][i], p.c_hi, p.c_lo, lse[x].hi) - lse[x].lo);
+                    if (!full) f = kb[g] + 4 * h4 + i < lim[x] ? f : 0.f;
+                    dp[x][g][i] = f * (dp[x][g][i] - delta[x]);
+                }
+            wt[x].set(dp[x]);
+        }
+        accumulate<KIND, DP, XG>(acc, rd, smem, 0, wt);
+        if (more) {
+            wait_reads();
+            ld.load(K, kb_next, p.n, ldb, p.d, lds, lane);
+        }
+    }
+    const float scale = p.scale;
+    combine_store<KIND, QUAD, DP, XG, NW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.dQ, base)), ldb, i0,
+                                      p.n, p.d, [&](int, int) { return scale; });
+}
+
+// dK, dV of 16 XG keys.  With kOwnDelta the row sums v of the streamed queries are formed here again (fp32: from the
+// fragments at hand; bf16: the diagonal of dO O^T), so that both halves of the backward run in one launch with nothing
+// between them.
+template <int KIND, bool QUAD, int DP, int XG, int NW>
+__device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, int bh, int blk) {
+    typedef Traits<KIND> TR;
+    typedef typename TR::T T;
+    typedef StageLoader<KIND, QUAD, DP> Loader;
+    constexpr int G = TR::kG, NS = DP / TR::kChunk, kG_ = Loader::kBytes, kO = 2 * Loader::kBytes;
+    constexpr bool kOwn = kOwnDelta<KIND, DP>;
+    constexpr int kRows = stage_lds<KIND, QUAD, DP>(true) - 512;  // LSE (and v) of the step's queries
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, h4 = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j0 = blk * 16 * XG;
+    const long base = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
+    const unsigned ldb = (unsigned)p.stride_n * sizeof(T);
+    const char *Q = head_base<T>(p.Q, base), *K = head_base<T>(p.K, base), *V = head_base<T>(p.V, base);
+    const char *dO = head_base<T>(p.dO, base), *O = head_base<T>(p.O_in, base);
+    const char* lse_row = uniform_ptr(reinterpret_cast<const char*>(p.LSE_in + (long)bh * p.n));
+    const char* delta_row = uniform_ptr(reinterpret_cast<const char*>(p.delta + (long)bh * p.n));
+    const Groups groups = make_groups(p, bh, true, j0, min(p.n, j0 + 16 * XG) - 1);
+
+    constexpr int C = Loader::kCopies;
+    const int wave_off = w * stage_lds<KIND, QUAD, DP>(true);
+    const unsigned lds = (unsigned)(size_t)(ATTN_LDS char*)smem + wave_off;
+    Loader ld;
+    ld.init(lane, ldb, p.d);
+    StageReader<KIND, DP> rd;
+    rd.init(lane, wave_off);
+    int qb[G], qb_next[G];
+    auto next_step = [&](int g0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) qb_next[g] = groups.start(g0 + g);
+    };
+    // O of the next step (or v) and LSE, one float per query
+    auto fetch_rows = [&]() {
+        int first = qb_next[0];
+        if constexpr (G == 2) first += (lane & 16) ? qb_next[1] - qb_next[0] : 0;
+        const int r = first + r16;
+        const unsigned off = (unsigned)min(r, p.n - 1) * 4u;
+        if constexpr (kOwn) ld.load(O, qb_next, p.n, ldb, p.d, lds + kO, lane);
+        else StageLoader<KIND, false, DP>::issue(lds + kRows + 256, off, delta_row);
+        StageLoader<KIND, false, DP>::issue(lds + kRows, off, lse_row);
+    };
+
+    if (w * G < groups.count) {
+        next_step(w * G);
+        fetch_rows();
+        ld.load(dO, qb_next, p.n, ldb, p.d, lds + kG_, lane);
+        ld.load(Q, qb_next, p.n, ldb, p.d, lds, lane);
+    }
+
+    typename TR::Row kf[XG][NS], vf[XG][NS];
+#pragma unroll
+    for (int x = 0; x < XG; ++x) {
+        const size_t o = (size_t)min(j0 + 16 * x + r16, p.n - 1) * ldb;
+        load_owned<KIND, QUAD, DP>(K + o, h4, p.d, kf[x]);
+        load_owned<KIND, QUAD, DP>(V + o, h4, p.d, vf[x]);
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            settle(kf[x][k]);
+            settle(vf[x][k]);
+        }
+    }
+    f32x4 dk[XG][DP / 16], dv[XG][DP / 16];
+#pragma unroll
+    for (int x = 0; x < XG; ++x)
+#pragma unroll
+        for (int nb = 0; nb < DP / 16; ++nb) dk[x][nb] = dv[x][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int g0 = w * G; g0 < groups.count; g0 += NW * G) {
+        const bool more = g0 + NW * G < groups.count;
+        bool full = true;
+        f32x4 st[XG][G], dp[XG][G];
+#pragma unroll
+        for (int x = 0; x < XG; ++x)
+#pragma unroll
+            for (int g = 0; g < G; ++g) st[x][g] = dp[x][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float lse[G][4], dl[G][4];
+        wait_copies<C>();  // O, LSE and dO are there; Q, requested after them, may be on its way
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            qb[g] = qb_next[g];
+            full = full && qb[g] + 16 <= p.n && (!p.causal || qb[g] >= j0 + 16 * XG - 1);
+            const f32x4 l4 = *reinterpret_cast<const f32x4*>(smem + wave_off + kRows + 64 * g + 16 * h4);
+            f32x4 d4;
+            if constexpr (!kOwn) d4 = *reinterpret_cast<const f32x4*>(smem + wave_off + kRows + 256 + 64 * g + 16 * h4);
+            f32x4 diag = {0.f, 0.f, 0.f, 0.f};
+            float dot = 0.f;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const typename TR::Row gr = rd.row(smem, kG_, g, s);
+#pragma unroll
+                for (int x = 0; x < XG; ++x) dp[x][g] = mma_rows(gr, vf[x][s], dp[x][g]);
+                if constexpr (kOwn) {
+                    typename TR::Row orow = rd.row(smem, kO, g, s);
+                    constexpr int kPer = 16 / sizeof(T);
+                    if (TR::kChunk * (s + 1) > DP - 32 && p.d < DP) {
+#pragma unroll
+                        for (int e = 0; e < kPer; ++e)
+                            if (TR::kChunk * s + kPer * h4 + e >= p.d) orow[e] = (T)0.f;
+                    }
+                    if constexpr (KIND == kF32) dot = dot_pair(orow, gr, dot);
+                    else diag = mma_rows(orow, gr, diag);
+                }
+            }
+            if constexpr (kOwn && KIND == kF32) {
+                dot += __shfl_xor(dot, 16, 64);
+                dot += __shfl_xor(dot, 32, 64);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                lse[g][i] = l4[i];
+                // row 4 h4 + i: its sum is in every lane with that r16 (fp32), or on the diagonal (bf16)
+                if constexpr (!kOwn) dl[g][i] = d4[i];
+                else if constexpr (KIND == kF32) dl[g][i] = __shfl(dot, 4 * h4 + i, 64);
+                else dl[g][i] = __shfl(diag[i], 20 * h4 + i, 64);
+            }
+        }
+        wait_copies<0>();
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const typename TR::Row qr = rd.row(smem, 0, g, s);
+#pragma unroll
+                for (int x = 0; x < XG; ++x) st[x][g] = mma_rows(qr, kf[x][s], st[x][g]);
+            }
+        wait_reads();
+        // the scores are taken out of the matrix pipe before the branch: read behind it, the compiler (ROCm 7.2) left out the
+        // wait that an MFMA result needs on the path around the copies
+#pragma unroll
+        for (int x = 0; x < XG; ++x)
+#pragma unroll
+            for (int g = 0; g < G; ++g) asm volatile("" : "+v"(st[x][g]));
+        if (more) {
+            next_step(g0 + NW * G);
+            fetch_rows();
+        }
+        Weights<KIND> wp[XG], wd[XG];
+        Lse2 l2[G][4];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) l2[g][i].set(lse[g][i]);
+#pragma unroll
+        for (int x = 0; x < XG; ++x) {
+            const int key = j0 + 16 * x + r16;
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float f = __builtin_amdgcn_exp2f(scaled(st[x][g][i], p.c_hi, p.c_lo, l2[g][i].hi) - l2[g][i].lo);
+                    if (!full) {
+                        const int q = qb[g] + 4 * h4 + i;
+                        f = q < p.n && (!p.causal || q >= key) ? f : 0.f;
+                    }
+                    st[x][g][i] = f;
+                    dp[x][g][i] = f * (dp[x][g][i] - dl[g][i]);
+                }
+            wp[x].set(st[x]);
+            wd[x].set(dp[x]);
+        }
+        accumulate<KIND, DP, XG>(dv, rd, smem, kG_, wp);
+        if (more) {
+            wait_reads();
+            ld.load(dO, qb_next, p.n, ldb, p.d, lds + kG_, lane);
+        }
+        accumulate<KIND, DP, XG>(dk, rd, smem, 0, wd);
+        if (more) {
+            wait_reads();
+            ld.load(Q, qb_next, p.n, ldb, p.d, lds, lane);
+        }
+    }
+    const float scale = p.scale;
+    combine_store<KIND, QUAD, DP, XG, NW>(dv, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.dV, base)), ldb, j0,
+                                      p.n, p.d, [&](int, int) { return 1.f; });
+    combine_store<KIND, QUAD, DP, XG, NW>(dk, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.dK, base)), ldb, j0,
+                                      p.n, p.d, [&](int, int) { return scale; });
+}
+
+// One launch for the whole backward: query blocks (dQ) and key blocks (dK, dV) side by side.
+template <int KIND, bool QUAD, int DP, int XG, int NW>
+__global__ void __launch_bounds__(NW * 64, NW == 8 || DP <= 96 ? 2 : 1) stream_bwd_kernel(GenericParams p) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int blocks = (p.n + 16 * XG - 1) / (16 * XG);
+    int bh, blk, role;
+    balanced_block(blockIdx.x, blocks, p.batch * p.heads, 2, p.causal, bh, blk, role);
+    if (role) stream_dkdv<KIND, QUAD, DP, XG, NW>(p, smem, bh, blk);
+    else stream_dq<KIND, QUAD, DP, XG, NW>(p, smem, bh, p.causal ? blocks - 1 - blk : blk);
+}
+
+template <int KIND, bool QUAD, int DP, int NW, bool BACKWARD>
+hipError_t launch_waves(const GenericParams& p, dim3 grid, hipStream_t stream) {
+    constexpr int XG = kOwned<KIND, DP>;
+    constexpr int stages = NW * stage_lds<KIND, QUAD, DP>(BACKWARD), red = NW * 16 * XG * (DP + 4) * (int)sizeof(float);
+    constexpr int lds = stages > red ? stages : red;
+    auto kernel = [] {
+        if constexpr (BACKWARD) return stream_bwd_kernel<KIND, QUAD, DP, XG, NW>;
+        else return stream_fwd_kernel<KIND, QUAD, DP, XG, NW>;
+    }();
+    if constexpr (lds > 60 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    if (BACKWARD && !kOwnDelta<KIND, DP>) launch_generic_delta(KIND != kF32, p, stream);
+    hipLaunchKernelGGL(kernel, grid, dim3(NW * 64), lds, stream, p);
+    return hipGetLastError();
+}
+
+// A wave's step is a chain of copies, LDS reads, products and exponentials, so two waves per SIMD are wanted and short
+// chains: eight waves per workgroup while there are at most two workgroups per CU, four beyond, where two or more
+// workgroups on a CU fill each other's prologue and final sum.  (Forward: bf16 b1 h8 n1500 d96 causal, 376 workgroups,
+// 26.6 us with four and 20.5 with eight; fp32 b2 h6 n777 d80 causal, 588 workgroups, 26 and 29; backward of the two,
+// 752 and 1176 workgroups, 51 and 59, 77 and 87.  Two and three stages per wave hid no more than one.)
+template <int KIND, bool QUAD, int DP, bool BACKWARD>
+hipError_t run_waves(const GenericParams& p, hipStream_t stream) {
+    constexpr int rows = 16 * kOwned<KIND, DP>;
+    const dim3 grid((unsigned)((p.n + rows - 1) / rows * p.batch * p.heads * (BACKWARD ? 2 : 1)));
+    if constexpr (eight_waves<KIND, QUAD, DP>(BACKWARD))
+        if (grid.x <= 512) return launch_waves<KIND, QUAD, DP, 8, BACKWARD>(p, grid, stream);
+    return launch_waves<KIND, QUAD, DP, 4, BACKWARD>(p, grid, stream);
+}
+template <int KIND, bool QUAD, int DP>
+hipError_t run_stream(const GenericParams& p, bool backward, hipStream_t stream) {
+    return backward ? run_waves<KIND, QUAD, DP, true>(p, stream) : run_waves<KIND, QUAD, DP, false>(p, stream);
+}
+
+template <int KIND, bool QUAD>
+hipError_t run_width(const GenericParams& p, bool backward, hipStream_t stream) {
+    switch ((p.d + 31) / 32) {  // the next multiple of 32: the loads bound columns in the last 32 only
+        case 1: return run_stream<KIND, QUAD, 32>(p, backward, stream);
+        case 2: return run_stream<KIND, QUAD, 64>(p, backward, stream);
+        case 3: return run_stream<KIND, QUAD, 96>(p, backward, stream);
+        case 4: return run_stream<KIND, QUAD, 128>(p, backward, stream);
+        default: break;
+    }
+    if constexpr (KIND != kF32) {
+        switch ((p.d + 31) / 32) {
+            case 5: return run_stream<KIND, QUAD, 160>(p, backward, stream);
+            case 6: return run_stream<KIND, QUAD, 192>(p, backward, stream);
+            case 7: return run_stream<KIND, QUAD, 224>(p, backward, stream);
+            case 8: return run_stream<KIND, QUAD, 256>(p, backward, stream);
+            default: break;
+        }
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// What is left to the FMA kernels: head dimensions whose accumulators, owned rows and stages do not fit a CU here,
+// block edges that cut through the rows a workgroup owns, and heads of 4 GB and more (32-bit byte offsets).
+bool stream_takes(bool is_bf16, const GenericParams& p) {
+    if (p.d > (is_bf16 ? 256 : 128)) return false;
+    if (p.csr_ptr && p.block % (is_bf16 && p.d <= 128 ? 32 : 16) != 0) return false;
+    return (double)p.n * (double)p.stride_n * (is_bf16 ? 2.0 : 4.0) < 4.0e9;
+}
+
+hipError_t launch_stream(bool is_bf16, bool backward, const GenericParams& p, hipStream_t stream) {
+    if (is_bf16) return run_width<kBf3, true>(p, backward, stream);
+    return p.d % 4 == 0 ? run_width<kF32, true>(p, backward, stream) : run_width<kF32, false>(p, backward, stream);
+}
+
+}  // namespace attn
