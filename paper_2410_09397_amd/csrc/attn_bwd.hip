@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_dkdv_kernel(Fu
     // past n) and the blocks come longest list first
     const int key_blocks = p.order ? 2 * ((p.n + 127) / 128) : (p.n + BC - 1) / BC;
     int bh, j;
-    decode_block(blockIdx.x, key_blocks, p.batch * p.heads, bh, j);
+    decode_block_causal(blockIdx.x, key_blocks, p.batch * p.heads, p.resident, bh, j);
     if (p.order) {
         j = 2 * p.order[(long)bh * p.order_stride + (j >> 1)] + (j & 1);
         if (j * BC >= p.n) return;
@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (QT == 1 && D <= 128 ?
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
     const int q_blocks = (p.n + BR - 1) / BR;
     int bh, blk;
-    decode_block(blockIdx.x, q_blocks, p.batch * p.heads, bh, blk);
+    decode_block_causal(blockIdx.x, q_blocks, p.batch * p.heads, p.resident, bh, blk);
     // longest rows first: under the causal rule the last blocks, under a block mask by the order list
     const int ib = p.order ? p.order[(long)bh * p.order_stride + blk] : (p.causal ? q_blocks - 1 - blk : blk);
     const long base = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
@@ -708,6 +708,7 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
         return launch_bwd_onepass(D, onepass_keys, pk, dq_acc, stream);
     }
     FusedParams pq = p;
+    if (p.causal && !csr_ptr) pq.resident = causal_resident(blocks128 * bh, D == 64 ? 4 : D == 128 ? 2 : 1);
     pq.list_ptr = csr_ptr;
     pq.list_idx = csr_idx;
     pq.order = order_q;
@@ -724,6 +725,7 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     pk.order = order_k;
     pk.order_stride = p.list_stride ? blocks128 : 0;
     const int key_blocks = order_k ? 2 * blocks128 : (p.n + 63) / 64;
+    if (p.causal && !csc_ptr) pk.resident = causal_resident(key_blocks * bh, D == 64 ? 3 : D == 128 ? 2 : 1);
     hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3((unsigned)(key_blocks * bh)), dim3(kThreads), kv_lds, stream, pk);
     return hipGetLastError();
 }

@@ -357,6 +357,33 @@ __device__ __forceinline__ void decode_block(int linear, int tiles, int bh_total
     }
 }
 
+// The same for a causal launch whose tiles differ in length: `rank` 0 is the longest tile of a head.  `resident` > 0: ranks
+// run over all heads of an XCD together, longest first, and the first `resident` rounds of 32 (the workgroups that
+// share the XCD's 32 CUs from the start) go back and forth, so that each CU gets a long, a short, a long ... one.
+// `resident` == 0: head after head.
+__device__ __forceinline__ void decode_block_causal(int linear, int tiles, int bh_total, int resident, int& bh, int& rank) {
+    if (resident == 0) {
+        decode_block(linear, tiles, bh_total, bh, rank);
+        return;
+    }
+    const bool by_xcd = (bh_total & 7) == 0;
+    const int xcds = by_xcd ? 8 : 1, cus = by_xcd ? 32 : 256;
+    const int xcd = linear & (xcds - 1), heads = bh_total / xcds;
+    int slot = linear / xcds;
+    const int round = slot / cus;
+    if ((round & 1) && round < resident && (round + 1) * cus <= tiles * heads) slot = (2 * round + 1) * cus - 1 - slot;
+    rank = slot / heads;
+    bh = (slot % heads) * xcds + xcd;
+}
+
+// `resident` for a causal launch of `grid` workgroups of which per_cu fit a CU.  In head order a CU got the same tile index of
+// two heads (the two longest, say) while the launch is small, and the last head's long tiles started late when it is a
+// few rounds long.  Over all heads, longest first (us, forward / dQ / dK dV): d = 64 b4 h16 n2048 70 / 83 / 97 -> 49 / 63 /
+// 87; d = 128 b2 h16 n1024 28 / 35 / 34 -> 27 / 34 / 29, n4096 178 / 229 / 263 -> 140 / 186 / 261; d = 256 b3 h5 n3000
+// 219 / 260 / 221 -> 134 / 157 / 184.  From eight rounds on head order is kept: the tail is short then, and an XCD that
+// works on one head at a time finds more in its L2 (d = 128 b2 h32 n8192: forward the same, dK dV 1982 against 2056 us).
+inline int causal_resident(int grid, int per_cu) { return grid < 8 * 256 * per_cu ? per_cu : 0; }
+
 // Kernel arguments common to the fused kernels.  Strides are in elements.
 struct FusedParams {
     const __bf16 *Q, *K, *V, *O, *dO;
@@ -376,6 +403,7 @@ struct FusedParams {
     const int32_t* order;
     // masks per (batch, head): entries between the list_ptr (order) arrays of consecutive pairs; 0 = one shared mask
     int list_stride, order_stride;
+    int resident;  // causal, no mask: see decode_block_causal
 };
 
 }  // namespace attn

@@ -28,7 +28,7 @@ __global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (D <= 128 ? 2 : 1)) fw
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
     const int q_blocks = (p.n + BR - 1) / BR;
     int bh, blk;
-    decode_block(blockIdx.x, q_blocks, p.batch * p.heads, bh, blk);
+    decode_block_causal(blockIdx.x, q_blocks, p.batch * p.heads, p.resident, bh, blk);
     const int ib = p.causal ? q_blocks - 1 - blk : blk;  // causal: longest rows first
     const long base = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
     const long ld = p.stride_n;
@@ -259,6 +259,7 @@ static hipError_t launch_fwd(const FusedParams& p, const int32_t* csr_ptr, const
     pf.list_ptr = csr_ptr;
     pf.list_idx = csr_idx;
     const int blocks = (p.n + 127) / 128 * p.batch * p.heads;
+    if (p.causal && !csr_ptr) pf.resident = causal_resident(blocks, D == 64 ? 4 : D == 128 ? 2 : 1);
     hipLaunchKernelGGL(fwd_kernel<D>, dim3((unsigned)blocks), dim3(kThreads), lds, stream, pf);
     return hipGetLastError();
 }

@@ -63,3 +63,29 @@ def test_gradient_invariants_at_full_size(index):
     err2 = float(((a - b).abs() / size).max())
     print("invariant %s: <dQ,Q> against <dK,K>, relative to sum |dQ||Q| %.3e" % (w.name, err2), flush=True)
     assert err2 <= 3e-4
+
+
+@pytest.mark.parametrize("d,bh,n", [(64, 24, 1400), (64, 20, 1000), (128, 24, 1500), (128, 37, 900), (256, 16, 1100), (256, 704, 300)])
+def test_causal_block_order_covers_every_block(d, bh, n):
+    """Under the causal rule the order in which workgroups take the blocks depends on how many there are (one round of the
+    chip, a few, from eight rounds on head after head) and on whether the heads divide over the XCDs.  The order changes no
+    arithmetic: every head of the whole call has the bits of a call on that head alone."""
+    import torch
+    from paper_2410_09397_amd import attn
+    print("case", d, bh, n, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + bh + n)
+    Q, K, V, dO = (torch.randn((1, bh, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    nan = lambda t: torch.full_like(t, float("nan"))
+    O, LSE, grads = nan(Q), torch.full((1, bh, n), float("nan"), device="cuda"), (nan(Q), nan(Q), nan(Q))
+    attn.attn_fwd(Q, K, V, d ** -0.5, causal=True, out=(O, LSE))
+    two_kernel = attn.ATTN_BWD_TWO_KERNEL
+    attn.attn_bwd(Q, K, V, O, dO, LSE, d ** -0.5, causal=True, out=grads, tiling=two_kernel)
+    for t in (O, LSE, *grads):
+        assert torch.isfinite(t).all()
+    for h in sorted({0, 1, 7, bh // 2, bh - 1}):
+        one = [t[:, h:h + 1].contiguous() for t in (Q, K, V, dO, O, LSE)]
+        o1, l1 = attn.attn_fwd(*one[:3], d ** -0.5, causal=True)
+        g1 = attn.attn_bwd(*one[:3], one[4], one[3], one[5], d ** -0.5, causal=True, tiling=two_kernel)
+        for a, b in zip((O, LSE, *grads), (o1, l1, *g1)):
+            assert torch.equal(a[:, h:h + 1], b), h
