@@ -415,31 +415,37 @@ __global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_dkdv_kernel(Fu
 //   S^T[T] = K_T Q_w^T, dP^T[T] = V_T dO_w^T        accumulator: lane <-> query, register <-> key
 //   dS^T = P^T (dP^T - delta)                        per-lane scalars lse2, delta
 //   dQ_w^T += K_T^T dS^T                             K^T from transposed LDS reads
-template <int D, int QT>
-__global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (QT == 1 && D <= 128 ? 2 : 1)) bwd_dq_kernel(FusedParams p) {
-    constexpr int BR = 128 * QT, BC = 64, KS = D / 16, MT = D / 32;
+// SPLIT = 2 (QT = 1): the block has 64 queries and wave (wq, wk) takes queries 32 wq .. +31 with key half wk of every tile; the two
+// sums of a query meet in LDS at the end.
+template <int D, int QT, int SPLIT>
+__device__ __forceinline__ void dq_block(const FusedParams p, char* smem) {
+    static_assert(SPLIT == 1 || QT == 1, "one way to share out the waves at a time");
+    constexpr int BR = 128 * QT / SPLIT, BC = 64, KS = D / 16, MT = D / 32;
+    constexpr int NT = 2 / SPLIT;  // 32-key halves of a tile per wave
     constexpr int kTileBytes = BC * D * 2;
     constexpr int kStageBytes = 2 * kTileBytes;
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
-    const int q_blocks = (p.n + BR - 1) / BR;
+    const int wq = SPLIT == 1 ? w : w & 1, wk = SPLIT == 1 ? 0 : w >> 1;
+    const int q_blocks = SPLIT > 1 && p.order ? SPLIT * ((p.n + 127) / 128) : (p.n + BR - 1) / BR;
     int bh, blk;
     decode_block_causal(blockIdx.x, q_blocks, p.batch * p.heads, p.resident, bh, blk);
     // longest rows first: under the causal rule the last blocks, under a block mask by the order list
-    const int ib = p.order ? p.order[(long)bh * p.order_stride + blk] : (p.causal ? q_blocks - 1 - blk : blk);
+    const int ib = p.order ? SPLIT * p.order[(long)bh * p.order_stride + blk / SPLIT] + blk % SPLIT
+                           : (p.causal ? q_blocks - 1 - blk : blk);
     const long base = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
     const long ld = p.stride_n;
     const int i0 = ib * BR;
-    const int w0 = i0 + 32 * QT * w;  // first query of this wave
+    const int w0 = i0 + 32 * QT * wq;  // first query of this wave
 
     int n_it, lp0 = 0;
     if (p.list_ptr) {  // block lists are per 128 queries: only with QT == 1
         const int32_t* lptr = p.list_ptr + (long)bh * p.list_stride;  // this (batch, head)'s mask
-        lp0 = lptr[ib];
-        int entries = lptr[ib + 1] - lp0;
-        if (p.causal) entries = causal_row_entries(p.list_idx, lp0, entries, ib);
+        const int lb = ib / SPLIT;
+        lp0 = lptr[lb];
+        int entries = lptr[lb + 1] - lp0;
+        if (p.causal) entries = causal_row_entries(p.list_idx, lp0, entries, lb);
         n_it = entries * (128 / BC);
     } else {
         const int k_end = p.causal ? min(p.n, i0 + BR) : p.n;
@@ -494,7 +500,7 @@ __global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (QT == 1 && D <= 128 ?
         }
         dsum += __shfl_xor(dsum, 32, 64);
         dl[t] = ok ? dsum : 0.f;
-        if (ok && h == 0) p.delta[(long)bh * p.n + q[t]] = dsum;
+        if (ok && h == 0 && wk == 0) p.delta[(long)bh * p.n + q[t]] = dsum;
     }
 
     f32x16 dq[QT][MT];
@@ -531,6 +537,7 @@ __global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (QT == 1 && D <= 128 ?
     lane_offsets.init(lane);
     FragAddrs<D> fo;
     fo.init(lane_offsets);
+    if constexpr (SPLIT > 1) fo.shift_rows(32 * wk);
     wait_direct_loads();
     __syncthreads();
 
@@ -544,7 +551,7 @@ __global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (QT == 1 && D <= 128 ?
         const int k_off = stage_off;  // K tile; the V tile follows it
         // the two 32-key halves one after the other: half the score registers live at a time
 #pragma unroll
-        for (int T = 0; T < 2; ++T) {
+        for (int T = 0; T < NT; ++T) {
             __builtin_amdgcn_s_setprio(kPrioScores);
             f32x16 st[QT], dpt[QT];
 #pragma unroll
@@ -569,7 +576,7 @@ __global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (QT == 1 && D <= 128 ?
 #pragma unroll
             for (int t = 0; t < QT; ++t) {
                 // key j0 + 32T + 8g + 4h + r is visible iff 8g + r <= lim (one per-lane bound)
-                const int lim = (p.causal ? min(q[t], p.n - 1) : p.n - 1) - j0 - 32 * T - 4 * h;
+                const int lim = (p.causal ? min(q[t], p.n - 1) : p.n - 1) - j0 - 32 * (T + wk) - 4 * h;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     float pv = __builtin_amdgcn_exp2f(st[t][i] * c - lse2[t]);
@@ -602,7 +609,10 @@ __global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (QT == 1 && D <= 128 ?
     // then a precomputed register plus an immediate); the rest takes the masked body with a
     // run-time stage.  Waves may leave the first loop at different tiles; both loops run the same
     // fetches and barriers.
-    auto needs_mask = [&](int j0) { return (p.causal && (j0 + BC - 1 > w0)) || (j0 + BC > p.n); };
+    constexpr int kWaveKeys = 32 * NT;  // keys of a tile that a wave looks at, from j0 + 32 wk on
+    auto needs_mask = [&](int j0) {
+        return (p.causal && (j0 + 32 * wk + kWaveKeys - 1 > w0)) || (j0 + 32 * wk + kWaveKeys > p.n);
+    };
     int it = 0;
     for (; it + 2 <= n_it; it += 2) {
         const int ja = j0_next, jb = tile_start(it + 1);
@@ -626,18 +636,48 @@ __global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (QT == 1 && D <= 128 ?
             j0_next = tile_start(it + 1);
             fetch(j0_next, (it + 1) & 1);
         }
-        // causal: this wave's last query precedes the tile's first key -> nothing visible
-        if (!(p.causal && (w0 + 32 * QT - 1 < j0))) tile((it & 1) * kStageBytes, j0, std::true_type{});
+        // causal: this wave's last query precedes its first key of the tile -> nothing visible
+        if (!(p.causal && (w0 + 32 * QT - 1 < j0 + 32 * wk))) tile((it & 1) * kStageBytes, j0, std::true_type{});
         wait_direct_loads();
         __syncthreads();
     }
 
+    constexpr int MW = MT / SPLIT;  // 32-column groups of dQ that a wave writes, from MW wk on
+    if constexpr (SPLIT > 1) {
+        // each of the two waves of a query hands the other the half of its sum that the other writes; the stages are
+        // free (every wave is past the last barrier of the loop)
+        auto slot = [&](int wave, int mt, int g) { return reinterpret_cast<f32x4*>(smem) + ((wave * MW + mt) * 4 + g) * 64 + lane; };
+        auto send = [&](auto first) {
+#pragma unroll
+            for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const f32x16& a = dq[0][decltype(first)::value + mt];
+                    *slot(w, mt, g) = f32x4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
+                }
+        };
+        auto meet = [&](auto first) {
+#pragma unroll
+            for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const f32x4 b = *slot(w ^ 2, mt, g);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) dq[0][mt][4 * g + r] = dq[0][decltype(first)::value + mt][4 * g + r] + b[r];
+                }
+        };
+        if (wk == 0) send(std::integral_constant<int, MW>{});
+        else send(std::integral_constant<int, 0>{});
+        __syncthreads();
+        if (wk == 0) meet(std::integral_constant<int, 0>{});
+        else meet(std::integral_constant<int, MW>{});
+    }
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
         if (q[t] < p.n) {
-            __bf16* row = p.dQ + base + (long)q[t] * ld;
+            __bf16* row = p.dQ + base + (long)q[t] * ld + 32 * MW * wk;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
+            for (int mt = 0; mt < MW; ++mt)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     u32x2 a;
@@ -647,6 +687,20 @@ __global__ void __launch_bounds__(kThreads, D == 64 ? 4 : (QT == 1 && D <= 128 ?
                 }
         }
     }
+}
+
+constexpr int dq_per_cu(int d) { return d == 64 ? 4 : d == 128 ? 2 : 1; }
+
+template <int D, int QT>
+__global__ void __launch_bounds__(kThreads, QT == 1 ? dq_per_cu(D) : 1) bwd_dq_kernel(FusedParams p) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    dq_block<D, QT, 1>(p, smem);
+}
+
+template <int D>
+__global__ void __launch_bounds__(kThreads, D == 64 ? 3 : dq_per_cu(D)) bwd_dq_split_kernel(FusedParams p) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    dq_block<D, 1, 2>(p, smem);
 }
 
 // ------------------------------------------------------------------------------ launchers
@@ -664,16 +718,17 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
 
     constexpr int kv_lds = 2 * (2 * 64 * D * 2) + 2 * 64 * 64 * 2;  // two stages of Q, dO; P and dS
     constexpr int q_lds = 2 * (2 * 64 * D * 2);
+    const int blocks128 = (p.n + 127) / 128;
+    const bool split = few_blocks(blocks128 * bh, dq_per_cu(D), p.causal && !csr_ptr);
+    void (*const dq_fn)(FusedParams) = split ? bwd_dq_split_kernel<D> : bwd_dq_kernel<D, 1>;
     const void* kv_fn = reinterpret_cast<const void*>(bwd_dkdv_kernel<D>);
     // set on every call (the attribute belongs to the current device, and the call is cheap)
     if (!onepass) {
         hipError_t e = hipFuncSetAttribute(kv_fn, hipFuncAttributeMaxDynamicSharedMemorySize, kv_lds);
         if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bwd_dq_kernel<D, 1>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, q_lds);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(dq_fn), hipFuncAttributeMaxDynamicSharedMemorySize, q_lds);
         if (e != hipSuccess) return e;
     }
-    const int blocks128 = (p.n + 127) / 128;
     int32_t* order_q = nullptr;
     int32_t* order_k = nullptr;
     const int masks = p.list_stride ? bh : 1;  // one mask per (batch, head), or one for all
@@ -708,7 +763,9 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
         return launch_bwd_onepass(D, onepass_keys, pk, dq_acc, stream);
     }
     FusedParams pq = p;
-    if (p.causal && !csr_ptr) pq.resident = causal_resident(blocks128 * bh, D == 64 ? 4 : D == 128 ? 2 : 1);
+    // with an order list both halves of every 128-query block (the last one may lie past n: it writes nothing)
+    const int q_blocks = !split ? blocks128 : order_q ? 2 * blocks128 : (p.n + 63) / 64;
+    if (p.causal && !csr_ptr) pq.resident = causal_resident(q_blocks * bh, dq_per_cu(D));
     pq.list_ptr = csr_ptr;
     pq.list_idx = csr_idx;
     pq.order = order_q;
@@ -717,7 +774,7 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     // LDS fragment feeding two MFMAs, halves the LDS traffic but measured 20 % slower at d = 128:
     // with a single wave per SIMD the softmax arithmetic no longer overlaps another wave's MFMAs.)
     if (!dkdv_only)
-        hipLaunchKernelGGL((bwd_dq_kernel<D, 1>), dim3((unsigned)(blocks128 * bh)), dim3(kThreads), q_lds, stream, pq);
+        hipLaunchKernelGGL(dq_fn, dim3((unsigned)(q_blocks * bh)), dim3(kThreads), q_lds, stream, pq);
     if (dq_only) return hipGetLastError();
     FusedParams pk = p;
     pk.list_ptr = csc_ptr;

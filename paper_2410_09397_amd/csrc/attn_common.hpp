@@ -181,6 +181,16 @@ struct FragAddrs {
             trk[mt][1] = fo.tr(mt, 1);
         }
     }
+    // all fetches `rows` (a multiple of 16) further down the tile
+    __device__ __forceinline__ void shift_rows(int rows) {
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) rmk[ks] += rows * (D * 2);
+#pragma unroll
+        for (int mt = 0; mt < D / 32; ++mt) {
+            trk[mt][0] += rows * (D * 2);
+            trk[mt][1] += rows * (D * 2);
+        }
+    }
     __device__ __forceinline__ bf16x8 frag(const char* lds, int tile_off_bytes, int row0, int ks) const {
         return FragOffsets<D>::read(lds, rmk[ks], tile_off_bytes + row0 * (D * 2));
     }
@@ -371,7 +381,10 @@ __device__ __forceinline__ void decode_block_causal(int linear, int tiles, int b
     const int xcd = linear & (xcds - 1), heads = bh_total / xcds;
     int slot = linear / xcds;
     const int round = slot / cus;
-    if ((round & 1) && round < resident && (round + 1) * cus <= tiles * heads) slot = (2 * round + 1) * cus - 1 - slot;
+    if ((round & 1) && round < resident) {  // (a last round that is not full starts with its shortest as well)
+        const int first = round * cus, last = min(first + cus, tiles * heads) - 1;
+        slot = first + last - slot;
+    }
     rank = slot / heads;
     bh = (slot % heads) * xcds + xcd;
 }
@@ -383,6 +396,19 @@ __device__ __forceinline__ void decode_block_causal(int linear, int tiles, int b
 // 219 / 260 / 221 -> 134 / 157 / 184.  From eight rounds on head order is kept: the tail is short then, and an XCD that
 // works on one head at a time finds more in its L2 (d = 128 b2 h32 n8192: forward the same, dK dV 1982 against 2056 us).
 inline int causal_resident(int grid, int per_cu) { return grid < 8 * 256 * per_cu ? per_cu : 0; }
+
+// Whether a launch of `blocks` blocks of 128 queries, per_cu of which fit a CU, leaves so much of the chip idle that blocks of 64
+// queries, with the two key halves of a tile on two waves, are faster: with one block on a CU a SIMD has one wave, which waits out
+// every latency of its chain.  The line lies where the smaller blocks still fit the chip twice per CU (once at d = 256); under the
+// causal rule half of their tiles do not exist, so they may be twice as many.  us, forward / dQ, 128 -> 64 queries, 16 heads:
+//   d = 128, full     n1024 26 / 32 -> 20 / 23    n2048 50 / 62 -> 47 / 57    n3072 (beyond the line) 88 / 117 -> 110 / 130
+//   d = 128, causal   n1024 26 / 31 -> 19 / 22    n2048 47 / 58 -> 38 / 42    n4096 105 / 131 -> 91 / 110
+//   d = 64, full      n2048 36 / 41 -> 33 / 35    n3072 (beyond) 62 / 75 -> 64 / 69    n4096 (beyond) 95 / 113 -> 102 / 131
+//   d = 256, full     n1024 53 / 64 -> 39 / 43    n1536 (beyond) 76 / 92 -> 100 / 107
+//   d = 256, causal   n2048 96 / 113 -> 77 / 84   n3072 (beyond) 140 / 164 -> 166 / 175
+inline bool few_blocks(int blocks, int per_cu, bool causal) {
+    return (long)blocks * (causal ? 1 : 2) <= 256 * (per_cu < 2 ? per_cu : 2);
+}
 
 // Kernel arguments common to the fused kernels.  Strides are in elements.
 struct FusedParams {
