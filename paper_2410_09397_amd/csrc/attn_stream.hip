@@ -20,8 +20,7 @@
 // backward reaches on the long blocks; for bf16 the vector instructions that split f and p (5.5 per value) and the
 // latency of a step; the shortest calls, launches.  Reading the row operands straight from global memory in MFMA order,
 // without LDS, costs one L1 access per lane (64 per KB instead of 16) and measured 135 and 90 us on the last two.
-#include "attn_common.hpp"
-#include "attn_internal.hpp"
+#include "attn_rows.hpp"
 
 namespace attn {
 
@@ -333,8 +332,9 @@ __device__ __forceinline__ Groups make_groups(const GenericParams& p, int bh, bo
 
 // ------------------------------------------------------------------------------ sum over the waves
 // `factor(w, row)` scales the part of wave w.  red: [NW][16 XG][DP + 4] floats, over the stages.
+// Returns whether this thread met a sum that is not finite.
 template <int KIND, bool QUAD, int DP, int XG, int NW, typename F>
-__device__ __forceinline__ void combine_store(const f32x4 (&acc)[XG][DP / 16], float* red, int w, int lane, char* out, unsigned ldb,
+__device__ __forceinline__ bool combine_store(const f32x4 (&acc)[XG][DP / 16], float* red, int w, int lane, char* out, unsigned ldb,
                                               int row0, int n, int d, F factor) {
     constexpr int kPitch = DP + 4;
     typedef typename Traits<KIND>::T T;
@@ -360,6 +360,7 @@ __device__ __forceinline__ void combine_store(const f32x4 (&acc)[XG][DP / 16], f
     }
     __syncthreads();
     constexpr int kQuads = DP / 4;
+    float bad = 0.f;  // 0 x finite stays 0
     for (int t = w * 64 + lane; t < 16 * XG * kQuads; t += NW * 64) {
         const int r = t / kQuads, c = (t % kQuads) * 4;
         f32x4 s = {0.f, 0.f, 0.f, 0.f};
@@ -371,6 +372,8 @@ __device__ __forceinline__ void combine_store(const f32x4 (&acc)[XG][DP / 16], f
             for (int e = 0; e < 4; ++e) s[e] = fmaf(v[e], f, s[e]);
         }
         if (row0 + r >= n || c >= d) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad = fmaf(s[e], 0.f, bad);
         char* o = out + (size_t)(row0 + r) * ldb + c * sizeof(T);
         if constexpr (KIND != kF32) {
             *reinterpret_cast<u32x2*>(o) = u32x2{pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3])};
@@ -382,6 +385,29 @@ __device__ __forceinline__ void combine_store(const f32x4 (&acc)[XG][DP / 16], f
                 if (c + e < d) reinterpret_cast<float*>(o)[e] = s[e];
         }
     }
+    return !(bad == 0.f);
+}
+
+// The rows of a workgroup once more, one per wave, where a result is not finite (the barrier is passed by every wave
+// either way).  In a matrix product an infinity or a NaN reaches results that must not depend on it: a weight of zero at an
+// invisible row of the step, a zero column of the padded width and the three bf16 parts of a weight all meet it.  The redone
+// rows have what the definition gives.  One test per result; a test of the staged steps doubled the accumulators' registers.
+template <int XG, int NW, typename F>
+__device__ __forceinline__ void redo_rows(bool bad, int w, int row0, int n, F row) {
+    if (!__syncthreads_or(bad)) return;
+    // the kernel's argument is read again here: held in scalar registers for this rare part, it made them spill
+    unsigned long long args = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const GenericParams& p = *reinterpret_cast<const GenericParams*>(args);
+#pragma unroll 1
+    for (int r = row0 + w; r < min(n, row0 + 16 * XG); r += NW) row(p, r);
+}
+
+template <typename T>
+__device__ __forceinline__ float dot_row_pair(const T* a, const T* b, int d) {
+    float s = 0.f;
+    for (int k = 0; k < d; ++k) s = fmaf(ldf(a + k), ldf(b + k), s);
+    return s;
 }
 
 template <typename T>
@@ -651,8 +677,11 @@ __global__ void __launch_bounds__(NW * 64, 2) stream_fwd_kernel(GenericParams p)
             p.LSE_out[(long)bh * p.n + i0 + tid] =
                 L > 0.f ? fmaf(M, kLn2, fmaf(M, -1.90465421e-9f, __builtin_amdgcn_logf(L) * kLn2)) : -__builtin_inff();  // (ln 2 in two parts)
     }
-    combine_store<KIND, QUAD, DP, XG, NW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.O, base)), ldb, i0,
-                                      p.n, p.d, [&](int k, int r) { return st_l[k][r]; });
+    const bool bad = combine_store<KIND, QUAD, DP, XG, NW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.O, base)),
+                                                       ldb, i0, p.n, p.d, [&](int k, int r) { return st_l[k][r]; });
+    redo_rows<XG, NW>(bad, w, i0, p.n, [&](const GenericParams& p, int i) {
+        row_forward<T, (DP + 63) / 64>(p, bh, i, lane, reinterpret_cast<float*>(smem) + w * DP);
+    });
 }
 
 // ----------------------------------------------------------------------------------- backward
@@ -786,8 +815,12 @@ __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, in
         }
     }
     const float scale = p.scale;
-    combine_store<KIND, QUAD, DP, XG, NW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.dQ, base)), ldb, i0,
-                                      p.n, p.d, [&](int, int) { return scale; });
+    const bool bad = combine_store<KIND, QUAD, DP, XG, NW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.dQ, base)),
+                                                       ldb, i0, p.n, p.d, [&](int, int) { return scale; });
+    redo_rows<XG, NW>(bad, w, i0, p.n, [&](const GenericParams& p, int i) {
+        float* rows = reinterpret_cast<float*>(smem) + w * 2 * DP;
+        row_dq<T, (DP + 63) / 64>(p, bh, i, lane, row_delta<T>(p, bh, i, lane), rows, rows + DP);
+    });
 }
 
 // dK, dV of 16 XG keys.  With kOwnDelta the row sums v of the streamed queries are formed here again (fp32: from the
@@ -964,10 +997,19 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
         }
     }
     const float scale = p.scale;
-    combine_store<KIND, QUAD, DP, XG, NW>(dv, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.dV, base)), ldb, j0,
-                                      p.n, p.d, [&](int, int) { return 1.f; });
-    combine_store<KIND, QUAD, DP, XG, NW>(dk, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.dK, base)), ldb, j0,
-                                      p.n, p.d, [&](int, int) { return scale; });
+    const bool bad_v = combine_store<KIND, QUAD, DP, XG, NW>(dv, reinterpret_cast<float*>(smem), w, lane,
+                                                         const_cast<char*>(head_base<T>(p.dV, base)), ldb, j0, p.n, p.d, [&](int, int) { return 1.f; });
+    const bool bad_k = combine_store<KIND, QUAD, DP, XG, NW>(dk, reinterpret_cast<float*>(smem), w, lane,
+                                                         const_cast<char*>(head_base<T>(p.dK, base)), ldb, j0, p.n, p.d, [&](int, int) { return scale; });
+    redo_rows<XG, NW>(bad_v || bad_k, w, j0, p.n, [&](const GenericParams& p, int j) {
+        float* rows = reinterpret_cast<float*>(smem) + w * 2 * DP;
+        const long at = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
+        const auto dot = [&](int i) {
+            const long o = at + (long)i * p.stride_n;
+            return dot_row_pair((const T*)p.O_in + o, (const T*)p.dO + o, p.d);
+        };
+        row_dkdv<T, (DP + 63) / 64>(p, bh, j, lane, dot, rows, rows + DP);
+    });
 }
 
 // One launch for the whole backward: query blocks (dQ) and key blocks (dK, dV) side by side.

@@ -54,3 +54,41 @@ def test_fp32_arithmetic_at_tile_edges(w):
         if np.abs(r).max() > 0:  # a single row has dQ = dK = 0 up to rounding
             den = max(np.abs(r).max(), 1e-3)
             assert np.abs(to_np(g) - r).max() <= tol * den, (w.name, name, np.abs(to_np(g) - r).max() / den)
+
+
+@pytest.mark.parametrize("d,dtype,n", [(80, "f32", 100), (64, "f32", 49), (30, "f32", 77), (96, "bf16", 100), (72, "bf16", 47), (200, "bf16", 81)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_invisible_rows_do_not_reach_results(d, dtype, n, value):
+    """Under the causal rule the results of a query depend on no later key, whatever it holds, and those of a key on no
+    earlier query: with the last keys (queries) not finite the others are what they are without."""
+    import torch
+    from paper_2410_09397_amd import attn
+    print("case", d, dtype, n, value, flush=True)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + n)
+    Q, K, V, dO = (torch.randn((1, 2, n, d), generator=gen, device="cuda").to(t) for _ in range(4))
+    scale, cut = d ** -0.5, n - 5
+    O, LSE = attn.attn_fwd(Q, K, V, scale, causal=True)
+    dQ, dK, dV = attn.attn_bwd(Q, K, V, O, dO, LSE, scale, causal=True)
+    K2, V2 = K.clone(), V.clone()
+    K2[:, :, cut:] = value
+    V2[:, :, cut:] = value
+    O2, LSE2 = attn.attn_fwd(Q, K2, V2, scale, causal=True)
+    dQ2, _, _ = attn.attn_bwd(Q, K2, V2, O, dO, LSE, scale, causal=True)
+    bound = 3e-6 if dtype == "f32" else 2 * BF16_BOUND  # two results, each rounded once
+    for a, b in ((O2, O), (LSE2, LSE), (dQ2, dQ)):
+        a, b = a[:, :, :cut].float(), b[:, :, :cut].float()
+        assert torch.isfinite(a).all()
+        assert (a - b).abs().max() <= bound * max(1.0, float(b.abs().max()))
+    assert not torch.isfinite(O2[:, :, cut:].float()).any()
+    # a bias of minus infinity in the first column leaves a key without weight
+    K3 = K.clone()
+    Q3 = Q.clone()
+    Q3[..., 0] = 1.0
+    K3[:, :, 1, 0] = -float("inf")
+    got = attn.attn_fwd(Q3, K3, V, scale, causal=True)[0].double()
+    s = (Q3.double() @ K3.double().transpose(-1, -2).contiguous()) * scale
+    s = s.masked_fill(torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1), -float("inf"))
+    want = torch.softmax(s, -1) @ V.double()
+    assert (got - want).abs().max() <= bound * float(want.abs().max())
