@@ -1092,7 +1092,13 @@ bool stream_takes(bool is_bf16, const GenericParams& p) {
 
 hipError_t launch_stream(bool is_bf16, bool backward, const GenericParams& p, hipStream_t stream) {
     if (is_bf16) return run_width<kBf3, true>(p, backward, stream);
-    return p.d % 4 == 0 ? run_width<kF32, true>(p, backward, stream) : run_width<kF32, false>(p, backward, stream);
+    // fp32 tensors may start on any 4 bytes: 16-byte copies only where every row does start on 16 (bf16 calls are checked
+    // for that where they enter)
+    uintptr_t all = 0;
+    for (const void* t : {p.Q, p.K, p.V, (const void*)p.O, p.O_in, p.dO, (const void*)p.dQ, (const void*)p.dK, (const void*)p.dV})
+        all |= reinterpret_cast<uintptr_t>(t);
+    const bool quad = (all & 15) == 0 && (p.d | p.stride_n | p.stride_h | p.stride_b) % 4 == 0;
+    return quad ? run_width<kF32, true>(p, backward, stream) : run_width<kF32, false>(p, backward, stream);
 }
 
 }  // namespace attn

@@ -92,3 +92,28 @@ def test_invisible_rows_do_not_reach_results(d, dtype, n, value):
     s = s.masked_fill(torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1), -float("inf"))
     want = torch.softmax(s, -1) @ V.double()
     assert (got - want).abs().max() <= bound * float(want.abs().max())
+
+
+@pytest.mark.parametrize("d,n", [(64, 100), (80, 49)])
+def test_fp32_tensors_that_start_on_4_bytes(d, n):
+    """fp32 tensors need no alignment beyond their own: the results are those of aligned copies."""
+    import torch
+    from paper_2410_09397_amd import attn
+    print("case", d, n, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + n)
+    aligned = [torch.randn((1, 2, n, d), generator=gen, device="cuda") for _ in range(4)]
+
+    def shifted(t):
+        return torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape)
+
+    def both(Q, K, V, dO, like):
+        O, LSE, grads = like(Q), torch.empty((1, 2, n), device="cuda"), tuple(like(t) for t in (Q, K, V))
+        attn.attn_fwd(Q, K, V, d ** -0.5, causal=True, out=(O, LSE))
+        attn.attn_bwd(Q, K, V, O, dO, LSE, d ** -0.5, causal=True, out=grads)
+        return (O, LSE) + grads
+
+    moved = [shifted(t) for t in aligned]
+    assert all(t.data_ptr() % 16 == 4 for t in moved)
+    for a, b in zip(both(*moved, shifted), both(*aligned, torch.empty_like)):
+        assert (a - b).abs().max() <= 3e-6 * max(1.0, float(b.abs().max()))
