@@ -15,8 +15,8 @@
 // Formulas: A, l, f, O, q, p of App. B.4 with the scale, mask and log-sum-exp readings.
 //
 // Forward and backward together, against the row-per-wave FMA kernels of attn_generic.hip (1 TFLOP/s: both operands of
-// every multiply-add come from memory): fp32 b1 h1 n256 d64 347 -> 24.5 us, b2 h6 n777 d80 causal 4250 -> 89 us;
-// bf16 b1 h8 n1500 d96 causal 11650 -> 62 us.  What bounds them now: the fp32 matrix rate (154 TFLOP/s), half of which the
+// every multiply-add come from memory): fp32 b1 h1 n256 d64 347 -> 25 us, b2 h6 n777 d80 causal 4250 -> 90 us;
+// bf16 b1 h8 n1500 d96 causal 11700 -> 63 us.  What bounds them now: the fp32 matrix rate (154 TFLOP/s), half of which the
 // backward reaches on the long blocks; for bf16 the vector instructions that split f and p (5.5 per value) and the
 // latency of a step; the shortest calls, launches.  Reading the row operands straight from global memory in MFMA order,
 // without LDS, costs one L1 access per lane (64 per KB instead of 16) and measured 135 and 90 us on the last two.
