@@ -142,6 +142,7 @@ FusedParams fused_params(const attn_desc* d) {
     p.n = d->n;
     p.scale = d->scale;
     p.causal = d->causal;
+    p.mask_form = true;
     return p;
 }
 

@@ -719,7 +719,7 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     constexpr int kv_lds = 2 * (2 * 64 * D * 2) + 2 * 64 * 64 * 2;  // two stages of Q, dO; P and dS
     constexpr int q_lds = 2 * (2 * 64 * D * 2);
     const int blocks128 = (p.n + 127) / 128;
-    const bool split = few_blocks(blocks128 * bh, dq_per_cu(D), p.causal && !csr_ptr);
+    const bool split = few_blocks(blocks128 * bh, dq_per_cu(D), p.causal && !p.mask_form);
     void (*const dq_fn)(FusedParams) = split ? bwd_dq_split_kernel<D> : bwd_dq_kernel<D, 1>;
     const void* kv_fn = reinterpret_cast<const void*>(bwd_dkdv_kernel<D>);
     // set on every call (the attribute belongs to the current device, and the call is cheap)

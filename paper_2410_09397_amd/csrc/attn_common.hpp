@@ -399,15 +399,18 @@ inline int causal_resident(int grid, int per_cu) { return grid < 8 * 256 * per_c
 
 // Whether a launch of `blocks` blocks of 128 queries, per_cu of which fit a CU, leaves so much of the chip idle that blocks of 64
 // queries, with the two key halves of a tile on two waves, are faster: with one block on a CU a SIMD has one wave, which waits out
-// every latency of its chain.  The line lies where the smaller blocks still fit the chip twice per CU (once at d = 256); under the
-// causal rule half of their tiles do not exist, so they may be twice as many.  us, forward / dQ, 128 -> 64 queries, 16 heads:
+// every latency of its chain.  The line lies where the smaller blocks still fit the chip twice per CU (once at d = 256).  Under the
+// causal rule half of their tiles do not exist, and twice as many are still faster, but not under a block mask, whose lists the
+// host does not know: a call that could have been made with a mask gets the line of the masked one, so that a causal call and
+// the same call through a lower-triangular mask have the same bits.  `half_exist`: causal, and there is no such call (the weight
+// gradient).  us, forward / dQ, 128 -> 64 queries, 16 heads:
 //   d = 128, full     n1024 26 / 32 -> 20 / 23    n2048 50 / 62 -> 47 / 57    n3072 (beyond the line) 88 / 117 -> 110 / 130
 //   d = 128, causal   n1024 26 / 31 -> 19 / 22    n2048 47 / 58 -> 38 / 42    n4096 105 / 131 -> 91 / 110
 //   d = 64, full      n2048 36 / 41 -> 33 / 35    n3072 (beyond) 62 / 75 -> 64 / 69    n4096 (beyond) 95 / 113 -> 102 / 131
 //   d = 256, full     n1024 53 / 64 -> 39 / 43    n1536 (beyond) 76 / 92 -> 100 / 107
 //   d = 256, causal   n2048 96 / 113 -> 77 / 84   n3072 (beyond) 140 / 164 -> 166 / 175
-inline bool few_blocks(int blocks, int per_cu, bool causal) {
-    return (long)blocks * (causal ? 1 : 2) <= 256 * (per_cu < 2 ? per_cu : 2);
+inline bool few_blocks(int blocks, int per_cu, bool half_exist) {
+    return (long)blocks * (half_exist ? 1 : 2) <= 256 * (per_cu < 2 ? per_cu : 2);
 }
 
 // Kernel arguments common to the fused kernels.  Strides are in elements.
@@ -430,6 +433,7 @@ struct FusedParams {
     // masks per (batch, head): entries between the list_ptr (order) arrays of consecutive pairs; 0 = one shared mask
     int list_stride, order_stride;
     int resident;  // causal, no mask: see decode_block_causal
+    bool mask_form;  // the entry point has a form with a block mask: see few_blocks
 };
 
 }  // namespace attn

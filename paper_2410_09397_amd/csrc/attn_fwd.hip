@@ -326,7 +326,7 @@ static hipError_t launch_fwd(const FusedParams& p, const int32_t* csr_ptr, const
                              hipStream_t stream) {
     constexpr int lds = 2 * (2 * 64 * D * 2);
     const int heads = p.batch * p.heads;
-    const bool split = few_blocks((p.n + 127) / 128 * heads, fwd_per_cu(D), p.causal && !csr_ptr);
+    const bool split = few_blocks((p.n + 127) / 128 * heads, fwd_per_cu(D), p.causal && !p.mask_form);
     void (*const fn)(FusedParams) = split ? fwd_split_kernel<D> : fwd_kernel<D>;
     // set on every call: the attribute belongs to the current device, and the call is cheap
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -138,3 +138,24 @@ def test_query_blocks_of_64_and_128_agree(d, kind):
                 assert torch.equal(t[~seen], u[~seen])
                 if n > 1 or k not in (2, 3):  # (one key: dQ = dK = 0 up to rounding)
                     assert_close_norm(t[seen], u[seen], (n, h, k))
+
+
+@pytest.mark.parametrize("d,heads,n", [(64, 24, 2000), (128, 16, 4096), (128, 24, 2000), (256, 12, 1990), (256, 16, 2048)])
+def test_causal_calls_and_lower_triangular_masks_have_the_same_bits(d, heads, n):
+    """Masks only select which tiles are visited: a lower-triangular block mask under the causal rule gives the bits of the causal
+    call, also where the number of blocks decides how a kernel shares them out (the sizes lie on both sides of each line)."""
+    import torch
+    from paper_2410_09397_amd import attn
+    print("case", d, heads, n, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + n)
+    Q, K, V, dO = (torch.randn((1, heads, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    nblk, scale = (n + 127) // 128, d ** -0.5
+    mask = attn.BlockMask(np.tril(np.ones((nblk, nblk), np.uint8)), 128, n)
+    O, LSE = attn.attn_fwd(Q, K, V, scale, causal=True)
+    Om, LSEm = attn.attn_fwd(Q, K, V, scale, causal=True, mask=mask)
+    assert torch.equal(O, Om) and torch.equal(LSE, LSEm)
+    dense = attn.attn_bwd(Q, K, V, O, dO, LSE, scale, causal=True)
+    masked = attn.attn_bwd_blocksparse(Q, K, V, O, dO, LSE, scale, mask, causal=True)
+    for a, b in zip(dense, masked):
+        assert torch.equal(a, b)
