@@ -404,13 +404,6 @@ __device__ __forceinline__ void redo_rows(bool bad, int w, int row0, int n, F ro
 }
 
 template <typename T>
-__device__ __forceinline__ float dot_row_pair(const T* a, const T* b, int d) {
-    float s = 0.f;
-    for (int k = 0; k < d; ++k) s = fmaf(ldf(a + k), ldf(b + k), s);
-    return s;
-}
-
-template <typename T>
 __device__ __forceinline__ const char* head_base(const void* ptr, long base) {
     return reinterpret_cast<const char*>(static_cast<const T*>(ptr) + base);
 }
@@ -680,7 +673,7 @@ __global__ void __launch_bounds__(NW * 64, 2) stream_fwd_kernel(GenericParams p)
     const bool bad = combine_store<KIND, QUAD, DP, XG, NW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.O, base)),
                                                        ldb, i0, p.n, p.d, [&](int k, int r) { return st_l[k][r]; });
     redo_rows<XG, NW>(bad, w, i0, p.n, [&](const GenericParams& p, int i) {
-        row_forward<T, (DP + 63) / 64>(p, bh, i, lane, reinterpret_cast<float*>(smem) + w * DP);
+        row_forward<T, row_words<T>(DP)>(p, bh, i, lane, reinterpret_cast<float*>(smem) + w * DP);
     });
 }
 
@@ -819,7 +812,7 @@ __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, in
                                                        ldb, i0, p.n, p.d, [&](int, int) { return scale; });
     redo_rows<XG, NW>(bad, w, i0, p.n, [&](const GenericParams& p, int i) {
         float* rows = reinterpret_cast<float*>(smem) + w * 2 * DP;
-        row_dq<T, (DP + 63) / 64>(p, bh, i, lane, row_delta<T>(p, bh, i, lane), rows, rows + DP);
+        row_dq<T, row_words<T>(DP)>(p, bh, i, lane, row_delta<T>(p, bh, i, lane), rows, rows + DP);
     });
 }
 
@@ -963,10 +956,16 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
         }
         Weights<KIND> wp[XG], wd[XG];
         Lse2 l2[G][4];
+        float lse_min = lse[0][0];
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) l2[g][i].set(lse[g][i]);
+            for (int i = 0; i < 4; ++i) {
+                l2[g][i].set(lse[g][i]);
+                lse_min = fminf(lse_min, lse[g][i]);
+            }
+        // a query that saw nothing, or nothing but NaN, takes no part whatever its scores and its v are
+        full = full && __builtin_amdgcn_ballot_w64(lse_min == -__builtin_inff()) == 0;
 #pragma unroll
         for (int x = 0; x < XG; ++x) {
             const int key = j0 + 16 * x + r16;
@@ -974,14 +973,20 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
             for (int g = 0; g < G; ++g)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    float f = __builtin_amdgcn_exp2f(scaled(st[x][g][i], p.c_hi, p.c_lo, l2[g][i].hi) - l2[g][i].lo);
-                    if (!full) {
-                        const int q = qb[g] + 4 * h4 + i;
-                        f = q < p.n && (!p.causal || q >= key) ? f : 0.f;
-                    }
-                    st[x][g][i] = f;
-                    dp[x][g][i] = f * (dp[x][g][i] - dl[g][i]);
+                    st[x][g][i] = __builtin_amdgcn_exp2f(scaled(st[x][g][i], p.c_hi, p.c_lo, l2[g][i].hi) - l2[g][i].lo);
+                    dp[x][g][i] = st[x][g][i] * (dp[x][g][i] - dl[g][i]);
                 }
+            if (!full) {  // (one branch for the block: one per value, and the compiler moves the comparisons in front of it)
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int q = qb[g] + 4 * h4 + i;
+                        const bool on = q < p.n && (!p.causal || q >= key) && lse[g][i] != -__builtin_inff();
+                        st[x][g][i] = on ? st[x][g][i] : 0.f;
+                        dp[x][g][i] = on ? dp[x][g][i] : 0.f;
+                    }
+            }
             wp[x].set(st[x]);
             wd[x].set(dp[x]);
         }
@@ -1003,12 +1008,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
                                                          const_cast<char*>(head_base<T>(p.dK, base)), ldb, j0, p.n, p.d, [&](int, int) { return scale; });
     redo_rows<XG, NW>(bad_v || bad_k, w, j0, p.n, [&](const GenericParams& p, int j) {
         float* rows = reinterpret_cast<float*>(smem) + w * 2 * DP;
-        const long at = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
-        const auto dot = [&](int i) {
-            const long o = at + (long)i * p.stride_n;
-            return dot_row_pair((const T*)p.O_in + o, (const T*)p.dO + o, p.d);
-        };
-        row_dkdv<T, (DP + 63) / 64>(p, bh, j, lane, dot, rows, rows + DP);
+        row_dkdv<T, row_words<T>(DP), kOwn>(p, bh, j, lane, rows, rows + DP);
     });
 }
 
