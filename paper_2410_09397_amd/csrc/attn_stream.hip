@@ -481,8 +481,10 @@ __device__ __forceinline__ void balanced_block(int linear, int blocks, int bh_to
 }
 
 // ------------------------------------------------------------------------------------ forward
+// fp32, 32 columns: as many waves as the registers of the loop alone allow (64 instead of 68, which the redone rows would take: 7 %
+// of the time of 32768 heads of 4 rows)
 template <int KIND, bool QUAD, int DP, int XG, int NW>
-__global__ void __launch_bounds__(NW * 64, 2) stream_fwd_kernel(GenericParams p) {
+__global__ void __launch_bounds__(NW * 64, KIND == kF32 && DP == 32 ? (QUAD ? 8 : 7) : 2) stream_fwd_kernel(GenericParams p) {
     typedef Traits<KIND> TR;
     typedef typename TR::T T;
     typedef StageLoader<KIND, QUAD, DP> Loader;
