@@ -77,7 +77,7 @@ static hipError_t run_width(const GenericParams& p, bool backward, hipStream_t s
 
 hipError_t launch_generic(bool is_bf16, bool backward, const GenericParams& p, hipStream_t stream) {
     if (p.d > kMaxD) return hipErrorInvalidValue;
-    if (stream_takes(is_bf16, p)) return launch_stream(is_bf16, backward, p, stream);
+    if (stream_takes(is_bf16, backward, p)) return launch_stream(is_bf16, backward, p, stream);
     return is_bf16 ? run_width<__bf16>(p, backward, stream) : run_width<float>(p, backward, stream);
 }
 

@@ -68,7 +68,7 @@ void launch_generic_delta(bool is_bf16, const GenericParams& p, hipStream_t stre
 hipError_t launch_generic(bool is_bf16, bool backward, const GenericParams& p, hipStream_t stream);
 
 // The same arithmetic on the matrix cores (attn_stream.hip), for the shapes that stream_takes() accepts.
-bool stream_takes(bool is_bf16, const GenericParams& p);
+bool stream_takes(bool is_bf16, bool backward, const GenericParams& p);
 hipError_t launch_stream(bool is_bf16, bool backward, const GenericParams& p, hipStream_t stream);
 
 // Weight gradient g = A_1^T dQ of the paper's loss (bf16, d in {64, 128, 256}, contiguous tensors).

@@ -1084,11 +1084,29 @@ hipError_t run_width(const GenericParams& p, bool backward, hipStream_t stream) 
 
 }  // namespace
 
+// Sequences of a few rows in many heads: a block of 16 or 32 rows costs what it costs with one row in it, and there is one
+// for every head; a row per wave costs by the row.  The line lies where the blocks are more than the CUs hold at a time, and at
+// the rows below which the row kernels win, measured over 64 to 32768 heads.  us, forward / backward, matrix cores -> rows:
+//   fp32 d16    n1 h32768 57 / 180 -> 22 / 47     n2 h4096 11 / 26 -> 11 / 21     n3 h32768 (beyond the line) 58 / 184 -> 65 / 123
+//   fp32 d64    n2 h4096 17 / 50 -> 12 / 28       n5 h4096 (beyond) 18 / 54 -> 31 / 71     n1 h512 (beyond) 11 / 14 -> 11 / 19
+//   fp32 d128   n1 h4096 37 / 216 -> 12 / 28      n6 h4096 backward 218 -> 133, forward (beyond) 39 -> 66
+//   bf16 d32    n2 h32768 91 / 372 -> 42 / 88     n4 h32768 92 / 375 -> 86 / 191   n8 h4096 (beyond) 15 / 46 -> 25 / 49
+//   bf16 d192   n6 h4096 80 / 246 -> 50 / 111     n8 h32768 (beyond) 643 / 2028 -> 722 / 1653
+static bool few_rows(bool is_bf16, bool backward, const GenericParams& p) {
+    const int rows = is_bf16 ? (p.d > 128 || (backward && p.d > 64) ? 6 : 4) : (backward && p.d > 96 ? 6 : 2);
+    const long width = (p.d + 31) / 32 * 32;
+    return p.n <= rows && (long)p.batch * p.heads * width >= (is_bf16 ? 65536 : 98304);
+}
+
 // What is left to the FMA kernels: head dimensions whose accumulators, owned rows and stages do not fit a CU here,
-// block edges that cut through the rows a workgroup owns, and heads of 4 GB and more (32-bit byte offsets).
-bool stream_takes(bool is_bf16, const GenericParams& p) {
+// block edges that cut through the rows a workgroup owns, heads of 4 GB and more (32-bit byte offsets), few rows in many
+// heads, and more blocks than a launch of 2^32 threads has.
+bool stream_takes(bool is_bf16, bool backward, const GenericParams& p) {
     if (p.d > (is_bf16 ? 256 : 128)) return false;
-    if (p.csr_ptr && p.block % (is_bf16 && p.d <= 128 ? 32 : 16) != 0) return false;
+    const int owned = is_bf16 && p.d <= 128 ? 32 : 16;
+    if (p.csr_ptr && p.block % owned != 0) return false;
+    if (few_rows(is_bf16, backward, p)) return false;
+    if ((double)p.batch * p.heads * (((long)p.n + owned - 1) / owned) * (backward ? 2 : 1) * 256.0 >= 4294967296.0) return false;
     return (double)p.n * (double)p.stride_n * (is_bf16 ? 2.0 : 4.0) < 4.0e9;
 }
 

@@ -188,3 +188,61 @@ def test_steps_that_are_not_finite_take_a_few_finite_ones(dtype, d, n, heads):
     print("step us, finite %.1f, NaN %.1f" % (finite, nan), flush=True)
     assert torch.isnan(out[1]).all() and torch.isnan(out[2]).all()
     assert nan <= 8 * finite
+
+
+def reference(Q, K, V, dO, scale, causal):
+    """O, LSE, dQ, dK, dV in float64, without a mask."""
+    import torch
+    Q, K, V, dO = (t.double() for t in (Q, K, V, dO))
+    s = scale * (Q @ K.transpose(-1, -2).contiguous())
+    if causal:
+        s = s.masked_fill(torch.ones(s.shape[-2:], dtype=torch.bool, device=s.device).triu(1), -float("inf"))
+    LSE = torch.logsumexp(s, -1)
+    f = torch.exp(s - LSE[..., None])
+    O = f @ V
+    p = f * (dO @ V.transpose(-1, -2).contiguous() - (O * dO).sum(-1, keepdim=True))
+    t = lambda x: x.transpose(-1, -2).contiguous()
+    return O, LSE, scale * (p @ K), scale * (t(p) @ Q), t(f) @ dO
+
+
+def check_reference(case, out, ref, dtype):
+    tol = 3e-6 if dtype == "f32" else BF16_BOUND
+    for name, x, r in zip(("O", "LSE", "dQ", "dK", "dV"), out, ref):
+        assert (x.double() - r).abs().max() <= (3e-6 if name == "LSE" else tol) * max(1.0, float(r.abs().max())), (case, name)
+
+
+# heads and rows on both sides of the line between the row kernels and the matrix-core kernels, and of where they meet in
+# one step (the backward has a line of its own)
+@pytest.mark.parametrize("dtype,d,heads,rows", [("f32", 64, (1535, 1536), (1, 2, 3)), ("f32", 17, (3071, 3072), (2, 3)), ("f32", 128, (767, 768), (2, 6, 7)),
+                                                ("bf16", 32, (2047, 2048), (4, 5)), ("bf16", 96, (682, 683), (4, 6, 7)), ("bf16", 192, (341, 342), (6, 7))])
+@pytest.mark.parametrize("causal", [False, True])
+def test_few_rows_in_many_heads(dtype, d, heads, rows, causal):
+    import torch
+    from paper_2410_09397_amd import attn
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    for h in heads:
+        for n in rows:
+            print("case", dtype, d, h, n, causal, flush=True)
+            Q, K, V, dO = (torch.randn((1, h, n, d), generator=gen, device="cuda").to(t) for _ in range(4))
+            O, LSE = attn.attn_fwd(Q, K, V, d ** -0.5, causal=causal)
+            ref = reference(Q, K, V, dO, d ** -0.5, causal)
+            grads = attn.attn_bwd(Q, K, V, ref[0].to(t), dO, ref[1].float(), d ** -0.5, causal=causal)
+            if t == torch.bfloat16:  # v from the rounded O, which the backward is given
+                f = torch.exp(d ** -0.5 * (Q.double() @ K.double().transpose(-1, -2).contiguous()) - ref[1][..., None])
+                f = f.tril() if causal else f
+                p = f * (dO.double() @ V.double().transpose(-1, -2).contiguous() - (ref[0].to(t).double() * dO.double()).sum(-1, keepdim=True))
+                ref = ref[:2] + (d ** -0.5 * (p @ K.double()), d ** -0.5 * (p.transpose(-1, -2).contiguous() @ Q.double()), ref[4])
+            check_reference((dtype, d, h, n, causal), (O, LSE) + grads, ref, dtype)
+
+
+def test_more_heads_than_one_launch_has_workgroups_for():
+    """2^23 heads of three rows: one workgroup of 256 threads per head and role would be 2^32 threads, which no launch has."""
+    import torch
+    from paper_2410_09397_amd import attn
+    print("case 2^23 heads", flush=True)
+    Q, K, V, dO = (torch.randn((4, 2 ** 21, 3, 1), device="cuda") for _ in range(4))
+    O, LSE = attn.attn_fwd(Q, K, V, 1.0, causal=True)
+    grads = attn.attn_bwd(Q, K, V, O, dO, LSE, 1.0, causal=True)
+    check_reference("2^23 heads", (O, LSE) + grads, reference(Q, K, V, dO, 1.0, True), "f32")
