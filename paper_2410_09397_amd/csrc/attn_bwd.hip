@@ -690,6 +690,7 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem) {
 }
 
 constexpr int dq_per_cu(int d) { return d == 64 ? 4 : d == 128 ? 2 : 1; }
+constexpr int dq_split_per_cu(int d) { return d == 64 ? 3 : dq_per_cu(d); }  // (130 registers at d = 64)
 
 template <int D, int QT>
 __global__ void __launch_bounds__(kThreads, QT == 1 ? dq_per_cu(D) : 1) bwd_dq_kernel(FusedParams p) {
@@ -698,7 +699,7 @@ __global__ void __launch_bounds__(kThreads, QT == 1 ? dq_per_cu(D) : 1) bwd_dq_k
 }
 
 template <int D>
-__global__ void __launch_bounds__(kThreads, D == 64 ? 3 : dq_per_cu(D)) bwd_dq_split_kernel(FusedParams p) {
+__global__ void __launch_bounds__(kThreads, dq_split_per_cu(D)) bwd_dq_split_kernel(FusedParams p) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     dq_block<D, 1, 2>(p, smem);
 }
@@ -765,7 +766,7 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     FusedParams pq = p;
     // with an order list both halves of every 128-query block (the last one may lie past n: it writes nothing)
     const int q_blocks = !split ? blocks128 : order_q ? 2 * blocks128 : (p.n + 63) / 64;
-    if (p.causal && !csr_ptr) pq.resident = causal_resident(q_blocks * bh, dq_per_cu(D));
+    if (p.causal && !csr_ptr) pq.resident = causal_resident(q_blocks * bh, split ? dq_split_per_cu(D) : dq_per_cu(D));
     pq.list_ptr = csr_ptr;
     pq.list_idx = csr_idx;
     pq.order = order_q;
