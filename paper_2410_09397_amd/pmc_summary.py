@@ -22,7 +22,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COPY_BYTES = float(1 << 30)  # bytes read, and bytes written, by the calibration copy
 BWD_KERNELS = ("delta_kernel", "bwd_dkdv", "bwd_dq", "ld_scores_kernel<2>", "ld_scores_kernel<(attn::ScoreMode)2>", "ld_gemm_kernel", "generic_delta",
                "generic_dq", "generic_dkdv", "block_len_kernel", "block_order_kernel", "block_order_fused_kernel", "bwd_prep_kernel",
-               "bwd_onepass_kernel", "bwd_splitd_kernel")
+               "bwd_onepass_kernel", "bwd_splitd_kernel", "stream_bwd_kernel")
 
 
 def source_hash():
@@ -41,8 +41,10 @@ def source_hash():
 
 def traffic_key(workload, tiling):
     return workload if not tiling else "%s@tiling%d" % (workload, tiling)
-FWD_KERNELS = ("fwd_kernel", "ld_scores_kernel<0>", "ld_scores_kernel<1>", "ld_scores_kernel<(attn::ScoreMode)0>",
+FWD_KERNELS = ("fwd_kernel", "fwd_split_kernel", "ld_scores_kernel<0>", "ld_scores_kernel<1>", "ld_scores_kernel<(attn::ScoreMode)0>",
                "ld_scores_kernel<(attn::ScoreMode)1>", "ld_lse_combine", "generic_fwd")
+# launched by neither attn_fwd nor attn_bwd: the weight gradient's own and the measurement aids
+OTHER_KERNELS = ("wgrad_partial", "wgrad_reduce", "proj_kernel", "tile_skeleton_kernel", "mfma_ceiling_kernel")
 
 
 def _one(pattern):
@@ -227,7 +229,7 @@ def kernel_resources(sources=None):
             if m.group(1):
                 name = subprocess.run(["c++filt", m.group(1)], capture_output=True, text=True).stdout.strip()
                 if name.startswith("_Z"):  # c++filt does not know the bf16 type code
-                    name = re.sub(r"^_ZN4attn\d+(\w+?)IDF16bEEv.*$", r"\1<bf16>", name)
+                    name = re.sub(r"^_ZN4attn\d+(\w+?)IDF16b(?:Li(\d+)E)?EEv.*$", lambda m: m.group(1) + ("<bf16, %s>" % m.group(2) if m.group(2) else "<bf16>"), name)
                 cur = {"kernel": short(name)}
                 rows.append(cur)
             elif cur is not None:
