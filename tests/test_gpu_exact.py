@@ -190,8 +190,8 @@ def test_steps_that_are_not_finite_take_a_few_finite_ones(dtype, d, n, heads):
     assert nan <= 8 * finite
 
 
-def reference(Q, K, V, dO, scale, causal):
-    """O, LSE, dQ, dK, dV in float64, without a mask."""
+def reference(Q, K, V, dO, scale, causal, O_in=None):
+    """O, LSE, dQ, dK, dV in float64, without a mask; the gradients with the O that the backward is given."""
     import torch
     Q, K, V, dO = (t.double() for t in (Q, K, V, dO))
     s = scale * (Q @ K.transpose(-1, -2).contiguous())
@@ -200,7 +200,7 @@ def reference(Q, K, V, dO, scale, causal):
     LSE = torch.logsumexp(s, -1)
     f = torch.exp(s - LSE[..., None])
     O = f @ V
-    p = f * (dO @ V.transpose(-1, -2).contiguous() - (O * dO).sum(-1, keepdim=True))
+    p = f * (dO @ V.transpose(-1, -2).contiguous() - ((O if O_in is None else O_in.double()) * dO).sum(-1, keepdim=True))
     t = lambda x: x.transpose(-1, -2).contiguous()
     return O, LSE, scale * (p @ K), scale * (t(p) @ Q), t(f) @ dO
 
@@ -211,6 +211,21 @@ def check_reference(case, out, ref, dtype):
         assert (x.double() - r).abs().max() <= (3e-6 if name == "LSE" else tol) * max(1.0, float(r.abs().max())), (case, name)
 
 
+def check_call(dtype, d, h, n, causal, gen):
+    """Forward, and backward on the rounded O and LSE, into outputs that hold NaN, against float64."""
+    import torch
+    from paper_2410_09397_amd import attn
+    t, scale = torch.float32 if dtype == "f32" else torch.bfloat16, d ** -0.5
+    Q, K, V, dO = (torch.randn((1, h, n, d), generator=gen, device="cuda").to(t) for _ in range(4))
+    nan = lambda: torch.full_like(Q, float("nan"))
+    O, LSE, grads = nan(), torch.full((1, h, n), float("nan"), device="cuda"), (nan(), nan(), nan())
+    attn.attn_fwd(Q, K, V, scale, causal=causal, out=(O, LSE))
+    ref = reference(Q, K, V, dO, scale, causal)
+    O_in = ref[0].to(t)
+    attn.attn_bwd(Q, K, V, O_in, dO, ref[1].float(), scale, causal=causal, out=grads)
+    check_reference((dtype, d, h, n, causal), (O, LSE) + grads, ref[:2] + reference(Q, K, V, dO, scale, causal, O_in)[2:], dtype)
+
+
 # heads and rows on both sides of the line between the row kernels and the matrix-core kernels, and of where they meet in
 # one step (the backward has a line of its own)
 @pytest.mark.parametrize("dtype,d,heads,rows", [("f32", 64, (1535, 1536), (1, 2, 3)), ("f32", 17, (3071, 3072), (2, 3)), ("f32", 128, (767, 768), (2, 6, 7)),
@@ -218,23 +233,12 @@ def check_reference(case, out, ref, dtype):
 @pytest.mark.parametrize("causal", [False, True])
 def test_few_rows_in_many_heads(dtype, d, heads, rows, causal):
     import torch
-    from paper_2410_09397_amd import attn
-    t = torch.float32 if dtype == "f32" else torch.bfloat16
     gen = torch.Generator(device="cuda")
     gen.manual_seed(d)
     for h in heads:
         for n in rows:
             print("case", dtype, d, h, n, causal, flush=True)
-            Q, K, V, dO = (torch.randn((1, h, n, d), generator=gen, device="cuda").to(t) for _ in range(4))
-            O, LSE = attn.attn_fwd(Q, K, V, d ** -0.5, causal=causal)
-            ref = reference(Q, K, V, dO, d ** -0.5, causal)
-            grads = attn.attn_bwd(Q, K, V, ref[0].to(t), dO, ref[1].float(), d ** -0.5, causal=causal)
-            if t == torch.bfloat16:  # v from the rounded O, which the backward is given
-                f = torch.exp(d ** -0.5 * (Q.double() @ K.double().transpose(-1, -2).contiguous()) - ref[1][..., None])
-                f = f.tril() if causal else f
-                p = f * (dO.double() @ V.double().transpose(-1, -2).contiguous() - (ref[0].to(t).double() * dO.double()).sum(-1, keepdim=True))
-                ref = ref[:2] + (d ** -0.5 * (p @ K.double()), d ** -0.5 * (p.transpose(-1, -2).contiguous() @ Q.double()), ref[4])
-            check_reference((dtype, d, h, n, causal), (O, LSE) + grads, ref, dtype)
+            check_call(dtype, d, h, n, causal, gen)
 
 
 def test_more_heads_than_one_launch_has_workgroups_for():
@@ -246,3 +250,47 @@ def test_more_heads_than_one_launch_has_workgroups_for():
     O, LSE = attn.attn_fwd(Q, K, V, 1.0, causal=True)
     grads = attn.attn_bwd(Q, K, V, O, dO, LSE, 1.0, causal=True)
     check_reference("2^23 heads", (O, LSE) + grads, reference(Q, K, V, dO, 1.0, True), "f32")
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 30), ("f32", 64), ("f32", 80), ("f32", 128), ("bf16", 32), ("bf16", 40), ("bf16", 96), ("bf16", 160)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_more_than_two_workgroups_per_cu(dtype, d, causal):
+    """From 513 workgroups on they have four waves instead of eight, and causal ones come in rounds of 256, every second one
+    reversed: a second full round and one that is not full, in the forward (the backward has twice as many), and several."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    per_head = -(-200 // (32 if dtype == "bf16" and d <= 128 else 16))
+    for blocks in (520, 1300):
+        h = -(-blocks // per_head)
+        print("case", dtype, d, h, causal, flush=True)
+        check_call(dtype, d, h, 200, causal, gen)
+
+
+@pytest.mark.parametrize("d,block,n,heads", [(64, 32, 300, 3), (128, 32, 200, 3), (128, 96, 500, 40)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_bf16_mask_blocks_that_are_multiples_of_32(d, block, n, heads, causal):
+    """Up to d = 128 a bf16 workgroup owns 32 rows, which a mask edge may not cut."""
+    test_fp32_arithmetic_at_tile_edges(W(1, heads, n, d, "bf16", sparse=True, block=block, extra_frac=0.3, causal=causal))
+
+
+@pytest.mark.parametrize("d", [96, 192])
+def test_weights_are_carried_in_full(d):
+    """Sums that cancel to 2^-9 of their terms: weights of 16 bits are four bounds off, of 8 bits thousands (tests/test_cancelling.py).
+    96 columns as they are, and with as many zero ones behind them, where a workgroup owns 16 rows instead of 32."""
+    import torch
+    from paper_2410_09397_amd import attn
+    from tests import cancelling
+    Q, K, V, dO, O_in, LSE, sums = cancelling.inputs(64, 7)
+
+    def dev(x):
+        return to_dev(np.concatenate([x, np.zeros(x.shape[:2] + (d - cancelling.D,))], axis=2)[None], "bf16")
+
+    Q, K, V, dO, O_in = (dev(x) for x in (Q, K, V, dO, O_in))
+    got = {"O": attn.attn_fwd(Q, K, V, cancelling.SCALE)[0]}
+    got["dQ"], got["dK"], got["dV"] = attn.attn_bwd(Q, K, V, O_in, dO, to_dev(LSE[None], "f32"), cancelling.SCALE)
+    for name in sums:
+        ref, bound = cancelling.expected(sums, name)
+        worst = float((np.abs(to_np(got[name])[0, :, 0, :cancelling.D][:, sums[name][4]] - ref) / bound).max())
+        print("cancelling d=%d %s: %.2f of the bound" % (d, name, worst), flush=True)
+        assert worst <= 1.0, name
