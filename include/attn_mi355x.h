@@ -33,7 +33,13 @@
  *     for d in {512, 1024} without block mask and n <= 32768 (four-phase path through the
  *     workspace; d = 1024 is supported there only); every other supported case, ATTN_F32 always,
  *     runs in fp32 arithmetic: on the matrix cores for d <= 128 (ATTN_F32) or d <= 256 (ATTN_BF16) and
- *     mask blocks that are a multiple of 16, on fp32 FMA kernels beyond.
+ *     mask blocks that are a multiple of 16 (ATTN_BF16 with d <= 128: of 32), on fp32 FMA kernels beyond and for
+ *     sequences of up to 2 to 6 rows in some hundreds of heads or more.
+ *   - The same call gives the same bits (but for dQ of the one-pass tilings, see below).  How a head's sums are shared out
+ *     over the waves depends on batch * heads and n: the bits of a head may differ in the last places
+ *     between calls with other heads beside it.  Where a call and its masked form run on the same kernels (blocks of 128
+ *     for d in {64, 128, 256} in bf16; the matrix-core kernels of fp32 arithmetic), a mask that keeps every block gives
+ *     the bits of the call without one, and one that keeps the lower triangle, with causal = 1, those of the causal call.
  */
 #ifndef ATTN_MI355X_H
 #define ATTN_MI355X_H

@@ -409,6 +409,12 @@ inline int causal_resident(int grid, int per_cu) { return grid < 8 * 256 * per_c
 //   d = 64, full      n2048 36 / 41 -> 33 / 35    n3072 (beyond) 62 / 75 -> 64 / 69    n4096 (beyond) 95 / 113 -> 102 / 131
 //   d = 256, full     n1024 53 / 64 -> 39 / 43    n1536 (beyond) 76 / 92 -> 100 / 107
 //   d = 256, causal   n2048 96 / 113 -> 77 / 84   n3072 (beyond) 140 / 164 -> 166 / 175
+// and calls on both sides of the line with the rule against 128 queries always (us, forward / backward with dK dV, 16 heads; a
+// mask keeps the diagonal and the stated share of the other blocks):
+//   d = 64, causal    n1024 19 / 39 -> 15 / 32    n2048 34 / 72 -> 26 / 57
+//   d = 64, mask 10 % n2048 14 / 35 -> 13 / 33    40 % and causal n2048 17 / 43 -> 15 / 41
+//   d = 128, mask 10 % n1024 13 / 35 -> 11 / 31   n2048 19 / 52 -> 18 / 51    40 % and causal n2048 23 / 65 -> 20 / 63
+//   d = 256, mask 10 % n600 26 / 57 -> 19 / 47    n1024 26 / 63 -> 20 / 53    40 % and causal n1024 38 / 80 -> 28 / 65
 inline bool few_blocks(int blocks, int per_cu, bool half_exist) {
     return (long)blocks * (half_exist ? 1 : 2) <= 256 * (per_cu < 2 ? per_cu : 2);
 }

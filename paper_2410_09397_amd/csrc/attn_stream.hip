@@ -14,12 +14,13 @@
 //          second products run once per part
 // Formulas: A, l, f, O, q, p of App. B.4 with the scale, mask and log-sum-exp readings.
 //
-// Forward and backward together, against the row-per-wave FMA kernels of attn_generic.hip (1 TFLOP/s: both operands of
-// every multiply-add come from memory): fp32 b1 h1 n256 d64 347 -> 25 us, b2 h6 n777 d80 causal 4250 -> 90 us;
-// bf16 b1 h8 n1500 d96 causal 11700 -> 63 us.  What bounds them now: the fp32 matrix rate (154 TFLOP/s), half of which the
-// backward reaches on the long blocks; for bf16 the vector instructions that split f and p (5.5 per value) and the
-// latency of a step; the shortest calls, launches.  Reading the row operands straight from global memory in MFMA order,
-// without LDS, costs one L1 access per lane (64 per KB instead of 16) and measured 135 and 90 us on the last two.
+// Forward + backward, each timed by itself with calls back to back, against the row-per-wave FMA kernels as they were when these
+// were written (1 TFLOP/s: both operands of every multiply-add came from memory): fp32 b1 h1 n256 d64 347 -> 25 us for the step,
+// b2 h6 n777 d80 causal 1416 + 2173 -> 21 + 69 us, bf16 b1 h8 n1500 d96 causal 4050 + 5550 -> 18 + 43 us.  What bounds them now:
+// fp32 the matrix pipe, busy for 60 % of the CUs' cycles in the long backward and 50 % in the forward; bf16 the vector
+// instructions that split f and p (6 to 9 per matrix instruction, which is busy for 19 to 30 %) and the latency of a step;
+// the shortest calls, launches.  Reading the row operands straight from global memory in MFMA order, without LDS, costs
+// one L1 access per lane (64 per KB instead of 16) and measured 135 and 90 us on the last two.
 #include "attn_rows.hpp"
 
 namespace attn {
@@ -462,7 +463,9 @@ __host__ __device__ constexpr bool eight_waves(bool backward) {
 // head on one XCD.  Under the causal rule a block's work grows with its distance from one end, and which workgroups share
 // a CU decides the run time: workgroup L lands on CU L mod 256 while there is room, so ranks (longest first over all heads)
 // are laid out in rounds of 256, every second one reversed, and each CU gets a long, a short, a long ... one.  (In
-// head order some CUs had twice the average work.)
+// head order some CUs had twice the average work.)  Time in head order over time in this order, the causal half of the shapes
+// below: forward 0.9 to 1.65, backward 0.82 to 1.66, on average 1.0 up to 256 workgroups, 1.1 to 1.5 up to 2048; beyond 4096 0.96 to 1.06:
+// there the order no longer matters, and it needs no upper line.
 __device__ __forceinline__ void balanced_block(int linear, int blocks, int bh_total, int roles, int causal, int& bh, int& rank, int& role) {
     const int per = bh_total * roles;
     if (!causal) {
@@ -1045,9 +1048,10 @@ hipError_t launch_waves(const GenericParams& p, dim3 grid, hipStream_t stream) {
 
 // A wave's step is a chain of copies, LDS reads, products and exponentials, so two waves per SIMD are wanted and short
 // chains: eight waves per workgroup while there are at most two workgroups per CU, four beyond, where two or more
-// workgroups on a CU fill each other's prologue and final sum.  (Forward: bf16 b1 h8 n1500 d96 causal, 376 workgroups,
-// 26.6 us with four and 20.5 with eight; fp32 b2 h6 n777 d80 causal, 588 workgroups, 26 and 29; backward of the two,
-// 752 and 1176 workgroups, 51 and 59, 77 and 87.  Two and three stages per wave hid no more than one.)
+// workgroups on a CU fill each other's prologue and final sum.  Time with eight over time with four, 324 shapes of n = 200 to
+// 2000, 2 to 64 heads, d = 32 to 192, both types, causal and full: up to 256 workgroups 0.69 to 1.0, 257 to 512 0.81 to 1.38 (either
+// can win, by how full the second round is), 513 to 768 0.96 to 1.59, beyond 0.96 to 1.96.  Two and three stages per wave hid
+// no more than one.
 template <int KIND, bool QUAD, int DP, bool BACKWARD>
 hipError_t run_waves(const GenericParams& p, hipStream_t stream) {
     constexpr int rows = 16 * kOwned<KIND, DP>;

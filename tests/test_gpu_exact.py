@@ -1,6 +1,8 @@
-"""The fp32-arithmetic matrix-core kernels (fp32 tensors, bf16 tensors of any head dimension, block masks of any edge
-that is a multiple of 16) at the edges of their tiles: head dimensions on both sides of every padded width, including
-those that are no multiple of 4 (fp32), and lengths around 16- and 32-row steps and the four waves' turns.
+"""The fp32-arithmetic matrix-core kernels (fp32 tensors, bf16 tensors of any head dimension, block masks whose edge is a
+multiple of the rows that a workgroup owns: 32 for bf16 up to d = 128, else 16) at the edges of their tiles: head dimensions on
+both sides of every padded width, including those that are no multiple of 4 (fp32), and lengths around 16- and 32-row steps and
+the turns of the eight waves that a workgroup has in calls of this size; larger calls, with four waves, further down, and with
+them the FMA kernels that take the rest (here: bf16 d = 128 under blocks of 16).
 
 Bounds: fp32 arithmetic on both storage types, so the error is that of sums of at most n + d terms in fp32, about
 sqrt(n + d) 2^-24 = 1.5e-6 of the largest value at the sizes here (fp32 storage: the regression bound of tests/helpers, 3e-6); with

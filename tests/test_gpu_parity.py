@@ -15,7 +15,7 @@ def W(name, index, b, h, n, d, dtype, **kw):
 
 
 CASES = [
-    # the fp32 workload as specified, and ragged fp32 shapes (generic fp32-FMA kernels)
+    # the fp32 workload as specified, and ragged fp32 shapes (fp32 arithmetic on the matrix cores)
     synth.workload(1),
     W("f32_ragged", 11, 2, 2, 77, 40, "f32"),
     W("f32_ragged_causal", 12, 1, 3, 131, 24, "f32", causal=True),
@@ -38,7 +38,7 @@ CASES = [
     W("bf16_d128_sparse_ragged", 42, 1, 1, 1000, 128, "bf16", sparse=True, extra_frac=0.15),
     W("bf16_d64_sparse_causal", 43, 1, 2, 768, 64, "bf16", sparse=True, causal=True, extra_frac=0.5),
     W("bf16_d128_sparse_causal_ragged", 44, 1, 2, 1100, 128, "bf16", sparse=True, causal=True, extra_frac=0.4),
-    # one mask per (batch, head) pair: fused kernels and the generic ones
+    # one mask per (batch, head) pair: fused kernels and those of fp32 arithmetic
     W("bf16_d128_masks_per_head", 45, 2, 3, 900, 128, "bf16", sparse=True, extra_frac=0.3, per_head_masks=True),
     W("bf16_d64_masks_per_head_causal", 46, 1, 4, 640, 64, "bf16", sparse=True, causal=True, extra_frac=0.5,
       per_head_masks=True),
@@ -59,8 +59,8 @@ CASES = [
     W("bf16_d1024_65_rows_causal", 65, 1, 1, 65, 1024, "bf16", causal=True),
     W("bf16_d1024", 58, 1, 1, 256, 1024, "bf16"),
     W("bf16_d1024_ragged_causal", 59, 1, 2, 150, 1024, "bf16", causal=True),
-    # shapes only the generic fp32-FMA kernels take: bf16 with d outside {64,128,256,512},
-    # d = 512 under a block mask, and a block edge other than 128
+    # bf16 with d outside {64,128,256,512} (fp32 arithmetic on the matrix cores), and d = 512 under a block mask (the fp32-FMA
+    # kernels)
     W("bf16_d96_generic", 56, 1, 2, 150, 96, "bf16", causal=True),
     W("bf16_d512_sparse_generic", 57, 1, 1, 256, 512, "bf16", sparse=True, block=64, extra_frac=0.4),
 ]
@@ -175,7 +175,7 @@ def test_backward_is_deterministic():
                                        (96, "bf16", 150), (40, "f32", 150)])
 def test_strided_layout_matches_contiguous(d, dtype, n):
     """[batch, n, heads, d] storage viewed as [batch, heads, n, d] gives the same bits, on every path:
-    fused (d = 64, 128, 256), four-phase (512) and the generic fp32-FMA kernels (bf16 d = 96, fp32)."""
+    fused (d = 64, 128, 256), four-phase (512) and fp32 arithmetic on the matrix cores (bf16 d = 96, fp32)."""
     import torch
     from paper_2410_09397_amd import attn
     w = W("strided", 63, 2, 3, n, d, dtype, causal=True)
@@ -245,7 +245,7 @@ def test_empty_and_fully_masked_rows():
     for g, r in zip((dQ, dK, dV), rg):
         assert rel_err(to_np(g), r) <= TOL["bf16"]
 
-    # the same on the generic fp32 kernels (block edge 16): rows 16..31 keep nothing
+    # the same in fp32 arithmetic (block edge 16): rows 16..31 keep nothing
     w = W("emptyrow_generic", 67, 1, 2, 48, 24, "f32", block=16)
     inp = synth.make_inputs(w)
     O, LSE, dQ, dK, dV = _run_all(w, inp, keep, False)
