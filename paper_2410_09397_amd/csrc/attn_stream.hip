@@ -979,7 +979,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     st[x][g][i] = __builtin_amdgcn_exp2f(scaled(st[x][g][i], p.c_hi, p.c_lo, l2[g][i].hi) - l2[g][i].lo);
-                    dp[x][g][i] = st[x][g][i] * (dp[x][g][i] - dl[g][i]);
+                    dp[x][g][i] -= dl[g][i];
                 }
             if (!full) {  // (one branch for the block: one per value, and the compiler moves the comparisons in front of it)
 #pragma unroll
@@ -992,6 +992,10 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
                         dp[x][g][i] = on ? dp[x][g][i] : 0.f;
                     }
             }
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dp[x][g][i] *= st[x][g][i];
             wp[x].set(st[x]);
             wd[x].set(dp[x]);
         }
