@@ -65,7 +65,8 @@ typedef enum { ATTN_F32 = 0, ATTN_BF16 = 1 } attn_dtype;
  * Tilings of the bf16 backward.  All compute the same gradients; they
  * differ in which block stays on chip, i.e. in the cache size M they need and in the traffic they
  * cause (the trade-off of Thm 1.1 / Sec. 4), and exist side by side so that it can be measured.
- *   ATTN_BWD_AUTO          the library's choice (the fastest measured for the shape)
+ *   ATTN_BWD_AUTO          the library's choice (the fastest measured for the shape); where that is the
+ *                          next one, small calls run its two owners in one launch, with the same bits
  *   ATTN_BWD_TWO_KERNEL    a query-block owner forms dQ and a key-block owner forms dK, dV; both
  *                          recompute f and p (14 d multiply-adds per pair for 10 d counted); no
  *                          atomics, every output bit-reproducible; d in {64, 128, 256}

@@ -143,6 +143,7 @@ FusedParams fused_params(const attn_desc* d) {
     p.scale = d->scale;
     p.causal = d->causal;
     p.mask_form = true;
+    p.may_join = d->bwd_tiling == ATTN_BWD_AUTO;
     return p;
 }
 

@@ -80,15 +80,17 @@ __global__ void __launch_bounds__(kThreads) block_order_kernel(const int32_t* le
 // kOrderFusedBlocks blocks: workgroup (mask, kind) keeps the lengths in LDS and ranks them there (four small
 // launches in front of the backward kernels cost as much as 2 % of a block-sparse call).
 constexpr int kOrderFusedBlocks = 256;
-__global__ void __launch_bounds__(kThreads) block_order_fused_kernel(const int32_t* row_ptr, const int32_t* col_idx,
-                                                                    const int32_t* col_ptr, const int32_t* row_idx,
-                                                                    int nblk, int causal, int32_t* order_q,
-                                                                    int32_t* order_k, int first_kind) {
-    __shared__ int32_t len[kOrderFusedBlocks];
-    const int kind = first_kind + blockIdx.y;  // 0: row lists (query blocks), 1: column lists (key blocks)
-    const int32_t* ptr = (kind ? col_ptr : row_ptr) + (long)blockIdx.x * (nblk + 1);  // mask blockIdx.x
-    const int32_t* idx = kind ? row_idx : col_idx;
-    int32_t* order = (kind ? order_k : order_q) + (long)blockIdx.x * nblk;
+struct OrderParams {
+    const int32_t *row_ptr, *col_idx, *col_ptr, *row_idx;
+    int32_t *order_q, *order_k;
+    int nblk, causal;
+};
+// kind 0: row lists (query blocks), 1: column lists (key blocks)
+__device__ __forceinline__ void rank_blocks(const OrderParams& p, int mask, int kind, int32_t* len) {
+    const int nblk = p.nblk, causal = p.causal;
+    const int32_t* ptr = (kind ? p.col_ptr : p.row_ptr) + (long)mask * (nblk + 1);
+    const int32_t* idx = kind ? p.row_idx : p.col_idx;
+    int32_t* order = (kind ? p.order_k : p.order_q) + (long)mask * nblk;
     for (int i = threadIdx.x; i < nblk; i += kThreads) {
         const int first = ptr[i];
         int count = ptr[i + 1] - first;
@@ -109,6 +111,42 @@ __global__ void __launch_bounds__(kThreads) block_order_fused_kernel(const int32
         order[rank] = i;
     }
 }
+__global__ void __launch_bounds__(kThreads) block_order_fused_kernel(OrderParams p, int first_kind) {
+    __shared__ int32_t len[kOrderFusedBlocks];
+    rank_blocks(p, blockIdx.x, first_kind + blockIdx.y, len);
+}
+
+// What the two halves of the backward need when they run side by side: v = rowsum(dO o O), and the block orders of the
+// masks (`orders` workgroups: both kinds of a mask one after the other).  Two lanes per row with the sum in the dQ kernel's order, so that the
+// bits of v do not depend on which of the two formed it.
+template <int D>
+__global__ void __launch_bounds__(kThreads) bwd_rows_kernel(FusedParams p, OrderParams op, int orders) {
+    __shared__ int32_t len[kOrderFusedBlocks];
+    if ((int)blockIdx.x < orders) {
+        rank_blocks(op, blockIdx.x >> 1, blockIdx.x & 1, len);
+        return;
+    }
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const long rows = (long)p.batch * p.heads * p.n;
+    const long r = ((long)(blockIdx.x - orders) * (kThreads / 64) + (threadIdx.x >> 6)) * 32 + (lane & 31);
+    float dsum = 0.f;
+    if (r < rows) {
+        const int bh = (int)(r / p.n), i = (int)(r % p.n);
+        const long off = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h + (long)i * p.stride_n + 8 * h;
+        bf16x8 o[D / 16], g[D / 16];
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {
+            o[ks] = *reinterpret_cast<const bf16x8*>(p.O + off + 16 * ks);
+            g[ks] = *reinterpret_cast<const bf16x8*>(p.dO + off + 16 * ks);
+        }
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dsum += (float)o[ks][e] * (float)g[ks][e];
+    }
+    dsum += __shfl_xor(dsum, 32, 64);
+    if (r < rows && h == 0) p.delta[r] = dsum;
+}
 
 // ------------------------------------------------------------------------------- dK, dV
 // A workgroup owns 64 keys and streams 64-query tiles; per tile its 4 waves work in two phases:
@@ -127,21 +165,15 @@ __global__ void __launch_bounds__(kThreads) block_order_fused_kernel(const int32
 // (measured: 2 % faster than without priorities, 3 % faster than with the exponentials in the middle).
 constexpr int kPrioPhase1 = 3, kPrioSoftmax = 0, kPrioPhase2 = 1;
 template <int D>
-__global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_dkdv_kernel(FusedParams p) {
+__device__ __forceinline__ void dkdv_block(const FusedParams p, char* smem, int bh, int j) {
     constexpr int BR = 64, BC = 64, KS = D / 16, MT = D / 32;
     constexpr int kTileBytes = BR * D * 2;
     constexpr int kStageBytes = 2 * kTileBytes;
     constexpr int kPBytes = BC * BR * 2;
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
     const int wk = w & 1, wx = w >> 1;
-    // with an order list the grid has both halves of every 128-key block (the last one may lie
-    // past n) and the blocks come longest list first
-    const int key_blocks = p.order ? 2 * ((p.n + 127) / 128) : (p.n + BC - 1) / BC;
-    int bh, j;
-    decode_block_causal(blockIdx.x, key_blocks, p.batch * p.heads, p.resident, bh, j);
     if (p.order) {
         j = 2 * p.order[(long)bh * p.order_stride + (j >> 1)] + (j & 1);
         if (j * BC >= p.n) return;
@@ -409,6 +441,17 @@ __global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_dkdv_kernel(Fu
     }
 }
 
+template <int D>
+__global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_dkdv_kernel(FusedParams p) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    // with an order list the grid has both halves of every 128-key block (the last one may lie
+    // past n) and the blocks come longest list first
+    const int key_blocks = p.order ? 2 * ((p.n + 127) / 128) : (p.n + 63) / 64;
+    int bh, j;
+    decode_block_causal(blockIdx.x, key_blocks, p.batch * p.heads, p.resident, bh, j);
+    dkdv_block<D>(p, smem, bh, j);
+}
+
 // ----------------------------------------------------------------------------------- dQ
 // Wave w owns queries i0 + 32w .. +31: their Q and dO rows stay in registers as B operands.
 // Per key tile (64 keys, two halves T):
@@ -417,8 +460,9 @@ __global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_dkdv_kernel(Fu
 //   dQ_w^T += K_T^T dS^T                             K^T from transposed LDS reads
 // SPLIT = 2 (QT = 1): the block has 64 queries and wave (wq, wk) takes queries 32 wq .. +31 with key half wk of every tile; the two
 // sums of a query meet in LDS at the end.
-template <int D, int QT, int SPLIT>
-__device__ __forceinline__ void dq_block(const FusedParams p, char* smem) {
+// OWN: delta is formed here and left in the workspace; else it is read from there.
+template <int D, int QT, int SPLIT, bool OWN>
+__device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh, int blk) {
     static_assert(SPLIT == 1 || QT == 1, "one way to share out the waves at a time");
     constexpr int BR = 128 * QT / SPLIT, BC = 64, KS = D / 16, MT = D / 32;
     constexpr int NT = 2 / SPLIT;  // 32-key halves of a tile per wave
@@ -428,9 +472,7 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem) {
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
     const int wq = SPLIT == 1 ? w : w & 1, wk = SPLIT == 1 ? 0 : w >> 1;
-    const int q_blocks = SPLIT > 1 && p.order ? SPLIT * ((p.n + 127) / 128) : (p.n + BR - 1) / BR;
-    int bh, blk;
-    decode_block_causal(blockIdx.x, q_blocks, p.batch * p.heads, p.resident, bh, blk);
+    const int q_blocks = (p.n + BR - 1) / BR;
     // longest rows first: under the causal rule the last blocks, under a block mask by the order list
     const int ib = p.order ? SPLIT * p.order[(long)bh * p.order_stride + blk / SPLIT] + blk % SPLIT
                            : (p.causal ? q_blocks - 1 - blk : blk);
@@ -489,18 +531,22 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem) {
         // read once here (and nowhere else in the backward); the two lane halves hold the two
         // halves of every 16-element chunk.  The dK / dV kernel, which runs after this one,
         // takes delta from the workspace.
-        float dsum = 0.f;
-        if (ok) {
+        if constexpr (OWN) {
+            float dsum = 0.f;
+            if (ok) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const bf16x8 of = *reinterpret_cast<const bf16x8*>(p.O + base + (long)q[t] * ld + 16 * ks + 8 * h);
+                for (int ks = 0; ks < KS; ++ks) {
+                    const bf16x8 of = *reinterpret_cast<const bf16x8*>(p.O + base + (long)q[t] * ld + 16 * ks + 8 * h);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) dsum += (float)of[e] * (float)gf[t][ks][e];
+                    for (int e = 0; e < 8; ++e) dsum += (float)of[e] * (float)gf[t][ks][e];
+                }
             }
+            dsum += __shfl_xor(dsum, 32, 64);
+            dl[t] = ok ? dsum : 0.f;
+            if (ok && h == 0 && wk == 0) p.delta[(long)bh * p.n + q[t]] = dsum;
+        } else {
+            dl[t] = ok ? p.delta[(long)bh * p.n + q[t]] : 0.f;
         }
-        dsum += __shfl_xor(dsum, 32, 64);
-        dl[t] = ok ? dsum : 0.f;
-        if (ok && h == 0 && wk == 0) p.delta[(long)bh * p.n + q[t]] = dsum;
     }
 
     f32x16 dq[QT][MT];
@@ -695,13 +741,55 @@ constexpr int dq_split_per_cu(int d) { return d == 64 ? 3 : dq_per_cu(d); }  // 
 template <int D, int QT>
 __global__ void __launch_bounds__(kThreads, QT == 1 ? dq_per_cu(D) : 1) bwd_dq_kernel(FusedParams p) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    dq_block<D, QT, 1>(p, smem);
+    int bh, blk;
+    decode_block_causal(blockIdx.x, (p.n + 128 * QT - 1) / (128 * QT), p.batch * p.heads, p.resident, bh, blk);
+    dq_block<D, QT, 1, true>(p, smem, bh, blk);
 }
 
 template <int D>
 __global__ void __launch_bounds__(kThreads, dq_split_per_cu(D)) bwd_dq_split_kernel(FusedParams p) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    dq_block<D, 1, 2>(p, smem);
+    int bh, blk;
+    decode_block_causal(blockIdx.x, p.order ? 2 * ((p.n + 127) / 128) : (p.n + 63) / 64, p.batch * p.heads, p.resident, bh, blk);
+    dq_block<D, 1, 2, true>(p, smem, bh, blk);
+}
+
+// Both halves of the backward side by side: for every 128 rows two blocks of 64 queries (SPLIT = 2) or one of 128 (dQ), and two of
+// 64 keys (dK, dV).  The same blocks as in the two kernels, so the same bits; v comes from bwd_rows_kernel for both.
+template <int D, int SPLIT>
+__global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_both_kernel(FusedParams pq, FusedParams pk) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    int bh, rank;
+    if constexpr (SPLIT == 2) {
+        const int blocks = pq.order ? 2 * ((pq.n + 127) / 128) : (pq.n + 63) / 64;
+        decode_block_causal(blockIdx.x, 2 * blocks, pq.batch * pq.heads, pq.resident, bh, rank);
+        if (rank & 1) dq_block<D, 1, 2, false>(pq, smem, bh, rank >> 1);
+        else dkdv_block<D>(pk, smem, bh, rank >> 1);
+    } else {
+        const int blocks = 3 * ((pq.n + 127) / 128);
+        decode_block_causal(blockIdx.x, blocks, pq.batch * pq.heads, pq.resident, bh, rank);
+        const int r = rank % 3, k = 2 * (rank / 3) + r - 1;
+        if (r == 0) dq_block<D, 1, 1, false>(pq, smem, bh, rank / 3);
+        else if (pk.order || 64 * k < pk.n) dkdv_block<D>(pk, smem, bh, k);
+    }
+}
+
+// Workgroups per CU of bwd_both_kernel and bwd_dkdv_kernel (their LDS and registers).
+constexpr int both_per_cu(int d) { return d == 64 ? 3 : d == 128 ? 2 : 1; }
+
+// Whether dQ and dK / dV run in one launch of `grid` workgroups, with v formed by a small launch in front.  One launch instead of two dependent ones
+// fills the CUs that the first leaves idle while its last blocks run, and a call with fewer blocks than CUs takes the longer of the
+// two instead of their sum; the price is the launch in front (3 to 4 us) and, at d = 64, three workgroups per CU for dQ instead of four.
+// With lists of equal length the two launches fill the chip as evenly as one, so there all blocks have to fit at once; causal
+// and masked lists leave a tail per launch, which is worth it up to four rounds (six at d = 64).  us of the backward, two launches -> one:
+//   full     d64  h8 n333 (causal) 17.0 -> 12.5   h4 n1500 45 -> 28   h12 n2048 69 -> 64     h16 n2048 (beyond) 75 -> 89
+//            d128 h8 n700 34 -> 21     h8 n2048 79 -> 69     h16 n2048 (beyond) 125 -> 132    h16 n4096 (beyond) 428 -> 488
+//            d256 h8 n1000 77 -> 45    h6 n2048 (beyond) 139 -> 146     h20 n3000 (beyond) 722 -> 760
+//   causal   d64  h16 n2048 57 -> 48   h64 n2048 153 -> 149     d256 h8 n4096 345 -> 278   h24 n2048 243 -> 235
+//            d128 h32 n1024 56 -> 50   h16 n4096 259 -> 241     h48 n2048 (four rounds and a half) 202 -> 204   h32 n4096 (beyond) 459 -> 482
+//   10 %     d128 h16 n4096 110 -> 84  h16 n8192 (beyond) 250 -> 248   h16 n16384 (beyond) 818 -> 870   d64 h16 n8192 156 -> 136   h32 n8192 (beyond) 271 -> 260
+inline bool side_by_side(long grid, int d, bool uneven) {
+    return grid <= 256L * both_per_cu(d) * (!uneven ? 1 : d == 64 ? 6 : 4);
 }
 
 // ------------------------------------------------------------------------------ launchers
@@ -721,70 +809,76 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     constexpr int q_lds = 2 * (2 * 64 * D * 2);
     const int blocks128 = (p.n + 127) / 128;
     const bool split = few_blocks(blocks128 * bh, dq_per_cu(D), p.causal && !p.mask_form);
+    const long both_grid = (long)bh * (split ? 2 * (csr_ptr ? 2 * blocks128 : (p.n + 63) / 64) : 3 * blocks128);
+    const bool both = p.may_join && !onepass && !dq_only && !dkdv_only && side_by_side(both_grid, D, p.causal || csr_ptr);
     void (*const dq_fn)(FusedParams) = split ? bwd_dq_split_kernel<D> : bwd_dq_kernel<D, 1>;
-    const void* kv_fn = reinterpret_cast<const void*>(bwd_dkdv_kernel<D>);
+    void (*const both_fn)(FusedParams, FusedParams) = split ? bwd_both_kernel<D, 2> : bwd_both_kernel<D, 1>;
     // set on every call (the attribute belongs to the current device, and the call is cheap)
-    if (!onepass) {
-        hipError_t e = hipFuncSetAttribute(kv_fn, hipFuncAttributeMaxDynamicSharedMemorySize, kv_lds);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(dq_fn), hipFuncAttributeMaxDynamicSharedMemorySize, q_lds);
-        if (e != hipSuccess) return e;
+    const auto set_lds = [](auto fn, int bytes) {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    };
+    hipError_t e = hipSuccess;
+    if (both) {
+        e = set_lds(both_fn, kv_lds);
+    } else if (!onepass) {
+        e = set_lds(bwd_dkdv_kernel<D>, kv_lds);
+        if (e == hipSuccess) e = set_lds(dq_fn, q_lds);
     }
-    int32_t* order_q = nullptr;
-    int32_t* order_k = nullptr;
+    if (e != hipSuccess) return e;
+    OrderParams op = {csr_ptr, csr_idx, csc_ptr, csc_idx, nullptr, nullptr, blocks128, p.causal};
     const int masks = p.list_stride ? bh : 1;  // one mask per (batch, head), or one for all
     if (order_scratch && csr_ptr && csc_ptr && masks <= 65535) {  // (grid.y limit; beyond it: ascending order)
-        order_q = order_scratch;
-        order_k = order_scratch + (long)masks * blocks128;
+        op.order_q = order_scratch;
+        op.order_k = order_scratch + (long)masks * blocks128;
         int32_t* len = order_scratch + 2L * masks * blocks128;
         const dim3 og((unsigned)((blocks128 + kThreads - 1) / kThreads), (unsigned)masks);
         const bool want_q = !onepass && !dkdv_only, want_k = !dq_only;
         if (blocks128 <= kOrderFusedBlocks) {
-            if (want_q || want_k)
+            if (!both && (want_q || want_k))
                 hipLaunchKernelGGL(block_order_fused_kernel, dim3((unsigned)masks, want_q && want_k ? 2u : 1u),
-                                   dim3(kThreads), 0, stream, csr_ptr, csr_idx, csc_ptr, csc_idx, blocks128, p.causal,
-                                   order_q, order_k, want_q ? 0 : 1);
+                                   dim3(kThreads), 0, stream, op, want_q ? 0 : 1);
         } else {
             if (want_q) {
                 hipLaunchKernelGGL(block_len_kernel, og, dim3(kThreads), 0, stream, csr_ptr, csr_idx, blocks128, p.causal, 0, len);
-                hipLaunchKernelGGL(block_order_kernel, og, dim3(kThreads), 0, stream, len, blocks128, order_q);
+                hipLaunchKernelGGL(block_order_kernel, og, dim3(kThreads), 0, stream, len, blocks128, op.order_q);
             }
             if (want_k) {
                 hipLaunchKernelGGL(block_len_kernel, og, dim3(kThreads), 0, stream, csc_ptr, csc_idx, blocks128, p.causal, 1, len);
-                hipLaunchKernelGGL(block_order_kernel, og, dim3(kThreads), 0, stream, len, blocks128, order_k);
+                hipLaunchKernelGGL(block_order_kernel, og, dim3(kThreads), 0, stream, len, blocks128, op.order_k);
             }
         }
     }
-    if (onepass) {
-        FusedParams pk = p;
-        pk.list_ptr = csc_ptr;
-        pk.list_idx = csc_idx;
-        pk.order = order_k;
-        pk.order_stride = p.list_stride ? blocks128 : 0;
-        return launch_bwd_onepass(D, onepass_keys, pk, dq_acc, stream);
-    }
-    FusedParams pq = p;
-    // with an order list both halves of every 128-query block (the last one may lie past n: it writes nothing)
-    const int q_blocks = !split ? blocks128 : order_q ? 2 * blocks128 : (p.n + 63) / 64;
-    if (p.causal && !csr_ptr) pq.resident = causal_resident(q_blocks * bh, split ? dq_split_per_cu(D) : dq_per_cu(D));
+    FusedParams pq = p, pk = p;
     pq.list_ptr = csr_ptr;
     pq.list_idx = csr_idx;
-    pq.order = order_q;
-    pq.order_stride = p.list_stride ? blocks128 : 0;
+    pq.order = op.order_q;
+    pk.list_ptr = csc_ptr;
+    pk.list_idx = csc_idx;
+    pk.order = op.order_k;
+    pq.order_stride = pk.order_stride = p.list_stride ? blocks128 : 0;
+    if (onepass) return launch_bwd_onepass(D, onepass_keys, pk, dq_acc, stream);
+    // with an order list both halves of every 128-row block (the last one may lie past n: it writes nothing)
+    const int halves = op.order_k ? 2 * blocks128 : (p.n + 63) / 64;
+    if (both) {
+        const int orders = op.order_q && blocks128 <= kOrderFusedBlocks ? 2 * masks : 0;
+        const long rows = (long)bh * p.n;
+        const unsigned grid = (unsigned)((split ? 2 * halves : 3 * blocks128) * bh);  // (both_grid, or a little less without orders)
+        if (p.causal && !csr_ptr) pq.resident = causal_resident((int)grid, both_per_cu(D));
+        hipLaunchKernelGGL(bwd_rows_kernel<D>, dim3((unsigned)(orders + (rows + kThreads / 2 - 1) / (kThreads / 2))), dim3(kThreads), 0, stream,
+                           p, op, orders);
+        hipLaunchKernelGGL(both_fn, dim3(grid), dim3(kThreads), kv_lds, stream, pq, pk);
+        return hipGetLastError();
+    }
+    const int q_blocks = split ? halves : blocks128;
+    if (p.causal && !csr_ptr) pq.resident = causal_resident(q_blocks * bh, split ? dq_split_per_cu(D) : dq_per_cu(D));
     // One query tile per wave and two workgroups per CU.  (QT = 2, i.e. one wave per SIMD with every
     // LDS fragment feeding two MFMAs, halves the LDS traffic but measured 20 % slower at d = 128:
     // with a single wave per SIMD the softmax arithmetic no longer overlaps another wave's MFMAs.)
     if (!dkdv_only)
         hipLaunchKernelGGL(dq_fn, dim3((unsigned)(q_blocks * bh)), dim3(kThreads), q_lds, stream, pq);
     if (dq_only) return hipGetLastError();
-    FusedParams pk = p;
-    pk.list_ptr = csc_ptr;
-    pk.list_idx = csc_idx;
-    pk.order = order_k;
-    pk.order_stride = p.list_stride ? blocks128 : 0;
-    const int key_blocks = order_k ? 2 * blocks128 : (p.n + 63) / 64;
-    if (p.causal && !csc_ptr) pk.resident = causal_resident(key_blocks * bh, D == 64 ? 3 : D == 128 ? 2 : 1);
-    hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3((unsigned)(key_blocks * bh)), dim3(kThreads), kv_lds, stream, pk);
+    if (p.causal && !csc_ptr) pk.resident = causal_resident(halves * bh, both_per_cu(D));
+    hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3((unsigned)(halves * bh)), dim3(kThreads), kv_lds, stream, pk);
     return hipGetLastError();
 }
 

@@ -440,6 +440,7 @@ struct FusedParams {
     int list_stride, order_stride;
     int resident;  // causal, no mask: see decode_block_causal
     bool mask_form;  // the entry point has a form with a block mask: see few_blocks
+    bool may_join;   // backward: the caller did not ask for two launches
 };
 
 }  // namespace attn

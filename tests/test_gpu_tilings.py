@@ -113,3 +113,33 @@ def test_unsupported_tilings_are_rejected():
         with pytest.raises(attn.AttnError) as e:
             attn.attn_bwd(x64, x64, x64, x64, x64, lse, 1.0, tiling=tiling)
         assert e.value.status == attn.ATTN_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("kind", ["full", "causal", "mask", "causal_masks_per_head"])
+def test_one_launch_and_two_have_the_same_bits(d, kind):
+    """The library's choice runs the two owners of small calls side by side, with the row sums from a launch of their own: the same
+    blocks, so the same bits as the two kernels, at the edges of the blocks, with query blocks of 64 and of 128 (many heads), in
+    tensors whose heads are interleaved, and with more blocks than are ranked in one workgroup."""
+    import torch
+    from paper_2410_09397_amd import attn
+    causal, masked = kind.startswith("causal"), "mask" in kind
+    shapes = [(1, 1, 1), (1, 3, 63), (2, 4, 65), (1, 8, 128), (3, 1, 333), (1, 5, 700), (1, 1, 1025), (1, 40 if d == 256 else 70, 513)]
+    if d == 64 and kind == "mask":
+        shapes.append((1, 1, 128 * 257 + 5))
+    for b, h, n in shapes:
+        print("case", kind, d, b, h, n, flush=True)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(n)
+        Q, K, V, dO = (torch.randn((b, n, h, d), generator=gen, device="cuda").to(torch.bfloat16).transpose(1, 2) for _ in range(4))
+        mask = None
+        if masked:
+            nblk = (n + 127) // 128
+            keep = np.random.default_rng(n).random((b * h, nblk, nblk) if "per_head" in kind else (nblk, nblk)) < min(0.5, 8 / nblk)
+            keep[..., 0, 0] = True
+            mask = attn.BlockMask(keep, 128, n)
+        w = synth.Workload("one_launch", 190, b, h, n, d, "bf16", causal=causal)
+        O, LSE = attn.attn_fwd(Q, K, V, w.scale, causal=causal, mask=mask, out=(torch.empty_like(Q), torch.empty((b, h, n), device="cuda")))
+        args = (Q, K, V, O, dO, LSE)
+        for x, y in zip(run_bwd(w, mask, 0, *args), run_bwd(w, mask, TWO_KERNEL, *args)):
+            assert torch.isfinite(x).all() and torch.equal(x, y)
