@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace attn {
 
@@ -22,6 +23,15 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kThreads = 256;  // four 64-lane wavefronts per workgroup, one per SIMD
 
+// f(std::integral_constant<int, 0>{}), ... , N - 1: for register arrays indexed by what is uniform but not known to the compiler
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // 32x32x16 bf16 MFMA.  Operand layout (lane l, h = l / 32):
 //   A (32 x 16): row l % 32, k = 8h .. 8h+7        B (16 x 32): column l % 32, k = 8h .. 8h+7
@@ -30,6 +40,10 @@ constexpr int kThreads = 256;  // four 64-lane wavefronts per workgroup, one per
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
+
+// The matrix instructions in front have written v.  For results that are read behind a branch: there the compiler (ROCm 7.2) has
+// left out the wait states that they need.
+__device__ __forceinline__ void products_done(f32x16& v) { asm volatile("s_nop 15\n\ts_nop 3" : "+v"(v)); }
 
 // Row of accumulator register i for a lane in half h.
 __device__ __forceinline__ int acc_row(int i, int h) { return 8 * (i >> 2) + 4 * h + (i & 3); }
@@ -167,16 +181,18 @@ struct FragOffsets {
     }
 };
 
-// The address registers of all fragments of a [rows x D] tile (static indices only).
+// The address registers of all fragments of a [rows x D] tile (static indices only).  The swizzle stays within 16 chunks
+// (256 bytes), so fragments 256 bytes apart share a register.
 template <int D>
 struct FragAddrs {
-    int rmk[D / 16];
-    int trk[D / 32][2];
+    static constexpr int kRm = D / 16 < 8 ? D / 16 : 8, kTr = D / 32 < 4 ? D / 32 : 4;
+    int rmk[kRm];
+    int trk[kTr][2];
     __device__ __forceinline__ void init(const FragOffsets<D>& fo) {
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) rmk[ks] = fo.rm(ks);
+        for (int ks = 0; ks < kRm; ++ks) rmk[ks] = fo.rm(ks);
 #pragma unroll
-        for (int mt = 0; mt < D / 32; ++mt) {
+        for (int mt = 0; mt < kTr; ++mt) {
             trk[mt][0] = fo.tr(mt, 0);
             trk[mt][1] = fo.tr(mt, 1);
         }
@@ -184,18 +200,22 @@ struct FragAddrs {
     // all fetches `rows` (a multiple of 16) further down the tile
     __device__ __forceinline__ void shift_rows(int rows) {
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) rmk[ks] += rows * (D * 2);
+        for (int ks = 0; ks < kRm; ++ks) rmk[ks] += rows * (D * 2);
+        shift_transposed(rows * (D * 2));
+    }
+    // the transposed fetches `bytes` (a multiple of 256) further on
+    __device__ __forceinline__ void shift_transposed(int bytes) {
 #pragma unroll
-        for (int mt = 0; mt < D / 32; ++mt) {
-            trk[mt][0] += rows * (D * 2);
-            trk[mt][1] += rows * (D * 2);
+        for (int mt = 0; mt < kTr; ++mt) {
+            trk[mt][0] += bytes;
+            trk[mt][1] += bytes;
         }
     }
     __device__ __forceinline__ bf16x8 frag(const char* lds, int tile_off_bytes, int row0, int ks) const {
-        return FragOffsets<D>::read(lds, rmk[ks], tile_off_bytes + row0 * (D * 2));
+        return FragOffsets<D>::read(lds, rmk[ks % kRm], tile_off_bytes + row0 * (D * 2) + 256 * (ks / kRm));
     }
     __device__ __forceinline__ bf16x8 frag_t(const char* lds, int tile_off_bytes, int mt, int row16) const {
-        return FragOffsets<D>::read_t(lds, trk[mt][0], trk[mt][1], row16, tile_off_bytes);
+        return FragOffsets<D>::read_t(lds, trk[mt % kTr][0], trk[mt % kTr][1], row16, tile_off_bytes + 256 * (mt / kTr));
     }
 };
 

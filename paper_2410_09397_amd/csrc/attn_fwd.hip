@@ -9,6 +9,82 @@
 
 namespace attn {
 
+// The end of a query block: O / l and LSE of wave (wq, wk)'s 32 queries.  SPLIT > 1: SPLIT waves hold a part of the keys each; of the
+// 4 MT groups of four registers of O each writes MG, from MG wk on, and hands the others theirs through LDS, whose stages are
+// free (every wave is past the last barrier of the loop).
+template <int D, int SPLIT>
+__device__ __forceinline__ void fwd_finish(const FusedParams& p, char* smem, long base, int bh, int q, int wq, int wk, f32x16 (&o)[D / 32],
+                                           float m_run, float l_run) {
+    constexpr int MT = D / 32, MG = 4 * MT / SPLIT;
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    float l = l_run + __shfl_xor(l_run, 32, 64);
+    if constexpr (SPLIT > 1) {
+        float* ml = reinterpret_cast<float*>(smem + 2 * SPLIT * (SPLIT - 1) * MG * 64 * 16);  // [wave][2][64]
+        // groups of wave `from` for the wave with key part `to`: [wave][SPLIT - 1][MG][64 lanes] x 16 bytes
+        auto slot = [&](int from, int to, int g) {
+            const int part = to - (to > from / 2 ? 1 : 0);
+            return reinterpret_cast<f32x4*>(smem) + ((from * (SPLIT - 1) + part) * MG + g) * 64 + lane;
+        };
+        static_for<SPLIT>([&](auto to) {
+            if (wk == decltype(to)::value) return;
+#pragma unroll
+            for (int g = 0; g < MG; ++g) {
+                constexpr int first = decltype(to)::value * MG;
+                const f32x16& a = o[(first + g) / 4];
+                const int r = 4 * ((first + g) % 4);
+                *slot(wq + 2 * wk, decltype(to)::value, g) = f32x4{a[r], a[r + 1], a[r + 2], a[r + 3]};
+            }
+        });
+        ml[(wq + 2 * wk) * 128 + lane] = m_run;
+        ml[(wq + 2 * wk) * 128 + 64 + lane] = l;
+        __syncthreads();
+        float m_part[SPLIT], m = m_run;
+#pragma unroll
+        for (int k = 0; k < SPLIT; ++k) {
+            m_part[k] = ml[(wq + 2 * k) * 128 + lane];
+            m = __builtin_elementwise_maximum(m, m_part[k]);
+        }
+        const float m_use = m == -__builtin_inff() ? 0.f : m;
+        l = 0.f;
+#pragma unroll
+        for (int k = 0; k < SPLIT; ++k) {
+            m_part[k] = __builtin_amdgcn_exp2f(m_part[k] - m_use);  // the factor of that part
+            l += ml[(wq + 2 * k) * 128 + 64 + lane] * m_part[k];
+        }
+        const float f_mine = __builtin_amdgcn_exp2f(m_run - m_use);
+        m_run = m;
+        static_for<SPLIT>([&](auto mine) {
+            if (wk != decltype(mine)::value) return;
+#pragma unroll
+            for (int g = 0; g < MG; ++g) {
+                constexpr int first = decltype(mine)::value * MG;
+                const f32x16& a = o[(first + g) / 4];
+                const int r = 4 * ((first + g) % 4);
+                f32x4 s = f32x4{a[r], a[r + 1], a[r + 2], a[r + 3]} * f_mine;
+#pragma unroll
+                for (int k = 0; k < SPLIT; ++k)
+                    if (k != decltype(mine)::value) s += *slot(wq + 2 * k, decltype(mine)::value, g) * m_part[k];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[g / 4][4 * (g % 4) + e] = s[e];
+            }
+        });
+    }
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    if (q < p.n) {
+        __bf16* row = p.Oout + base + (long)q * p.stride_n;
+#pragma unroll
+        for (int gi = 0; gi < MG; ++gi) {
+            const int col = MG * wk + gi;  // 8 columns each
+            u32x2 a;
+            a[0] = pack_bf16(o[gi / 4][4 * (gi % 4) + 0] * inv, o[gi / 4][4 * (gi % 4) + 1] * inv);
+            a[1] = pack_bf16(o[gi / 4][4 * (gi % 4) + 2] * inv, o[gi / 4][4 * (gi % 4) + 3] * inv);
+            *reinterpret_cast<u32x2*>(row + 8 * col + 4 * h) = a;
+        }
+        if (h == 0 && wk == 0)
+            p.LSEout[(long)bh * p.n + q] = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : -__builtin_inff();
+    }
+}
+
 // Wave w owns queries i0 + 32w .. +31 (Q rows resident in registers as B operands).
 // Per key tile (64 keys, two halves T):
 //   S^T[T] = K_T Q_w^T                 accumulator: lane <-> query, register <-> key
@@ -24,7 +100,6 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
     constexpr int BR = 128 / SPLIT, BC = 64, KS = D / 16, MT = D / 32;
     constexpr int NT = 2 / SPLIT;  // 32-key halves of a tile per wave
     constexpr int kTileBytes = BC * D * 2;
-    constexpr int kStageBytes = 2 * kTileBytes;
 
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
@@ -55,10 +130,11 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
     // iteration ago; rows past n repeat the last row and are masked below.
     TileLoader<D, BC> loader;
     loader.init(tid, ld);
+    // [K stage 0][K stage 1][V stage 0][V stage 1]: every fetch of a fragment is a register plus an immediate of 16 bits
     auto fetch = [&](int j0, int stage) {
-        char* s = smem + stage * kStageBytes;
+        char* s = smem + stage * kTileBytes;
         loader.load(p.K + base, ld, j0, p.n, s, tid);
-        loader.load(p.V + base, ld, j0, p.n, s + kTileBytes, tid);
+        loader.load(p.V + base, ld, j0, p.n, s + 2 * kTileBytes, tid);
     };
     // the first tile is requested before the resident Q rows, so that the two latencies overlap
     int j0_next = n_it > 0 ? tile_start(0) : 0;
@@ -104,6 +180,7 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
     FragAddrs<D> fo;
     fo.init(lane_offsets);
     if constexpr (SPLIT > 1) fo.shift_rows(32 * wk);
+    fo.shift_transposed(2 * kTileBytes);
     wait_direct_loads();
     __syncthreads();
 
@@ -114,7 +191,7 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
     // wave run ahead while the other fills the gaps (measured: 5-7 % faster at d = 128).
     constexpr int kPrioScores = 2, kPrioSoftmax = 0, kPrioPV = 1;
     auto tile = [&](auto stage_off, int j0, auto masked) {
-        const int k_off = stage_off;  // K tile; the V tile follows it
+        const int k_off = stage_off;  // of the stage among those of K, and of V
         __builtin_amdgcn_s_setprio(kPrioScores);
         f32x16 st[NT];
 #pragma unroll
@@ -197,13 +274,13 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
         // requested before the MFMAs of the current one so that LDS latency hides behind them
         bf16x8 va[2][MT];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) va[0][mt] = fo.frag_t(smem, k_off + kTileBytes, mt, 0);
+        for (int mt = 0; mt < MT; ++mt) va[0][mt] = fo.frag_t(smem, k_off, mt, 0);
 #pragma unroll
         for (int g = 0; g < 2 * NT; ++g) {
             if (g + 1 < 2 * NT) {
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
-                    va[(g + 1) & 1][mt] = fo.frag_t(smem, k_off + kTileBytes, mt, 16 * (g + 1));
+                    va[(g + 1) & 1][mt] = fo.frag_t(smem, k_off, mt, 16 * (g + 1));
             }
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) o[mt] = mfma32(va[g & 1][mt], pb[g >> 1][g & 1], o[mt]);
@@ -232,7 +309,7 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
             j0_next = tile_start(it + 2);
             fetch(j0_next, 0);
         }
-        tile(std::integral_constant<int, kStageBytes>{}, jb, std::false_type{});
+        tile(std::integral_constant<int, kTileBytes>{}, jb, std::false_type{});
         wait_direct_loads();
         __syncthreads();
     }
@@ -243,69 +320,337 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
             fetch(j0_next, (it + 1) & 1);
         }
         // causal: this wave's last query precedes its first key of the tile -> nothing visible
-        if (!(p.causal && (i0 + 32 * wq + 31 < j0 + 32 * wk))) tile((it & 1) * kStageBytes, j0, std::true_type{});
+        if (!(p.causal && (i0 + 32 * wq + 31 < j0 + 32 * wk))) tile((it & 1) * kTileBytes, j0, std::true_type{});
         wait_direct_loads();
         __syncthreads();
     }
 
-    float l = l_run + __shfl_xor(l_run, 32, 64);
-    constexpr int MW = MT / SPLIT;  // 32-column groups of O that a wave writes, from MW wk on
-    if constexpr (SPLIT > 1) {
-        // each of the two waves of a query hands the other the half of its O that the other writes; the stages are free
-        // (every wave is past the last barrier of the loop)
-        float* ox = reinterpret_cast<float*>(smem);                         // [wave][MW * 4][64 lanes] x 16 bytes
-        float* ml = reinterpret_cast<float*>(smem + 4 * MW * 4 * 64 * 16);  // [wave][2][64]
-        auto slot = [&](int wave, int mt, int g) { return reinterpret_cast<f32x4*>(ox) + ((wave * MW + mt) * 4 + g) * 64 + lane; };
-        auto send = [&](auto first) {
-#pragma unroll
-            for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const f32x16& a = o[decltype(first)::value + mt];
-                    *slot(w, mt, g) = f32x4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
-                }
-        };
-        if (wk == 0) send(std::integral_constant<int, MW>{});
-        else send(std::integral_constant<int, 0>{});
-        ml[w * 128 + lane] = m_run;
-        ml[w * 128 + 64 + lane] = l;
-        __syncthreads();
-        const int other = w ^ 2;
-        const float m_o = ml[other * 128 + lane], l_o = ml[other * 128 + 64 + lane];
-        const float m = __builtin_elementwise_maximum(m_run, m_o), m_use = m == -__builtin_inff() ? 0.f : m;
-        const float f_mine = __builtin_amdgcn_exp2f(m_run - m_use), f_o = __builtin_amdgcn_exp2f(m_o - m_use);
-        l = l * f_mine + l_o * f_o;
-        m_run = m;
-        auto meet = [&](auto first) {
-#pragma unroll
-            for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const f32x4 b = *slot(other, mt, g);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        o[mt][4 * g + r] = o[decltype(first)::value + mt][4 * g + r] * f_mine + b[r] * f_o;
-                }
-        };
-        if (wk == 0) meet(std::integral_constant<int, 0>{});
-        else meet(std::integral_constant<int, MW>{});
-    }
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    if (q_ok) {
-        __bf16* row = p.Oout + base + (long)q * ld + 32 * MW * wk;
-#pragma unroll
-        for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                u32x2 a;
-                a[0] = pack_bf16(o[mt][4 * g + 0] * inv, o[mt][4 * g + 1] * inv);
-                a[1] = pack_bf16(o[mt][4 * g + 2] * inv, o[mt][4 * g + 3] * inv);
-                *reinterpret_cast<u32x2*>(row + 32 * mt + 8 * g + 4 * h) = a;
-            }
-        if (h == 0 && wk == 0)
-            p.LSEout[(long)bh * p.n + q] = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : -__builtin_inff();
-    }
+    fwd_finish<D, SPLIT>(p, smem, base, bh, q, wq, wk, o, m_run, l_run);
 }
+
+// The same forward with the three parts of a tile's work taken from three tiles, so that the matrix instructions of one wave have vector
+// instructions of the same wave between them: step t forms the scores of tile t + 1 and the product of tile t - 1 while it
+// takes the exponentials of tile t.  For a wave that has a SIMD to itself (d = 256, whose 512 registers leave room for one) or shares
+// it with one wave in step with it (SPLIT = 4: eight waves, 64 queries, tiles of 128 keys, each wave 32 of them); with two workgroups on
+// a CU the plain body is as fast or faster.  K runs one step ahead of V: during step t the copies of K(t + 2) and V(t) arrive in the places of
+// K(t) and V(t - 2).  What is left per step is instruction issue: a wave alone issues one about every 5 cycles, and taking away copies,
+// exponentials or maxima one at a time shortens a step by 5 to 25 % each.
+// us, before -> now: d = 256  h8 n4096 188 -> 145   b2 h16 n8192 causal 1607 -> 1240   h8 n1024 36 -> 28   h16 n2048 causal 77 -> 61
+// (SPLIT = 4: see eight_waves)
+template <int D, int SPLIT>
+__device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
+    constexpr int NW = SPLIT == 4 ? 8 : 4;  // waves
+    constexpr int BR = SPLIT == 1 ? 128 : 64, BC = SPLIT == 4 ? 128 : 64, KS = D / 16, MT = D / 32;
+    constexpr int NT = SPLIT == 1 ? 2 : 1;  // 32-key parts of a tile per wave
+    constexpr int kTileBytes = BC * D * 2;
+
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
+    const int wq = SPLIT == 1 ? w : w & 1, wk = SPLIT == 1 ? 0 : w >> 1;
+    const int q_blocks = (p.n + BR - 1) / BR;
+    int bh, blk;
+    decode_block_causal(blockIdx.x, q_blocks, p.batch * p.heads, p.resident, bh, blk);
+    const int ib = p.causal ? q_blocks - 1 - blk : blk;  // causal: longest rows first
+    const long base = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
+    const long ld = p.stride_n;
+    const int i0 = ib * BR;
+
+    int n_it, lp0 = 0;
+    if (p.list_ptr) {
+        const int32_t* lptr = p.list_ptr + (long)bh * p.list_stride;  // this (batch, head)'s mask
+        const int lb = ib / (128 / BR);  // the lists are per 128 rows
+        lp0 = lptr[lb];
+        int entries = lptr[lb + 1] - lp0;
+        if (p.causal) entries = causal_row_entries(p.list_idx, lp0, entries, lb);
+        n_it = entries * (128 / BC);
+    } else {
+        const int k_end = p.causal ? min(p.n, i0 + BR) : p.n;
+        n_it = (k_end + BC - 1) / BC;
+    }
+    auto tile_start = [&](int it) -> int { return tile_start_row<BC>(p.list_idx, lp0, 0, it); };
+
+    // K and V tiles go straight from global memory into the LDS stage that was last read one
+    // iteration ago; rows past n repeat the last row and are masked below.
+    TileLoader<D, BC, NW> loader;
+    loader.init(tid, ld);
+    // [K stage 0][K stage 1][V stage 0][V stage 1]: every fetch of a fragment is a register plus an immediate of 16 bits
+    auto fetch_k = [&](int j0, int stage) { loader.load(p.K + base, ld, j0, p.n, smem + stage * kTileBytes, tid); };
+    auto fetch_v = [&](int j0, int stage) { loader.load(p.V + base, ld, j0, p.n, smem + (2 + stage) * kTileBytes, tid); };
+    // the first tile is requested before the resident Q rows, so that the two latencies overlap
+    auto start_of = [&](int t) { return t < n_it ? tile_start(t) : 0; };
+    int j[3] = {start_of(0), start_of(1), start_of(2)};  // of tiles t, t + 1, t + 2
+    if (n_it > 0) fetch_k(j[0], 0);
+    if (n_it > 1) fetch_k(j[1], 1);
+
+    const int q = i0 + 32 * wq + l32;
+    const bool q_ok = q < p.n;
+    bf16x8 qf[KS];
+    {
+        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            qf[ks] = zero;
+            if (q_ok) qf[ks] = *reinterpret_cast<const bf16x8*>(p.Q + base + (long)q * ld + 16 * ks + 8 * h);
+        }
+    }
+
+    f32x16 o[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[mt][i] = 0.f;
+    float m_run = -__builtin_inff();  // running maximum of scale * log2(e) * s
+    float l_run = 0.f;                // this lane's share of sum exp2(scaled s - m_run)
+
+    // Scores are kept raw in the accumulators and scaled inside the exponential: with
+    // cs = |scale| log2(e) > 0 the row maximum commutes with the scaling.  A negative scale is
+    // moved into Q (sign flip of the resident fragments), a zero scale becomes a denormal-sized
+    // positive one so that masked (-inf) scores stay -inf.
+    const float cs = fmaxf(fabsf(p.scale) * kLog2e, 1.17549435e-38f);
+    if (p.scale < 0.f) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            u32x4 v = __builtin_bit_cast(u32x4, qf[ks]);
+            v ^= 0x80008000u;
+            qf[ks] = __builtin_bit_cast(bf16x8, v);
+        }
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) settle(qf[ks]);
+    FragOffsets<D> lane_offsets;
+    lane_offsets.init(lane);
+    FragAddrs<D> fo;
+    fo.init(lane_offsets);
+    if constexpr (SPLIT > 1) fo.shift_rows(32 * wk);
+    fo.shift_transposed(2 * kTileBytes);
+    wait_direct_loads();
+    __syncthreads();
+
+    f32x16 st[NT];      // scores of the tile whose exponentials come next
+    bf16x8 pb[NT][2];   // weights of the tile before it
+    auto scores = [&](auto off, f32x16 (&s)[NT]) {
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[T][i] = 0.f;
+        // (fragments are requested a few products ahead and no further: all of them at once would not fit the registers)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if (ks % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int T = 0; T < NT; ++T) s[T] = mfma32(fo.frag(smem, off, 32 * T, ks), qf[ks], s[T]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int T = 0; T < NT; ++T) products_done(s[T]);
+    };
+    auto values = [&](auto off) {
+#pragma unroll
+        for (int g = 0; g < 2 * NT; ++g) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) o[mt] = mfma32(fo.frag_t(smem, off, mt, 16 * g), pb[g >> 1][g & 1], o[mt]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto mask_scores = [&](int j0) {
+        const int lim = (p.causal ? min(q, p.n - 1) : p.n - 1) - j0 - 32 * wk - 4 * h;
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                st[T][i] = (32 * T + 8 * (i >> 2) + (i & 3) > lim) ? -__builtin_inff() : st[T][i];
+    };
+    constexpr float kSlack = 8.f;
+    // whether some row's reference point has to move, seen from each lane's own scores; then m_run, l_run and `alpha`
+    auto reference = [&](float& alpha) -> bool {
+        float mxa = max3(st[0][0], st[0][1], st[0][2]), mxb = max3(st[NT - 1][3], st[NT - 1][4], st[NT - 1][5]);
+        if constexpr (NT == 1) {
+#pragma unroll
+            for (int i = 6; i < 14; i += 4) {
+                mxa = max3(mxa, st[0][i], st[0][i + 1]);
+                mxb = max3(mxb, st[0][i + 2], st[0][i + 3]);
+            }
+            mxa = max3(mxa, st[0][14], st[0][15]);
+        } else {
+#pragma unroll
+            for (int i = 3; i < 15; i += 2) mxa = max3(mxa, st[0][i], st[0][i + 1]);
+            mxb = max3(mxb, st[1][0], st[1][1]);
+#pragma unroll
+            for (int i = 6; i < 16; i += 2) mxb = max3(mxb, st[1][i], st[1][i + 1]);
+            mxb = max3(mxb, st[0][15], st[1][2]);
+        }
+        float mx = __builtin_elementwise_maximum(mxa, mxb);
+        if (__builtin_amdgcn_ballot_w64(mx * cs > m_run + kSlack) == 0) return false;
+        mx = __builtin_elementwise_maximum(mx, __shfl_xor(mx, 32, 64));
+        const float cand = mx * cs;
+        const float m_new = cand > m_run + kSlack ? cand : m_run;
+        alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -__builtin_inff() ? 0.f : m_new));
+        l_run *= alpha;
+        m_run = m_new;
+        return true;
+    };
+    auto weights = [&]() {
+        const float m_use = (m_run == -__builtin_inff()) ? 0.f : m_run;
+        float sum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float pv = __builtin_amdgcn_exp2f(fmaf(st[T][i], cs, -m_use));
+                st[T][i] = pv;
+                sum[i & 1] += pv;
+            }
+        l_run += sum[0] + sum[1];
+    };
+    auto pack = [&]() {
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+#pragma unroll
+            for (int ss = 0; ss < 2; ++ss) pb[T][ss] = acc_to_operand(st[T], ss);
+    };
+    auto rescale = [&](float alpha) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) products_done(o[mt]);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[mt][i] *= alpha;
+    };
+    constexpr int kWaveKeys = 32 * NT;
+    auto needs_mask = [&](int j0) {
+        return (p.causal && (j0 + 32 * wk + kWaveKeys - 1 > i0 + 32 * wq)) || (j0 + 32 * wk + kWaveKeys > p.n);
+    };
+    auto visible = [&](int j0) { return !(p.causal && (i0 + 32 * wq + 31 < j0 + 32 * wk)); };
+    if (n_it > 0) scores(std::integral_constant<int, 0>{}, st);
+    __syncthreads();  // the first step overwrites what these scores came from
+    bool prev = false;  // pb holds weights
+    auto advance = [&](int t) {
+        j[0] = j[1];
+        j[1] = j[2];
+        j[2] = start_of(t + 3);
+    };
+    constexpr int kInst = TileLoader<D, BC, NW>::kInst;
+    // step t: exponentials of tile t, scores of tile t + 1, product of tile t - 1
+    auto general = [&](int t) {
+        const int j0 = j[0];
+        const bool more = t + 1 < n_it;
+        if (t + 2 < n_it) fetch_k(j[2], t & 1);
+        fetch_v(j0, t & 1);
+        float alpha = 1.f;
+        f32x16 nx[NT];
+        const bool vis = visible(j0);
+        if (more) scores((~t & 1) * kTileBytes, nx);
+        if (prev) values((~t & 1) * kTileBytes);
+        if (vis) {
+            if (needs_mask(j0)) mask_scores(j0);
+            const bool grow = reference(alpha);
+            weights();
+            pack();
+            if (grow) rescale(alpha);
+        }
+        prev = vis;
+        if (more) {
+#pragma unroll
+            for (int T = 0; T < NT; ++T) st[T] = nx[T];
+        }
+        wait_direct_loads();
+        __syncthreads();
+        advance(t);
+    };
+    auto fast = [&](int t, auto stage) {
+        constexpr int here = decltype(stage)::value * kTileBytes, there = kTileBytes - here;  // stages of tiles t, and t - 1 and t + 1
+        static_assert(KS == 2 * MT && 2 * kInst == KS, "as many value as score products, and one copy, per slot");
+        float alpha = 1.f;
+        // a tile past the end: the first one again, into a place that is not read any more
+        const int jk = t + 2 < n_it ? j[2] : 0;
+        const __bf16* next_k = p.K + base + (unsigned long long)(unsigned)jk * (unsigned)ld;
+        const __bf16* next_v = p.V + base + (unsigned long long)(unsigned)j[0] * (unsigned)ld;
+        advance(t);
+        bf16x8 fk[KS][NT], fv[KS][NT];
+        constexpr int kAhead = 2;
+        auto request = [&](auto i) {
+#pragma unroll
+            for (int T = 0; T < NT; ++T) {
+                const int v = i * NT + T;
+                fk[i][T] = fo.frag(smem, there, 32 * T, i);
+                fv[i][T] = fo.frag_t(smem, there, v % MT, 16 * (v / MT));
+            }
+        };
+        static_for<kAhead>(request);
+        const bool grow = reference(alpha);
+        const float m_use = (m_run == -__builtin_inff()) ? 0.f : m_run;
+        f32x16 nx[NT];
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) nx[T][i] = 0.f;
+        float sum[2] = {0.f, 0.f};
+        bf16x8 nb[NT][2];
+        static_for<KS>([&](auto slot) {
+            constexpr int sl = decltype(slot)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (sl + kAhead < KS) request(std::integral_constant<int, sl + kAhead>{});
+#pragma unroll
+            for (int T = 0; T < NT; ++T) nx[T] = mfma32(fk[sl][T], qf[sl], nx[T]);
+            if constexpr (sl < kInst) loader.load_one(sl, next_k, smem + here);
+            else loader.load_one(sl - kInst, next_v, smem + 2 * kTileBytes + here);
+            constexpr int per = 16 * NT / KS;
+#pragma unroll
+            for (int e = 0; e < per; ++e) {
+                const int x = sl * per + e, T = x / 16, i = x % 16;
+                const float pv = __builtin_amdgcn_exp2f(fmaf(st[T][i], cs, -m_use));
+                st[T][i] = pv;
+                sum[x & 1] += pv;
+                asm volatile("" : "+v"(st[T][i]));  // formed in this slot
+            }
+#pragma unroll
+            for (int x = 0; x < 2 * NT; ++x)
+                if ((sl + 1) * per >= 8 * (x + 1) && sl * per < 8 * (x + 1)) nb[x / 2][x % 2] = acc_to_operand(st[x / 2], x % 2);
+#pragma unroll
+            for (int T = 0; T < NT; ++T) {
+                const int v = sl * NT + T, g = v / MT;
+                o[v % MT] = mfma32(fv[sl][T], pb[g / 2][g % 2], o[v % MT]);
+            }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        l_run += sum[0] + sum[1];
+#pragma unroll
+        for (int T = 0; T < NT; ++T) {
+            pb[T][0] = nb[T][0];
+            pb[T][1] = nb[T][1];
+            st[T] = nx[T];
+        }
+        if (grow) rescale(alpha);
+        wait_direct_loads();
+        __syncthreads();
+    };
+    int t = 0;
+    // tile t takes the fast body: there is a next one, nothing of t is masked, and the tiles fetched meanwhile lie inside
+    auto fast_ok = [&](int t) {
+        return prev && t + 1 < n_it && !needs_mask(j[0]) && j[1] + BC <= p.n && (t + 2 >= n_it || j[2] + BC <= p.n);
+    };
+    while (t < n_it) {
+        for (; t < n_it && !((t & 1) && fast_ok(t)); ++t) general(t);
+        while (t < n_it && fast_ok(t)) {
+            fast(t++, std::integral_constant<int, 1>{});
+            if (!(t < n_it && fast_ok(t))) break;
+            fast(t++, std::integral_constant<int, 0>{});
+        }
+    }
+    if (prev) values((~n_it & 1) * kTileBytes);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) products_done(o[mt]);
+    if constexpr (SPLIT > 1) __syncthreads();
+
+    fwd_finish<D, SPLIT>(p, smem, base, bh, q, wq, wk, o, m_run, l_run);
+}
+
+// Whether a launch of blocks of 64 queries takes eight waves (two query halves, four key parts of tiles of 128 keys, the pipelined
+// body) instead of four.  Half the steps, each 1.2 to 1.3 times as long with two waves per SIMD from one workgroup, of which a CU
+// holds one: it wins while there is at most one for each CU, unless a row is only a few steps long.  us, four waves -> eight:
+//   d = 128  h8 n700 14.5 -> 14.7   h16 n1024 19.2 -> 17.7   h8 n2048 32.5 -> 26   h1 n8192 119 -> 75   h16 n2048 (beyond the line) 44 -> 48
+//   d = 64   h8 n333 7.5 -> 8.1 (too short)   b2 h12 n600 causal 10.4 -> 9.9   h8 n1024 14.1 -> 12.0   h4 n1500 19.8 -> 15.0
+inline bool eight_waves(int d, int blocks, int n) { return blocks <= 256 && n >= (d == 64 ? 512 : 768); }
 
 constexpr int fwd_per_cu(int d) { return d == 64 ? 4 : d == 128 ? 2 : 1; }
 
@@ -321,22 +666,31 @@ __global__ void __launch_bounds__(kThreads, fwd_per_cu(D)) fwd_split_kernel(Fuse
     fwd_block<D, 2>(p, smem);
 }
 
+template <int D, int SPLIT>
+__global__ void __launch_bounds__(SPLIT == 4 ? 2 * kThreads : kThreads, D <= 128 ? 2 : 1) fwd_pipe_kernel(FusedParams p) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    fwd_pipe<D, SPLIT>(p, smem);
+}
+
 template <int D>
 static hipError_t launch_fwd(const FusedParams& p, const int32_t* csr_ptr, const int32_t* csr_idx,
                              hipStream_t stream) {
-    constexpr int lds = 2 * (2 * 64 * D * 2);
     const int heads = p.batch * p.heads;
     const bool split = few_blocks((p.n + 127) / 128 * heads, fwd_per_cu(D), p.causal && !p.mask_form);
-    void (*const fn)(FusedParams) = split ? fwd_split_kernel<D> : fwd_kernel<D>;
+    const int blocks = (split ? (p.n + 63) / 64 : (p.n + 127) / 128) * heads;
+    const bool eight = D <= 128 && split && eight_waves(D, blocks, p.n);
+    void (*fn)(FusedParams);
+    if constexpr (D == 256) fn = split ? fwd_pipe_kernel<D, 2> : fwd_pipe_kernel<D, 1>;
+    else fn = eight ? fwd_pipe_kernel<D, 4> : split ? fwd_split_kernel<D> : fwd_kernel<D>;
+    const int lds = (eight ? 2 : 1) * 2 * (2 * 64 * D * 2);
     // set on every call: the attribute belongs to the current device, and the call is cheap
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     FusedParams pf = p;
     pf.list_ptr = csr_ptr;
     pf.list_idx = csr_idx;
-    const int blocks = (split ? (p.n + 63) / 64 : (p.n + 127) / 128) * heads;
-    if (p.causal && !csr_ptr) pf.resident = causal_resident(blocks, fwd_per_cu(D));
-    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kThreads), lds, stream, pf);
+    if (p.causal && !csr_ptr) pf.resident = causal_resident(blocks, eight ? 1 : fwd_per_cu(D));
+    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(eight ? 2 * kThreads : kThreads), lds, stream, pf);
     return hipGetLastError();
 }
 

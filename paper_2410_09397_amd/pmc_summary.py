@@ -41,7 +41,7 @@ def source_hash():
 
 def traffic_key(workload, tiling):
     return workload if not tiling else "%s@tiling%d" % (workload, tiling)
-FWD_KERNELS = ("fwd_kernel", "fwd_split_kernel", "ld_scores_kernel<0>", "ld_scores_kernel<1>", "ld_scores_kernel<(attn::ScoreMode)0>",
+FWD_KERNELS = ("fwd_kernel", "fwd_split_kernel", "fwd_pipe_kernel", "ld_scores_kernel<0>", "ld_scores_kernel<1>", "ld_scores_kernel<(attn::ScoreMode)0>",
                "ld_scores_kernel<(attn::ScoreMode)1>", "ld_lse_combine", "generic_fwd")
 # launched by neither attn_fwd nor attn_bwd: the weight gradient's own and the measurement aids
 OTHER_KERNELS = ("wgrad_partial", "wgrad_reduce", "proj_kernel", "tile_skeleton_kernel", "mfma_ceiling_kernel")

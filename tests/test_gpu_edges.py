@@ -159,3 +159,37 @@ def test_causal_calls_and_lower_triangular_masks_have_the_same_bits(d, heads, n)
     masked = attn.attn_bwd_blocksparse(Q, K, V, O, dO, LSE, scale, mask, causal=True)
     for a, b in zip(dense, masked):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("d,heads", [(64, 2), (128, 2), (256, 1), (256, 40)])
+@pytest.mark.parametrize("kind", ["full", "causal", "mask", "causal_mask"])
+def test_pipelined_forward_against_float64(d, heads, kind):
+    """The pipelined forward (eight waves at d = 64 and 128, query blocks of 64 and of 128 at d = 256) at lengths around its tiles of 64
+    and 128 keys and its first and last steps, with a scale whose row maxima move along the row and a negative one."""
+    import torch
+    from paper_2410_09397_amd import attn
+    causal, masked = kind.startswith("causal"), kind.endswith("mask")
+    base = {64: 512, 128: 768, 256: 64}[d]
+    for i, n in enumerate([base, base + 1, base + 63, base + 65, base + 127, base + 128, base + 193, base + 320] + ([1, 5, 130] if d == 256 else [])):
+        scale = (-1 if i % 2 else 1) * (0.5 if i % 3 == 0 else d ** -0.5)
+        print("case", kind, d, heads, n, scale, flush=True)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(d + n)
+        Q, K, V = (torch.randn((1, heads, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+        K *= torch.linspace(0.2, 2.0, n, device="cuda").to(torch.bfloat16)[:, None]  # later keys have larger scores
+        nblk = (n + 127) // 128
+        keep = np.random.default_rng(n).random((nblk, nblk)) < 0.6
+        keep[np.arange(nblk), np.arange(nblk)] = True
+        O, LSE = attn.attn_fwd(Q, K, V, scale, causal=causal, mask=attn.BlockMask(keep, 128, n) if masked else None)
+        h = heads - 1
+        s = Q[0, h].double() @ K[0, h].double().T * scale
+        if masked:
+            s = s.masked_fill(~torch.from_numpy(keep).cuda().repeat_interleave(128, 0).repeat_interleave(128, 1)[:n, :n], float("-inf"))
+        if causal:
+            s = s.masked_fill(torch.ones(n, n, device="cuda", dtype=torch.bool).triu(1), float("-inf"))
+        ref = torch.softmax(s, 1) @ V[0, h].double()
+        # f and O are rounded to bf16 (2^-9 each) and the scores' 2^-24 grow with their size
+        err = float((O[0, h].double() - ref).norm() / ref.norm())
+        assert err <= 5e-3, (n, err)
+        lse = torch.logsumexp(s, 1)
+        assert float((LSE[0, h].double() - lse).abs().max()) <= 2e-3 * max(1.0, float(lse.abs().max()))
