@@ -813,16 +813,12 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     const bool both = p.may_join && !onepass && !dq_only && !dkdv_only && side_by_side(both_grid, D, p.causal || csr_ptr);
     void (*const dq_fn)(FusedParams) = split ? bwd_dq_split_kernel<D> : bwd_dq_kernel<D, 1>;
     void (*const both_fn)(FusedParams, FusedParams) = split ? bwd_both_kernel<D, 2> : bwd_both_kernel<D, 1>;
-    // set on every call (the attribute belongs to the current device, and the call is cheap)
-    const auto set_lds = [](auto fn, int bytes) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    };
     hipError_t e = hipSuccess;
     if (both) {
-        e = set_lds(both_fn, kv_lds);
+        e = allow_lds(both_fn, kv_lds);
     } else if (!onepass) {
-        e = set_lds(bwd_dkdv_kernel<D>, kv_lds);
-        if (e == hipSuccess) e = set_lds(dq_fn, q_lds);
+        e = allow_lds(bwd_dkdv_kernel<D>, kv_lds);
+        if (e == hipSuccess) e = allow_lds(dq_fn, q_lds);
     }
     if (e != hipSuccess) return e;
     OrderParams op = {csr_ptr, csr_idx, csc_ptr, csc_idx, nullptr, nullptr, blocks128, p.causal};

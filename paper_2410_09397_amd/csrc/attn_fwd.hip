@@ -683,8 +683,7 @@ static hipError_t launch_fwd(const FusedParams& p, const int32_t* csr_ptr, const
     if constexpr (D == 256) fn = split ? fwd_pipe_kernel<D, 2> : fwd_pipe_kernel<D, 1>;
     else fn = eight ? fwd_pipe_kernel<D, 4> : split ? fwd_split_kernel<D> : fwd_kernel<D>;
     const int lds = (eight ? 2 : 1) * 2 * (2 * 64 * D * 2);
-    // set on every call: the attribute belongs to the current device, and the call is cheap
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t e = allow_lds(fn, lds);
     if (e != hipSuccess) return e;
     FusedParams pf = p;
     pf.list_ptr = csr_ptr;

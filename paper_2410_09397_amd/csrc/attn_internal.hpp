@@ -6,6 +6,14 @@
 
 namespace attn {
 
+// Dynamic LDS of a kernel beyond the 64 KB that a launch may have without asking.  Set on every call: the attribute belongs to
+// the current device, and the call is cheap.
+template <typename F>
+inline hipError_t allow_lds(F* kernel, int bytes) {
+    if (bytes <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
 // Fused bf16 paths, d in {64, 128, 256}.  csr_* / csc_* are device pointers or nullptr (dense).
 hipError_t launch_fwd_fused(int d, const FusedParams& p, const int32_t* csr_ptr, const int32_t* csr_idx,
                             hipStream_t stream);
