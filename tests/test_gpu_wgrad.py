@@ -58,6 +58,21 @@ def test_wgrad_with_scale_and_causal_mask(n, d, scale, causal):
         assert helpers.rel_err(g[b, h], _composed_reference(inp, b, h, scale, causal)) <= TOL
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_wgrad_at_the_edges_of_row_blocks_and_chunks(d):
+    """Rows on both sides of the projections' blocks of 128 and of the chunks of 256 and 512 rows, whose products may or may not fit
+    where Q, V and O were."""
+    for n in (1, 127, 129, 257, 512, 513):
+        print("case wgrad edges", d, n, flush=True)
+        inp = synth.make_wgrad_inputs(synth.workload(2).small(batch=1, heads=3, n=n, d=d))
+        g = _run_gpu(None, inp, 0.8, n % 2 == 0)
+        if n == 1:  # one key: f = 1, p = 0 up to the rounding of dP - v, which is of the size of v 2^-8 at most
+            assert np.abs(g).max() <= 2.0 ** -7 * np.abs(inp["A1"]).max() * np.abs(inp["A2"]).max() * np.abs(inp["dO"]).max() * d
+            continue
+        for h in (0, 2):
+            assert helpers.rel_err(g[0, h], _composed_reference(inp, 0, h, 0.8, n % 2 == 0)) <= TOL
+
+
 def test_wgrad_is_deterministic():
     w = synth.workload(3).small(batch=1, heads=4, n=2048, d=128)
     inp = synth.make_wgrad_inputs(w)
