@@ -8,8 +8,8 @@
 //                   because v = rowsum(dO o O) is precomputed) -> P, dS in HBM
 //   gemm kernel   : dV = P^T dO, dK = scale dS^T Q, dQ = scale dS K as tiled products with the
 //                   k-loop over n (phase 4 written for dQ/dK/dV instead of A_1^T p A_2)
-// The forward uses the same kernels: partial row statistics of S per 64-key chunk, a combine
-// step for LSE, P = exp(S - LSE) written to HBM, and O = P V.
+// The forward uses the same kernels: exp(S) written to HBM with its sum per row and chunk of 64 keys, a combine step for LSE,
+// and O = diag(l)^-1 exp(S) V.
 #include <type_traits>
 
 #include "attn_common.hpp"
@@ -20,13 +20,23 @@ namespace attn {
 // Scores kernel, tiles of 128 queries x 256 keys, four waves with a 128 x 64 block (4 x 2 accumulators) each; a
 // k-step needs 32-column chunks of two operands (24 KB), and three LDS stages (copies two steps ahead) fit two
 // workgroups on a CU.  Accumulator: lane <-> query, register <-> key.  Modes:
-//   kStats    row maximum and sum of exp of S per 64-key chunk (the forward's first sweep)
-//   kProbs    P = exp(S - LSE) written to the workspace (the forward's second sweep)
+//   kProbs    exp2(s - e) of the scores s (times log2 e) written to the workspace in bf16, and e and the row sum per 64-key chunk (the
+//             forward).  bf16 has the exponents of fp32, so e = 0 loses nothing while a chunk's largest score is moderate, and no sweep
+//             over the scores has to come first (it took 154 of 481 us at b1 h8 n4096 d512; the forward is 370 without it).  A
+//             chunk whose largest score is beyond 2^+-kModerate gets its own whole number e, and the product kernel aligns the
+//             chunks of such a row: a whole number is an exact shift of the exponents.
 //   kBackward P and dS.  The two products of a tile are formed one after the other - S^T over all of d, then dP^T
 //             over all of d - so that the wave can hold its block of the one in progress: 256 x 128 tiles move 384 bytes
 //             from memory per MFMA instead of the 512 of 128 x 128 tiles with both products at once.  Between the
 //             passes P stays in registers, rounded to bf16 as it is stored (dS = P (dP - delta) uses that rounded P).
-enum ScoreMode { kStats = 0, kProbs = 1, kBackward = 2 };
+enum ScoreMode { kProbs = 1, kBackward = 2 };
+constexpr float kModerate = 24.f;
+// O is divided by the sum of what was written, rounded to bf16, not by l: a row that is one key then has that key's value, and the
+// roundings of the other rows cancel in part (with l the error at d = 512 was up to 1.2 times that of rounding f).  A chunk's
+// stat_m holds e and the ratio of the two sums, which is off one by 2^-9 at most: e + kRatio (ratio - 1).
+constexpr float kRatio = 16.f;
+// [bh][chunk][query] places in stat_l that the combine step reuses for a row's results (a row has at least four chunks)
+enum RowSlot { kRowInverse = 0, kRowTop = 1, kRowShifted = 2 };
 constexpr int kScoreStage = (256 + 128) * 32 * 2, kScoreLds = 3 * kScoreStage;
 template <int MODE>
 __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) {
@@ -153,13 +163,13 @@ __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) 
     product(p.K + base, p.Q + base);
     const float cs = p.scale * kLog2e;
     const bool need_mask = (p.causal && k0 + kKeys - 1 > q0) || (k0 + kKeys > p.n);
-    if constexpr (MODE == kStats) {
+    if constexpr (MODE == kProbs) {
 #pragma unroll
         for (int tn = 0; tn < 2; ++tn) {
             const int q = q0 + 64 * wn + 32 * tn + l32;
+            char* prow = smem + (64 * wn + 32 * tn + l32) * (kKeys * 2);
 #pragma unroll
             for (int half = 0; half < 2; ++half) {  // the two 64-key chunks of this wave's 128 keys
-                float x[2][16];
                 float mx = -__builtin_inff();
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
@@ -168,33 +178,53 @@ __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) 
                         float v = c[2 * half + t][tn][i] * cs;
                         const int key = k0 + 128 * wm + 64 * half + 32 * t + acc_row(i, h);
                         if (need_mask && (key >= p.n || (p.causal && key > q))) v = -__builtin_inff();
-                        x[t][i] = v;
+                        c[2 * half + t][tn][i] = v;
                         mx = fmaxf(mx, v);
                     }
                 mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-                const float m_use = mx == -__builtin_inff() ? 0.f : mx;
-                float sum = 0.f;
+                const float e = fabsf(mx) <= kModerate || mx == -__builtin_inff() ? 0.f : __builtin_ceilf(mx);
+                float sum = 0.f, sum_r = 0.f;
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(x[t][i] - m_use);
+                    for (int g = 0; g < 4; ++g) {
+                        float pv[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            pv[r] = __builtin_amdgcn_exp2f(c[2 * half + t][tn][4 * g + r] - e);
+                            sum += pv[r];
+                        }
+                        u32x2 a;
+                        a[0] = q < p.n ? pack_bf16(pv[0], pv[1]) : 0;
+                        a[1] = q < p.n ? pack_bf16(pv[2], pv[3]) : 0;
+#pragma unroll
+                        for (int x = 0; x < 2; ++x) {
+                            const unsigned pair = a[x];
+                            sum_r += __builtin_bit_cast(float, pair << 16);
+                            sum_r += __builtin_bit_cast(float, pair & 0xffff0000u);
+                        }
+                        const int slot = (((16 * wm + 8 * half + 4 * t + g) ^ swz<kKeys>(64 * wn + 32 * tn + l32)) << 4) + 8 * h;
+                        *reinterpret_cast<u32x2*>(prow + slot) = a;
+                    }
                 sum += __shfl_xor(sum, 32, 64);
+                sum_r += __shfl_xor(sum_r, 32, 64);
                 if (q < p.n && h == 0) {
                     const long o = ((long)bh * (2 * nbq) + k0 / 64 + 2 * wm + half) * p.n + q;  // [bh][chunk][query]
-                    p.stat_m[o] = mx;
+                    p.stat_m[o] = sum > 0.f ? fmaf(sum_r / sum - 1.f, kRatio, e) : e;
                     p.stat_l[o] = sum;
                 }
             }
         }
+        store_tile(p.P);
         return;
     }
     // P (bf16): written out and, in the backward, kept packed in registers
-    uint32_t pk[MODE == kBackward ? 4 : 1][2][8];
+    uint32_t pk[4][2][8];
 #pragma unroll
     for (int tn = 0; tn < 2; ++tn) {
         const int q = q0 + 64 * wn + 32 * tn + l32;
         const bool q_ok = q < p.n;
-        const float lse2 = q_ok ? (MODE == kBackward ? p.LSE : p.LSEout)[(long)bh * p.n + q] * kLog2e : __builtin_inff();
+        const float lse2 = q_ok ? p.LSE[(long)bh * p.n + q] * kLog2e : __builtin_inff();
         char* prow = smem + (64 * wn + 32 * tn + l32) * (kKeys * 2);
 #pragma unroll
         for (int tm = 0; tm < 4; ++tm)
@@ -212,16 +242,13 @@ __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) 
                 u32x2 a;
                 a[0] = pack_bf16(pv[0], pv[1]);
                 a[1] = pack_bf16(pv[2], pv[3]);
-                if constexpr (MODE == kBackward) {
-                    pk[tm][tn][2 * g] = a[0];
-                    pk[tm][tn][2 * g + 1] = a[1];
-                }
+                pk[tm][tn][2 * g] = a[0];
+                pk[tm][tn][2 * g + 1] = a[1];
                 const int slot = (((16 * wm + 4 * tm + g) ^ swz<kKeys>(64 * wn + 32 * tn + l32)) << 4) + 8 * h;
                 *reinterpret_cast<u32x2*>(prow + slot) = a;
             }
     }
     store_tile(p.P);
-    if constexpr (MODE != kBackward) return;
 
     // ---- pass 2: dP^T -> dS = P (dP - delta)
     product(p.V + base, p.dO + base);
@@ -251,13 +278,14 @@ __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) 
     store_tile(p.dS);
 }
 
-// LSE from the per-chunk statistics.  A workgroup takes 16 rows; 16 threads per row each fold every 16th chunk into a
-// running (maximum, sum) pair, and the 16 pairs of a row are folded through LDS (one thread per row alone spent its time
+// LSE from the per-chunk sums, and for the product kernel a row's 1 / l, the largest e of its chunks and whether any chunk has one.
+// A workgroup takes 16 rows; 16 threads per row each fold every 16th chunk into a running (e, sum) pair, and the 16 pairs of a row are folded through LDS (one thread per row alone spent its time
 // waiting for one load after the other).  Statistics are [bh][chunk][query]: threads that stand for consecutive
 // queries read consecutive floats.
 constexpr int kCombineRows = 16, kCombineParts = kThreads / kCombineRows;
 __global__ void __launch_bounds__(kThreads) ld_lse_combine_kernel(LargeDParams p) {
-    __shared__ float part_m[kCombineParts][kCombineRows], part_l[kCombineParts][kCombineRows];
+    __shared__ float part_m[kCombineParts][kCombineRows], part_l[kCombineParts][kCombineRows], part_r[kCombineParts][kCombineRows];
+    __shared__ int shifted[kCombineRows];
     const int rl = threadIdx.x % kCombineRows, g = threadIdx.x / kCombineRows;
     const long rows = (long)p.batch * p.heads * p.n;
     const long r = (long)blockIdx.x * kCombineRows + rl;
@@ -267,28 +295,33 @@ __global__ void __launch_bounds__(kThreads) ld_lse_combine_kernel(LargeDParams p
     const int chunks = ok ? 2 * (p.causal ? q / 128 + 1 : nb) : 0;
     const long pitch = p.n;
     const long head = ok ? (r / p.n) * (2 * nb) * pitch + q : 0;
-    float M = -__builtin_inff(), L = 0.f;
+    if (threadIdx.x < kCombineRows) shifted[threadIdx.x] = 0;
+    __syncthreads();
+    float M = -__builtin_inff(), L = 0.f, R = 0.f;  // R: the sum of the rounded values
+    bool any = false;
+    auto fold = [&](float m, float l, float r) {
+        if (l == 0.f) return;  // (a chunk with nothing visible has no say)
+        const float top = fmaxf(M, m), old = __builtin_amdgcn_exp2f(M - top), now = __builtin_amdgcn_exp2f(m - top);  // (exp2(-inf) = 0 at the start)
+        L = L * old + l * now;
+        R = R * old + r * now;
+        M = top;
+    };
     for (int c = g; c < chunks; c += kCombineParts) {
-        const float mc = p.stat_m[head + c * pitch], lc = p.stat_l[head + c * pitch];
-        if (mc != -__builtin_inff()) {
-            const float top = fmaxf(M, mc);
-            L = L * __builtin_amdgcn_exp2f(M - top) + lc * __builtin_amdgcn_exp2f(mc - top);  // (exp2(-inf) = 0 at the start)
-            M = top;
-        }
+        const float mc = p.stat_m[head + c * pitch], lc = p.stat_l[head + c * pitch], e = rintf(mc);
+        any = any || e != 0.f;
+        fold(e, lc, fmaf(lc, (mc - e) * (1.f / kRatio), lc));
     }
     part_m[g][rl] = M;
     part_l[g][rl] = L;
+    part_r[g][rl] = R;
+    if (any) shifted[rl] = 1;
     __syncthreads();
     if (g != 0 || !ok) return;
-    for (int k = 1; k < kCombineParts; ++k) {
-        const float mk = part_m[k][rl], lk = part_l[k][rl];
-        if (mk != -__builtin_inff()) {
-            const float top = fmaxf(M, mk);
-            L = L * __builtin_amdgcn_exp2f(M - top) + lk * __builtin_amdgcn_exp2f(mk - top);
-            M = top;
-        }
-    }
+    for (int k = 1; k < kCombineParts; ++k) fold(part_m[k][rl], part_l[k][rl], part_r[k][rl]);
     p.LSEout[r] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
+    p.stat_l[head + kRowInverse * pitch] = L > 0.f ? 1.f / R : 0.f;
+    p.stat_l[head + kRowTop * pitch] = M;
+    p.stat_l[head + kRowShifted * pitch] = shifted[rl] ? 1.f : 0.f;
 }
 
 // C[m][n] = alpha * sum_k A(m, k) B(k, n): 128 x 128 output tile per workgroup, k-loop over the
@@ -308,8 +341,11 @@ struct GemmArgs {
 // from global memory for 64 MFMAs.  (With 128 x 128 tiles the copies alone, at the 64 B/clk that
 // the vector memory path delivers per CU, took as long as the MFMAs.)
 constexpr int kGemmBK = 32, kGemmM = 256;
-template <bool A_KMAJOR>
+// ROWS: A holds exp2(s - e) of the forward: rows whose chunks have an e other than 0 are aligned to the row's largest on the way into
+// the product (e - top whole steps of the exponent: a saturating subtraction on pairs of bf16), and a row of C is divided by its l.
+template <bool A_KMAJOR, bool ROWS>
 __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, GemmArgs g) {
+    static_assert(!(A_KMAJOR && ROWS), "the rows of A are the rows of C");
     constexpr int BK = kGemmBK, TM = kGemmM;
     constexpr int kTileA = TM * BK * 2, kTileB = 128 * BK * 2, kStage = kTileA + kTileB;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -395,9 +431,31 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
         wait_direct_loads();
     }
     __syncthreads();
+    const float* row_l = p.stat_l + (long)bh * (p.npad / 64) * p.n;
+    bool shifted = false;
+    float top[4];
+    if constexpr (ROWS) {
+        shifted = __syncthreads_or(m0 + tid < p.n && row_l[(long)kRowShifted * p.n + m0 + tid] != 0.f);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) top[t] = row_l[(long)kRowTop * p.n + min(m0 + 128 * wm + 32 * t + l32, p.n - 1)];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) settle(top[t]);
+    }
     auto step = [&](int k, auto stage_index) {
         constexpr int si = decltype(stage_index)::value, so = si * kStage;
         const bool more = k + 2 * BK < k_end;
+        unsigned lower[4] = {0, 0, 0, 0};  // this k-step's shift of the exponents of a pair, per 32-row tile
+        if constexpr (ROWS) {
+            if (shifted) {
+                const float* e = p.stat_m + ((long)bh * (p.npad / 64) + k / 64) * p.n;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float by = top[t] - rintf(e[min(m0 + 128 * wm + 32 * t + l32, p.n - 1)]);
+                    lower[t] = (unsigned)fminf(fmaxf(by, 0.f), 255.f) * 0x00800080u;
+                    settle(lower[t]);
+                }
+            }
+        }
         if (more) fetch(k + 2 * BK, (si + 2) % 3);
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
@@ -408,6 +466,21 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
                     a[t] = FragOffsets<TM>::read_t(smem, ra[t][0], ra[t][1], 16 * ks, so);
                 } else {
                     a[t] = FragOffsets<BK>::read(smem, rc[ks], so + 32 * t * (BK * 2));
+                }
+            }
+            if constexpr (ROWS) {
+                if (shifted) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+                        u32x4 v = __builtin_bit_cast(u32x4, a[t]);
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) {
+                            const unsigned pair = v[x], by = lower[t];  // (a bit cast of a vector's element takes element 0)
+                            v[x] = __builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, pair), __builtin_bit_cast(u16x2, by)));
+                        }
+                        a[t] = __builtin_bit_cast(bf16x8, v);
+                    }
                 }
             }
 #pragma unroll
@@ -434,6 +507,11 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
         step(k, std::integral_constant<int, 0>{});
         if (k + BK < k_end) step(k + BK, std::integral_constant<int, 1>{});
     }
+    float* inverse = reinterpret_cast<float*>(smem);  // 1 / l of the tile's rows (the stages are free)
+    if constexpr (ROWS) {
+        inverse[tid] = m0 + tid < p.n ? row_l[(long)kRowInverse * p.n + m0 + tid] : 0.f;
+        __syncthreads();
+    }
     // accumulator: lane <-> output column, register <-> output row
 #pragma unroll
     for (int tm = 0; tm < 4; ++tm)
@@ -442,8 +520,12 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
             const int col = n0 + 64 * wn + 32 * tn + l32;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int row = m0 + 128 * wm + 32 * tm + acc_row(i, h);
-                if (row < p.n && col < p.d) g.C[base + (long)row * p.stride_n + col] = (__bf16)(c[tm][tn][i] * g.alpha);
+                const int rel = 128 * wm + 32 * tm + acc_row(i, h), row = m0 + rel;
+                float f = g.alpha;
+                if constexpr (ROWS) f = inverse[rel];
+                float v = c[tm][tn][i] * f;
+                if (ROWS && f == 0.f) v = 0.f;  // a row with no finite sum
+                if (row < p.n && col < p.d) g.C[base + (long)row * p.stride_n + col] = (__bf16)v;
             }
         }
 }
@@ -453,21 +535,21 @@ static hipError_t set_lds(const void* fn, int bytes) {
 }
 
 constexpr int kGemmLds = 3 * (kGemmM + 128) * kGemmBK * 2;  // three stages of an A and a B tile (72 KB: two workgroups per CU)
-template <bool A_KMAJOR>
+template <bool A_KMAJOR, bool ROWS>
 static void run_gemm(const LargeDParams& p, const __bf16* A, const __bf16* B, __bf16* C, float alpha,
                      hipStream_t stream) {
     const dim3 grid((unsigned)(((p.d + 127) / 128) * (p.npad / kGemmM) * p.batch * p.heads));
     GemmArgs g{A, B, C, alpha};
-    hipLaunchKernelGGL(ld_gemm_kernel<A_KMAJOR>, grid, dim3(kThreads), kGemmLds, stream, p, g);
+    hipLaunchKernelGGL((ld_gemm_kernel<A_KMAJOR, ROWS>), grid, dim3(kThreads), kGemmLds, stream, p, g);
 }
 
 // LDS sizes of the large-d kernels on the current device (set on every call: cheap, and per device).
 hipError_t configure_larged() {
-    hipError_t e = set_lds(reinterpret_cast<const void*>(ld_scores_kernel<kStats>), kScoreLds);
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_scores_kernel<kProbs>), kScoreLds);
+    hipError_t e = set_lds(reinterpret_cast<const void*>(ld_scores_kernel<kProbs>), kScoreLds);
     if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_scores_kernel<kBackward>), kScoreLds);
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<true>), kGemmLds);
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<false>), kGemmLds);
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<true, false>), kGemmLds);
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<false, false>), kGemmLds);
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<false, true>), kGemmLds);
     return e;
 }
 
@@ -479,16 +561,15 @@ hipError_t launch_larged(bool backward, const LargeDParams& p, hipStream_t strea
     const dim3 sgrid(nbq * (unsigned)(p.npad / 256) * bh);  // score tiles: 128 queries x 256 keys
     const dim3 block(kThreads);
     if (!backward) {
-        hipLaunchKernelGGL(ld_scores_kernel<kStats>, sgrid, block, kScoreLds, stream, p);
+        hipLaunchKernelGGL(ld_scores_kernel<kProbs>, sgrid, block, kScoreLds, stream, p);
         const long rows = (long)bh * p.n;
         hipLaunchKernelGGL(ld_lse_combine_kernel, dim3((unsigned)((rows + kCombineRows - 1) / kCombineRows)), block, 0, stream, p);
-        hipLaunchKernelGGL(ld_scores_kernel<kProbs>, sgrid, block, kScoreLds, stream, p);
-        run_gemm<false>(p, p.P, p.V, p.Oout, 1.f, stream);
+        run_gemm<false, true>(p, p.P, p.V, p.Oout, 1.f, stream);
     } else {
         hipLaunchKernelGGL(ld_scores_kernel<kBackward>, sgrid, block, kScoreLds, stream, p);
-        run_gemm<true>(p, p.P, p.dO, p.dV, 1.f, stream);
-        run_gemm<true>(p, p.dS, p.Q, p.dK, p.scale, stream);
-        run_gemm<false>(p, p.dS, p.K, p.dQ, p.scale, stream);
+        run_gemm<true, false>(p, p.P, p.dO, p.dV, 1.f, stream);
+        run_gemm<true, false>(p, p.dS, p.Q, p.dK, p.scale, stream);
+        run_gemm<false, false>(p, p.dS, p.K, p.dQ, p.scale, stream);
     }
     return hipGetLastError();
 }

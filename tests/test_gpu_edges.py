@@ -193,3 +193,34 @@ def test_pipelined_forward_against_float64(d, heads, kind):
         assert err <= 5e-3, (n, err)
         lse = torch.logsumexp(s, 1)
         assert float((LSE[0, h].double() - lse).abs().max()) <= 2e-3 * max(1.0, float(lse.abs().max()))
+
+
+@pytest.mark.parametrize("d", [512, 1024])
+@pytest.mark.parametrize("causal", [False, True])
+def test_large_d_forward_with_scores_of_any_size(d, causal):
+    """exp(S) is written without a reference where a chunk's largest score is moderate and with one of its own beyond: rows of
+    moderate, large positive, large negative and mixed scores, in blocks with and without each other, and rows whose other chunks
+    vanish beside one, against float64."""
+    import torch
+    from paper_2410_09397_amd import attn
+    for n in (1, 64, 65, 333, 700):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(d + n)
+        Q, K, V = (torch.randn((1, 3, n, d), generator=gen, device="cuda") for _ in range(3))
+        Q[0, 0] *= torch.linspace(0.1, 60.0, n, device="cuda")[:, None]      # scores of -250 to 250 in the last rows
+        Q[0, 1, n // 2:] = 12.0                                              # rows whose scores are large and of one sign
+        K[0, 1] = K[0, 1].abs() * torch.where(torch.arange(n, device="cuda") % 97 < 60, 1.0, -1.0)[:, None]
+        Q, K, V = (t.to(torch.bfloat16) for t in (Q, K, V))
+        print("case large d scores", d, causal, n, flush=True)
+        scale = d ** -0.5
+        O, LSE = attn.attn_fwd(Q, K, V, scale, causal=causal)
+        for h in range(3):
+            s = Q[0, h].double() @ K[0, h].double().T * scale
+            if causal:
+                s = s.masked_fill(torch.ones(n, n, device="cuda", dtype=torch.bool).triu(1), float("-inf"))
+            ref = torch.softmax(s, 1) @ V[0, h].double()
+            rows = ((O[0, h].double() - ref).norm(dim=1) / ref.norm(dim=1)).max()
+            # per row: f and O are rounded to bf16 (2^-9 each), and scores up to 500 are off by their 2^-22 in fp32 (their sum over d)
+            assert float(rows) <= 2.0 ** -7, (n, h, float(rows))
+            lse = torch.logsumexp(s, 1)
+            assert float(((LSE[0, h].double() - lse).abs() / lse.abs().clamp(min=1.0)).max()) <= 1e-5
