@@ -149,7 +149,12 @@ __device__ __forceinline__ void wait_reads() { asm volatile("s_waitcnt lgkmcnt(0
 //   block4   fp32: columns 64 B + 4 r16 .. + 3 of row 4 h4 + i, i.e. four operands; used as A operand number b, output row m
 //            <-> column 64 B + 4 m + b
 //   block2   fp32, the last 32 columns of an odd width: columns 2 r16, 2 r16 + 1
-template <int KIND, int DP>
+//   block1   fp32, the first 16 of these 32 where d needs no more: column r16
+// NARROW (fp32, widths that are not whole 64s, where output columns come four to an operand): columns from DP - 16 on lie past d, and
+// their pieces are left out of the first products and of the output columns of the second.  Kernels of their own: tested in
+// the loop, d = 96 lost 3.6 %, and bf16, which would save one block of the second products, as much as it gained.  us, forward / backward:
+// b2 h6 n777 d80 causal 21.3 / 68.8 -> 19.9 / 61.0, b2 h3 n1000 d16 15.5 / 37.4 -> 11.9 / 26.2, h2 n1000 d77 26.1 / 44.0 -> 24.2 / 39.5
+template <int KIND, int DP, bool NARROW>
 struct StageReader {
     static constexpr int P = DP * (int)sizeof(typename Traits<KIND>::T), kGroupBytes = 16 * P, kN4 = DP / 64;
     typedef typename Traits<KIND>::Row Row;
@@ -163,7 +168,8 @@ struct StageReader {
             for (int i = 0; i < 4; ++i) {
                 const int row = 4 * h4 + i;
                 cb[i] = wave_off + row * P + ((r16 ^ stage_swz<P>(row)) << 4);
-                c2[i] = wave_off + row * P + 256 * kN4 + (((r16 >> 1) ^ stage_swz<P>(row)) << 4) + 8 * (r16 & 1);
+                const int piece = NARROW ? r16 >> 2 : r16 >> 1, in = NARROW ? 4 * (r16 & 3) : 8 * (r16 & 1);
+                c2[i] = wave_off + row * P + 256 * kN4 + ((piece ^ stage_swz<P>(row)) << 4) + in;
             }
         } else {
             const int row = 4 * h4 + (r16 >> 2);
@@ -188,6 +194,9 @@ struct StageReader {
     }
     __device__ __forceinline__ f32x2 block2(const char* smem, int imm, int i) const {
         return *reinterpret_cast<const f32x2*>(smem + c2[i] + imm);
+    }
+    __device__ __forceinline__ float block1(const char* smem, int imm, int i) const {
+        return *reinterpret_cast<const float*>(smem + c2[i] + imm);
     }
 };
 
@@ -245,8 +254,8 @@ struct Weights<kF32> {
 };
 
 // acc[x][nb] += columns^T weights[x]: every column operand read from LDS feeds XG products (per part)
-template <int KIND, int DP, int XG>
-__device__ __forceinline__ void accumulate(f32x4 (&acc)[XG][DP / 16], const StageReader<KIND, DP>& rd, const char* smem, int imm,
+template <int KIND, int DP, int XG, bool NARROW>
+__device__ __forceinline__ void accumulate(f32x4 (&acc)[XG][DP / 16], const StageReader<KIND, DP, NARROW>& rd, const char* smem, int imm,
                                            const Weights<KIND> (&w)[XG]) {
     if constexpr (KIND != kF32) {
 #pragma unroll
@@ -270,6 +279,16 @@ __device__ __forceinline__ void accumulate(f32x4 (&acc)[XG][DP / 16], const Stag
                         acc[x][4 * B + b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b], w[x].w[i], acc[x][4 * B + b], 0, 0, 0);
             }
         if constexpr (DP % 64 != 0) {
+            if constexpr (NARROW) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float a = rd.block1(smem, imm, i);
+#pragma unroll
+                    for (int x = 0; x < XG; ++x)
+                        acc[x][DP / 16 - 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w[x].w[i], acc[x][DP / 16 - 2], 0, 0, 0);
+                }
+                return;
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const f32x2 a = rd.block2(smem, imm, i);
@@ -334,7 +353,7 @@ __device__ __forceinline__ Groups make_groups(const GenericParams& p, int bh, bo
 // ------------------------------------------------------------------------------ sum over the waves
 // `factor(w, row)` scales the part of wave w.  red: [NW][16 XG][DP + 4] floats, over the stages.
 // Returns whether this thread met a sum that is not finite.
-template <int KIND, bool QUAD, int DP, int XG, int NW, typename F>
+template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW, typename F>
 __device__ __forceinline__ bool combine_store(const f32x4 (&acc)[XG][DP / 16], float* red, int w, int lane, char* out, unsigned ldb,
                                               int row0, int n, int d, F factor) {
     constexpr int kPitch = DP + 4;
@@ -354,8 +373,10 @@ __device__ __forceinline__ bool combine_store(const f32x4 (&acc)[XG][DP / 16], f
                 for (int B = 0; B < DP / 64; ++B)
                     *reinterpret_cast<f32x4*>(row + 64 * B + 16 * h4 + 4 * i) =
                         f32x4{acc[x][4 * B][i], acc[x][4 * B + 1][i], acc[x][4 * B + 2][i], acc[x][4 * B + 3][i]};
-                if constexpr (DP % 64 != 0)
-                    *reinterpret_cast<f32x2*>(row + 64 * (DP / 64) + 8 * h4 + 2 * i) = f32x2{acc[x][DP / 16 - 2][i], acc[x][DP / 16 - 1][i]};
+                if constexpr (DP % 64 != 0) {
+                    if constexpr (NARROW) row[64 * (DP / 64) + 4 * h4 + i] = acc[x][DP / 16 - 2][i];
+                    else *reinterpret_cast<f32x2*>(row + 64 * (DP / 64) + 8 * h4 + 2 * i) = f32x2{acc[x][DP / 16 - 2][i], acc[x][DP / 16 - 1][i]};
+                }
             }
         }
     }
@@ -486,7 +507,7 @@ __device__ __forceinline__ void balanced_block(int linear, int blocks, int bh_to
 // ------------------------------------------------------------------------------------ forward
 // fp32, 32 columns: as many waves as the registers of the loop alone allow (64 instead of 68, which the redone rows would take: 7 %
 // of the time of 32768 heads of 4 rows)
-template <int KIND, bool QUAD, int DP, int XG, int NW>
+template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW>
 __global__ void __launch_bounds__(NW * 64, KIND == kF32 && DP == 32 ? (QUAD ? 8 : 7) : 2) stream_fwd_kernel(GenericParams p) {
     typedef Traits<KIND> TR;
     typedef typename TR::T T;
@@ -511,7 +532,7 @@ __global__ void __launch_bounds__(NW * 64, KIND == kF32 && DP == 32 ? (QUAD ? 8 
     const unsigned lds = (unsigned)(size_t)(ATTN_LDS char*)smem + wave_off;
     Loader ld;
     ld.init(lane, ldb, p.d);
-    StageReader<KIND, DP> rd;
+    StageReader<KIND, DP, NARROW> rd;
     rd.init(lane, wave_off);
     int kb[G], kb_next[G];
     auto next_step = [&](int g0) {
@@ -577,7 +598,7 @@ __global__ void __launch_bounds__(NW * 64, KIND == kF32 && DP == 32 ? (QUAD ? 8 
 #pragma unroll
             for (int g = 0; g < G; ++g) st[x][g] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
+        for (int s = 0; s < NS - NARROW; ++s)
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const typename TR::Row kf = rd.row(smem, 0, g, s);
@@ -639,7 +660,7 @@ __global__ void __launch_bounds__(NW * 64, KIND == kF32 && DP == 32 ? (QUAD ? 8 
         }
         if (more) wait_copies<C>();
         else wait_copies<0>();
-        accumulate<KIND, DP, XG>(acc, rd, smem, kV, wt);
+        accumulate(acc, rd, smem, kV, wt);
         if (more) {
             wait_reads();
             ld.load(V, kb_next, p.n, ldb, p.d, lds + kV, lane);
@@ -675,7 +696,7 @@ __global__ void __launch_bounds__(NW * 64, KIND == kF32 && DP == 32 ? (QUAD ? 8 
             p.LSE_out[(long)bh * p.n + i0 + tid] =
                 L > 0.f ? fmaf(M, kLn2, fmaf(M, -1.90465421e-9f, __builtin_amdgcn_logf(L) * kLn2)) : -__builtin_inff();  // (ln 2 in two parts)
     }
-    const bool bad = combine_store<KIND, QUAD, DP, XG, NW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.O, base)),
+    const bool bad = combine_store<KIND, QUAD, DP, XG, NW, NARROW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.O, base)),
                                                        ldb, i0, p.n, p.d, [&](int k, int r) { return st_l[k][r]; });
     redo_rows<XG, NW>(bad, w, i0, p.n, [&](const GenericParams& p, int i) {
         row_forward<T, row_words<T>(DP)>(p, bh, i, lane, reinterpret_cast<float*>(smem) + w * DP);
@@ -684,7 +705,7 @@ __global__ void __launch_bounds__(NW * 64, KIND == kF32 && DP == 32 ? (QUAD ? 8 
 
 // ----------------------------------------------------------------------------------- backward
 // dQ of 16 XG queries
-template <int KIND, bool QUAD, int DP, int XG, int NW>
+template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW>
 __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, int bh, int blk) {
     typedef Traits<KIND> TR;
     typedef typename TR::T T;
@@ -704,7 +725,7 @@ __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, in
     const unsigned lds = (unsigned)(size_t)(ATTN_LDS char*)smem + wave_off;
     Loader ld;
     ld.init(lane, ldb, p.d);
-    StageReader<KIND, DP> rd;
+    StageReader<KIND, DP, NARROW> rd;
     rd.init(lane, wave_off);
     int kb[G], kb_next[G];
     auto next_step = [&](int g0) {
@@ -766,7 +787,7 @@ __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, in
             for (int g = 0; g < G; ++g) st[x][g] = dp[x][g] = f32x4{0.f, 0.f, 0.f, 0.f};
         wait_copies<C>();  // V is there; K, requested after it, may be on its way
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
+        for (int s = 0; s < NS - NARROW; ++s)
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const typename TR::Row vf = rd.row(smem, kV, g, s);
@@ -775,7 +796,7 @@ __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, in
             }
         wait_copies<0>();
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
+        for (int s = 0; s < NS - NARROW; ++s)
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const typename TR::Row kf = rd.row(smem, 0, g, s);
@@ -806,14 +827,14 @@ __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, in
                 }
             wt[x].set(dp[x]);
         }
-        accumulate<KIND, DP, XG>(acc, rd, smem, 0, wt);
+        accumulate(acc, rd, smem, 0, wt);
         if (more) {
             wait_reads();
             ld.load(K, kb_next, p.n, ldb, p.d, lds, lane);
         }
     }
     const float scale = p.scale;
-    const bool bad = combine_store<KIND, QUAD, DP, XG, NW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.dQ, base)),
+    const bool bad = combine_store<KIND, QUAD, DP, XG, NW, NARROW>(acc, reinterpret_cast<float*>(smem), w, lane, const_cast<char*>(head_base<T>(p.dQ, base)),
                                                        ldb, i0, p.n, p.d, [&](int, int) { return scale; });
     redo_rows<XG, NW>(bad, w, i0, p.n, [&](const GenericParams& p, int i) {
         float* rows = reinterpret_cast<float*>(smem) + w * 2 * DP;
@@ -824,7 +845,7 @@ __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, in
 // dK, dV of 16 XG keys.  With kOwnDelta the row sums v of the streamed queries are formed here again (fp32: from the
 // fragments at hand; bf16: the diagonal of dO O^T), so that both halves of the backward run in one launch with nothing
 // between them.
-template <int KIND, bool QUAD, int DP, int XG, int NW>
+template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW>
 __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, int bh, int blk) {
     typedef Traits<KIND> TR;
     typedef typename TR::T T;
@@ -848,7 +869,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
     const unsigned lds = (unsigned)(size_t)(ATTN_LDS char*)smem + wave_off;
     Loader ld;
     ld.init(lane, ldb, p.d);
-    StageReader<KIND, DP> rd;
+    StageReader<KIND, DP, NARROW> rd;
     rd.init(lane, wave_off);
     int qb[G], qb_next[G];
     auto next_step = [&](int g0) {
@@ -910,7 +931,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
             f32x4 diag = {0.f, 0.f, 0.f, 0.f};
             float dot = 0.f;
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
+            for (int s = 0; s < NS - NARROW; ++s) {
                 const typename TR::Row gr = rd.row(smem, kG_, g, s);
 #pragma unroll
                 for (int x = 0; x < XG; ++x) dp[x][g] = mma_rows(gr, vf[x][s], dp[x][g]);
@@ -941,7 +962,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
         }
         wait_copies<0>();
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
+        for (int s = 0; s < NS - NARROW; ++s)
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const typename TR::Row qr = rd.row(smem, 0, g, s);
@@ -999,21 +1020,21 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
             wp[x].set(st[x]);
             wd[x].set(dp[x]);
         }
-        accumulate<KIND, DP, XG>(dv, rd, smem, kG_, wp);
+        accumulate(dv, rd, smem, kG_, wp);
         if (more) {
             wait_reads();
             ld.load(dO, qb_next, p.n, ldb, p.d, lds + kG_, lane);
         }
-        accumulate<KIND, DP, XG>(dk, rd, smem, 0, wd);
+        accumulate(dk, rd, smem, 0, wd);
         if (more) {
             wait_reads();
             ld.load(Q, qb_next, p.n, ldb, p.d, lds, lane);
         }
     }
     const float scale = p.scale;
-    const bool bad_v = combine_store<KIND, QUAD, DP, XG, NW>(dv, reinterpret_cast<float*>(smem), w, lane,
+    const bool bad_v = combine_store<KIND, QUAD, DP, XG, NW, NARROW>(dv, reinterpret_cast<float*>(smem), w, lane,
                                                          const_cast<char*>(head_base<T>(p.dV, base)), ldb, j0, p.n, p.d, [&](int, int) { return 1.f; });
-    const bool bad_k = combine_store<KIND, QUAD, DP, XG, NW>(dk, reinterpret_cast<float*>(smem), w, lane,
+    const bool bad_k = combine_store<KIND, QUAD, DP, XG, NW, NARROW>(dk, reinterpret_cast<float*>(smem), w, lane,
                                                          const_cast<char*>(head_base<T>(p.dK, base)), ldb, j0, p.n, p.d, [&](int, int) { return scale; });
     redo_rows<XG, NW>(bad_v || bad_k, w, j0, p.n, [&](const GenericParams& p, int j) {
         float* rows = reinterpret_cast<float*>(smem) + w * 2 * DP;
@@ -1022,24 +1043,24 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
 }
 
 // One launch for the whole backward: query blocks (dQ) and key blocks (dK, dV) side by side.
-template <int KIND, bool QUAD, int DP, int XG, int NW>
+template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW>
 __global__ void __launch_bounds__(NW * 64, NW == 8 || DP <= 96 ? 2 : 1) stream_bwd_kernel(GenericParams p) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int blocks = (p.n + 16 * XG - 1) / (16 * XG);
     int bh, blk, role;
     balanced_block(blockIdx.x, blocks, p.batch * p.heads, 2, p.causal, bh, blk, role);
-    if (role) stream_dkdv<KIND, QUAD, DP, XG, NW>(p, smem, bh, blk);
-    else stream_dq<KIND, QUAD, DP, XG, NW>(p, smem, bh, p.causal ? blocks - 1 - blk : blk);
+    if (role) stream_dkdv<KIND, QUAD, DP, XG, NW, NARROW>(p, smem, bh, blk);
+    else stream_dq<KIND, QUAD, DP, XG, NW, NARROW>(p, smem, bh, p.causal ? blocks - 1 - blk : blk);
 }
 
-template <int KIND, bool QUAD, int DP, int NW, bool BACKWARD>
+template <int KIND, bool QUAD, int DP, int NW, bool BACKWARD, bool NARROW>
 hipError_t launch_waves(const GenericParams& p, dim3 grid, hipStream_t stream) {
     constexpr int XG = kOwned<KIND, DP>;
     constexpr int stages = NW * stage_lds<KIND, QUAD, DP>(BACKWARD), red = NW * 16 * XG * (DP + 4) * (int)sizeof(float);
     constexpr int lds = stages > red ? stages : red;
     auto kernel = [] {
-        if constexpr (BACKWARD) return stream_bwd_kernel<KIND, QUAD, DP, XG, NW>;
-        else return stream_fwd_kernel<KIND, QUAD, DP, XG, NW>;
+        if constexpr (BACKWARD) return stream_bwd_kernel<KIND, QUAD, DP, XG, NW, NARROW>;
+        else return stream_fwd_kernel<KIND, QUAD, DP, XG, NW, NARROW>;
     }();
     if constexpr (lds > 60 * 1024) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1056,17 +1077,19 @@ hipError_t launch_waves(const GenericParams& p, dim3 grid, hipStream_t stream) {
 // 2000, 2 to 64 heads, d = 32 to 192, both types, causal and full: up to 256 workgroups 0.69 to 1.0, 257 to 512 0.81 to 1.38 (either
 // can win, by how full the second round is), 513 to 768 0.96 to 1.59, beyond 0.96 to 1.96.  Two and three stages per wave hid
 // no more than one.
-template <int KIND, bool QUAD, int DP, bool BACKWARD>
+template <int KIND, bool QUAD, int DP, bool BACKWARD, bool NARROW>
 hipError_t run_waves(const GenericParams& p, hipStream_t stream) {
     constexpr int rows = 16 * kOwned<KIND, DP>;
     const dim3 grid((unsigned)((p.n + rows - 1) / rows * p.batch * p.heads * (BACKWARD ? 2 : 1)));
     if constexpr (eight_waves<KIND, QUAD, DP>(BACKWARD))
-        if (grid.x <= 512) return launch_waves<KIND, QUAD, DP, 8, BACKWARD>(p, grid, stream);
-    return launch_waves<KIND, QUAD, DP, 4, BACKWARD>(p, grid, stream);
+        if (grid.x <= 512) return launch_waves<KIND, QUAD, DP, 8, BACKWARD, NARROW>(p, grid, stream);
+    return launch_waves<KIND, QUAD, DP, 4, BACKWARD, NARROW>(p, grid, stream);
 }
 template <int KIND, bool QUAD, int DP>
 hipError_t run_stream(const GenericParams& p, bool backward, hipStream_t stream) {
-    return backward ? run_waves<KIND, QUAD, DP, true>(p, stream) : run_waves<KIND, QUAD, DP, false>(p, stream);
+    if constexpr (KIND == kF32 && DP % 64 != 0)
+        if (p.d <= DP - 16) return backward ? run_waves<KIND, QUAD, DP, true, true>(p, stream) : run_waves<KIND, QUAD, DP, false, true>(p, stream);
+    return backward ? run_waves<KIND, QUAD, DP, true, false>(p, stream) : run_waves<KIND, QUAD, DP, false, false>(p, stream);
 }
 
 template <int KIND, bool QUAD>

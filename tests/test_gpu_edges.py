@@ -224,3 +224,31 @@ def test_large_d_forward_with_scores_of_any_size(d, causal):
             assert float(rows) <= 2.0 ** -7, (n, h, float(rows))
             lse = torch.logsumexp(s, 1)
             assert float(((LSE[0, h].double() - lse).abs() / lse.abs().clamp(min=1.0)).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("causal", [False, True])
+def test_fp32_head_dimensions_around_the_last_sixteen_columns(causal):
+    """fp32 head dimensions on both sides of the width from which the last 16 padded columns are left out, aligned and not,
+    against float64 on the GPU."""
+    import torch
+    from paper_2410_09397_amd import attn
+    for d in (1, 15, 16, 17, 32, 65, 72, 79, 80, 81, 96):
+        for n in (33, 200):
+            print("case fp32 width", causal, d, n, flush=True)
+            gen = torch.Generator(device="cuda")
+            gen.manual_seed(d + n)
+            Q, K, V, dO = (torch.randn((2, 3, n, d), generator=gen, device="cuda") for _ in range(4))
+            scale = d ** -0.5
+            O, LSE = attn.attn_fwd(Q, K, V, scale, causal=causal)
+            grads = attn.attn_bwd(Q, K, V, O, dO, LSE, scale, causal=causal)
+            q, k, v, g = (t.double() for t in (Q, K, V, dO))
+            s = torch.matmul(q, k.transpose(2, 3).contiguous()) * scale
+            if causal:
+                s = s.masked_fill(torch.ones(n, n, device="cuda", dtype=torch.bool).triu(1), float("-inf"))
+            f = torch.softmax(s, 3)
+            o = f @ v
+            p = f * (torch.matmul(g, v.transpose(2, 3).contiguous()) - (g * o).sum(3, keepdim=True))
+            want = (o, p @ k * scale, torch.matmul(p.transpose(2, 3).contiguous(), q) * scale, torch.matmul(f.transpose(2, 3).contiguous(), g))
+            for got, ref in zip((O,) + tuple(grads), want):
+                # fp32 sums of n + d terms: the bound that the other fp32 comparisons hold
+                assert float((got.double() - ref).abs().max()) <= 3e-6 * max(float(ref.abs().max()), 1.0), (d, n)
