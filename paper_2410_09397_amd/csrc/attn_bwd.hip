@@ -3,7 +3,8 @@
 //   dQ      : one workgroup owns a block of 128 queries and streams key tiles; its prologue also
 //             forms delta = rowsum(dO o O) (second matrix form of p, App. B.4) for those queries
 //   dK, dV  : one workgroup owns a block of 64 keys and streams query tiles
-//   (delta_kernel, the stand-alone row sum, serves the large-d path)
+//   calls of few blocks run both kinds of blocks side by side in one launch (bwd_both_kernel), with delta from a small
+//   launch in front (bwd_rows_kernel); delta_kernel serves the large-d path
 // Per tile pair this is the inner body of the paper's large-cache phase-2 algorithm (App. D):
 // q = dO h^T, A = S A_2^T, f = exp(A) / l, p = f o q - diag(v) f, followed by the three
 // products that use f and p.  The resident operand is the owned block, so dK/dV (resp. dQ)

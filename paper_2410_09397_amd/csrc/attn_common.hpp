@@ -429,6 +429,8 @@ inline int causal_resident(int grid, int per_cu) { return grid < 8 * 256 * per_c
 //   d = 64, full      n2048 36 / 41 -> 33 / 35    n3072 (beyond) 62 / 75 -> 64 / 69    n4096 (beyond) 95 / 113 -> 102 / 131
 //   d = 256, full     n1024 53 / 64 -> 39 / 43    n1536 (beyond) 76 / 92 -> 100 / 107
 //   d = 256, causal   n2048 96 / 113 -> 77 / 84   n3072 (beyond) 140 / 164 -> 166 / 175
+// (the forward of d = 256 before it was pipelined; since then, full, n1024 42 -> 30, n1536 (beyond) 59 -> 78; causal, n2048 74 -> 62, but
+// a full call of that size lies on the same side of the line, n3072 (beyond) 105 -> 126)
 // and calls on both sides of the line with the rule against 128 queries always (us, forward / backward with dK dV, 16 heads; a
 // mask keeps the diagonal and the stated share of the other blocks):
 //   d = 64, causal    n1024 19 / 39 -> 15 / 32    n2048 34 / 72 -> 26 / 57

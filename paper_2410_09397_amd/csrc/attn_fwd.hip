@@ -92,7 +92,7 @@ __device__ __forceinline__ void fwd_finish(const FusedParams& p, char* smem, lon
 //            see the same maximum; their partial sums are added at the end)
 //   O_w^T += V_T^T P^T                 V^T from transposed LDS reads, P^T straight from registers
 // Workgroups per CU: 4 at d = 64 (128 registers per lane; measured 5-6 % faster than 3 per CU at 134
-// registers on a grid of 1024 workgroups), 2 at d = 128, 1 at d = 256.
+// registers on a grid of 1024 workgroups), 2 at d = 128.
 // SPLIT = 2: the block has 64 queries and wave (wq, wk) takes queries 32 wq .. +31 with key half wk of every tile; each wave keeps
 // a maximum, a sum and an O of its own, and the two of a query meet in LDS at the end.
 template <int D, int SPLIT>
@@ -650,9 +650,9 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
 // Whether a launch of blocks of 64 queries takes eight waves (two query halves, four key parts of tiles of 128 keys, the pipelined
 // body) instead of four.  Half the steps, each 1.2 to 1.3 times as long with two waves per SIMD from one workgroup, of which a CU
 // holds one: it wins while there is at most one for each CU, unless a row is only a few steps long.  us, four waves -> eight:
-//   d = 128  h8 n700 14.5 -> 14.7   h16 n1024 19.2 -> 17.7   h8 n2048 32.5 -> 26   h1 n8192 119 -> 75   h16 n2048 (beyond the line) 44 -> 48
-//   d = 64   h8 n333 7.5 -> 8.1 (too short)   b2 h12 n600 causal 10.4 -> 9.9   h8 n1024 14.1 -> 12.0   h4 n1500 19.8 -> 15.0
-inline bool eight_waves(int d, int blocks, int n) { return blocks <= 256 && n >= (d == 64 ? 512 : 768); }
+//   d = 128  h8 n800 15.8 -> 15.9   h16 n1024 18.5 -> 16.9   h8 n2048 31.1 -> 25.8   h1 n8192 108 -> 79   h16 n2048 (beyond the line) 42 -> 48
+//   d = 64   h8 n333 7.2 -> 8.1 and b2 h12 n600 causal 9.9 -> 10.4 (too short)   h8 n1024 13.3 -> 12.0   h4 n1500 18.4 -> 16.0
+inline bool eight_waves(int blocks, int n) { return blocks <= 256 && n >= 768; }
 
 constexpr int fwd_per_cu(int d) { return d == 64 ? 4 : d == 128 ? 2 : 1; }
 
@@ -680,7 +680,7 @@ static hipError_t launch_fwd(const FusedParams& p, const int32_t* csr_ptr, const
     const int heads = p.batch * p.heads;
     const bool split = few_blocks((p.n + 127) / 128 * heads, fwd_per_cu(D), p.causal && !p.mask_form);
     const int blocks = (split ? (p.n + 63) / 64 : (p.n + 127) / 128) * heads;
-    const bool eight = D <= 128 && split && eight_waves(D, blocks, p.n);
+    const bool eight = D <= 128 && split && eight_waves(blocks, p.n);
     void (*fn)(FusedParams);
     if constexpr (D == 256) fn = split ? fwd_pipe_kernel<D, 2> : fwd_pipe_kernel<D, 1>;
     else fn = eight ? fwd_pipe_kernel<D, 4> : split ? fwd_split_kernel<D> : fwd_kernel<D>;

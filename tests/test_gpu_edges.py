@@ -169,7 +169,7 @@ def test_pipelined_forward_against_float64(d, heads, kind):
     import torch
     from paper_2410_09397_amd import attn
     causal, masked = kind.startswith("causal"), kind.endswith("mask")
-    base = {64: 512, 128: 768, 256: 64}[d]
+    base = 64 if d == 256 else 768
     for i, n in enumerate([base, base + 1, base + 63, base + 65, base + 127, base + 128, base + 193, base + 320] + ([1, 5, 130] if d == 256 else [])):
         scale = (-1 if i % 2 else 1) * (0.5 if i % 3 == 0 else d ** -0.5)
         print("case", kind, d, heads, n, scale, flush=True)
