@@ -20,7 +20,7 @@ import os
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COPY_BYTES = float(1 << 30)  # bytes read, and bytes written, by the calibration copy
-BWD_KERNELS = ("delta_kernel", "bwd_dkdv", "bwd_dq", "ld_scores_kernel<2>", "ld_scores_kernel<(attn::ScoreMode)2>", "ld_gemm_kernel", "generic_delta",
+BWD_KERNELS = ("delta_kernel", "bwd_dkdv", "bwd_dq", "ld_scores_kernel<2>", "ld_scores_kernel<(attn::ScoreMode)2>", "ld_gemm_kernel<true, false>", "ld_gemm_kernel<false, false>", "generic_delta",
                "generic_dq", "generic_dkdv", "block_len_kernel", "block_order_kernel", "block_order_fused_kernel", "bwd_prep_kernel", "bwd_rows_kernel", "bwd_both_kernel",
                "bwd_onepass_kernel", "bwd_splitd_kernel", "stream_bwd_kernel")
 
@@ -41,8 +41,8 @@ def source_hash():
 
 def traffic_key(workload, tiling):
     return workload if not tiling else "%s@tiling%d" % (workload, tiling)
-FWD_KERNELS = ("fwd_kernel", "fwd_split_kernel", "fwd_pipe_kernel", "ld_scores_kernel<0>", "ld_scores_kernel<1>", "ld_scores_kernel<(attn::ScoreMode)0>",
-               "ld_scores_kernel<(attn::ScoreMode)1>", "ld_lse_combine", "generic_fwd")
+FWD_KERNELS = ("fwd_kernel", "fwd_split_kernel", "fwd_pipe_kernel", "ld_scores_kernel<1>", "ld_scores_kernel<(attn::ScoreMode)1>", "ld_gemm_kernel<false, true>",
+               "ld_lse_combine", "generic_fwd")
 # launched by neither attn_fwd nor attn_bwd: the weight gradient's own and the measurement aids
 OTHER_KERNELS = ("wgrad_partial", "wgrad_reduce", "proj_kernel", "tile_skeleton_kernel", "mfma_ceiling_kernel")
 
@@ -79,10 +79,8 @@ def counter_avg(d, counter):
     return {k: (sum(v) / COPIES if "copyBuffer" in k else sum(v) / len(v)) for k, v in acc.items()}
 
 
-def per_call_weights(name, calls, base_calls, four_phase_bwd=True):
+def per_call_weights(name, calls, base_calls):
     """(launches per attn_bwd call, launches per attn_fwd call) of a kernel."""
-    if "ld_gemm_kernel<false>" in name:  # dQ = dS K in the four-phase backward, O = P V in the large-d forward
-        return (1.0, 1.0) if four_phase_bwd else (0.0, calls / float(base_calls))
     k = calls / float(base_calls)
     return (k, 0.0) if is_in(name, BWD_KERNELS) else (0.0, k)
 
@@ -156,7 +154,7 @@ def main():
         rd = fetch.get(name, 0.0) * f_r * 1024.0
         wr = write.get(name, 0.0) * f_w * 1024.0
         # a kernel launched more than once per call (the large-d GEMM) counts that many times
-        wb, wf = per_call_weights(name, calls, base_calls, any("ld_scores_kernel<2>" in n or "ScoreMode)2>" in n for n in stats))
+        wb, wf = per_call_weights(name, calls, base_calls)
         for grp, k in (("bwd", wb), ("fwd", wf)):
             tot[grp][0] += avg * k
             tot[grp][1] += rd * k
