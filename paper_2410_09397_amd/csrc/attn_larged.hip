@@ -9,7 +9,8 @@
 //   gemm kernel   : dV = P^T dO, dK = scale dS^T Q, dQ = scale dS K as tiled products with the
 //                   k-loop over n (phase 4 written for dQ/dK/dV instead of A_1^T p A_2)
 // The forward uses the same kernels: exp(S) written to HBM with its sum per row and chunk of 64 keys, a combine step for LSE,
-// and O = diag(l)^-1 exp(S) V.
+// and O = exp(S) V, its rows divided by the sum of the
+// weights as written.
 #include <type_traits>
 
 #include "attn_common.hpp"
@@ -21,22 +22,19 @@ namespace attn {
 // k-step needs 32-column chunks of two operands (24 KB), and three LDS stages (copies two steps ahead) fit two
 // workgroups on a CU.  Accumulator: lane <-> query, register <-> key.  Modes:
 //   kProbs    exp2(s - e) of the scores s (times log2 e) written to the workspace in bf16, and e and the row sum per 64-key chunk (the
-//             forward).  bf16 has the exponents of fp32, so e = 0 loses nothing while a chunk's largest score is moderate, and no sweep
-//             over the scores has to come first (it took 154 of 481 us at b1 h8 n4096 d512; the forward is 370 without it).  A
-//             chunk whose largest score is beyond 2^+-kModerate gets its own whole number e, and the product kernel aligns the
-//             chunks of such a row: a whole number is an exact shift of the exponents.
+//             forward).  e is the chunk's largest score rounded up to a whole number, so what is written is at most 1 and no sweep over
+//             the scores has to come first (it took 154 of 481 us at b1 h8 n4096 d512); the product kernel aligns the
+//             chunks of a row: a whole number is an exact shift of the exponents.
 //   kBackward P and dS.  The two products of a tile are formed one after the other - S^T over all of d, then dP^T
 //             over all of d - so that the wave can hold its block of the one in progress: 256 x 128 tiles move 384 bytes
 //             from memory per MFMA instead of the 512 of 128 x 128 tiles with both products at once.  Between the
 //             passes P stays in registers, rounded to bf16 as it is stored (dS = P (dP - delta) uses that rounded P).
 enum ScoreMode { kProbs = 1, kBackward = 2 };
-constexpr float kModerate = 24.f;
 // O is divided by the sum of what was written, rounded to bf16, not by l: a row that is one key then has that key's value, and the
 // roundings of the other rows cancel in part (with l the error at d = 512 was up to 1.2 times that of rounding f).  A chunk's
-// stat_m holds e and the ratio of the two sums, which is off one by 2^-9 at most: e + kRatio (ratio - 1).
+// stat_m holds e and the ratio of the two sums, which is off one by 2^-9 at most: e + kRatio (ratio - 1).  The combine step leaves there by
+// how many powers of two the product kernel lowers the chunk, as exponents of a pair of bf16, and a row's factor in stat_l of its first chunk.
 constexpr float kRatio = 16.f;
-// [bh][chunk][query] places in stat_l that the combine step reuses for a row's results (a row has at least four chunks)
-enum RowSlot { kRowInverse = 0, kRowTop = 1, kRowShifted = 2 };
 constexpr int kScoreStage = (256 + 128) * 32 * 2, kScoreLds = 3 * kScoreStage;
 template <int MODE>
 __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) {
@@ -182,7 +180,7 @@ __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) 
                         mx = fmaxf(mx, v);
                     }
                 mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-                const float e = fabsf(mx) <= kModerate || mx == -__builtin_inff() ? 0.f : __builtin_ceilf(mx);
+                const float e = mx == -__builtin_inff() ? 0.f : __builtin_ceilf(mx);
                 float sum = 0.f, sum_r = 0.f;
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
@@ -278,14 +276,15 @@ __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) 
     store_tile(p.dS);
 }
 
-// LSE from the per-chunk sums, and for the product kernel a row's 1 / l, the largest e of its chunks and whether any chunk has one.
+// LSE from the per-chunk sums, and for the product kernel a row's factor and the shift of each of its chunks: weights of a row are
+// lowered to sum to at least 1/2 and at most 1, so that the product is finite wherever the row of O is.
 // A workgroup takes 16 rows; 16 threads per row each fold every 16th chunk into a running (e, sum) pair, and the 16 pairs of a row are folded through LDS (one thread per row alone spent its time
 // waiting for one load after the other).  Statistics are [bh][chunk][query]: threads that stand for consecutive
 // queries read consecutive floats.
 constexpr int kCombineRows = 16, kCombineParts = kThreads / kCombineRows;
 __global__ void __launch_bounds__(kThreads) ld_lse_combine_kernel(LargeDParams p) {
     __shared__ float part_m[kCombineParts][kCombineRows], part_l[kCombineParts][kCombineRows], part_r[kCombineParts][kCombineRows];
-    __shared__ int shifted[kCombineRows];
+    __shared__ float row_top[kCombineRows];
     const int rl = threadIdx.x % kCombineRows, g = threadIdx.x / kCombineRows;
     const long rows = (long)p.batch * p.heads * p.n;
     const long r = (long)blockIdx.x * kCombineRows + rl;
@@ -295,10 +294,7 @@ __global__ void __launch_bounds__(kThreads) ld_lse_combine_kernel(LargeDParams p
     const int chunks = ok ? 2 * (p.causal ? q / 128 + 1 : nb) : 0;
     const long pitch = p.n;
     const long head = ok ? (r / p.n) * (2 * nb) * pitch + q : 0;
-    if (threadIdx.x < kCombineRows) shifted[threadIdx.x] = 0;
-    __syncthreads();
     float M = -__builtin_inff(), L = 0.f, R = 0.f;  // R: the sum of the rounded values
-    bool any = false;
     auto fold = [&](float m, float l, float r) {
         if (l == 0.f) return;  // (a chunk with nothing visible has no say)
         const float top = fmaxf(M, m), old = __builtin_amdgcn_exp2f(M - top), now = __builtin_amdgcn_exp2f(m - top);  // (exp2(-inf) = 0 at the start)
@@ -308,20 +304,28 @@ __global__ void __launch_bounds__(kThreads) ld_lse_combine_kernel(LargeDParams p
     };
     for (int c = g; c < chunks; c += kCombineParts) {
         const float mc = p.stat_m[head + c * pitch], lc = p.stat_l[head + c * pitch], e = rintf(mc);
-        any = any || e != 0.f;
         fold(e, lc, fmaf(lc, (mc - e) * (1.f / kRatio), lc));
     }
     part_m[g][rl] = M;
     part_l[g][rl] = L;
     part_r[g][rl] = R;
-    if (any) shifted[rl] = 1;
     __syncthreads();
-    if (g != 0 || !ok) return;
-    for (int k = 1; k < kCombineParts; ++k) fold(part_m[k][rl], part_l[k][rl], part_r[k][rl]);
-    p.LSEout[r] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
-    p.stat_l[head + kRowInverse * pitch] = L > 0.f ? 1.f / R : 0.f;
-    p.stat_l[head + kRowTop * pitch] = M;
-    p.stat_l[head + kRowShifted * pitch] = shifted[rl] ? 1.f : 0.f;
+    if (g == 0 && ok) {
+        for (int k = 1; k < kCombineParts; ++k) fold(part_m[k][rl], part_l[k][rl], part_r[k][rl]);
+        p.LSEout[r] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
+        const int up = L > 0.f ? max(__builtin_amdgcn_frexp_expf(R), 0) : 0;  // R <= 2^up
+        p.stat_l[head] = L > 0.f ? __builtin_amdgcn_ldexpf(1.f, up) / R : 0.f;
+        row_top[rl] = M + (float)up;
+    }
+    __syncthreads();
+    // every chunk that the product kernel reads: whole blocks of 256 keys
+    const int read = ok ? 4 * (p.causal ? q / 256 + 1 : nb / 2) : 0;
+    const float top = row_top[rl];
+    for (int c = g; c < read; c += kCombineParts) {
+        float* e = p.stat_m + head + c * pitch;
+        const float by = c < chunks ? top - rintf(*e) : 0.f;
+        *e = __builtin_bit_cast(float, (unsigned)fminf(fmaxf(by, 0.f), 255.f) * 0x00800080u);
+    }
 }
 
 // C[m][n] = alpha * sum_k A(m, k) B(k, n): 128 x 128 output tile per workgroup, k-loop over the
@@ -341,13 +345,18 @@ struct GemmArgs {
 // from global memory for 64 MFMAs.  (With 128 x 128 tiles the copies alone, at the 64 B/clk that
 // the vector memory path delivers per CU, took as long as the MFMAs.)
 constexpr int kGemmBK = 32, kGemmM = 256;
-// ROWS: A holds exp2(s - e) of the forward: rows whose chunks have an e other than 0 are aligned to the row's largest on the way into
-// the product (e - top whole steps of the exponent: a saturating subtraction on pairs of bf16), and a row of C is divided by its l.
+constexpr int gemm_stage(bool rows) { return (kGemmM + 128) * kGemmBK * 2 + (rows ? kGemmM * 4 : 0); }  // (ROWS: and a shift per row)
+// ROWS: A holds exp2(s - e) of the forward.  The chunks of a row are aligned on the way into the product, by a saturating subtraction of
+// exponents on pairs of bf16 (two vector instructions per MFMA), and a row of C is multiplied by its factor.  The shifts come with the
+// operands, 1 KB per k-step: a load in the step, whose wait would drain the copies in flight, made the forward of scores of
+// standard deviation 8 slower than two sweeps were.  us of the forward, b1 h8 n4096 d512, standard deviation of the scores 1 / 4 / 8, two sweeps with
+// P = exp(S - LSE), shifts loaded where a tile needs any, and now: full 548 / 555 / 520, 422 / 484 / 451, 428 / 433 / 407; causal
+// 300 / - / 325, 234 / - / 330, 243 / - / 258; b1 h2 n700 causal 59 / - / 60, 50 / - / 64, 48 / - / 48.
 template <bool A_KMAJOR, bool ROWS>
 __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, GemmArgs g) {
     static_assert(!(A_KMAJOR && ROWS), "the rows of A are the rows of C");
     constexpr int BK = kGemmBK, TM = kGemmM;
-    constexpr int kTileA = TM * BK * 2, kTileB = 128 * BK * 2, kStage = kTileA + kTileB;
+    constexpr int kTileA = TM * BK * 2, kTileB = 128 * BK * 2, kStage = gemm_stage(ROWS);
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
@@ -391,11 +400,17 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
     if (A_KMAJOR) copy_at.init(tid, p.npad);
     else copy_a.init(tid, p.npad);
     copy_b.init(tid, p.stride_n);
+    const unsigned row_off = (unsigned)min(m0 + tid, p.n - 1) * 4u;  // the shift of this lane's row
     auto fetch = [&](int k, int stage) {
         char* at = smem + stage * kStage;
         if (A_KMAJOR) copy_at.load(gA + m0 + (long)k * p.npad, at);
         else copy_a.load(gA + k + (long)m0 * p.npad, at);
         copy_b.load(gB + n0, p.stride_n, k, p.n, at + kTileA, tid);
+        if constexpr (ROWS) {  // rows past n repeat the last row
+            const float* shifts = p.stat_m + ((long)bh * (p.npad / 64) + k / 64) * p.n;
+            const unsigned dst = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(ATTN_LDS char*)(at + kTileA + kTileB)) + 256u * w;
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(dst), "v"(row_off), "s"(shifts) : "memory", "m0");
+        }
     };
     // A read transposed: one register pair per 32-row tile t.  A as stored: one register per k-step, the 16-byte
     // chunk 2 ks + h of this lane's row (the 32-row tiles are immediates apart); B is then fetched with its k index
@@ -422,7 +437,7 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
     }
     // Three stages: the copies of step k + 2 are issued while step k is multiplied, so two steps' worth of bytes
     // (48 KB per workgroup) are in flight; with two stages the product kernels waited for memory at every step.
-    constexpr int kCopiesPerFetch = (kTileA + kTileB) / (1024 * 4);  // per wave
+    constexpr int kCopiesPerFetch = (kTileA + kTileB) / (1024 * 4) + (ROWS ? 1 : 0);  // per wave
     fetch(k_begin, 0);
     if (k_begin + BK < k_end) {
         fetch(k_begin + BK, 1);
@@ -431,32 +446,16 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
         wait_direct_loads();
     }
     __syncthreads();
-    const float* row_l = p.stat_l + (long)bh * (p.npad / 64) * p.n;
-    bool shifted = false;
-    float top[4];
-    if constexpr (ROWS) {
-        shifted = __syncthreads_or(m0 + tid < p.n && row_l[(long)kRowShifted * p.n + m0 + tid] != 0.f);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) top[t] = row_l[(long)kRowTop * p.n + min(m0 + 128 * wm + 32 * t + l32, p.n - 1)];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) settle(top[t]);
-    }
     auto step = [&](int k, auto stage_index) {
         constexpr int si = decltype(stage_index)::value, so = si * kStage;
         const bool more = k + 2 * BK < k_end;
-        unsigned lower[4] = {0, 0, 0, 0};  // this k-step's shift of the exponents of a pair, per 32-row tile
-        if constexpr (ROWS) {
-            if (shifted) {
-                const float* e = p.stat_m + ((long)bh * (p.npad / 64) + k / 64) * p.n;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float by = top[t] - rintf(e[min(m0 + 128 * wm + 32 * t + l32, p.n - 1)]);
-                    lower[t] = (unsigned)fminf(fmaxf(by, 0.f), 255.f) * 0x00800080u;
-                    settle(lower[t]);
-                }
-            }
-        }
         if (more) fetch(k + 2 * BK, (si + 2) % 3);
+        unsigned lower[4];  // of a pair of weights, per 32-row tile
+        if constexpr (ROWS) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                lower[t] = *reinterpret_cast<const unsigned*>(smem + so + kTileA + kTileB + (128 * wm + 32 * t + l32) * 4);
+        }
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
             bf16x8 a[4], b[2];
@@ -469,18 +468,16 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
                 }
             }
             if constexpr (ROWS) {
-                if (shifted) {
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-                        u32x4 v = __builtin_bit_cast(u32x4, a[t]);
+                for (int t = 0; t < 4; ++t) {
+                    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+                    u32x4 v = __builtin_bit_cast(u32x4, a[t]);
 #pragma unroll
-                        for (int x = 0; x < 4; ++x) {
-                            const unsigned pair = v[x], by = lower[t];  // (a bit cast of a vector's element takes element 0)
-                            v[x] = __builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, pair), __builtin_bit_cast(u16x2, by)));
-                        }
-                        a[t] = __builtin_bit_cast(bf16x8, v);
+                    for (int x = 0; x < 4; ++x) {
+                        const unsigned pair = v[x], by = lower[t];  // (a bit cast of a vector's element takes element 0)
+                        v[x] = __builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, pair), __builtin_bit_cast(u16x2, by)));
                     }
+                    a[t] = __builtin_bit_cast(bf16x8, v);
                 }
             }
 #pragma unroll
@@ -507,9 +504,9 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
         step(k, std::integral_constant<int, 0>{});
         if (k + BK < k_end) step(k + BK, std::integral_constant<int, 1>{});
     }
-    float* inverse = reinterpret_cast<float*>(smem);  // 1 / l of the tile's rows (the stages are free)
+    float* factor = reinterpret_cast<float*>(smem);  // of the tile's rows (the stages are free)
     if constexpr (ROWS) {
-        inverse[tid] = m0 + tid < p.n ? row_l[(long)kRowInverse * p.n + m0 + tid] : 0.f;
+        factor[tid] = m0 + tid < p.n ? p.stat_l[(long)bh * (p.npad / 64) * p.n + m0 + tid] : 0.f;
         __syncthreads();
     }
     // accumulator: lane <-> output column, register <-> output row
@@ -522,7 +519,7 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
             for (int i = 0; i < 16; ++i) {
                 const int rel = 128 * wm + 32 * tm + acc_row(i, h), row = m0 + rel;
                 float f = g.alpha;
-                if constexpr (ROWS) f = inverse[rel];
+                if constexpr (ROWS) f = factor[rel];
                 float v = c[tm][tn][i] * f;
                 if (ROWS && f == 0.f) v = 0.f;  // a row with no finite sum
                 if (row < p.n && col < p.d) g.C[base + (long)row * p.stride_n + col] = (__bf16)v;
@@ -534,22 +531,22 @@ static hipError_t set_lds(const void* fn, int bytes) {
     return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-constexpr int kGemmLds = 3 * (kGemmM + 128) * kGemmBK * 2;  // three stages of an A and a B tile (72 KB: two workgroups per CU)
+constexpr int gemm_lds(bool rows) { return 3 * gemm_stage(rows); }  // three stages of an A and a B tile (72 or 75 KB: two workgroups per CU)
 template <bool A_KMAJOR, bool ROWS>
 static void run_gemm(const LargeDParams& p, const __bf16* A, const __bf16* B, __bf16* C, float alpha,
                      hipStream_t stream) {
     const dim3 grid((unsigned)(((p.d + 127) / 128) * (p.npad / kGemmM) * p.batch * p.heads));
     GemmArgs g{A, B, C, alpha};
-    hipLaunchKernelGGL((ld_gemm_kernel<A_KMAJOR, ROWS>), grid, dim3(kThreads), kGemmLds, stream, p, g);
+    hipLaunchKernelGGL((ld_gemm_kernel<A_KMAJOR, ROWS>), grid, dim3(kThreads), gemm_lds(ROWS), stream, p, g);
 }
 
 // LDS sizes of the large-d kernels on the current device (set on every call: cheap, and per device).
 hipError_t configure_larged() {
     hipError_t e = set_lds(reinterpret_cast<const void*>(ld_scores_kernel<kProbs>), kScoreLds);
     if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_scores_kernel<kBackward>), kScoreLds);
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<true, false>), kGemmLds);
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<false, false>), kGemmLds);
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<false, true>), kGemmLds);
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<true, false>), gemm_lds(false));
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<false, false>), gemm_lds(false));
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void*>(ld_gemm_kernel<false, true>), gemm_lds(true));
     return e;
 }
 

@@ -198,15 +198,16 @@ def test_pipelined_forward_against_float64(d, heads, kind):
 @pytest.mark.parametrize("d", [512, 1024])
 @pytest.mark.parametrize("causal", [False, True])
 def test_large_d_forward_with_scores_of_any_size(d, causal):
-    """exp(S) is written without a reference where a chunk's largest score is moderate and with one of its own beyond: rows of
-    moderate, large positive, large negative and mixed scores, in blocks with and without each other, and rows whose other chunks
-    vanish beside one, against float64."""
+    """exp(S) is written with a reference per row and chunk of 64 keys: rows of moderate, large positive, large negative and mixed scores,
+    in blocks with and without each other, rows whose other chunks vanish beside one, and more than the 16 chunks that
+    one thread of a row's sum takes first, with maxima that grow along the row, against float64."""
     import torch
     from paper_2410_09397_amd import attn
-    for n in (1, 64, 65, 333, 700):
+    for n in (1, 64, 65, 333, 700, 2100):
         gen = torch.Generator(device="cuda")
         gen.manual_seed(d + n)
         Q, K, V = (torch.randn((1, 3, n, d), generator=gen, device="cuda") for _ in range(3))
+        K[0, 2] *= torch.linspace(0.1, 25.0, n, device="cuda")[:, None]      # a reference of its own for every chunk, later ones larger
         Q[0, 0] *= torch.linspace(0.1, 60.0, n, device="cuda")[:, None]      # scores of -250 to 250 in the last rows
         Q[0, 1, n // 2:] = 12.0                                              # rows whose scores are large and of one sign
         K[0, 1] = K[0, 1].abs() * torch.where(torch.arange(n, device="cuda") % 97 < 60, 1.0, -1.0)[:, None]
@@ -224,6 +225,33 @@ def test_large_d_forward_with_scores_of_any_size(d, causal):
             assert float(rows) <= 2.0 ** -7, (n, h, float(rows))
             lse = torch.logsumexp(s, 1)
             assert float(((LSE[0, h].double() - lse).abs() / lse.abs().clamp(min=1.0)).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("d", [512, 1024])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("score", [16.0, -16.0, 40.0])
+def test_large_d_forward_holds_the_range_of_the_values(d, causal, score):
+    """Values near both ends of the exponent range with scores far from 0: the weights that meet them sum to about 1, so O is
+    finite and keeps its precision wherever exp(S - LSE) V does."""
+    import torch
+    from paper_2410_09397_amd import attn
+    for n in (130, 700, 1300):
+        for size in (1e36, 1e-36):
+            print("case range of V", d, causal, score, n, size, flush=True)
+            gen = torch.Generator(device="cuda")
+            gen.manual_seed(d + n)
+            Q, K, V = (torch.randn((1, 2, n, d), generator=gen, device="cuda") for _ in range(3))
+            Q = 1.0 + 0.1 * Q
+            K = score * d ** -0.5 + 0.1 * K  # scores of `score` plus about 0.2
+            Q, K, V = Q.to(torch.bfloat16), K.to(torch.bfloat16), (V * size).to(torch.bfloat16)
+            O, _ = attn.attn_fwd(Q, K, V, d ** -0.5, causal=causal)
+            for h in range(2):
+                s = Q[0, h].double() @ K[0, h].double().T * d ** -0.5
+                if causal:
+                    s = s.masked_fill(torch.ones(n, n, device="cuda", dtype=torch.bool).triu(1), float("-inf"))
+                ref = torch.softmax(s, 1) @ (V[0, h].double() / size)
+                rows = ((O[0, h].double() / size - ref).norm(dim=1) / ref.norm(dim=1)).max()
+                assert float(rows) <= 2.0 ** -7, (n, h, float(rows))  # as above
 
 
 @pytest.mark.parametrize("causal", [False, True])
