@@ -208,7 +208,7 @@ __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) 
                 sum_r += __shfl_xor(sum_r, 32, 64);
                 if (q < p.n && h == 0) {
                     const long o = ((long)bh * (2 * nbq) + k0 / 64 + 2 * wm + half) * p.n + q;  // [bh][chunk][query]
-                    p.stat_m[o] = sum > 0.f ? fmaf(sum_r / sum - 1.f, kRatio, e) : e;
+                    p.stat_m[o] = mx == -__builtin_inff() ? mx : sum > 0.f ? fmaf(sum_r / sum - 1.f, kRatio, e) : e;
                     p.stat_l[o] = sum;
                 }
             }
@@ -296,7 +296,10 @@ __global__ void __launch_bounds__(kThreads) ld_lse_combine_kernel(LargeDParams p
     const long head = ok ? (r / p.n) * (2 * nb) * pitch + q : 0;
     float M = -__builtin_inff(), L = 0.f, R = 0.f;  // R: the sum of the rounded values
     auto fold = [&](float m, float l, float r) {
-        if (l == 0.f) return;  // (a chunk with nothing visible has no say)
+        if (m == -__builtin_inff()) {  // nothing visible, or nothing but NaN, which leaves LSE alone and makes the row of O NaN
+            R += r;
+            return;
+        }
         const float top = fmaxf(M, m), old = __builtin_amdgcn_exp2f(M - top), now = __builtin_amdgcn_exp2f(m - top);  // (exp2(-inf) = 0 at the start)
         L = L * old + l * now;
         R = R * old + r * now;
@@ -304,7 +307,7 @@ __global__ void __launch_bounds__(kThreads) ld_lse_combine_kernel(LargeDParams p
     };
     for (int c = g; c < chunks; c += kCombineParts) {
         const float mc = p.stat_m[head + c * pitch], lc = p.stat_l[head + c * pitch], e = rintf(mc);
-        fold(e, lc, fmaf(lc, (mc - e) * (1.f / kRatio), lc));
+        fold(e, lc, mc == -__builtin_inff() ? lc : fmaf(lc, (mc - e) * (1.f / kRatio), lc));
     }
     part_m[g][rl] = M;
     part_l[g][rl] = L;

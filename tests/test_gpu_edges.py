@@ -254,6 +254,30 @@ def test_large_d_forward_holds_the_range_of_the_values(d, causal, score):
                 assert float(rows) <= 2.0 ** -7, (n, h, float(rows))  # as above
 
 
+@pytest.mark.parametrize("d", [512, 1024])
+@pytest.mark.parametrize("n", [65, 300, 1100])
+def test_large_d_forward_shows_keys_that_are_nan(d, n):
+    """A chunk of 64 keys that a row sees nothing but NaN of makes the row of O NaN (not 0); rows that do not see it, and other heads,
+    keep their bits."""
+    import torch
+    from paper_2410_09397_amd import attn
+    for causal, keys in ((False, slice(0, 64)), (True, slice(0, 64)), (False, slice(64 * ((n - 1) // 64), n)), (True, slice(n - 1, n))):
+        print("case nan keys", d, n, causal, keys, flush=True)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(d + n)
+        Q, K, V = (torch.randn((1, 2, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+        O, LSE = attn.attn_fwd(Q, K, V, d ** -0.5, causal=causal)
+        K[0, 0, keys, 3] = float("nan")
+        O_nan, LSE_nan = attn.attn_fwd(Q, K, V, d ** -0.5, causal=causal)
+        alone = keys.start // 64 * 64 == keys.start  # the rows that see a key of it see none of its chunk that is finite
+        first = keys.start if causal else 0
+        if alone:  # (the first chunk's own rows have no other weight: no finite sum, a row of zeros)
+            rows = O_nan[0, 0, max(first, 64 if causal and keys.start == 0 else 0):]
+            assert bool(torch.isnan(rows).all())
+        assert torch.equal(O_nan[0, 0, :first], O[0, 0, :first]) and torch.equal(LSE_nan[0, 0, :first], LSE[0, 0, :first])
+        assert torch.equal(O_nan[0, 1], O[0, 1]) and torch.equal(LSE_nan[0, 1], LSE[0, 1])
+
+
 @pytest.mark.parametrize("causal", [False, True])
 def test_fp32_head_dimensions_around_the_last_sixteen_columns(causal):
     """fp32 head dimensions on both sides of the width from which the last 16 padded columns are left out, aligned and not,
