@@ -307,6 +307,8 @@ __device__ __forceinline__ void dkdv_block(const FusedParams p, char* smem, int 
             if (spread) {
                 next_q = p.Q + base + (long)i0_next * ld;
                 next_g = p.dO + base + (long)i0_next * ld;
+                loader.hold(next_q);
+                loader.hold(next_g);
                 fetch_rows(i0_next);
             } else {
                 fetch(i0_next, kStageBytes - q_off);

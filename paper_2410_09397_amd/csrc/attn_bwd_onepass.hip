@@ -221,6 +221,8 @@ __global__ void __launch_bounds__(512, 1) bwd_onepass_kernel(FusedParams p, floa
                 if (spread) {
                     next_q = p.Q + base + (long)i0_next * ld;
                     next_g = p.dO + base + (long)i0_next * ld;
+                    loader.hold(next_q);
+                    loader.hold(next_g);
                     fetch_rows(i0_next);
                 } else {
                     fetch(i0_next, ((it + 1) % 3) * kStageBytes);

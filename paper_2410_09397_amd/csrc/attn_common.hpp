@@ -231,6 +231,31 @@ __device__ __forceinline__ bf16x8 load_frag_perm(const char* tile, int row0, int
     return __builtin_bit_cast(bf16x8, r);
 }
 
+// One copy instruction: BYTES (4 or 16) per lane from global memory to LDS at dst + imm + BYTES lane; off: byte offset of the lane
+// from the uniform address base.  Inline assembly hides from the compiler what it would otherwise put in between: one wait state
+// from the write of M0 to the copy, and five from a vector instruction that has written base (readfirstlane, or a scalar
+// register restored from a lane) to the copy.  The hardware checks neither.  FIRST: base may just have been formed.
+template <int BYTES, bool FIRST>
+__device__ __forceinline__ void copy_to_lds(unsigned dst, int imm, unsigned off, const void* base) {
+    static_assert(BYTES == 16 || BYTES == 4, "widths of the instruction");
+    constexpr int kWait = FIRST ? 3 : 0;  // s_nop n is n + 1 states
+    if constexpr (BYTES == 16)
+        asm volatile("s_add_u32 m0, %0, %1\n\ts_nop %4\n\tglobal_load_lds_dwordx4 %2, %3"
+                     :
+                     : "s"(dst), "i"(imm), "v"(off), "s"(base), "n"(kWait)
+                     : "memory", "m0", "scc");
+    else
+        asm volatile("s_add_u32 m0, %0, %1\n\ts_nop %4\n\tglobal_load_lds_dword %2, %3"
+                     :
+                     : "s"(dst), "i"(imm), "v"(off), "s"(base), "n"(kWait)
+                     : "memory", "m0", "scc");
+}
+template <int BYTES>
+__device__ __forceinline__ void copy_to_lds(unsigned dst, int imm, unsigned off, const void* base, bool first) {  // (first: known after inlining)
+    if (first) copy_to_lds<BYTES, true>(dst, imm, off, base);
+    else copy_to_lds<BYTES, false>(dst, imm, off, base);
+}
+
 // Asynchronous copy of a [ROWS x D] bf16 tile from global memory straight into a swizzled LDS
 // tile (global_load_lds_dwordx4: no staging registers).  One instruction moves 1 KB per wave and
 // lands lane l's 16 bytes at LDS base + 16 l, so the lane that owns LDS position (row, chunk p)
@@ -254,7 +279,7 @@ __device__ __forceinline__ void load_tile_direct(const __bf16* base, long ld, in
         // next transposing LDS read, i.e. in the middle of the iteration.  Here the wait is ours:
         // wait_direct_loads() right before the barrier that publishes the stage.
         const unsigned dst = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(ATTN_LDS char*)(tile + (u * NW + w) * 1024));
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                      :
                      : "s"(dst), "v"(base + (long)grow * ld + c * 8)
                      : "memory", "m0");
@@ -274,6 +299,9 @@ struct TileLoader {
     static constexpr int kRowsPerInst = 1024 / (D * 2);
     static constexpr int kInst = ROWS / (NW * kRowsPerInst);
     static_assert(ROWS % (NW * kRowsPerInst) == 0, "tile must split evenly over the workgroup's waves");
+    // whether the tile's address may come from vector registers: at d = 256 the scalar ones do not hold it in every kernel (the
+    // CPU tests look for a copy without its waits in the assembly of every kernel)
+    static constexpr bool kFormed = D == 256;
     unsigned voff[kInst];
     unsigned lds0;  // byte offset of this wave's first 1 KB piece inside a tile
     __device__ __forceinline__ void init(int tid, long ld) {
@@ -300,23 +328,19 @@ struct TileLoader {
         const unsigned t0 =
             __builtin_amdgcn_readfirstlane((unsigned)(size_t)(ATTN_LDS char*)tile) + lds0;
 #pragma unroll
-        for (int u = 0; u < kInst; ++u) {
-            const unsigned dst = t0 + u * NW * 1024;
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :
-                         : "s"(dst), "v"(voff[u]), "s"(first_row)
-                         : "memory", "m0");
-        }
+        for (int u = 0; u < kInst; ++u) copy_to_lds<16>(t0, u * NW * 1024, voff[u], first_row, kFormed && u == 0);
     }
-    // copy instruction u of load() on its own, for callers that spread the copies over their MFMAs
+    // Copy instruction u of load() on its own, for callers that spread the copies over their MFMAs.  Their address has been through
+    // hold(): formed from vector registers for each copy it would need the wait of a first copy every time.
+    static __device__ __forceinline__ void hold(const __bf16*& first_row) {
+        first_row = uniform(first_row);
+        asm volatile("" : "+s"(first_row));
+    }
     __device__ __forceinline__ void load_one(int u, const __bf16* first_row_in, char* tile) const {
         const __bf16* first_row = uniform(first_row_in);
-        const unsigned dst =
-            __builtin_amdgcn_readfirstlane((unsigned)(size_t)(ATTN_LDS char*)tile) + lds0 + u * NW * 1024;
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :
-                     : "s"(dst), "v"(voff[u]), "s"(first_row)
-                     : "memory", "m0");
+        const unsigned t0 =
+            __builtin_amdgcn_readfirstlane((unsigned)(size_t)(ATTN_LDS char*)tile) + lds0;
+        copy_to_lds<16>(t0, u * NW * 1024, voff[u], first_row, kFormed && u == 0);
     }
     // any tile: clamps rows at rows_valid - 1 when the tile reaches past the end
     __device__ __forceinline__ void load(const __bf16* base, long ld, int row_begin, int rows_valid, char* tile,

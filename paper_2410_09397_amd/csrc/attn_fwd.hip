@@ -567,6 +567,8 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
         const int jk = t + 2 < n_it ? j[2] : 0;
         const __bf16* next_k = p.K + base + (unsigned long long)(unsigned)jk * (unsigned)ld;
         const __bf16* next_v = p.V + base + (unsigned long long)(unsigned)j[0] * (unsigned)ld;
+        loader.hold(next_k);
+        loader.hold(next_v);
         advance(t);
         bf16x8 fk[KS][NT], fv[KS][NT];
         constexpr int kAhead = 2;

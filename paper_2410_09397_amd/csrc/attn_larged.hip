@@ -411,8 +411,8 @@ __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, Ge
         copy_b.load(gB + n0, p.stride_n, k, p.n, at + kTileA, tid);
         if constexpr (ROWS) {  // rows past n repeat the last row
             const float* shifts = p.stat_m + ((long)bh * (p.npad / 64) + k / 64) * p.n;
-            const unsigned dst = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(ATTN_LDS char*)(at + kTileA + kTileB)) + 256u * w;
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(dst), "v"(row_off), "s"(shifts) : "memory", "m0");
+            const unsigned dst = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(ATTN_LDS char*)at) + 256u * w;
+            copy_to_lds<4, false>(dst, kTileA + kTileB, row_off, shifts);
         }
     };
     // A read transposed: one register pair per 32-row tile t.  A as stored: one register per k-step, the 16-byte

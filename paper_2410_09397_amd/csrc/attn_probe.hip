@@ -177,10 +177,7 @@ __global__ void __launch_bounds__(kThreads, 2) tile_skeleton_kernel(float* resul
             asm volatile("" : "+v"(b));
             acc[j & 3] = mfma32(a, b, acc[j & 3]);
             if (j % 4 == 0)  // this wave's 8 KB of the tile copy, 1 KB per instruction
-                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                             :
-                             : "s"(copy_dst + (j / 4) * 1024), "v"(voff + (j / 4) * 1024), "s"(tile)
-                             : "memory", "m0");
+                copy_to_lds<16>(copy_dst, (j / 4) * 1024, voff + (j / 4) * 1024, reinterpret_cast<const void*>(tile), j == 0);
             if (j % 2 == 0) {
                 e[j / 2] = __builtin_amdgcn_exp2f(e[j / 2]);
                 asm volatile("" : "+v"(e[j / 2]));

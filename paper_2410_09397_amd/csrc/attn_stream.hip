@@ -106,11 +106,11 @@ struct StageLoader {
         for (int g = 0; g < G; ++g) {
             // the counter of outstanding copies holds 63: whole rows in 16-byte pieces stay below it by the size of LDS
             if constexpr (!QUAD) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(62 - kInst) : "memory");
-            const unsigned dst = lds + g * kGroupBytes;
+            const unsigned dst = __builtin_amdgcn_readfirstlane(lds) + g * kGroupBytes;
             if (start[g] + 16 <= n) {
                 const char* first = uniform_ptr(base + (size_t)start[g] * ldb);
 #pragma unroll
-                for (int u = 0; u < kInst; ++u) issue(dst + u * kPiece, voff[u], first);
+                for (int u = 0; u < kInst; ++u) copy_to_lds<kLane>(dst, u * kPiece, voff[u], first, u == 0);
             } else {
                 const char* first = uniform_ptr(base);
                 int l = lane;
@@ -120,17 +120,10 @@ struct StageLoader {
                     int row;
                     unsigned cb;
                     where(u, l, d, row, cb);
-                    issue(dst + u * kPiece, (unsigned)min(start[g] + row, n - 1) * ldb + cb, first);
+                    copy_to_lds<kLane>(dst, u * kPiece, (unsigned)min(start[g] + row, n - 1) * ldb + cb, first, u == 0);
                 }
             }
         }
-    }
-    static __device__ __forceinline__ void issue(unsigned lds_in, unsigned off, const char* first) {
-        const unsigned lds = __builtin_amdgcn_readfirstlane(lds_in);
-        if constexpr (QUAD)
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(first) : "memory", "m0");
-        else
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds), "v"(off), "s"(first) : "memory", "m0");
     }
 };
 
@@ -883,8 +876,8 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
         const int r = first + r16;
         const unsigned off = (unsigned)min(r, p.n - 1) * 4u;
         if constexpr (kOwn) ld.load(O, qb_next, p.n, ldb, p.d, lds + kO, lane);
-        else StageLoader<KIND, false, DP>::issue(lds + kRows + 256, off, delta_row);
-        StageLoader<KIND, false, DP>::issue(lds + kRows, off, lse_row);
+        else copy_to_lds<4, true>(__builtin_amdgcn_readfirstlane(lds), kRows + 256, off, delta_row);
+        copy_to_lds<4, true>(__builtin_amdgcn_readfirstlane(lds), kRows, off, lse_row);
     };
 
     if (w * G < groups.count) {

@@ -201,17 +201,19 @@ def main():
 
 
 # ------------------------------------------------------------------ compiler resource usage
-def kernel_resources(sources=None):
+def kernel_resources(sources=None, assembly=None):
     """Registers, scratch and occupancy of every kernel in the given sources (default: all of the library's), from
-    hipcc -Rpass-analysis=kernel-resource-usage: a list of dicts with the compiler's field names plus "kernel"."""
+    hipcc -Rpass-analysis=kernel-resource-usage: a list of dicts with the compiler's field names plus "kernel".
+    assembly: a folder that the GPU assembly of each source is left in."""
     import re
     import subprocess
     from concurrent.futures import ThreadPoolExecutor
     from paper_2410_09397_amd import build as hip_build
 
     def one(src):
-        cmd = ["hipcc", *hip_build.FLAGS, "-Rpass-analysis=kernel-resource-usage", "-c",
-               os.path.join(hip_build.CSRC, src), "-o", os.devnull]
+        out = os.path.join(assembly, src.replace(".hip", ".s")) if assembly else os.devnull
+        cmd = ["hipcc", *hip_build.FLAGS, "-Rpass-analysis=kernel-resource-usage", "--cuda-device-only", "-S",
+               os.path.join(hip_build.CSRC, src), "-o", out]
         return subprocess.run(cmd, capture_output=True, text=True).stderr
 
     srcs = list(sources or hip_build.SOURCES)

@@ -2,8 +2,10 @@
 them spill (a few more live registers under a launch bound) costs a multiple of its run time and no parity
 test notices.  CPU only: hipcc cross-compiles the sources with -Rpass-analysis=kernel-resource-usage."""
 import functools
+import glob
 import re
 import shutil
+import tempfile
 
 import pytest
 
@@ -23,8 +25,31 @@ STREAM_OCCUPANCY = {("fwd", 0): {32: 7, 64: 5, 96: 4, 128: 3}, ("bwd", 0): {32: 
 
 
 @functools.lru_cache(maxsize=None)
+def compiled():
+    """Every kernel of the library: resources by name, and the instructions of each as (operation, operands), labels as (None, name)."""
+    with tempfile.TemporaryDirectory() as folder:
+        rows = {r["kernel"]: r for r in pmc_summary.kernel_resources(assembly=folder)}
+        code = {}
+        for path in glob.glob(folder + "/*.s"):
+            body = None
+            with open(path) as f:
+                for line in f:
+                    line = line.split(";")[0].strip()
+                    label = re.match(r"(_Z\w+|\.LBB\w+):", line)
+                    if line.startswith(".Lfunc_end"):
+                        body = None
+                    elif label and label.group(1).startswith("_Z"):
+                        body = code.setdefault(label.group(1), [])
+                    elif body is not None and label:
+                        body.append((None, [label.group(1)]))
+                    elif body is not None and line and not line.startswith("."):
+                        op, _, operands = line.partition(" ")
+                        body.append((op, [o.strip() for o in operands.split(",")]))
+    return rows, code
+
+
 def resources():
-    return {r["kernel"]: r for r in pmc_summary.kernel_resources()}  # every kernel of the library
+    return compiled()[0]
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
@@ -56,3 +81,56 @@ def test_profile_summaries_count_every_kernel():
     for name in resources():
         groups = [pmc_summary.is_in(name, g) for g in (pmc_summary.FWD_KERNELS, pmc_summary.BWD_KERNELS, pmc_summary.OTHER_KERNELS)]
         assert sum(groups) == 1, (name, groups)
+
+
+def scalar_registers(operand):
+    m = re.match(r"s\[(\d+):(\d+)\]$|s(\d+)$", operand)
+    if not m:
+        return set()
+    return set(range(int(m.group(1)), int(m.group(2)) + 1)) if m.group(1) else {int(m.group(3))}
+
+
+def reached(body, labels, start, states):
+    """Instructions that some path from `start` executes with fewer than `states` wait states in between."""
+    best, todo = {}, [(0, start)]
+    while todo:
+        waited, i = todo.pop()
+        op, operands = body[i]
+        if op == "s_endpgm":
+            continue
+        follow = [labels[operands[0]]] if op and (op == "s_branch" or op.startswith("s_cbranch")) else []
+        if op != "s_branch":
+            follow.append(i + 1)
+        if i != start and op:
+            waited += int(operands[0], 0) + 1 if op == "s_nop" else 1
+        for j in follow:
+            if waited < states and j < len(body) and waited < best.get(j, states):
+                best[j] = waited
+                todo.append((waited, j))
+    return [body[j] for j in best if body[j][0]]
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_copies_to_lds_wait_for_the_registers_they_read():
+    """The copies are inline assembly, around which the compiler puts no wait states: one is needed between a write of M0 and a copy, five
+    between a vector instruction that writes a scalar register and a memory instruction that reads it."""
+    copies = 0
+    for name, body in compiled()[1].items():
+        labels = {operands[0]: i for i, (op, operands) in enumerate(body) if op is None}
+        for i, (op, operands) in enumerate(body):
+            if op is None:
+                continue
+            copies += "_lds_" in op
+            if op.startswith("s_") and operands[0] == "m0":
+                late = [c for c in reached(body, labels, i, 1) if "_lds_" in c[0]]
+                assert not late, (name, i, late)
+            written = set()
+            if op.startswith(("v_readfirstlane", "v_readlane", "v_cmp")):
+                written = scalar_registers(operands[0])
+            elif op.startswith("v_") and len(operands) > 1:  # carries
+                written = scalar_registers(operands[1]) if "_co_" in op or "mad_u64" in op or "mad_i64" in op or "div_scale" in op else set()
+            if written:
+                late = [c for c in reached(body, labels, i, 5) if c[0].startswith(("global_", "buffer_", "flat_", "scratch_"))
+                        and any(written & scalar_registers(o.split()[0]) for o in c[1] if o)]
+                assert not late, (name, i, late)
+    assert copies > 5000  # (the kernels of fp32 arithmetic alone hold most of them)
