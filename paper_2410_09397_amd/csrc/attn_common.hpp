@@ -41,9 +41,9 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// The matrix instructions in front have written v.  For results that are read behind a branch: there the compiler (ROCm 7.2) has
-// left out the wait states that they need.
-__device__ __forceinline__ void products_done(f32x16& v) { asm volatile("s_nop 15\n\ts_nop 3" : "+v"(v)); }
+// Results of matrix products that vector instructions read next, moved to ordinary registers here where the compiler keeps them in accumulator
+// registers.  (No wait states: the compiler adds those itself, also behind branches.)
+__device__ __forceinline__ void to_vector_registers(f32x16& v) { asm volatile("" : "+v"(v)); }
 
 // Row of accumulator register i for a lane in half h.
 __device__ __forceinline__ int acc_row(int i, int h) { return 8 * (i >> 2) + 4 * h + (i & 3); }

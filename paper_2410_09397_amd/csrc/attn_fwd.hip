@@ -443,8 +443,9 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
             for (int T = 0; T < NT; ++T) s[T] = mfma32(fo.frag(smem, off, 32 * T, ks), qf[ks], s[T]);
         }
         __builtin_amdgcn_sched_barrier(0);
+        // (d = 256, 128 queries: 470 registers per lane; left to the compiler 512 and 60 bytes of scratch)
 #pragma unroll
-        for (int T = 0; T < NT; ++T) products_done(s[T]);
+        for (int T = 0; T < NT; ++T) to_vector_registers(s[T]);
     };
     auto values = [&](auto off) {
 #pragma unroll
@@ -512,7 +513,7 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
     };
     auto rescale = [&](float alpha) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) products_done(o[mt]);
+        for (int mt = 0; mt < MT; ++mt) to_vector_registers(o[mt]);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -642,8 +643,6 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
         }
     }
     if (prev) values((~n_it & 1) * kTileBytes);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) products_done(o[mt]);
     if constexpr (SPLIT > 1) __syncthreads();
 
     fwd_finish<D, SPLIT>(p, smem, base, bh, q, wq, wk, o, m_run, l_run);
