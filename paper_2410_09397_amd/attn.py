@@ -157,8 +157,10 @@ def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
     import torch
-    # the handle of torch.cuda.current_stream(), without the object around it
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # the handle of torch.cuda.current_stream() without the object around it (3 us); the name is not a public one, and where
+    # torch does not have it the object gives the handle
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw is not None else torch.cuda.current_stream().cuda_stream
 
 
 def attn_workspace_bytes(desc, mask=None):

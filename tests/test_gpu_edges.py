@@ -304,3 +304,13 @@ def test_fp32_head_dimensions_around_the_last_sixteen_columns(causal):
             for got, ref in zip((O,) + tuple(grads), want):
                 # fp32 sums of n + d terms: the bound that the other fp32 comparisons hold
                 assert float((got.double() - ref).abs().max()) <= 3e-6 * max(float(ref.abs().max()), 1.0), (d, n)
+
+
+def test_current_stream_is_the_one_that_torch_names():
+    import torch
+    from paper_2410_09397_amd import attn
+    assert attn._stream(None) == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert attn._stream(None) == side.cuda_stream
+    assert attn._stream(side) == side.cuda_stream

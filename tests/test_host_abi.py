@@ -184,3 +184,13 @@ def test_mfma_ceiling_rejects_bad_arguments_before_launch():
     assert L.attn_mfma_ceiling(5000000, 0, P, ctypes.byref(flops), None) == attn.ATTN_ERR_INVALID_ARG
     assert L.attn_mfma_ceiling(100, 0, None, ctypes.byref(flops), None) == attn.ATTN_ERR_INVALID_ARG
     assert L.attn_mfma_ceiling(100, 0, P, None, None) == attn.ATTN_ERR_INVALID_ARG
+
+
+def test_current_stream_without_the_private_shortcut_of_torch(monkeypatch):
+    """The handle comes from torch's public interface where the shortcut does not exist."""
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    assert attn._stream(None) == 1234
+    assert attn._stream(types.SimpleNamespace(cuda_stream=5)) == 5
