@@ -12,11 +12,15 @@ import pytest
 from paper_2410_09397_amd import pmc_summary
 
 # scratch bytes per lane that each kernel is allowed: the d = 64 forward and dQ kernels keep their
-# 4-workgroups-per-CU launch bound and spill 7 and 3 registers (measured faster than the build without scratch)
-ALLOWED_SCRATCH = {"fwd_kernel<64>": 28, "bwd_dq_kernel<64, 1>": 12}
+# 4-workgroups-per-CU launch bound and spill 4 and 2 registers (measured faster than the build without scratch)
+ALLOWED_SCRATCH = {"fwd_kernel<64>": 20, "bwd_dq_kernel<64, 1>": 12}
 MIN_OCCUPANCY = {"fwd_kernel<64>": 4, "bwd_dq_kernel<64, 1>": 4, "bwd_dkdv_kernel<64>": 3, "fwd_kernel<128>": 2,
                  "bwd_dq_kernel<128, 1>": 2, "bwd_dkdv_kernel<128>": 2,
-                 "fwd_split_kernel<64>": 4, "fwd_split_kernel<128>": 2, "bwd_dq_split_kernel<64>": 3, "bwd_dq_split_kernel<128>": 2}
+                 "fwd_split_kernel<64>": 4, "fwd_split_kernel<128>": 2, "bwd_dq_split_kernel<64>": 3, "bwd_dq_split_kernel<128>": 2,
+                 # eight waves on a CU, and the workgroups per CU that the rule for one backward launch counts on
+                 "fwd_pipe_kernel<64, 4>": 2, "fwd_pipe_kernel<128, 4>": 2, "fwd_pipe_kernel<256, 1>": 1, "fwd_pipe_kernel<256, 2>": 1,
+                 "bwd_both_kernel<64, 1>": 3, "bwd_both_kernel<64, 2>": 3, "bwd_both_kernel<128, 1>": 2, "bwd_both_kernel<128, 2>": 2,
+                 "bwd_both_kernel<256, 1>": 1, "bwd_both_kernel<256, 2>": 1}
 # fp32-arithmetic kernels, per kind of storage (0: fp32, 3: bf16) and padded width: two waves per SIMD where two workgroups of
 # four waves or one of eight fit the LDS, more where the width leaves room
 STREAM_OCCUPANCY = {("fwd", 0): {32: 7, 64: 5, 96: 4, 128: 3}, ("bwd", 0): {32: 5, 64: 4, 96: 2, 128: 1},
