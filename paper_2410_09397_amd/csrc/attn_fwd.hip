@@ -240,7 +240,7 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
         // m_run + log2(l) are unchanged.  After the first tiles of a row this almost never
         // happens, which saves the 16 MT + 1 multiplications per lane and tile of the rescaling.
         // Whether it has to move is seen from each lane's own scores; the two halves of a row meet only then.
-        // (The exchange between the halves sat in the chain of every tile: d = 128 h16 n1900 causal 32.5 -> 30.5 us,
+        // (The exchange between the halves sat in the chain of every tile; the forward alone: d = 128 h16 n1900 causal 32.5 -> 30.5 us,
         // b2 h16 n1024 causal 21.3 -> 19.9, b2 h32 n8192 causal 1057 -> 1047; d = 64 b4 h16 n2048 84.1 -> 82.4.)
         constexpr float kSlack = 8.f;
         if (__builtin_amdgcn_ballot_w64(mx * cs > m_run + kSlack) != 0) {  // also the first finite maximum after -inf
@@ -337,7 +337,7 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
 // a CU the plain body is as fast or faster.  K runs one step ahead of V: during step t the copies of K(t + 2) and V(t) arrive in the places of
 // K(t) and V(t - 2).  What is left per step is instruction issue: a wave alone issues one about every 5 cycles, and taking away copies,
 // exponentials or maxima one at a time shortens a step by 5 to 25 % each.
-// us, before -> now: d = 256  h8 n4096 188 -> 145   b2 h16 n8192 causal 1607 -> 1240   h8 n1024 36 -> 28   h16 n2048 causal 77 -> 61
+// us, before -> now: d = 256  h8 n4096 182 -> 148   b2 h16 n8192 causal 1596 -> 1217   h8 n1024 36 -> 28   h16 n2048 causal 96 -> 73
 // (SPLIT = 4: see eight_waves)
 template <int D, int SPLIT>
 __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {

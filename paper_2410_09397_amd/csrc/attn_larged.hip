@@ -9,8 +9,7 @@
 //   gemm kernel   : dV = P^T dO, dK = scale dS^T Q, dQ = scale dS K as tiled products with the
 //                   k-loop over n (phase 4 written for dQ/dK/dV instead of A_1^T p A_2)
 // The forward uses the same kernels: exp(S) written to HBM with its sum per row and chunk of 64 keys, a combine step for LSE,
-// and O = exp(S) V, its rows divided by the sum of the
-// weights as written.
+// and O = exp(S) V, its rows divided by the sum of the weights as written.
 #include <type_traits>
 
 #include "attn_common.hpp"
@@ -23,7 +22,7 @@ namespace attn {
 // workgroups on a CU.  Accumulator: lane <-> query, register <-> key.  Modes:
 //   kProbs    exp2(s - e) of the scores s (times log2 e) written to the workspace in bf16, and e and the row sum per 64-key chunk (the
 //             forward).  e is the chunk's largest score rounded up to a whole number, so what is written is at most 1 and no sweep over
-//             the scores has to come first (it took 154 of 481 us at b1 h8 n4096 d512); the product kernel aligns the
+//             the scores has to come first (it took 154 of 487 us at b1 h8 n4096 d512); the product kernel aligns the
 //             chunks of a row: a whole number is an exact shift of the exponents.
 //   kBackward P and dS.  The two products of a tile are formed one after the other - S^T over all of d, then dP^T
 //             over all of d - so that the wave can hold its block of the one in progress: 256 x 128 tiles move 384 bytes
@@ -276,8 +275,8 @@ __global__ void __launch_bounds__(kThreads, 2) ld_scores_kernel(LargeDParams p) 
     store_tile(p.dS);
 }
 
-// LSE from the per-chunk sums, and for the product kernel a row's factor and the shift of each of its chunks: weights of a row are
-// lowered to sum to at least 1/2 and at most 1, so that the product is finite wherever the row of O is.
+// LSE from the per-chunk sums, and for the product kernel a row's factor and the shift of each of its chunks: the weights of a row are
+// lowered to sum to at most 1, so that the product is finite wherever the row of O is.
 // A workgroup takes 16 rows; 16 threads per row each fold every 16th chunk into a running (e, sum) pair, and the 16 pairs of a row are folded through LDS (one thread per row alone spent its time
 // waiting for one load after the other).  Statistics are [bh][chunk][query]: threads that stand for consecutive
 // queries read consecutive floats.
@@ -352,9 +351,11 @@ constexpr int gemm_stage(bool rows) { return (kGemmM + 128) * kGemmBK * 2 + (row
 // ROWS: A holds exp2(s - e) of the forward.  The chunks of a row are aligned on the way into the product, by a saturating subtraction of
 // exponents on pairs of bf16 (two vector instructions per MFMA), and a row of C is multiplied by its factor.  The shifts come with the
 // operands, 1 KB per k-step: a load in the step, whose wait would drain the copies in flight, made the forward of scores of
-// standard deviation 8 slower than two sweeps were.  us of the forward, b1 h8 n4096 d512, standard deviation of the scores 1 / 4 / 8, two sweeps with
-// P = exp(S - LSE), shifts loaded where a tile needs any, and now: full 548 / 555 / 520, 422 / 484 / 451, 428 / 433 / 407; causal
-// 300 / - / 325, 234 / - / 330, 243 / - / 258; b1 h2 n700 causal 59 / - / 60, 50 / - / 64, 48 / - / 48.
+// standard deviation 4 slower than two sweeps were.  us of the forward for scores of standard deviation 1 / 4 / 8, two sweeps with P =
+// exp(S - LSE), one sweep with shifts loaded where a tile needs any, and now:
+//   d = 512   h8 n4096         487 / 496 / 495   372 / 438 / 436   373 / 378 / 379
+//             h8 n4096 causal  296 / 302 / 301   233 / 324 / 324   233 / 235 / 236      h2 n700 causal 58 / - / 59   49 / - / 63   47 / - / 47
+//   d = 1024  h8 n2000 causal  177 / - / 180     131 / - / 168     131 / - / 132
 template <bool A_KMAJOR, bool ROWS>
 __global__ void __launch_bounds__(kThreads, 2) ld_gemm_kernel(LargeDParams p, GemmArgs g) {
     static_assert(!(A_KMAJOR && ROWS), "the rows of A are the rows of C");

@@ -17,7 +17,7 @@
 // Forward + backward, each timed by itself with calls back to back, against the row-per-wave FMA kernels as they were when these
 // were written (1 TFLOP/s: both operands of every multiply-add came from memory): fp32 b1 h1 n256 d64 347 -> 25 us for the step,
 // b2 h6 n777 d80 causal 1416 + 2173 -> 20 + 61 us, bf16 b1 h8 n1500 d96 causal 4050 + 5550 -> 18 + 43 us.  What bounds them now:
-// fp32 the matrix pipe, busy for 60 % of the CUs' cycles in the long backward and 50 % in the forward; bf16 the vector
+// fp32 the matrix pipe, busy for 57 % of the CUs' cycles in the long backward and 46 % in the forward; bf16 the vector
 // instructions that split f and p (6 to 9 per matrix instruction, which is busy for 19 to 30 %) and the latency of a step;
 // the shortest calls, launches.  Reading the row operands straight from global memory in MFMA order, without LDS, costs
 // one L1 access per lane (64 per KB instead of 16) and measured 135 and 90 us on the last two.
