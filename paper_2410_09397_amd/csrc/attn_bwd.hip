@@ -202,20 +202,6 @@ __device__ __forceinline__ void dkdv_block(const FusedParams p, char* smem, int 
     }
     auto tile_start = [&](int it) -> int { return tile_start_row<BR>(p.list_idx, lp0, t0, it); };
 
-    const int key = j0 + 32 * wk + l32;
-    bf16x8 kf[KS], vf[KS];
-    {
-        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            kf[ks] = zero;
-            vf[ks] = zero;
-            if (key < p.n) {
-                kf[ks] = *reinterpret_cast<const bf16x8*>(p.K + base + (long)key * ld + 16 * ks + 8 * h);
-                vf[ks] = *reinterpret_cast<const bf16x8*>(p.V + base + (long)key * ld + 16 * ks + 8 * h);
-            }
-        }
-    }
     // phase-2 role of this wave: wx = 0 accumulates dV^T (from P and dO^T), wx = 1 dK^T (from dS
     // and Q^T), each for all 64 keys and the half wk of d: a 2 x 2 block of accumulators, so that
     // every fragment read from LDS feeds two MFMAs
@@ -247,20 +233,28 @@ __device__ __forceinline__ void dkdv_block(const FusedParams p, char* smem, int 
         loader.load(p.dO + base, ld, i0, p.n, s + kTileBytes, tid);
         fetch_rows(i0);
     };
+    // The resident K and V rows come through the second stage, which is free until the first tile is worked on: read straight from
+    // memory as operands, every load takes 16 bytes from each of 64 places, and a workgroup stood 3 to 5 us in front of its first tile.
+    // Rows past n repeat the last row; their gradients are not stored.  The gradients leave through LDS as well (8-byte pieces of 32 rows
+    // before).  us of the kernel, before -> now: d = 64 b4 h16 n2048 158 -> 154   d = 128 b2 h16 n1024 causal 28.6 -> 26.0,
+    // b2 h32 n8192 causal 2157 -> 2108   d = 256 h8 n1000 37.3 -> 32.9, b2 h23 n97 causal 14.9 -> 10.5
     int i0_next = n_it > 0 ? tile_start(0) : 0;
+    loader.load(p.K + base, ld, j0, p.n, smem + kStageBytes, tid);
+    loader.load(p.V + base, ld, j0, p.n, smem + kStageBytes + kTileBytes, tid);
     if (n_it > 0) fetch(i0_next, 0);
-    wait_direct_loads();
-    __syncthreads();
-
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        settle(kf[ks]);
-        settle(vf[ks]);
-    }
     FragOffsets<D> fo;    // Q / dO tiles
     FragOffsets<BC> fp;   // P / dS tiles
     fo.init(lane);
     fp.init(lane);
+    wait_direct_loads();
+    __syncthreads();
+    bf16x8 kf[KS], vf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        kf[ks] = fo.frag(smem, kStageBytes, 32 * wk, ks);
+        vf[ks] = fo.frag(smem, kStageBytes + kTileBytes, 32 * wk, ks);
+    }
+    lds_barrier();  // (the first tile's copies go into that stage)
     constexpr int kPOff = 2 * kStageBytes, kDsOff = kPOff + kPBytes;
     // This lane's 8-byte slot of group g in the [query][key] tiles: p_wr ^ (g << 4).  The two
     // 8-byte halves of a chunk swap places in odd rows: rows 2k and 2k+1 share their swizzle
@@ -426,22 +420,23 @@ __device__ __forceinline__ void dkdv_block(const FusedParams p, char* smem, int 
     for (; it < n_it; ++it) tile((it & 1) * kStageBytes, it, i0_next, false, std::true_type{});
 
     const float f = wx == 0 ? 1.f : p.scale;
+    typedef RowStage<D> Rows;
+    constexpr int kGradBytes = 2 * Rows::kBytes;  // 64 rows: dV, then dK
+    static_assert(2 * kGradBytes <= 2 * kStageBytes + 2 * kPBytes, "the stages are free after the last tile");
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-        const int okey = j0 + 32 * kt + l32;  // accumulator column
-        if (okey < p.n) {
-            __bf16* row = (wx == 0 ? p.dV : p.dK) + base + (long)okey * ld + 32 * MH * wk;
+    for (int kt = 0; kt < 2; ++kt)  // accumulator column: key j0 + 32 kt + l32
 #pragma unroll
-            for (int m = 0; m < MH; ++m)
+        for (int m = 0; m < MH; ++m)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    u32x2 a;
-                    a[0] = pack_bf16(acc[m][kt][4 * g + 0] * f, acc[m][kt][4 * g + 1] * f);
-                    a[1] = pack_bf16(acc[m][kt][4 * g + 2] * f, acc[m][kt][4 * g + 3] * f);
-                    *reinterpret_cast<u32x2*>(row + 32 * m + 8 * g + 4 * h) = a;
-                }
-        }
-    }
+            for (int g = 0; g < 4; ++g)
+                Rows::put(smem + wx * kGradBytes + kt * Rows::kBytes, 4 * (MH * wk + m) + g,
+                          u32x2{pack_bf16(acc[m][kt][4 * g + 0] * f, acc[m][kt][4 * g + 1] * f),
+                                pack_bf16(acc[m][kt][4 * g + 2] * f, acc[m][kt][4 * g + 3] * f)},
+                          lane);
+    __syncthreads();
+    const long out = base + (long)j0 * ld;
+    Rows::template store<64, 4>(smem, p.dV + out, ld, p.n - j0, lane, w);
+    Rows::template store<64, 4>(smem + kGradBytes, p.dK + out, ld, p.n - j0, lane, w);
 }
 
 template <int D>

@@ -352,6 +352,30 @@ struct TileLoader {
     }
 };
 
+// A wave's result of 32 rows x W columns of bf16 on its way to memory through LDS: accumulators hold four consecutive columns of a
+// row per lane, and stored as they are every instruction writes 8 bytes to each of 32 rows.  From here it leaves in whole rows,
+// 16 bytes per lane.  (Rows 2 W + 16 bytes apart: 16 lanes that write one column group together touch every bank once.)
+template <int W>
+struct RowStage {
+    static constexpr int kPitch = 2 * W + 16, kBytes = 32 * kPitch, kLanes = W / 8;  // lanes per row
+    // columns 8 g + 4 h .. +3 of row l % 32
+    static __device__ __forceinline__ void put(char* at, int g, u32x2 v, int lane) {
+        *reinterpret_cast<u32x2*>(at + (lane & 31) * kPitch + 16 * g + 8 * (lane >> 5)) = v;
+    }
+    // rows 0 .. min(32, rows) - 1 to dst, ld elements apart, by `waves` waves of which this is number `wave`
+    template <int ROWS = 32, int WAVES = 1>
+    static __device__ __forceinline__ void store(const char* at, __bf16* dst, long ld, int rows, int lane, int wave = 0) {
+        constexpr int kRows = 64 * WAVES / kLanes;
+        const int c = lane % kLanes;
+#pragma unroll
+        for (int r = 0; r < ROWS; r += kRows) {
+            const int row = r + (64 * wave + lane) / kLanes;
+            if (row < rows && (kRows <= ROWS || row < ROWS))
+                *reinterpret_cast<u32x4*>(dst + (long)row * ld + 8 * c) = *reinterpret_cast<const u32x4*>(at + row * kPitch + 16 * c);
+        }
+    }
+};
+
 // Marks a register value as used here.  Ordinary global loads issued before the streaming loop
 // must be complete before it starts: otherwise the compiler's own wait for them lands inside the
 // loop and, vmcnt being one in-order counter, also drains the tile copies in flight.
