@@ -456,13 +456,12 @@ __global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_dkdv_kernel(Fu
 //   S^T[T] = K_T Q_w^T, dP^T[T] = V_T dO_w^T        accumulator: lane <-> query, register <-> key
 //   dS^T = P^T (dP^T - delta)                        per-lane scalars lse2, delta
 //   dQ_w^T += K_T^T dS^T                             K^T from transposed LDS reads
-// SPLIT = 2 (QT = 1): the block has 64 queries and wave (wq, wk) takes queries 32 wq .. +31 with key half wk of every tile; the two
+// SPLIT = 2: the block has 64 queries and wave (wq, wk) takes queries 32 wq .. +31 with key half wk of every tile; the two
 // sums of a query meet in LDS at the end.
 // OWN: delta is formed here and left in the workspace; else it is read from there.
-template <int D, int QT, int SPLIT, bool OWN>
+template <int D, int SPLIT, bool OWN>
 __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh, int blk) {
-    static_assert(SPLIT == 1 || QT == 1, "one way to share out the waves at a time");
-    constexpr int BR = 128 * QT / SPLIT, BC = 64, KS = D / 16, MT = D / 32;
+    constexpr int BR = 128 / SPLIT, BC = 64, KS = D / 16, MT = D / 32;
     constexpr int NT = 2 / SPLIT;  // 32-key halves of a tile per wave
     constexpr int kTileBytes = BC * D * 2;
     constexpr int kStageBytes = 2 * kTileBytes;
@@ -477,10 +476,10 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
     const long base = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
     const long ld = p.stride_n;
     const int i0 = ib * BR;
-    const int w0 = i0 + 32 * QT * wq;  // first query of this wave
+    const int w0 = i0 + 32 * wq;  // first query of this wave
 
     int n_it, lp0 = 0;
-    if (p.list_ptr) {  // block lists are per 128 queries: only with QT == 1
+    if (p.list_ptr) {  // block lists are per 128 queries
         const int32_t* lptr = p.list_ptr + (long)bh * p.list_stride;  // this (batch, head)'s mask
         const int lb = ib / SPLIT;
         lp0 = lptr[lb];
@@ -502,92 +501,95 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
         loader.load(p.K + base, ld, j0, p.n, s, tid);
         loader.load(p.V + base, ld, j0, p.n, s + kTileBytes, tid);
     };
-    // the first tile is requested before the resident rows, so that the two latencies overlap
-    int j0_next = n_it > 0 ? tile_start(0) : 0;
-    if (n_it > 0) fetch(j0_next, 0);
-
-    // resident operands: QT tiles of 32 queries per wave
-    int q[QT];
-    bf16x8 qf[QT][KS], gf[QT][KS];
-    float lse2[QT], dl[QT];
-#pragma unroll
-    for (int t = 0; t < QT; ++t) {
-        q[t] = w0 + 32 * t + l32;
-        const bool ok = q[t] < p.n;
-        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            qf[t][ks] = zero;
-            gf[t][ks] = zero;
-            if (ok) {
-                qf[t][ks] = *reinterpret_cast<const bf16x8*>(p.Q + base + (long)q[t] * ld + 16 * ks + 8 * h);
-                gf[t][ks] = *reinterpret_cast<const bf16x8*>(p.dO + base + (long)q[t] * ld + 16 * ks + 8 * h);
-            }
-        }
-        lse2[t] = ok ? p.LSE[(long)bh * p.n + q[t]] * kLog2e : __builtin_inff();
-        // delta = rowsum(dO o O) of this lane's query: the dO fragments are at hand, the O row is
-        // read once here (and nowhere else in the backward); the two lane halves hold the two
-        // halves of every 16-element chunk.  The dK / dV kernel, which runs after this one,
-        // takes delta from the workspace.
-        if constexpr (OWN) {
-            float dsum = 0.f;
-            if (ok) {
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    const bf16x8 of = *reinterpret_cast<const bf16x8*>(p.O + base + (long)q[t] * ld + 16 * ks + 8 * h);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) dsum += (float)of[e] * (float)gf[t][ks][e];
-                }
-            }
-            dsum += __shfl_xor(dsum, 32, 64);
-            dl[t] = ok ? dsum : 0.f;
-            if (ok && h == 0 && wk == 0) p.delta[(long)bh * p.n + q[t]] = dsum;
-        } else {
-            dl[t] = ok ? p.delta[(long)bh * p.n + q[t]] : 0.f;
-        }
-    }
-
-    f32x16 dq[QT][MT];
-#pragma unroll
-    for (int t = 0; t < QT; ++t)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) dq[t][mt][i] = 0.f;
-
-    const float c = p.scale * kLog2e;
-#pragma unroll
-    for (int t = 0; t < QT; ++t) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            settle(qf[t][ks]);
-            settle(gf[t][ks]);
-        }
-        settle(lse2[t]);
-        settle(dl[t]);
-    }
-    // -delta of this lane's query in all 16 registers of an accumulator block: the dP^T chains start
-    // from it (C operand of their first MFMA), so dP^T - delta costs no vector instruction per tile.
-    // Not at d = 64: there the kernel is built for four workgroups per CU (128 registers) and the
-    // 16 extra registers would spill (measured: 12 -> 332 bytes of scratch per lane, four times slower).
-    constexpr bool kDeltaInAcc = D >= 128;
-    f32x16 ndl[QT];
-#pragma unroll
-    for (int t = 0; t < QT; ++t) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) ndl[t][i] = kDeltaInAcc ? -dl[t] : 0.f;
+    // Resident operands: 32 queries per wave.  Their rows come through LDS (read straight from memory as operands, every load takes 16
+    // bytes from each of 64 places): blocks of 64 queries through the second stage and, for O, a tile behind the stages, while the first
+    // tile arrives in the first; of 128 queries Q and dO through both stages, then O while the first tile arrives.  Rows past n repeat the
+    // last row; nothing of theirs is stored.  dQ leaves through LDS as well.  us of the kernel, before -> now: d = 64
+    // b4 h16 n2048 103 -> 103, causal h12 n2048 25.7 -> 23.6   d = 128 b2 h16 n1024 causal 26.1 -> 23.7, b2 h32 n8192 causal 1383 -> 1357   d = 256
+    // h8 n1000 39.1 -> 35.6, b2 h23 n97 causal 13.8 -> 11.9
+    const int q = w0 + l32;
+    const bool ok = q < p.n;
+    const float lse2 = ok ? p.LSE[(long)bh * p.n + q] * kLog2e : __builtin_inff();
+    float dl = 0.f;
+    if constexpr (!OWN) {
+        if (ok) dl = p.delta[(long)bh * p.n + q];
     }
     FragOffsets<D> lane_offsets;
     lane_offsets.init(lane);
     FragAddrs<D> fo;
     fo.init(lane_offsets);
+    bf16x8 qf[KS], gf[KS];
+    int j0_next = n_it > 0 ? tile_start(0) : 0;
+    // delta = rowsum(dO o O) of this lane's query: the dO fragments are at hand, the O row is
+    // read once here (and nowhere else in the backward); the two lane halves hold the two
+    // halves of every 16-element chunk.  The dK / dV kernel, which runs after this one,
+    // takes delta from the workspace.
+    auto form_delta = [&](int o_off) {
+        float dsum = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const bf16x8 of = fo.frag(smem, o_off, 32 * wq, ks);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dsum += (float)of[e] * (float)gf[ks][e];
+        }
+        dsum += __shfl_xor(dsum, 32, 64);
+        if (ok) dl = dsum;
+        if (ok && h == 0 && wk == 0) p.delta[(long)bh * p.n + q] = dsum;
+    };
+    auto read_operands = [&](int q_off, int g_off) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            qf[ks] = fo.frag(smem, q_off, 32 * wq, ks);
+            gf[ks] = fo.frag(smem, g_off, 32 * wq, ks);
+        }
+    };
+    if constexpr (SPLIT == 2) {
+        loader.load(p.Q + base, ld, i0, p.n, smem + kStageBytes, tid);
+        loader.load(p.dO + base, ld, i0, p.n, smem + kStageBytes + kTileBytes, tid);
+        if constexpr (OWN) loader.load(p.O + base, ld, i0, p.n, smem + 2 * kStageBytes, tid);
+        if (n_it > 0) fetch(j0_next, 0);
+        wait_direct_loads();
+        __syncthreads();
+        read_operands(kStageBytes, kStageBytes + kTileBytes);
+        if constexpr (OWN) form_delta(2 * kStageBytes);
+    } else {
+        TileLoader<D, BR> rows;  // a stage holds 128 rows
+        rows.init(tid, ld);
+        rows.load(p.Q + base, ld, i0, p.n, smem + kStageBytes, tid);
+        rows.load(p.dO + base, ld, i0, p.n, smem, tid);
+        wait_direct_loads();
+        __syncthreads();
+        read_operands(kStageBytes, 0);
+        lds_barrier();
+        if constexpr (OWN) rows.load(p.O + base, ld, i0, p.n, smem + kStageBytes, tid);
+        if (n_it > 0) fetch(j0_next, 0);
+        wait_direct_loads();
+        __syncthreads();
+        if constexpr (OWN) form_delta(kStageBytes);
+    }
+    lds_barrier();  // (the first tile's copies go into the second stage)
+    settle(lse2);
+    settle(dl);
+
+    f32x16 dq[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dq[mt][i] = 0.f;
+
+    const float c = p.scale * kLog2e;
+    // -delta of this lane's query in all 16 registers of an accumulator block: the dP^T chains start
+    // from it (C operand of their first MFMA), so dP^T - delta costs no vector instruction per tile.
+    // Not at d = 64: there the kernel is built for four workgroups per CU (128 registers) and the
+    // 16 extra registers would spill (measured: 12 -> 332 bytes of scratch per lane, four times slower).
+    constexpr bool kDeltaInAcc = D >= 128;
+    f32x16 ndl;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) ndl[i] = kDeltaInAcc ? -dl : 0.f;
     if constexpr (SPLIT > 1) fo.shift_rows(32 * wk);
-    wait_direct_loads();
-    __syncthreads();
 
     // One streamed tile.  `masked` selects the copy of the body that applies the causal / tail
-    // bound; the other copy has no mask arithmetic at all.  Every K, V and K^T fragment read
-    // from LDS feeds QT MFMAs (one per resident query tile).
+    // bound; the other copy has no mask arithmetic at all.
     // Wave priorities per phase (see the forward kernel): score MFMAs, then the dQ MFMAs, the
     // exponentials last.
     constexpr int kPrioScores = 2, kPrioSoftmax = 0, kPrioDq = 1;
@@ -597,39 +599,29 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
 #pragma unroll
         for (int T = 0; T < NT; ++T) {
             __builtin_amdgcn_s_setprio(kPrioScores);
-            f32x16 st[QT], dpt[QT];
+            f32x16 st, dpt = ndl;
 #pragma unroll
-            for (int t = 0; t < QT; ++t)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) st[t][i] = 0.f;
-#pragma unroll
-            for (int t = 0; t < QT; ++t) dpt[t] = ndl[t];
+            for (int i = 0; i < 16; ++i) st[i] = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {  // independent accumulation chains, interleaved
                 const bf16x8 kfr = fo.frag(smem, k_off, 32 * T, ks);
                 const bf16x8 vfr = fo.frag(smem, k_off + kTileBytes, 32 * T, ks);
-#pragma unroll
-                for (int t = 0; t < QT; ++t) {
-                    st[t] = mfma32(kfr, qf[t][ks], st[t]);
-                    dpt[t] = mfma32(vfr, gf[t][ks], dpt[t]);
-                }
+                st = mfma32(kfr, qf[ks], st);
+                dpt = mfma32(vfr, gf[ks], dpt);
             }
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_setprio(kPrioSoftmax);
-            bf16x8 dsb[QT][2], kt[2][MT];
+            bf16x8 dsb[2], kt[2][MT];
+            // key j0 + 32T + 8g + 4h + r is visible iff 8g + r <= lim (one per-lane bound)
+            const int lim = (p.causal ? min(q, p.n - 1) : p.n - 1) - j0 - 32 * (T + wk) - 4 * h;
 #pragma unroll
-            for (int t = 0; t < QT; ++t) {
-                // key j0 + 32T + 8g + 4h + r is visible iff 8g + r <= lim (one per-lane bound)
-                const int lim = (p.causal ? min(q[t], p.n - 1) : p.n - 1) - j0 - 32 * (T + wk) - 4 * h;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    float pv = __builtin_amdgcn_exp2f(st[t][i] * c - lse2[t]);
-                    if constexpr (decltype(masked)::value) pv = (8 * (i >> 2) + (i & 3) > lim) ? 0.f : pv;
-                    dpt[t][i] = kDeltaInAcc ? pv * dpt[t][i] : pv * (dpt[t][i] - dl[t]);
-                }
-#pragma unroll
-                for (int ss = 0; ss < 2; ++ss) dsb[t][ss] = acc_to_operand(dpt[t], ss);
+            for (int i = 0; i < 16; ++i) {
+                float pv = __builtin_amdgcn_exp2f(st[i] * c - lse2);
+                if constexpr (decltype(masked)::value) pv = (8 * (i >> 2) + (i & 3) > lim) ? 0.f : pv;
+                dpt[i] = kDeltaInAcc ? pv * dpt[i] : pv * (dpt[i] - dl);
             }
+#pragma unroll
+            for (int ss = 0; ss < 2; ++ss) dsb[ss] = acc_to_operand(dpt, ss);
             __builtin_amdgcn_s_setprio(kPrioDq);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) kt[0][mt] = fo.frag_t(smem, k_off, mt, 32 * T);
@@ -640,9 +632,7 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
                     for (int mt = 0; mt < MT; ++mt) kt[1][mt] = fo.frag_t(smem, k_off, mt, 32 * T + 16);
                 }
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int t = 0; t < QT; ++t) dq[t][mt] = mfma32(kt[ss][mt], dsb[t][ss], dq[t][mt]);
+                for (int mt = 0; mt < MT; ++mt) dq[mt] = mfma32(kt[ss][mt], dsb[ss], dq[mt]);
             }
             __builtin_amdgcn_sched_barrier(0);  // the next half starts after this one is issued
         }
@@ -681,7 +671,7 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
             fetch(j0_next, (it + 1) & 1);
         }
         // causal: this wave's last query precedes its first key of the tile -> nothing visible
-        if (!(p.causal && (w0 + 32 * QT - 1 < j0 + 32 * wk))) tile((it & 1) * kStageBytes, j0, std::true_type{});
+        if (!(p.causal && (w0 + 31 < j0 + 32 * wk))) tile((it & 1) * kStageBytes, j0, std::true_type{});
         wait_direct_loads();
         __syncthreads();
     }
@@ -696,7 +686,7 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
             for (int mt = 0; mt < MW; ++mt)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const f32x16& a = dq[0][decltype(first)::value + mt];
+                    const f32x16& a = dq[decltype(first)::value + mt];
                     *slot(w, mt, g) = f32x4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
                 }
         };
@@ -707,7 +697,7 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
                 for (int g = 0; g < 4; ++g) {
                     const f32x4 b = *slot(w ^ 2, mt, g);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) dq[0][mt][4 * g + r] = dq[0][decltype(first)::value + mt][4 * g + r] + b[r];
+                    for (int r = 0; r < 4; ++r) dq[mt][4 * g + r] = dq[decltype(first)::value + mt][4 * g + r] + b[r];
                 }
         };
         if (wk == 0) send(std::integral_constant<int, MW>{});
@@ -716,32 +706,34 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
         if (wk == 0) meet(std::integral_constant<int, 0>{});
         else meet(std::integral_constant<int, MW>{});
     }
+    // (a wave's own rows and columns: nothing to wait for but its own writes; behind the slots of the two sums)
+    typedef RowStage<32 * MW> Rows;
+    constexpr int kSlots = SPLIT > 1 ? 4 * MW * 4096 : 0;
+    static_assert(kSlots + 4 * Rows::kBytes <= 2 * kStageBytes, "the stages are free after the last tile");
+    int out_lane = lane;  // formed again here, so that no address is carried through the loop (d = 64 has no register to spare)
+    asm volatile("" : "+v"(out_lane));
+    char* mine = smem + kSlots + w * Rows::kBytes;
 #pragma unroll
-    for (int t = 0; t < QT; ++t) {
-        if (q[t] < p.n) {
-            __bf16* row = p.dQ + base + (long)q[t] * ld + 32 * MW * wk;
+    for (int mt = 0; mt < MW; ++mt)
 #pragma unroll
-            for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    u32x2 a;
-                    a[0] = pack_bf16(dq[t][mt][4 * g + 0] * p.scale, dq[t][mt][4 * g + 1] * p.scale);
-                    a[1] = pack_bf16(dq[t][mt][4 * g + 2] * p.scale, dq[t][mt][4 * g + 3] * p.scale);
-                    *reinterpret_cast<u32x2*>(row + 32 * mt + 8 * g + 4 * h) = a;
-                }
-        }
-    }
+        for (int g = 0; g < 4; ++g)
+            Rows::put(mine, 4 * mt + g,
+                      u32x2{pack_bf16(dq[mt][4 * g + 0] * p.scale, dq[mt][4 * g + 1] * p.scale),
+                            pack_bf16(dq[mt][4 * g + 2] * p.scale, dq[mt][4 * g + 3] * p.scale)},
+                      out_lane);
+    Rows::store(mine, p.dQ + base + (long)w0 * ld + 32 * MW * wk, ld, p.n - w0, out_lane);
 }
 
 constexpr int dq_per_cu(int d) { return d == 64 ? 4 : d == 128 ? 2 : 1; }
 constexpr int dq_split_per_cu(int d) { return d == 64 ? 3 : dq_per_cu(d); }  // (130 registers at d = 64)
 
-template <int D, int QT>
-__global__ void __launch_bounds__(kThreads, QT == 1 ? dq_per_cu(D) : 1) bwd_dq_kernel(FusedParams p) {
+template <int D, int QT>  // QT: 32-query tiles per wave
+__global__ void __launch_bounds__(kThreads, dq_per_cu(D)) bwd_dq_kernel(FusedParams p) {
+    static_assert(QT == 1, "two tiles per wave do not leave two waves per SIMD");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int bh, blk;
-    decode_block_causal(blockIdx.x, (p.n + 128 * QT - 1) / (128 * QT), p.batch * p.heads, p.resident, bh, blk);
-    dq_block<D, QT, 1, true>(p, smem, bh, blk);
+    decode_block_causal(blockIdx.x, (p.n + 127) / 128, p.batch * p.heads, p.resident, bh, blk);
+    dq_block<D, 1, true>(p, smem, bh, blk);
 }
 
 template <int D>
@@ -749,7 +741,7 @@ __global__ void __launch_bounds__(kThreads, dq_split_per_cu(D)) bwd_dq_split_ker
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int bh, blk;
     decode_block_causal(blockIdx.x, p.order ? 2 * ((p.n + 127) / 128) : (p.n + 63) / 64, p.batch * p.heads, p.resident, bh, blk);
-    dq_block<D, 1, 2, true>(p, smem, bh, blk);
+    dq_block<D, 2, true>(p, smem, bh, blk);
 }
 
 // Both halves of the backward side by side: for every 128 rows two blocks of 64 queries (SPLIT = 2) or one of 128 (dQ), and two of
@@ -761,13 +753,13 @@ __global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_both_kernel(Fu
     if constexpr (SPLIT == 2) {
         const int blocks = pq.order ? 2 * ((pq.n + 127) / 128) : (pq.n + 63) / 64;
         decode_block_causal(blockIdx.x, 2 * blocks, pq.batch * pq.heads, pq.resident, bh, rank);
-        if (rank & 1) dq_block<D, 1, 2, false>(pq, smem, bh, rank >> 1);
+        if (rank & 1) dq_block<D, 2, false>(pq, smem, bh, rank >> 1);
         else dkdv_block<D>(pk, smem, bh, rank >> 1);
     } else {
         const int blocks = 3 * ((pq.n + 127) / 128);
         decode_block_causal(blockIdx.x, blocks, pq.batch * pq.heads, pq.resident, bh, rank);
         const int r = rank % 3, k = 2 * (rank / 3) + r - 1;
-        if (r == 0) dq_block<D, 1, 1, false>(pq, smem, bh, rank / 3);
+        if (r == 0) dq_block<D, 1, false>(pq, smem, bh, rank / 3);
         else if (pk.order || 64 * k < pk.n) dkdv_block<D>(pk, smem, bh, k);
     }
 }
@@ -804,9 +796,9 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     const bool onepass = onepass_keys != 0 && !dq_only;
 
     constexpr int kv_lds = 2 * (2 * 64 * D * 2) + 2 * 64 * 64 * 2;  // two stages of Q, dO; P and dS
-    constexpr int q_lds = 2 * (2 * 64 * D * 2);
     const int blocks128 = (p.n + 127) / 128;
     const bool split = few_blocks(blocks128 * bh, dq_per_cu(D), p.causal && !p.mask_form);
+    const int q_lds = (split ? 5 : 4) * (64 * D * 2);  // two stages of K, V; blocks of 64 queries: and their O rows
     const long both_grid = (long)bh * (split ? 2 * (csr_ptr ? 2 * blocks128 : (p.n + 63) / 64) : 3 * blocks128);
     const bool both = p.may_join && !onepass && !dq_only && !dkdv_only && side_by_side(both_grid, D, p.causal || csr_ptr);
     void (*const dq_fn)(FusedParams) = split ? bwd_dq_split_kernel<D> : bwd_dq_kernel<D, 1>;
