@@ -9,14 +9,14 @@
 
 namespace attn {
 
-// The end of a query block: O / l and LSE of wave (wq, wk)'s 32 queries.  SPLIT > 1: SPLIT waves hold a part of the keys each; of the
+// The end of a query block: O / l and LSE of wave (wq, wk)'s 32 queries, from w0 on.  SPLIT > 1: SPLIT waves hold a part of the keys each; of the
 // 4 MT groups of four registers of O each writes MG, from MG wk on, and hands the others theirs through LDS, whose stages are
 // free (every wave is past the last barrier of the loop).
-template <int D, int SPLIT>
-__device__ __forceinline__ void fwd_finish(const FusedParams& p, char* smem, long base, int bh, int q, int wq, int wk, f32x16 (&o)[D / 32],
+template <int D, int SPLIT, int kLdsBytes>
+__device__ __forceinline__ void fwd_finish(const FusedParams& p, char* smem, long base, int bh, int w0, int wq, int wk, f32x16 (&o)[D / 32],
                                            float m_run, float l_run) {
     constexpr int MT = D / 32, MG = 4 * MT / SPLIT;
-    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int lane = threadIdx.x & 63, h = lane >> 5, q = w0 + (lane & 31);
     float l = l_run + __shfl_xor(l_run, 32, 64);
     if constexpr (SPLIT > 1) {
         float* ml = reinterpret_cast<float*>(smem + 2 * SPLIT * (SPLIT - 1) * MG * 64 * 16);  // [wave][2][64]
@@ -70,19 +70,23 @@ __device__ __forceinline__ void fwd_finish(const FusedParams& p, char* smem, lon
         });
     }
     const float inv = l > 0.f ? 1.f / l : 0.f;
-    if (q < p.n) {
-        __bf16* row = p.Oout + base + (long)q * p.stride_n;
+    if (h == 0 && wk == 0 && q < p.n)
+        p.LSEout[(long)bh * p.n + q] = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : -__builtin_inff();
+    // (a wave's own rows and columns: nothing to wait for but its own writes; behind the slots of the other parts)
+    typedef RowStage<8 * MG> Rows;
+    constexpr int kWaves = 4 * (SPLIT > 1 ? SPLIT / 2 : 1);
+    constexpr int kSlots = SPLIT > 1 ? 2 * SPLIT * (SPLIT - 1) * MG * 64 * 16 + kWaves * 512 : 0;
+    static_assert(kSlots + kWaves * Rows::kBytes <= kLdsBytes, "the stages are free after the last tile");
+    int out_lane = lane;  // formed again here, so that no address is carried through the loop (d = 64 has no register to spare)
+    asm volatile("" : "+v"(out_lane));
+    char* mine = smem + kSlots + (SPLIT > 1 ? wq + 2 * wk : wq) * Rows::kBytes;
 #pragma unroll
-        for (int gi = 0; gi < MG; ++gi) {
-            const int col = MG * wk + gi;  // 8 columns each
-            u32x2 a;
-            a[0] = pack_bf16(o[gi / 4][4 * (gi % 4) + 0] * inv, o[gi / 4][4 * (gi % 4) + 1] * inv);
-            a[1] = pack_bf16(o[gi / 4][4 * (gi % 4) + 2] * inv, o[gi / 4][4 * (gi % 4) + 3] * inv);
-            *reinterpret_cast<u32x2*>(row + 8 * col + 4 * h) = a;
-        }
-        if (h == 0 && wk == 0)
-            p.LSEout[(long)bh * p.n + q] = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : -__builtin_inff();
-    }
+    for (int g = 0; g < MG; ++g)  // 8 columns each, from MG wk on
+        Rows::put(mine, g,
+                  u32x2{pack_bf16(o[g / 4][4 * (g % 4) + 0] * inv, o[g / 4][4 * (g % 4) + 1] * inv),
+                        pack_bf16(o[g / 4][4 * (g % 4) + 2] * inv, o[g / 4][4 * (g % 4) + 3] * inv)},
+                  out_lane);
+    Rows::store(mine, p.Oout + base + (long)w0 * p.stride_n + 8 * MG * wk, p.stride_n, p.n - w0, out_lane);
 }
 
 // Wave w owns queries i0 + 32w .. +31 (Q rows resident in registers as B operands).
@@ -136,21 +140,24 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
         loader.load(p.K + base, ld, j0, p.n, s, tid);
         loader.load(p.V + base, ld, j0, p.n, s + 2 * kTileBytes, tid);
     };
-    // the first tile is requested before the resident Q rows, so that the two latencies overlap
+    // The Q rows of a wave come through a piece of the second stage that only it reads (straight from memory as operands, every load takes
+    // 16 bytes from each of 64 places), and O leaves through LDS in whole rows (8-byte pieces of 32 rows before); the latency of
+    // the first tile overlaps.  Rows past n repeat the last row; nothing of theirs is stored.  us, before -> now: d = 64 b4 h16 n2048
+    // 84.9 -> 82.6   d = 128 b2 h16 n1024 causal 19.9 -> 18.7, h11 n700 14.2 -> 13.3, b2 h32 n8192 causal 1086 -> 1075   d = 256 h8 n1000 29.1 -> 27.2
     int j0_next = n_it > 0 ? tile_start(0) : 0;
     if (n_it > 0) fetch(j0_next, 0);
 
     const int q = i0 + 32 * wq + l32;
-    const bool q_ok = q < p.n;
+    TileLoader<D, 32, 1> rows;
+    rows.init(lane, ld);
+    char* q_rows = smem + (w < 2 ? 1 : 3) * kTileBytes + (w & 1) * (32 * D * 2);
+    rows.load(p.Q + base, ld, i0 + 32 * wq, p.n, q_rows, lane);
+    FragOffsets<D> lane_offsets;
+    lane_offsets.init(lane);
+    wait_direct_loads();
     bf16x8 qf[KS];
-    {
-        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            qf[ks] = zero;
-            if (q_ok) qf[ks] = *reinterpret_cast<const bf16x8*>(p.Q + base + (long)q * ld + 16 * ks + 8 * h);
-        }
-    }
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = lane_offsets.frag(q_rows, 0, 0, ks);
 
     f32x16 o[MT];
 #pragma unroll
@@ -175,8 +182,6 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
     }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) settle(qf[ks]);
-    FragOffsets<D> lane_offsets;
-    lane_offsets.init(lane);
     FragAddrs<D> fo;
     fo.init(lane_offsets);
     if constexpr (SPLIT > 1) fo.shift_rows(32 * wk);
@@ -327,7 +332,7 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
         __syncthreads();
     }
 
-    fwd_finish<D, SPLIT>(p, smem, base, bh, q, wq, wk, o, m_run, l_run);
+    fwd_finish<D, SPLIT, 4 * kTileBytes>(p, smem, base, bh, i0 + 32 * wq, wq, wk, o, m_run, l_run);
 }
 
 // The same forward with the three parts of a tile's work taken from three tiles, so that the matrix instructions of one wave have vector
@@ -378,23 +383,23 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
     // [K stage 0][K stage 1][V stage 0][V stage 1]: every fetch of a fragment is a register plus an immediate of 16 bits
     auto fetch_k = [&](int j0, int stage) { loader.load(p.K + base, ld, j0, p.n, smem + stage * kTileBytes, tid); };
     auto fetch_v = [&](int j0, int stage) { loader.load(p.V + base, ld, j0, p.n, smem + (2 + stage) * kTileBytes, tid); };
-    // the first tile is requested before the resident Q rows, so that the two latencies overlap
+    // the first tiles are requested before the resident Q rows, so that the latencies overlap; those come through the places of V (see fwd_block)
     auto start_of = [&](int t) { return t < n_it ? tile_start(t) : 0; };
     int j[3] = {start_of(0), start_of(1), start_of(2)};  // of tiles t, t + 1, t + 2
     if (n_it > 0) fetch_k(j[0], 0);
     if (n_it > 1) fetch_k(j[1], 1);
 
     const int q = i0 + 32 * wq + l32;
-    const bool q_ok = q < p.n;
+    TileLoader<D, 32, 1> rows;
+    rows.init(lane, ld);
+    char* q_rows = smem + 2 * kTileBytes + w * (32 * D * 2);
+    rows.load(p.Q + base, ld, i0 + 32 * wq, p.n, q_rows, lane);
+    FragOffsets<D> lane_offsets;
+    lane_offsets.init(lane);
+    wait_direct_loads();
     bf16x8 qf[KS];
-    {
-        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            qf[ks] = zero;
-            if (q_ok) qf[ks] = *reinterpret_cast<const bf16x8*>(p.Q + base + (long)q * ld + 16 * ks + 8 * h);
-        }
-    }
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = lane_offsets.frag(q_rows, 0, 0, ks);
 
     f32x16 o[MT];
 #pragma unroll
@@ -419,8 +424,6 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
     }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) settle(qf[ks]);
-    FragOffsets<D> lane_offsets;
-    lane_offsets.init(lane);
     FragAddrs<D> fo;
     fo.init(lane_offsets);
     if constexpr (SPLIT > 1) fo.shift_rows(32 * wk);
@@ -643,9 +646,9 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
         }
     }
     if (prev) values((~n_it & 1) * kTileBytes);
-    if constexpr (SPLIT > 1) __syncthreads();
+    __syncthreads();  // (the end of the block uses the stages)
 
-    fwd_finish<D, SPLIT>(p, smem, base, bh, q, wq, wk, o, m_run, l_run);
+    fwd_finish<D, SPLIT, 4 * kTileBytes>(p, smem, base, bh, i0 + 32 * wq, wq, wk, o, m_run, l_run);
 }
 
 // Whether a launch of blocks of 64 queries takes eight waves (two query halves, four key parts of tiles of 128 keys, the pipelined
