@@ -20,7 +20,7 @@ import os
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COPY_BYTES = float(1 << 30)  # bytes read, and bytes written, by the calibration copy
-BWD_KERNELS = ("delta_kernel", "bwd_dkdv", "bwd_dq", "ld_scores_kernel<2>", "ld_scores_kernel<(attn::ScoreMode)2>", "ld_gemm_kernel<true, false>", "ld_gemm_kernel<false, false>", "generic_delta",
+BWD_KERNELS = ("delta_kernel", "bwd_dkdv", "bwd_dq", "ld_scores_kernel<2", "ld_gemm_kernel<true>", "ld_gemm_wide_kernel<true>", "generic_delta",
                "generic_dq", "generic_dkdv", "block_len_kernel", "block_order_kernel", "block_order_fused_kernel", "bwd_prep_kernel", "bwd_rows_kernel", "bwd_both_kernel",
                "bwd_onepass_kernel", "bwd_splitd_kernel", "stream_bwd_kernel")
 
@@ -41,7 +41,7 @@ def source_hash():
 
 def traffic_key(workload, tiling):
     return workload if not tiling else "%s@tiling%d" % (workload, tiling)
-FWD_KERNELS = ("fwd_kernel", "fwd_split_kernel", "fwd_pipe_kernel", "ld_scores_kernel<1>", "ld_scores_kernel<(attn::ScoreMode)1>", "ld_gemm_kernel<false, true>",
+FWD_KERNELS = ("fwd_kernel", "fwd_split_kernel", "fwd_pipe_kernel", "ld_scores_kernel<1", "ld_gemm_kernel<false>", "ld_gemm_wide_kernel<false>",
                "ld_lse_combine", "generic_fwd")
 # launched by neither attn_fwd nor attn_bwd: the weight gradient's own and the measurement aids
 OTHER_KERNELS = ("wgrad_partial", "wgrad_reduce", "proj_kernel", "tile_skeleton_kernel", "mfma_ceiling_kernel")
