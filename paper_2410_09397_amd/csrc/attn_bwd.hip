@@ -165,15 +165,18 @@ __global__ void __launch_bounds__(kThreads) bwd_rows_kernel(FusedParams p, Order
 // fall into step; ranking phase 1 above phase 2 above the exponentials lets one of them run ahead
 // (measured: 2 % faster than without priorities, 3 % faster than with the exponentials in the middle).
 constexpr int kPrioPhase1 = 3, kPrioSoftmax = 0, kPrioPhase2 = 1;
-template <int D>
-__device__ __forceinline__ void dkdv_block(const FusedParams p, char* smem, int bh, int j) {
+template <int D, int NG = 1>
+__device__ __forceinline__ void dkdv_block(const FusedParams& p, char* lds, int bh, int j) {
     constexpr int BR = 64, BC = 64, KS = D / 16, MT = D / 32;
     constexpr int kTileBytes = BR * D * 2;
     constexpr int kStageBytes = 2 * kTileBytes;
     constexpr int kPBytes = BC * BR * 2;
 
-    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
+    // NG = 2: two groups of four waves, each with stages and P / dS tiles of its own, take the streamed tiles in turn (eight_waves_bwd)
+    const int group = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads);
+    char* smem = lds + group * (2 * kStageBytes + 2 * kPBytes);
+    const int tid = threadIdx.x % kThreads, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index within the group, uniform
     const int wk = w & 1, wx = w >> 1;
     if (p.order) {
         j = 2 * p.order[(long)bh * p.order_stride + (j >> 1)] + (j & 1);
@@ -200,7 +203,9 @@ __device__ __forceinline__ void dkdv_block(const FusedParams p, char* smem, int 
         t0 = p.causal ? j0 / BR : 0;
         n_it = (p.n + BR - 1) / BR - t0;
     }
-    auto tile_start = [&](int it) -> int { return tile_start_row<BR>(p.list_idx, lp0, t0, it); };
+    const int n_all = n_it;
+    if constexpr (NG > 1) n_it = (n_all - group + NG - 1) / NG;  // this group's tiles: every NG-th, from `group` on
+    auto tile_start = [&](int it) -> int { return tile_start_row<BR>(p.list_idx, lp0, t0, NG * it + group); };
 
     // phase-2 role of this wave: wx = 0 accumulates dV^T (from P and dO^T), wx = 1 dK^T (from dS
     // and Q^T), each for all 64 keys and the half wk of d: a 2 x 2 block of accumulators, so that
@@ -239,7 +244,7 @@ __device__ __forceinline__ void dkdv_block(const FusedParams p, char* smem, int 
     // before).  us of the kernel, before -> now: d = 64 b4 h16 n2048 158 -> 154   d = 128 b2 h16 n1024 causal 28.6 -> 26.0,
     // b2 h32 n8192 causal 2157 -> 2108   d = 256 h8 n1000 37.3 -> 32.9, b2 h23 n97 causal 14.9 -> 10.5
     int i0_next = n_it > 0 ? tile_start(0) : 0;
-    loader.load(p.K + base, ld, j0, p.n, smem + kStageBytes, tid);
+    loader.load(p.K + base, ld, j0, p.n, smem + kStageBytes, tid);  // (every group for itself)
     loader.load(p.V + base, ld, j0, p.n, smem + kStageBytes + kTileBytes, tid);
     if (n_it > 0) fetch(i0_next, 0);
     FragOffsets<D> fo;    // Q / dO tiles
@@ -419,24 +424,59 @@ __device__ __forceinline__ void dkdv_block(const FusedParams p, char* smem, int 
     }
     for (; it < n_it; ++it) tile((it & 1) * kStageBytes, it, i0_next, false, std::true_type{});
 
+    if constexpr (NG > 1) {
+        static_assert(NG == 2, "one group hands its sums to the other");
+        if (n_it < (n_all + 1) / 2) {  // (the barriers of the tile that the first group has more)
+            lds_barrier();
+            __syncthreads();
+        }
+        auto slot = [&](int m, int kt, int q) { return reinterpret_cast<f32x4*>(lds) + (((w * MH + m) * 2 + kt) * 4 + q) * 64 + lane; };
+        if (group == 1) {
+#pragma unroll
+            for (int m = 0; m < MH; ++m)
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *slot(m, kt, q) = f32x4{acc[m][kt][4 * q], acc[m][kt][4 * q + 1], acc[m][kt][4 * q + 2], acc[m][kt][4 * q + 3]};
+        }
+        __syncthreads();
+        if (group == 0) {
+#pragma unroll
+            for (int m = 0; m < MH; ++m)
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 other = *slot(m, kt, q);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[m][kt][4 * q + e] += other[e];
+                    }
+        }
+    }
+
     const float f = wx == 0 ? 1.f : p.scale;
     typedef RowStage<D> Rows;
     constexpr int kGradBytes = 2 * Rows::kBytes;  // 64 rows: dV, then dK
-    static_assert(2 * kGradBytes <= 2 * kStageBytes + 2 * kPBytes, "the stages are free after the last tile");
+    constexpr int kSlots = NG > 1 ? 4 * MH * 2 * 4096 : 0;
+    static_assert(kSlots + 2 * kGradBytes <= NG * (2 * kStageBytes + 2 * kPBytes), "the stages are free after the last tile");
+    char* rows = lds + kSlots;
+    if (group == 0) {
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)  // accumulator column: key j0 + 32 kt + l32
 #pragma unroll
         for (int m = 0; m < MH; ++m)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                Rows::put(smem + wx * kGradBytes + kt * Rows::kBytes, 4 * (MH * wk + m) + g,
+                Rows::put(rows + wx * kGradBytes + kt * Rows::kBytes, 4 * (MH * wk + m) + g,
                           u32x2{pack_bf16(acc[m][kt][4 * g + 0] * f, acc[m][kt][4 * g + 1] * f),
                                 pack_bf16(acc[m][kt][4 * g + 2] * f, acc[m][kt][4 * g + 3] * f)},
                           lane);
+    }
     __syncthreads();
     const long out = base + (long)j0 * ld;
-    Rows::template store<64, 4>(smem, p.dV + out, ld, p.n - j0, lane, w);
-    Rows::template store<64, 4>(smem + kGradBytes, p.dK + out, ld, p.n - j0, lane, w);
+    Rows::template store<64, 4 * NG>(rows, p.dV + out, ld, p.n - j0, lane, 4 * group + w);
+    Rows::template store<64, 4 * NG>(rows + kGradBytes, p.dK + out, ld, p.n - j0, lane, 4 * group + w);
 }
 
 template <int D>
@@ -459,15 +499,19 @@ __global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_dkdv_kernel(Fu
 // SPLIT = 2: the block has 64 queries and wave (wq, wk) takes queries 32 wq .. +31 with key half wk of every tile; the two
 // sums of a query meet in LDS at the end.
 // OWN: delta is formed here and left in the workspace; else it is read from there.
-template <int D, int SPLIT, bool OWN>
-__device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh, int blk) {
+template <int D, int SPLIT, bool OWN, int NG = 1>
+__device__ __forceinline__ void dq_block(const FusedParams p, char* lds, int bh, int blk) {
+    static_assert(NG == 1 || SPLIT == 2, "two groups: blocks of 64 queries");
     constexpr int BR = 128 / SPLIT, BC = 64, KS = D / 16, MT = D / 32;
     constexpr int NT = 2 / SPLIT;  // 32-key halves of a tile per wave
     constexpr int kTileBytes = BC * D * 2;
     constexpr int kStageBytes = 2 * kTileBytes;
 
-    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
+    // group of four waves, each with stages of its own; the key tiles take turns (see dkdv_block)
+    const int group = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads);
+    char* smem = lds + group * ((OWN && SPLIT == 2 ? 5 : 4) * kTileBytes);
+    const int tid = threadIdx.x % kThreads, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index within the group, uniform
     const int wq = SPLIT == 1 ? w : w & 1, wk = SPLIT == 1 ? 0 : w >> 1;
     const int q_blocks = (p.n + BR - 1) / BR;
     // longest rows first: under the causal rule the last blocks, under a block mask by the order list
@@ -490,7 +534,9 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
         const int k_end = p.causal ? min(p.n, i0 + BR) : p.n;
         n_it = (k_end + BC - 1) / BC;
     }
-    auto tile_start = [&](int it) -> int { return tile_start_row<BC>(p.list_idx, lp0, 0, it); };
+    const int n_all = n_it;
+    if constexpr (NG > 1) n_it = (n_all - group + NG - 1) / NG;
+    auto tile_start = [&](int it) -> int { return tile_start_row<BC>(p.list_idx, lp0, 0, NG * it + group); };
 
     // K and V tiles go straight from global memory into the LDS stage that was last read one
     // iteration ago; rows past n repeat the last row and are masked below.
@@ -534,7 +580,7 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
         }
         dsum += __shfl_xor(dsum, 32, 64);
         if (ok) dl = dsum;
-        if (ok && h == 0 && wk == 0) p.delta[(long)bh * p.n + q] = dsum;
+        if (ok && h == 0 && wk == 0 && group == 0) p.delta[(long)bh * p.n + q] = dsum;
     };
     auto read_operands = [&](int q_off, int g_off) {
 #pragma unroll
@@ -676,6 +722,28 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
         __syncthreads();
     }
 
+    if constexpr (NG > 1) {
+        if (n_it < (n_all + 1) / 2) __syncthreads();  // (the barrier of the tile that the first group has more)
+        auto slot = [&](int mt, int q) { return reinterpret_cast<f32x4*>(lds) + ((w * MT + mt) * 4 + q) * 64 + lane; };
+        if (group == 1) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) *slot(mt, q4) = f32x4{dq[mt][4 * q4], dq[mt][4 * q4 + 1], dq[mt][4 * q4 + 2], dq[mt][4 * q4 + 3]};
+        }
+        __syncthreads();
+        if (group == 0) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const f32x4 other = *slot(mt, q4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dq[mt][4 * q4 + e] += other[e];
+                }
+        }
+        __syncthreads();
+    }
     constexpr int MW = MT / SPLIT;  // 32-column groups of dQ that a wave writes, from MW wk on
     if constexpr (SPLIT > 1) {
         // each of the two waves of a query hands the other the half of its sum that the other writes; the stages are
@@ -700,9 +768,12 @@ __device__ __forceinline__ void dq_block(const FusedParams p, char* smem, int bh
                     for (int r = 0; r < 4; ++r) dq[mt][4 * g + r] = dq[decltype(first)::value + mt][4 * g + r] + b[r];
                 }
         };
-        if (wk == 0) send(std::integral_constant<int, MW>{});
-        else send(std::integral_constant<int, 0>{});
+        if (group == 0) {
+            if (wk == 0) send(std::integral_constant<int, MW>{});
+            else send(std::integral_constant<int, 0>{});
+        }
         __syncthreads();
+        if (group == 1) return;
         if (wk == 0) meet(std::integral_constant<int, 0>{});
         else meet(std::integral_constant<int, MW>{});
     }
@@ -764,6 +835,32 @@ __global__ void __launch_bounds__(kThreads, D <= 128 ? 2 : 1) bwd_both_kernel(Fu
     }
 }
 
+// The same, and each half alone, with eight waves for blocks of 64 queries and of 64 keys: see eight_waves_bwd
+template <int D>
+__global__ void __launch_bounds__(2 * kThreads, 2) bwd_dkdv_eight_kernel(FusedParams p) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int key_blocks = p.order ? 2 * ((p.n + 127) / 128) : (p.n + 63) / 64;
+    int bh, j;
+    decode_block_causal(blockIdx.x, key_blocks, p.batch * p.heads, p.resident, bh, j);
+    dkdv_block<D, 2>(p, smem, bh, j);
+}
+template <int D>
+__global__ void __launch_bounds__(2 * kThreads, 2) bwd_dq_eight_kernel(FusedParams p) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    int bh, blk;
+    decode_block_causal(blockIdx.x, p.order ? 2 * ((p.n + 127) / 128) : (p.n + 63) / 64, p.batch * p.heads, p.resident, bh, blk);
+    dq_block<D, 2, true, 2>(p, smem, bh, blk);
+}
+template <int D>
+__global__ void __launch_bounds__(2 * kThreads, 2) bwd_both_eight_kernel(FusedParams pq, FusedParams pk) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int blocks = pq.order ? 2 * ((pq.n + 127) / 128) : (pq.n + 63) / 64;
+    int bh, rank;
+    decode_block_causal(blockIdx.x, 2 * blocks, pq.batch * pq.heads, pq.resident, bh, rank);
+    if (rank & 1) dq_block<D, 2, false, 2>(pq, smem, bh, rank >> 1);
+    else dkdv_block<D, 2>(pk, smem, bh, rank >> 1);
+}
+
 // Workgroups per CU of bwd_both_kernel and bwd_dkdv_kernel (their LDS and registers).
 constexpr int both_per_cu(int d) { return d == 64 ? 3 : d == 128 ? 2 : 1; }
 
@@ -782,6 +879,20 @@ inline bool side_by_side(long grid, int d, bool uneven) {
     return grid <= 256L * both_per_cu(d) * (!uneven ? 1 : d == 64 ? 6 : 4);
 }
 
+// Whether blocks of 64 queries and of 64 keys get eight waves instead of four (two groups that take a block's tiles in turn and add up at
+// the end; all the LDS of a CU at d = 128).  A block of four waves that has a CU to itself waits out every latency of its chain (1.3 us a
+// tile at d = 128); two of them on a CU take 2 us for a tile each, and eight waves as long for two tiles of one block.  So the line lies where every block has
+// a CU; under the causal rule, whose blocks differ in length, at one and a half.  Not for a few tiles, which the end of the block
+// costs more.  The rule does not look at the mask (see few_blocks) nor at whether one launch or two are made: the sums of a block keep their order.
+// `mask_form`: dQ and dK / dV share the chip; else (the weight gradient) dQ is alone.  us of the backward, four waves -> eight:
+//   full     d128 h11 n700 24.0 -> 21.6   h4 n2048 48.9 -> 41.6   h1 n8000 163 -> 127   h10 n1024 (beyond) 32 -> 44   d64 h4 n1500 27.3 -> 22.0
+//   causal   d128 h16 n700 21.9 -> 21.0   h2 n4000 72.5 -> 61.9   h14 n1024 (beyond) 29.2 -> 30.0   d64 h12 n1000 20.3 -> 18.6   h24 n600 (beyond) 16.0 -> 17.4
+//   weight gradient   full d128 h16 n1024 54.8 -> 52.8, h5 n2412 85 -> 77, d64 h12 n1500 (beyond) 56 -> 64   causal d64 h16 n1200 44.6 -> 41.8, d128 h2 n9251 275 -> 237
+inline bool eight_waves_bwd(const FusedParams& p, int bh) {
+    const long blocks = (long)((p.n + 63) / 64) * bh * (p.mask_form ? 2 : 1);
+    return p.n > 256 && blocks <= (p.causal ? 384 : 256);
+}
+
 // ------------------------------------------------------------------------------ launchers
 void launch_delta(const FusedParams& p, int d, hipStream_t stream) {
     const long lanes = (long)p.batch * p.heads * p.n * (d / 8 < 64 ? d / 8 : 64);
@@ -798,16 +909,27 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     constexpr int kv_lds = 2 * (2 * 64 * D * 2) + 2 * 64 * 64 * 2;  // two stages of Q, dO; P and dS
     const int blocks128 = (p.n + 127) / 128;
     const bool split = few_blocks(blocks128 * bh, dq_per_cu(D), p.causal && !p.mask_form);
-    const int q_lds = (split ? 5 : 4) * (64 * D * 2);  // two stages of K, V; blocks of 64 queries: and their O rows
     const long both_grid = (long)bh * (split ? 2 * (csr_ptr ? 2 * blocks128 : (p.n + 63) / 64) : 3 * blocks128);
     const bool both = p.may_join && !onepass && !dq_only && !dkdv_only && side_by_side(both_grid, D, p.causal || csr_ptr);
-    void (*const dq_fn)(FusedParams) = split ? bwd_dq_split_kernel<D> : bwd_dq_kernel<D, 1>;
-    void (*const both_fn)(FusedParams, FusedParams) = split ? bwd_both_kernel<D, 2> : bwd_both_kernel<D, 1>;
+    const bool eight = D <= 128 && split && eight_waves_bwd(p, bh);
+    const int groups = eight ? 2 : 1;
+    const int q_lds = groups * (split ? 5 : 4) * (64 * D * 2);  // two stages of K, V; blocks of 64 queries: and their O rows
+    void (*dq_fn)(FusedParams) = split ? bwd_dq_split_kernel<D> : bwd_dq_kernel<D, 1>;
+    void (*dkdv_fn)(FusedParams) = bwd_dkdv_kernel<D>;
+    void (*both_fn)(FusedParams, FusedParams) = split ? bwd_both_kernel<D, 2> : bwd_both_kernel<D, 1>;
+    if constexpr (D <= 128) {
+        if (eight) {
+            dq_fn = bwd_dq_eight_kernel<D>;
+            dkdv_fn = bwd_dkdv_eight_kernel<D>;
+            both_fn = bwd_both_eight_kernel<D>;
+        }
+    }
+    const dim3 block((unsigned)(groups * kThreads));
     hipError_t e = hipSuccess;
     if (both) {
-        e = allow_lds(both_fn, kv_lds);
+        e = allow_lds(both_fn, groups * kv_lds);
     } else if (!onepass) {
-        e = allow_lds(bwd_dkdv_kernel<D>, kv_lds);
+        e = allow_lds(dkdv_fn, groups * kv_lds);
         if (e == hipSuccess) e = allow_lds(dq_fn, q_lds);
     }
     if (e != hipSuccess) return e;
@@ -849,22 +971,22 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
         const int orders = op.order_q && blocks128 <= kOrderFusedBlocks ? 2 * masks : 0;
         const long rows = (long)bh * p.n;
         const unsigned grid = (unsigned)((split ? 2 * halves : 3 * blocks128) * bh);  // (both_grid, or a little less without orders)
-        if (p.causal && !csr_ptr) pq.resident = causal_resident((int)grid, both_per_cu(D));
+        if (p.causal && !csr_ptr) pq.resident = causal_resident((int)grid, eight ? 1 : both_per_cu(D));
         hipLaunchKernelGGL(bwd_rows_kernel<D>, dim3((unsigned)(orders + (rows + kThreads / 2 - 1) / (kThreads / 2))), dim3(kThreads), 0, stream,
                            p, op, orders);
-        hipLaunchKernelGGL(both_fn, dim3(grid), dim3(kThreads), kv_lds, stream, pq, pk);
+        hipLaunchKernelGGL(both_fn, dim3(grid), block, groups * kv_lds, stream, pq, pk);
         return hipGetLastError();
     }
     const int q_blocks = split ? halves : blocks128;
-    if (p.causal && !csr_ptr) pq.resident = causal_resident(q_blocks * bh, split ? dq_split_per_cu(D) : dq_per_cu(D));
+    if (p.causal && !csr_ptr) pq.resident = causal_resident(q_blocks * bh, eight ? 1 : split ? dq_split_per_cu(D) : dq_per_cu(D));
     // One query tile per wave and two workgroups per CU.  (QT = 2, i.e. one wave per SIMD with every
     // LDS fragment feeding two MFMAs, halves the LDS traffic but measured 20 % slower at d = 128:
     // with a single wave per SIMD the softmax arithmetic no longer overlaps another wave's MFMAs.)
     if (!dkdv_only)
-        hipLaunchKernelGGL(dq_fn, dim3((unsigned)(q_blocks * bh)), dim3(kThreads), q_lds, stream, pq);
+        hipLaunchKernelGGL(dq_fn, dim3((unsigned)(q_blocks * bh)), block, q_lds, stream, pq);
     if (dq_only) return hipGetLastError();
-    if (p.causal && !csc_ptr) pk.resident = causal_resident(halves * bh, both_per_cu(D));
-    hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3((unsigned)(halves * bh)), dim3(kThreads), kv_lds, stream, pk);
+    if (p.causal && !csc_ptr) pk.resident = causal_resident(halves * bh, eight ? 1 : both_per_cu(D));
+    hipLaunchKernelGGL(dkdv_fn, dim3((unsigned)(halves * bh)), block, groups * kv_lds, stream, pk);
     return hipGetLastError();
 }
 

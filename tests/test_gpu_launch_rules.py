@@ -4,6 +4,7 @@ of sampled heads and sampled rows of the gradients against the oracle, and ident
 import pytest
 
 from paper_2410_09397_amd import synth
+from tests.helpers import check, oracle_reference, to_dev, to_np
 from tests.test_gpu_fullsize import check_at_full_size
 
 pytestmark = pytest.mark.gpu
@@ -21,3 +22,30 @@ RULES = [
 @pytest.mark.parametrize("w", RULES, ids=lambda w: w.name)
 def test_large_calls_of_odd_length(w):
     check_at_full_size(w, w.index)
+
+
+@pytest.mark.parametrize("kind", ["full", "causal", "mask"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_blocks_of_eight_waves_at_the_edges_of_their_tiles(d, kind):
+    """Fused backward of few blocks: two groups of four waves take a block's tiles of 64 in turn, so odd and even numbers of tiles, a last
+    tile of one row, and blocks with a single tile (causal, masked) or none (masked) that the second group sits out."""
+    import numpy as np
+    from paper_2410_09397_amd import attn
+    for k, n in enumerate((257, 320, 321, 385, 448)):
+        w = synth.Workload("eight_waves_d%d_n%d_%s" % (d, n, kind), 90 + k, 1, 3, n, d, "bf16", causal=kind == "causal", sparse=kind == "mask", extra_frac=0.5)
+        print("case", w.name, flush=True)
+        inp = synth.make_inputs(w)
+        mask = None
+        if kind == "mask":
+            inp["keep"] = np.asarray(inp["keep"]).copy()
+            inp["keep"][:, 1] = inp["keep"][1, :] = False  # a column and a row without a block
+            mask = attn.BlockMask(inp["keep"], w.block, n)
+        ref = oracle_reference(w, inp)
+        Q, K, V, dO = (to_dev(inp[t], "bf16") for t in ("Q", "K", "V", "dO"))
+        O_in, LSE_in = to_dev(ref["O_in"], "bf16"), to_dev(ref["LSE_in"], "f32")
+        if mask is None:
+            grads = attn.attn_bwd(Q, K, V, O_in, dO, LSE_in, w.scale, causal=w.causal)
+        else:
+            grads = attn.attn_bwd_blocksparse(Q, K, V, O_in, dO, LSE_in, w.scale, mask)
+        for name, g, r in zip(("dQ", "dK", "dV"), grads, ref["iso"]):
+            check(w.name, name, to_np(g), r, "bf16")
