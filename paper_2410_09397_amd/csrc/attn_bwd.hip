@@ -117,6 +117,26 @@ __global__ void __launch_bounds__(kThreads) block_order_fused_kernel(OrderParams
     rank_blocks(p, blockIdx.x, first_kind + blockIdx.y, len);
 }
 
+// v = rowsum(dO o O) of a row (0 past n) by two lanes, 32 apart, in the order of the dQ kernel.
+template <int D>
+__device__ __forceinline__ float row_dot(const FusedParams& p, long base, int row, int h) {
+    float dsum = 0.f;
+    if (row < p.n) {
+        const long off = base + (long)row * p.stride_n + 8 * h;
+        bf16x8 o[D / 16], g[D / 16];
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {
+            o[ks] = *reinterpret_cast<const bf16x8*>(p.O + off + 16 * ks);
+            g[ks] = *reinterpret_cast<const bf16x8*>(p.dO + off + 16 * ks);
+        }
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dsum += (float)o[ks][e] * (float)g[ks][e];
+    }
+    return dsum + __shfl_xor(dsum, 32, 64);
+}
+
 // What the two halves of the backward need when they run side by side: v = rowsum(dO o O), and the block orders of the
 // masks (`orders` workgroups: both kinds of a mask one after the other).  Two lanes per row with the sum in the dQ kernel's order, so that the
 // bits of v do not depend on which of the two formed it.
@@ -130,22 +150,9 @@ __global__ void __launch_bounds__(kThreads) bwd_rows_kernel(FusedParams p, Order
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const long rows = (long)p.batch * p.heads * p.n;
     const long r = ((long)(blockIdx.x - orders) * (kThreads / 64) + (threadIdx.x >> 6)) * 32 + (lane & 31);
-    float dsum = 0.f;
-    if (r < rows) {
-        const int bh = (int)(r / p.n), i = (int)(r % p.n);
-        const long off = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h + (long)i * p.stride_n + 8 * h;
-        bf16x8 o[D / 16], g[D / 16];
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-            o[ks] = *reinterpret_cast<const bf16x8*>(p.O + off + 16 * ks);
-            g[ks] = *reinterpret_cast<const bf16x8*>(p.dO + off + 16 * ks);
-        }
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) dsum += (float)o[ks][e] * (float)g[ks][e];
-    }
-    dsum += __shfl_xor(dsum, 32, 64);
+    const int bh = r < rows ? (int)(r / p.n) : 0;
+    const long base = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h;
+    const float dsum = row_dot<D>(p, base, r < rows ? (int)(r - (long)bh * p.n) : p.n, h);
     if (r < rows && h == 0) p.delta[r] = dsum;
 }
 
@@ -165,7 +172,7 @@ __global__ void __launch_bounds__(kThreads) bwd_rows_kernel(FusedParams p, Order
 // fall into step; ranking phase 1 above phase 2 above the exponentials lets one of them run ahead
 // (measured: 2 % faster than without priorities, 3 % faster than with the exponentials in the middle).
 constexpr int kPrioPhase1 = 3, kPrioSoftmax = 0, kPrioPhase2 = 1;
-template <int D, int NG = 1>
+template <int D, int NG = 1, bool OWN = false>
 __device__ __forceinline__ void dkdv_block(const FusedParams& p, char* lds, int bh, int j) {
     constexpr int BR = 64, BC = 64, KS = D / 16, MT = D / 32;
     constexpr int kTileBytes = BR * D * 2;
@@ -230,7 +237,7 @@ __device__ __forceinline__ void dkdv_block(const FusedParams& p, char* lds, int 
         const int q = i0 + 32 * wx + l32;
         row_ok = q < p.n;
         lse_raw = lse_g[min(q, p.n - 1)];
-        delta_raw = delta_g[min(q, p.n - 1)];
+        if constexpr (!OWN) delta_raw = delta_g[min(q, p.n - 1)];
     };
     auto fetch = [&](int i0, int stage_off) {
         char* s = smem + stage_off;
@@ -247,6 +254,13 @@ __device__ __forceinline__ void dkdv_block(const FusedParams& p, char* lds, int 
     loader.load(p.K + base, ld, j0, p.n, smem + kStageBytes, tid);  // (every group for itself)
     loader.load(p.V + base, ld, j0, p.n, smem + kStageBytes + kTileBytes, tid);
     if (n_it > 0) fetch(i0_next, 0);
+    // OWN: v = rowsum(dO o O) of every query that these keys see, formed here (with the bits of bwd_rows_kernel) and kept behind the stages
+    float* own_delta = reinterpret_cast<float*>(lds + NG * (2 * kStageBytes + 2 * kPBytes));
+    if constexpr (OWN)
+        for (int r0 = BR * t0 + 32 * (w + 4 * group); r0 < p.n; r0 += 32 * 4 * NG) {
+            const float v = row_dot<D>(p, base, r0 + l32, h);
+            if (h == 0 && r0 + l32 < p.n) own_delta[r0 + l32] = v;
+        }
     FragOffsets<D> fo;    // Q / dO tiles
     FragOffsets<BC> fp;   // P / dS tiles
     fo.init(lane);
@@ -290,7 +304,7 @@ __device__ __forceinline__ void dkdv_block(const FusedParams& p, char* lds, int 
     // the causal bound.
     auto tile = [&](auto stage_off, int it, int i0, bool skip, auto masked) {
         const float lse_cur = row_ok ? lse_raw * kLog2e : __builtin_inff();
-        const float delta_cur = row_ok ? delta_raw : 0.f;
+        const float delta_cur = row_ok ? (OWN ? own_delta[i0 + 32 * wx + l32] : delta_raw) : 0.f;
         const int q_off = stage_off;  // Q tile; the dO tile follows it
         // The copies of the next tile go into the stage that was last read before barrier B of the
         // previous tile.  In the mask-free body they are issued one by one between the MFMAs of
@@ -861,6 +875,16 @@ __global__ void __launch_bounds__(2 * kThreads, 2) bwd_both_eight_kernel(FusedPa
     else dkdv_block<D, 2>(pk, smem, bh, rank >> 1);
 }
 
+// The whole backward of a short call in one launch: every block forms the row sums it needs (see own_rows).
+template <int D, int NG>
+__global__ void __launch_bounds__(NG * kThreads, D <= 128 ? 2 : 1) bwd_short_kernel(FusedParams p) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    int bh, rank;
+    decode_block_causal(blockIdx.x, 2 * ((p.n + 63) / 64), p.batch * p.heads, p.resident, bh, rank);
+    if (rank & 1) dq_block<D, 2, true, NG>(p, smem, bh, rank >> 1);
+    else dkdv_block<D, NG, true>(p, smem, bh, rank >> 1);
+}
+
 // Workgroups per CU of bwd_both_kernel and bwd_dkdv_kernel (their LDS and registers).
 constexpr int both_per_cu(int d) { return d == 64 ? 3 : d == 128 ? 2 : 1; }
 
@@ -878,6 +902,15 @@ constexpr int both_per_cu(int d) { return d == 64 ? 3 : d == 128 ? 2 : 1; }
 inline bool side_by_side(long grid, int d, bool uneven) {
     return grid <= 256L * both_per_cu(d) * (!uneven ? 1 : d == 64 ? 6 : 4);
 }
+
+// Whether a short call runs in one launch alone (bwd_short_kernel): every key block forms the row sums of the queries it sees again and keeps
+// them in LDS, instead of a launch in front that forms each once (3 to 4 us, and 2 us of the host).  The price grows with the rows and with
+// the blocks that share a CU, so the line lies at 256 rows (d = 64: 448) and one block per CU (d = 64: three).  Not under a block mask, whose
+// order of blocks needs the launch in front anyway.  us of the backward, two launches -> one:
+//   d64  h2 n300 11.3 -> 9.1   h8 n333 causal 11.4 -> 10.2   b4 h16 n333 causal 14.5 -> 13.7   h16 n500 (beyond) 12.3 -> 12.4
+//   d128 b4 h5 n250 causal 13.5 -> 12.5   b4 h32 n100 (beyond) 13.5 -> 15.2     d256 b4 h16 n66 16.7 -> 12.7   b2 h23 n97 causal 17.8 -> 14.2
+constexpr int kOwnRows = 448;
+inline bool own_rows(int n, int d, long grid, bool masked) { return !masked && n <= (d == 64 ? kOwnRows : 256) && grid <= (d == 64 ? 768 : 256); }
 
 // Whether blocks of 64 queries and of 64 keys get eight waves instead of four (two groups that take a block's tiles in turn and add up at
 // the end; all the LDS of a CU at d = 128).  A block of four waves that has a CU to itself waits out every latency of its chain (1.3 us a
@@ -926,6 +959,19 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     }
     const dim3 block((unsigned)(groups * kThreads));
     hipError_t e = hipSuccess;
+    if (both && split && own_rows(p.n, D, both_grid, csr_ptr != nullptr)) {
+        void (*fn)(FusedParams) = bwd_short_kernel<D, 1>;
+        if constexpr (D == 64) {
+            if (eight) fn = bwd_short_kernel<D, 2>;
+        }
+        const int kv = groups * kv_lds + kOwnRows * (int)sizeof(float), lds = kv > q_lds ? kv : q_lds;
+        e = allow_lds(fn, lds);
+        if (e != hipSuccess) return e;
+        FusedParams ps = p;
+        if (p.causal) ps.resident = causal_resident((int)both_grid, eight ? 1 : both_per_cu(D));
+        hipLaunchKernelGGL(fn, dim3((unsigned)both_grid), block, lds, stream, ps);
+        return hipGetLastError();
+    }
     if (both) {
         e = allow_lds(both_fn, groups * kv_lds);
     } else if (!onepass) {
