@@ -921,9 +921,11 @@ inline bool own_rows(int n, int d, long grid, bool masked) { return !masked && n
 //   full     d128 h11 n700 24.0 -> 21.6   h4 n2048 48.9 -> 41.6   h1 n8000 163 -> 127   h10 n1024 (beyond) 32 -> 44   d64 h4 n1500 27.3 -> 22.0
 //   causal   d128 h16 n700 21.9 -> 21.0   h2 n4000 72.5 -> 61.9   h14 n1024 (beyond) 29.2 -> 30.0   d64 h12 n1000 20.3 -> 18.6   h24 n600 (beyond) 16.0 -> 17.4
 //   weight gradient   full d128 h16 n1024 54.8 -> 52.8, h5 n2412 85 -> 77, d64 h12 n1500 (beyond) 56 -> 64   causal d64 h16 n1200 44.6 -> 41.8, d128 h2 n9251 275 -> 237
+// dQ alone under the causal rule: of 1500 and more queries up to two blocks for each CU, there being no masked call whose shorter lists lose by it (see eight_waves):
+//   causal   d64 h20 n1500 54.9 -> 53.9, h6 n5000 118 -> 107, h30 n1024 (beyond) 44.8 -> 45.3   d128 h16 n1900 85.6 -> 82.3, h4 n8192 268 -> 243, h22 n1900 (660 blocks, beyond) 98 -> 105
 inline bool eight_waves_bwd(const FusedParams& p, int bh) {
     const long blocks = (long)((p.n + 63) / 64) * bh * (p.mask_form ? 2 : 1);
-    return p.n > 256 && blocks <= (p.causal ? 384 : 256);
+    return p.n > 256 && blocks <= (!p.causal ? 256 : p.mask_form || p.n < 1500 ? 384 : 512);
 }
 
 // ------------------------------------------------------------------------------ launchers

@@ -656,7 +656,15 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
 // holds one: it wins while there is at most one for each CU, unless a row is only a few steps long.  us, four waves -> eight:
 //   d = 128  h8 n800 15.8 -> 15.9   h16 n1024 18.5 -> 16.9   h8 n2048 31.1 -> 25.8   h1 n8192 108 -> 79   h16 n2048 (beyond the line) 42 -> 48
 //   d = 64   h8 n333 7.2 -> 8.1 and b2 h12 n600 causal 9.9 -> 10.4 (too short)   h8 n1024 13.3 -> 12.0   h4 n1500 18.4 -> 16.0
-inline bool eight_waves(int blocks, int n) { return blocks <= 256 && n >= 768; }
+// Causal blocks differ in length, and a launch that holds all of them at once takes as long as its longest: there one and a half blocks per CU
+// in turn are still faster, of long sequences two.  Not where the call has a form with a block mask, whose lists are shorter and in no such
+// order (causal with half of the other blocks, d = 128 h14 n1500 19.1 -> 24.8, h4 n8192 66 -> 73), and whose bits have to be those of the
+// call without one: the weight gradient alone.  us of all of it, causal:
+//   d = 128  h16 n1500 70.4 -> 66.7   h3 n8192 219 -> 193   h4 n8192 267 -> 244   h30 n1024 (480 blocks, beyond) 65.6 -> 69.3
+//   d = 64   h20 n1024 39.2 -> 37.4   h5 n4096 86 -> 79   h8 n4000 99.6 -> 95.9   h20 n1500 (480, beyond) 55.0 -> 56.5
+inline bool eight_waves(const FusedParams& p, int blocks) {
+    return p.n >= 768 && blocks <= (!p.causal || p.mask_form ? 256 : p.n < 2560 ? 384 : 512);
+}
 
 constexpr int fwd_per_cu(int d) { return d == 64 ? 4 : d == 128 ? 2 : 1; }
 
@@ -684,7 +692,7 @@ static hipError_t launch_fwd(const FusedParams& p, const int32_t* csr_ptr, const
     const int heads = p.batch * p.heads;
     const bool split = few_blocks((p.n + 127) / 128 * heads, fwd_per_cu(D), p.causal && !p.mask_form);
     const int blocks = (split ? (p.n + 63) / 64 : (p.n + 127) / 128) * heads;
-    const bool eight = D <= 128 && split && eight_waves(blocks, p.n);
+    const bool eight = D <= 128 && split && eight_waves(p, blocks);
     void (*fn)(FusedParams);
     if constexpr (D == 256) fn = split ? fwd_pipe_kernel<D, 2> : fwd_pipe_kernel<D, 1>;
     else fn = eight ? fwd_pipe_kernel<D, 4> : split ? fwd_split_kernel<D> : fwd_kernel<D>;

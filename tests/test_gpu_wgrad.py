@@ -73,6 +73,18 @@ def test_wgrad_at_the_edges_of_row_blocks_and_chunks(d):
             assert helpers.rel_err(g[0, h], _composed_reference(inp, 0, h, 0.8, n % 2 == 0)) <= TOL
 
 
+@pytest.mark.parametrize("n,heads", [(1537, 18), (2561, 10)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_wgrad_causal_with_more_blocks_than_compute_units(d, n, heads):
+    """256 to 512 blocks of 64 queries, the last of one row: dQ with eight waves per block, from 2560 rows on the forward too."""
+    assert 384 < -(-n // 64) * heads <= 512
+    inp = synth.make_wgrad_inputs(synth.workload(3).small(batch=1, heads=heads, n=n, d=d))
+    g = _run_gpu(None, inp, 0.9, True)
+    assert np.isfinite(g).all()
+    for h in (0, heads - 1):
+        assert helpers.rel_err(g[0, h], _composed_reference(inp, 0, h, 0.9, True)) <= TOL
+
+
 def test_wgrad_is_deterministic():
     w = synth.workload(3).small(batch=1, heads=4, n=2048, d=128)
     inp = synth.make_wgrad_inputs(w)
