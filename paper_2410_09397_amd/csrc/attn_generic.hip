@@ -48,7 +48,8 @@ __global__ void __launch_bounds__(kThreads) generic_dkdv_kernel(GenericParams p)
     row_dkdv<T, row_words<T>(D), false>(p, bh, j, threadIdx.x & 63, ks[w], vs[w]);
 }
 
-void launch_generic_delta(bool is_bf16, const GenericParams& p, hipStream_t stream) {
+// delta[b, h, i] (p.O_in, p.dO, p.delta), any d
+static void launch_generic_delta(bool is_bf16, const GenericParams& p, hipStream_t stream) {
     const dim3 grid((unsigned)(((long)p.batch * p.heads * p.n + 3) / 4));
     if (is_bf16) hipLaunchKernelGGL(generic_delta_kernel<__bf16>, grid, dim3(kThreads), 0, stream, p);
     else hipLaunchKernelGGL(generic_delta_kernel<float>, grid, dim3(kThreads), 0, stream, p);

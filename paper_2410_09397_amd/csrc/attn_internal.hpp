@@ -71,8 +71,6 @@ struct GenericParams {
     int mask_stride;  // entries between the pointer arrays of consecutive (batch, head) masks; 0 = one shared mask
     float c_hi, c_lo;  // scale * log2(e) as a sum of two floats
 };
-// delta[b, h, i] of the generic path (p.O_in, p.dO, p.delta), any d
-void launch_generic_delta(bool is_bf16, const GenericParams& p, hipStream_t stream);
 hipError_t launch_generic(bool is_bf16, bool backward, const GenericParams& p, hipStream_t stream);
 
 // The same arithmetic on the matrix cores (attn_stream.hip), for the shapes that stream_takes() accepts.

@@ -16,7 +16,7 @@
 //
 // Forward + backward, each timed by itself with calls back to back, against the row-per-wave FMA kernels as they were when these
 // were written (1 TFLOP/s: both operands of every multiply-add came from memory): fp32 b1 h1 n256 d64 347 -> 25 us for the step,
-// b2 h6 n777 d80 causal 1416 + 2173 -> 20 + 61 us, bf16 b1 h8 n1500 d96 causal 4050 + 5550 -> 18 + 43 us.  What bounds them now:
+// b2 h6 n777 d80 causal 1416 + 2173 -> 20 + 58 us, bf16 b1 h8 n1500 d96 causal 4050 + 5550 -> 18 + 41 us.  What bounds them now:
 // fp32 the matrix pipe, busy for 57 % of the CUs' cycles in the long backward and 46 % in the forward; bf16 the vector
 // instructions that split f and p (6 to 9 per matrix instruction, which is busy for 19 to 30 %) and the latency of a step;
 // the shortest calls, launches.  Reading the row operands straight from global memory in MFMA order, without LDS, costs
@@ -456,21 +456,22 @@ __device__ __forceinline__ float dot_pair(bf16x8 a, bf16x8 b, float c) {
 // so there each feeds two; fp32 operands feed 32 cycles per 256 bytes.
 template <int KIND, int DP>
 constexpr int kOwned = KIND != kF32 && DP <= 128 ? 2 : 1;
-// Whether the key owners form v = rowsum(dO o O) of the streamed queries themselves (then the backward is one launch) or
-// read it (where the stages of Q, dO and O do not fit LDS together).
-template <int KIND, int DP>
-constexpr bool kOwnDelta = DP <= 192;
+// Whether the key owners can form v = rowsum(dO o O) of the streamed queries themselves (then the backward is one launch):
+// where the stages of Q, dO and O fit LDS together.  Which of the two a call takes: own_rows.
+template <int DP>
+constexpr bool kCanOwnDelta = DP <= 192;
 
 // One step's stage of a wave: K, V forward; Q, dO, O (or v) and LSE backward.
-template <int KIND, bool QUAD, int DP>
+template <int KIND, bool QUAD, int DP, bool OWN>
 __host__ __device__ constexpr int stage_lds(bool backward) {
     typedef StageLoader<KIND, QUAD, DP> L;
-    return L::kBytes * (backward && kOwnDelta<KIND, DP> ? 3 : 2) + (backward ? 512 : 0);
+    return L::kBytes * (backward && OWN ? 3 : 2) + (backward ? 512 : 0);
 }
 // Whether a workgroup can have eight waves (their stages fit LDS) instead of four; which it has is decided at launch.
-template <int KIND, bool QUAD, int DP>
+template <int KIND, bool QUAD, int DP, bool OWN>
 __host__ __device__ constexpr bool eight_waves(bool backward) {
-    return 8 * stage_lds<KIND, QUAD, DP>(backward) <= 156 * 1024;
+    if (backward && KIND != kF32 && DP == 128) return false;  // (256 registers per lane and accumulators beside them)
+    return 8 * stage_lds<KIND, QUAD, DP, OWN>(backward) <= 156 * 1024;
 }
 
 // Which (batch, head), block and role (0: queries, 1: keys) a workgroup has.  Dense lists of equal length: all of one
@@ -521,7 +522,7 @@ __global__ void __launch_bounds__(NW * 64, KIND == kF32 && DP == 32 ? (QUAD ? 8 
     const Groups groups = make_groups(p, bh, false, i0, min(p.n, i0 + 16 * XG) - 1);
 
     constexpr int C = Loader::kCopies;
-    const int wave_off = w * stage_lds<KIND, QUAD, DP>(false);
+    const int wave_off = w * stage_lds<KIND, QUAD, DP, false>(false);
     const unsigned lds = (unsigned)(size_t)(ATTN_LDS char*)smem + wave_off;
     Loader ld;
     ld.init(lane, ldb, p.d);
@@ -698,7 +699,7 @@ __global__ void __launch_bounds__(NW * 64, KIND == kF32 && DP == 32 ? (QUAD ? 8 
 
 // ----------------------------------------------------------------------------------- backward
 // dQ of 16 XG queries
-template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW>
+template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW, bool OWN>
 __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, int bh, int blk) {
     typedef Traits<KIND> TR;
     typedef typename TR::T T;
@@ -714,7 +715,7 @@ __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, in
     const Groups groups = make_groups(p, bh, false, i0, min(p.n, i0 + 16 * XG) - 1);
 
     constexpr int C = Loader::kCopies;
-    const int wave_off = w * stage_lds<KIND, QUAD, DP>(true);
+    const int wave_off = w * stage_lds<KIND, QUAD, DP, OWN>(true);
     const unsigned lds = (unsigned)(size_t)(ATTN_LDS char*)smem + wave_off;
     Loader ld;
     ld.init(lane, ldb, p.d);
@@ -835,17 +836,16 @@ __device__ __forceinline__ void stream_dq(const GenericParams& p, char* smem, in
     });
 }
 
-// dK, dV of 16 XG keys.  With kOwnDelta the row sums v of the streamed queries are formed here again (fp32: from the
+// dK, dV of 16 XG keys.  With OWN the row sums v of the streamed queries are formed here again (fp32: from the
 // fragments at hand; bf16: the diagonal of dO O^T), so that both halves of the backward run in one launch with nothing
 // between them.
-template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW>
+template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW, bool OWN>
 __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, int bh, int blk) {
     typedef Traits<KIND> TR;
     typedef typename TR::T T;
     typedef StageLoader<KIND, QUAD, DP> Loader;
     constexpr int G = TR::kG, NS = DP / TR::kChunk, kG_ = Loader::kBytes, kO = 2 * Loader::kBytes;
-    constexpr bool kOwn = kOwnDelta<KIND, DP>;
-    constexpr int kRows = stage_lds<KIND, QUAD, DP>(true) - 512;  // LSE (and v) of the step's queries
+    constexpr int kRows = stage_lds<KIND, QUAD, DP, OWN>(true) - 512;  // LSE (and v) of the step's queries
     const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, h4 = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j0 = blk * 16 * XG;
@@ -858,7 +858,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
     const Groups groups = make_groups(p, bh, true, j0, min(p.n, j0 + 16 * XG) - 1);
 
     constexpr int C = Loader::kCopies;
-    const int wave_off = w * stage_lds<KIND, QUAD, DP>(true);
+    const int wave_off = w * stage_lds<KIND, QUAD, DP, OWN>(true);
     const unsigned lds = (unsigned)(size_t)(ATTN_LDS char*)smem + wave_off;
     Loader ld;
     ld.init(lane, ldb, p.d);
@@ -875,7 +875,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
         if constexpr (G == 2) first += (lane & 16) ? qb_next[1] - qb_next[0] : 0;
         const int r = first + r16;
         const unsigned off = (unsigned)min(r, p.n - 1) * 4u;
-        if constexpr (kOwn) ld.load(O, qb_next, p.n, ldb, p.d, lds + kO, lane);
+        if constexpr (OWN) ld.load(O, qb_next, p.n, ldb, p.d, lds + kO, lane);
         else copy_to_lds<4, true>(__builtin_amdgcn_readfirstlane(lds), kRows + 256, off, delta_row);
         copy_to_lds<4, true>(__builtin_amdgcn_readfirstlane(lds), kRows, off, lse_row);
     };
@@ -920,7 +920,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
             full = full && qb[g] + 16 <= p.n && (!p.causal || qb[g] >= j0 + 16 * XG - 1);
             const f32x4 l4 = *reinterpret_cast<const f32x4*>(smem + wave_off + kRows + 64 * g + 16 * h4);
             f32x4 d4;
-            if constexpr (!kOwn) d4 = *reinterpret_cast<const f32x4*>(smem + wave_off + kRows + 256 + 64 * g + 16 * h4);
+            if constexpr (!OWN) d4 = *reinterpret_cast<const f32x4*>(smem + wave_off + kRows + 256 + 64 * g + 16 * h4);
             f32x4 diag = {0.f, 0.f, 0.f, 0.f};
             float dot = 0.f;
 #pragma unroll
@@ -928,7 +928,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
                 const typename TR::Row gr = rd.row(smem, kG_, g, s);
 #pragma unroll
                 for (int x = 0; x < XG; ++x) dp[x][g] = mma_rows(gr, vf[x][s], dp[x][g]);
-                if constexpr (kOwn) {
+                if constexpr (OWN) {
                     typename TR::Row orow = rd.row(smem, kO, g, s);
                     constexpr int kPer = 16 / sizeof(T);
                     if (TR::kChunk * (s + 1) > DP - 32 && p.d < DP) {
@@ -940,7 +940,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
                     else diag = mma_rows(orow, gr, diag);
                 }
             }
-            if constexpr (kOwn && KIND == kF32) {
+            if constexpr (OWN && KIND == kF32) {
                 dot += __shfl_xor(dot, 16, 64);
                 dot += __shfl_xor(dot, 32, 64);
             }
@@ -948,7 +948,7 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
             for (int i = 0; i < 4; ++i) {
                 lse[g][i] = l4[i];
                 // row 4 h4 + i: its sum is in every lane with that r16 (fp32), or on the diagonal (bf16)
-                if constexpr (!kOwn) dl[g][i] = d4[i];
+                if constexpr (!OWN) dl[g][i] = d4[i];
                 else if constexpr (KIND == kF32) dl[g][i] = __shfl(dot, 4 * h4 + i, 64);
                 else dl[g][i] = __shfl(diag[i], 20 * h4 + i, 64);
             }
@@ -1031,37 +1031,86 @@ __device__ __forceinline__ void stream_dkdv(const GenericParams& p, char* smem, 
                                                          const_cast<char*>(head_base<T>(p.dK, base)), ldb, j0, p.n, p.d, [&](int, int) { return scale; });
     redo_rows<XG, NW>(bad_v || bad_k, w, j0, p.n, [&](const GenericParams& p, int j) {
         float* rows = reinterpret_cast<float*>(smem) + w * 2 * DP;
-        row_dkdv<T, row_words<T>(DP), kOwn>(p, bh, j, lane, rows, rows + DP);
+        row_dkdv<T, row_words<T>(DP), kCanOwnDelta<DP>>(p, bh, j, lane, rows, rows + DP);
     });
 }
 
-// One launch for the whole backward: query blocks (dQ) and key blocks (dK, dV) side by side.
-template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW>
+// One launch for dQ, dK and dV: query blocks and key blocks side by side.
+template <int KIND, bool QUAD, int DP, int XG, int NW, bool NARROW, bool OWN>
 __global__ void __launch_bounds__(NW * 64, NW == 8 || DP <= 96 ? 2 : 1) stream_bwd_kernel(GenericParams p) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int blocks = (p.n + 16 * XG - 1) / (16 * XG);
     int bh, blk, role;
     balanced_block(blockIdx.x, blocks, p.batch * p.heads, 2, p.causal, bh, blk, role);
-    if (role) stream_dkdv<KIND, QUAD, DP, XG, NW, NARROW>(p, smem, bh, blk);
-    else stream_dq<KIND, QUAD, DP, XG, NW, NARROW>(p, smem, bh, p.causal ? blocks - 1 - blk : blk);
+    if (role) stream_dkdv<KIND, QUAD, DP, XG, NW, NARROW, OWN>(p, smem, bh, blk);
+    else stream_dq<KIND, QUAD, DP, XG, NW, NARROW, OWN>(p, smem, bh, p.causal ? blocks - 1 - blk : blk);
 }
 
-template <int KIND, bool QUAD, int DP, int NW, bool BACKWARD, bool NARROW>
+// v = rowsum(dO o O), 16 rows per wave, in front of a backward whose key owners read it (own_rows): the sums of stream_dkdv in the
+// same order, so the same bits.  Reads O and dO once; a launch of its own costs 2 to 3 us.
+template <int KIND, bool QUAD, int DP>
+__global__ void __launch_bounds__(kThreads) stream_rows_kernel(GenericParams p) {
+    typedef Traits<KIND> TR;
+    typedef typename TR::T T;
+    constexpr int NS = DP / TR::kChunk;
+    const int lane = threadIdx.x & 63, r16 = lane & 15, h4 = lane >> 4;
+    const unsigned rows = (unsigned)p.batch * p.heads * p.n, row = (blockIdx.x * (kThreads / 64) + threadIdx.x / 64) * 16 + r16;
+    const unsigned in = min(row, rows - 1), bh = in / p.n;  // rows past the end repeat the last one
+    const long first = (long)(bh / p.heads) * p.stride_b + (long)(bh % p.heads) * p.stride_h + (long)(in % p.n) * p.stride_n;
+    typename TR::Row of[NS], gf[NS];
+    load_owned<KIND, QUAD, DP>(head_base<T>(p.O_in, first), h4, p.d, of);
+    load_owned<KIND, QUAD, DP>(head_base<T>(p.dO, first), h4, p.d, gf);
+    float v = 0.f;
+    if constexpr (KIND == kF32) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) v = dot_pair(of[s], gf[s], v);
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+    } else {
+        f32x4 diag = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) diag = mma_rows(of[s], gf[s], diag);
+        v = (r16 & 2) ? ((r16 & 1) ? diag[3] : diag[2]) : ((r16 & 1) ? diag[1] : diag[0]);
+    }
+    if (row < rows && h4 == (KIND == kF32 ? 0 : r16 >> 2)) p.delta[row] = v;
+}
+
+template <int KIND, bool QUAD, int DP, int NW, bool BACKWARD, bool NARROW, bool OWN>
 hipError_t launch_waves(const GenericParams& p, dim3 grid, hipStream_t stream) {
     constexpr int XG = kOwned<KIND, DP>;
-    constexpr int stages = NW * stage_lds<KIND, QUAD, DP>(BACKWARD), red = NW * 16 * XG * (DP + 4) * (int)sizeof(float);
+    constexpr int stages = NW * stage_lds<KIND, QUAD, DP, OWN>(BACKWARD), red = NW * 16 * XG * (DP + 4) * (int)sizeof(float);
     constexpr int lds = stages > red ? stages : red;
     auto kernel = [] {
-        if constexpr (BACKWARD) return stream_bwd_kernel<KIND, QUAD, DP, XG, NW, NARROW>;
+        if constexpr (BACKWARD) return stream_bwd_kernel<KIND, QUAD, DP, XG, NW, NARROW, OWN>;
         else return stream_fwd_kernel<KIND, QUAD, DP, XG, NW, NARROW>;
     }();
     if constexpr (lds > 60 * 1024) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
-    if (BACKWARD && !kOwnDelta<KIND, DP>) launch_generic_delta(KIND != kF32, p, stream);
+    if constexpr (BACKWARD && !OWN) {
+        const long rows = (long)p.batch * p.heads * p.n;  // (below 2^28: stream_takes)
+        hipLaunchKernelGGL((stream_rows_kernel<KIND, QUAD, DP>), dim3((unsigned)((rows + kThreads / 4 - 1) / (kThreads / 4))), dim3(kThreads), 0, stream, p);
+    }
     hipLaunchKernelGGL(kernel, grid, dim3(NW * 64), lds, stream, p);
     return hipGetLastError();
+}
+
+// Whether the key owners form the row sums themselves or read those of stream_rows_kernel.  Read, a step copies two tensors instead of
+// three, so that a third or a fourth workgroup fits a CU's LDS (fp32 beyond d = 96: eight waves instead of four) and a third of its LDS
+// reads go; the price is the launch in front, 2 to 3 us with the host's share.  So the line is one of work, pairs times padded columns,
+// and narrow fp32 heads with at most one workgroup per CU gain nothing.  The sums have the same bits either way, so a masked call, whose
+// lists the host does not know, keeps its one launch; but not where the wave count goes with it.  us of the backward, one launch -> two:
+//   fp32  d32 h32 n1100 201 -> 185   d64 h8 n1100 causal 62 -> 52   d77 h6 n700 82 -> 66   d80 h12 n777 causal 60.8 -> 58   d80 h9 n900 causal 60.5 -> 59.4
+//         d128 h16 n1024 429 -> 308, h13 n300 46 -> 41   (below the lines) d64 h3 n900 causal 24.3 -> 27.7, d128 h8 n390 causal 31.3 -> 30.7
+//   bf16  d56 h8 n1100 49 -> 44   d96 h8 n1100 60 -> 53, h2 n1300 23.9 -> 23.6   d120 h8 n1100 110 -> 91   d192 h8 n1100 168 -> 125
+//         (below) d96 h20 n512 causal 21.9 -> 22.4   d120 h13 n300 causal 18.7 -> 18.9   d160 h5 n512 causal 17.6 -> 18.1
+inline bool own_rows(bool f32, int width, const GenericParams& p) {
+    const double rows = (double)p.batch * p.heads * p.n, work = rows * p.n * width * (p.causal ? 0.5 : 1.0);
+    if (f32 && width > 96) return work < 1e8;
+    if (p.csr_ptr) return true;
+    if (f32) return work < 2e8 || rows <= 16 * 128;  // (128 blocks of 16 queries and as many of keys)
+    return work < (width > 96 ? 2e8 : 3e8);
 }
 
 // A wave's step is a chain of copies, LDS reads, products and exponentials, so two waves per SIMD are wanted and short
@@ -1070,19 +1119,26 @@ hipError_t launch_waves(const GenericParams& p, dim3 grid, hipStream_t stream) {
 // 2000, 2 to 64 heads, d = 32 to 192, both types, causal and full: up to 256 workgroups 0.69 to 1.0, 257 to 512 0.81 to 1.38 (either
 // can win, by how full the second round is), 513 to 768 0.96 to 1.59, beyond 0.96 to 1.96.  Two and three stages per wave hid
 // no more than one.
-template <int KIND, bool QUAD, int DP, bool BACKWARD, bool NARROW>
+template <int KIND, bool QUAD, int DP, bool BACKWARD, bool NARROW, bool OWN>
 hipError_t run_waves(const GenericParams& p, hipStream_t stream) {
     constexpr int rows = 16 * kOwned<KIND, DP>;
     const dim3 grid((unsigned)((p.n + rows - 1) / rows * p.batch * p.heads * (BACKWARD ? 2 : 1)));
-    if constexpr (eight_waves<KIND, QUAD, DP>(BACKWARD))
-        if (grid.x <= 512) return launch_waves<KIND, QUAD, DP, 8, BACKWARD, NARROW>(p, grid, stream);
-    return launch_waves<KIND, QUAD, DP, 4, BACKWARD, NARROW>(p, grid, stream);
+    if constexpr (eight_waves<KIND, QUAD, DP, OWN>(BACKWARD))
+        if (grid.x <= 512) return launch_waves<KIND, QUAD, DP, 8, BACKWARD, NARROW, OWN>(p, grid, stream);
+    return launch_waves<KIND, QUAD, DP, 4, BACKWARD, NARROW, OWN>(p, grid, stream);
+}
+template <int KIND, bool QUAD, int DP, bool NARROW>
+hipError_t run_direction(const GenericParams& p, bool backward, hipStream_t stream) {
+    if (!backward) return run_waves<KIND, QUAD, DP, false, NARROW, false>(p, stream);
+    if constexpr (kCanOwnDelta<DP>)
+        if (own_rows(KIND == kF32, DP, p)) return run_waves<KIND, QUAD, DP, true, NARROW, true>(p, stream);
+    return run_waves<KIND, QUAD, DP, true, NARROW, false>(p, stream);
 }
 template <int KIND, bool QUAD, int DP>
 hipError_t run_stream(const GenericParams& p, bool backward, hipStream_t stream) {
     if constexpr (KIND == kF32 && DP % 64 != 0)
-        if (p.d <= DP - 16) return backward ? run_waves<KIND, QUAD, DP, true, true>(p, stream) : run_waves<KIND, QUAD, DP, false, true>(p, stream);
-    return backward ? run_waves<KIND, QUAD, DP, true, false>(p, stream) : run_waves<KIND, QUAD, DP, false, false>(p, stream);
+        if (p.d <= DP - 16) return run_direction<KIND, QUAD, DP, true>(p, backward, stream);
+    return run_direction<KIND, QUAD, DP, false>(p, backward, stream);
 }
 
 template <int KIND, bool QUAD>

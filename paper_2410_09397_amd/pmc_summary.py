@@ -22,7 +22,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COPY_BYTES = float(1 << 30)  # bytes read, and bytes written, by the calibration copy
 BWD_KERNELS = ("delta_kernel", "bwd_dkdv", "bwd_dq", "ld_scores_kernel<2", "ld_gemm_kernel<true>", "ld_gemm_wide_kernel<true>", "generic_delta",
                "generic_dq", "generic_dkdv", "block_len_kernel", "block_order_kernel", "block_order_fused_kernel", "bwd_prep_kernel", "bwd_rows_kernel", "bwd_both_kernel", "bwd_both_eight_kernel", "bwd_short_kernel",
-               "bwd_onepass_kernel", "bwd_splitd_kernel", "stream_bwd_kernel")
+               "bwd_onepass_kernel", "bwd_splitd_kernel", "stream_rows_kernel", "stream_bwd_kernel")
 
 
 def source_hash():
