@@ -806,9 +806,11 @@ constexpr int gemm_lds(bool rows) { return 3 * gemm_stage(rows); }  // three sta
 //   full    h8 n4096 346 / 716 -> 313 / 672   h8 n1000 46 / 62 -> 49 / 59   h1 n4096 98 / 102 -> 107 / 114   h16 n128 28 / 36 -> 29 / 37
 //   causal  h8 n4096 208 / 426 -> 214 / 420   h16 n1880 109 / 233 -> 108 / 227   h2 n4096 115 / 158 -> 123 / 142   h8 n1000 45 / 54 -> 47 / 57
 // d = 1024: h16 n577 58 / 106 -> 53 / 108, h8 n2000 causal 106 / 223 -> 105 / 219, h1 n3000 causal 90 / 110 -> 95 / 108
+// (d = 1024 has twice the tiles at a length, so causal ones may be half as long; the backward: h7 n1571 240 -> 198, h12 n1200 199 -> 159,
+// h5 n1300 125 -> 101, h16 n1000 131 -> 129)
 inline bool wide_products(const LargeDParams& p, unsigned tiles, bool backward) {
     if (p.d < kWide) return false;
-    return backward ? tiles > 128 && !(p.causal && p.npad < 2048) : tiles > (p.causal ? 256u : 128u);
+    return backward ? tiles > 128 && !(p.causal && p.npad * (p.d / 512) < 2048) : tiles > (p.causal ? 256u : 128u);
 }
 template <bool BACKWARD>
 static void run_gemm(const LargeDParams& p, const GradArgs& g, hipStream_t stream) {
