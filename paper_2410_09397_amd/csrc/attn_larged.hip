@@ -266,6 +266,9 @@ __global__ void __launch_bounds__(kWideThreads, 2) ld_scores_kernel(LargeDParams
     };
     if constexpr (MODE == kProbs) {
         by_mask([&](auto masked) {
+// The scaled score is rounded once, for the maximum and for its exponential, in both bodies: joined to the subtraction of e (which the
+// compiler does where no mask stands between) a score had one rounding more or less by whether its tile touches the diagonal or the end.
+#pragma clang fp contract(off)
 #pragma unroll
             for (int tm = 0; tm < 4; ++tm) {
                 const int q = q0 + 128 * wm + 32 * tm + l32;

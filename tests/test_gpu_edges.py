@@ -259,6 +259,23 @@ def test_large_d_forward_holds_the_range_of_the_values(d, causal, score):
 
 
 @pytest.mark.parametrize("d", [512, 1024])
+def test_large_d_scores_are_rounded_the_same_in_every_tile(d):
+    """The last row sees every key with and without the causal rule, but its last tile takes the body with the bound in one call and
+    the body without it in the other: the same scores, so the same bits of O and LSE."""
+    import torch
+    from paper_2410_09397_amd import attn
+    for size in (1.0, 4.0, 8.0):  # standard deviation of the scores
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(1)
+        Q, K, V = (torch.randn((1, 16384 // d, 512, d), generator=gen, device="cuda") for _ in range(3))
+        Q, K, V = ((t * f).to(torch.bfloat16) for t, f in ((Q, size), (K, 1.0), (V, 1.0)))
+        print("case rounding of scores", d, size, flush=True)
+        full, causal = (attn.attn_fwd(Q, K, V, d ** -0.5, causal=c) for c in (False, True))
+        for x, y in zip(full, causal):
+            assert torch.equal(x[:, :, -1], y[:, :, -1])
+
+
+@pytest.mark.parametrize("d", [512, 1024])
 @pytest.mark.parametrize("n", [65, 300, 1100])
 def test_large_d_forward_shows_keys_that_are_nan(d, n):
     """A chunk of 64 keys that a row sees nothing but NaN of makes the row of O NaN (not 0); rows that do not see it, and other heads,
