@@ -62,19 +62,29 @@ ATTN_HD ScoreTile score_tile(int block, int nb, int bhs, bool causal) {
 struct ProductTile {
     int which, bh, mb, nb;
 };
-// Tiles of a head follow one another on one XCD.  Under the causal rule the tiles differ in length: longest first.
+// The column tiles of a row block read the same rows of P or dS, so they follow one another on one XCD.  Under the causal rule row blocks differ
+// in length: longest first, the row blocks to the XCDs in turn (the last count * mbs * bhs % 8 of them, the shortest, tile by tile).  Dealt out tile
+// by tile where the (batch, head) pairs are no multiple of 8, every XCD read all of P.  us of the call, causal, tile by tile -> row block by row block:
+// d = 512 h9 n1571 forward 68 -> 66, backward 145 -> 104; h6 n3824 163 -> 154, 285 -> 265; d = 1024 h4 n4096 220 -> 188, 388 -> 375; h5 n1571 74 -> 71, 120 -> 111
 ATTN_HD ProductTile product_tile(int block, int count, int mbs, int nbs, int bhs, bool causal) {
     ProductTile t;
     int s = block;
     if (causal) {
-        const int xcds = (bhs & 7) == 0 ? 8 : 1, heads = bhs / xcds, xcd = s % xcds;
-        s /= xcds;
+        const int units = count * mbs * bhs, in_turn = (units & ~7) * nbs;
+        int unit;
+        if (s < in_turn) {
+            const int xcd = s & 7;
+            s >>= 3;
+            unit = (s / nbs) * 8 + xcd;
+        } else {
+            s -= in_turn;
+            unit = (units & ~7) + s / nbs;
+        }
         t.nb = s % nbs;
-        s /= nbs;
-        t.bh = (s % heads) * xcds + xcd;
-        s /= heads;
-        t.which = s % count;
-        const int rank = s / count;
+        t.bh = unit % bhs;
+        unit /= bhs;
+        t.which = unit % count;
+        const int rank = unit / count;
         t.mb = count == 3 && t.which < 2 ? rank : mbs - 1 - rank;  // keys from the first block on, queries from the last
     } else {
         const int total = count * mbs * nbs * bhs;
