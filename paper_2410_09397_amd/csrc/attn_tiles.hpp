@@ -10,6 +10,15 @@
 
 namespace attn {
 
+// Consecutive workgroups go to the 8 XCDs in turn.  The tile of a workgroup, so that each XCD gets a contiguous run of the tiles (runs that differ by
+// one at most): neighbours share their operands in the XCD's L2.  us of the call, such runs only for multiples of 8 -> always: causal, whose visible tiles
+// often are none, d = 512 h7 n2600 forward 105 -> 99, backward 168 -> 163; d = 128 in four phases h7 n3000 (546 tiles) 114 -> 109; d = 1024 h7 n1571
+// 79 -> 75, 133 -> 128; full d = 512 h5 n1571 68 -> 63, 100 -> 86; d = 1024 h6 n3824 418 -> 390, 901 -> 871.
+ATTN_HD int xcd_run(int block, int total) {
+    const int xcd = block & 7, each = total >> 3, more = total & 7;
+    return xcd * each + (xcd < more ? xcd : more) + (block >> 3);
+}
+
 // Score tiles of 256 queries x 256 keys, nb by nb of them for each of bhs (batch, head) pairs.  Under the causal rule only the tiles on and below the
 // diagonal are launched.  With all of them launched and the others ending at once, the others still had their share of the chip: a workgroup takes
 // nearly all the LDS of a CU, workgroups start in order, and one that will end at once waits for a CU while those behind it could have started.  us
@@ -19,12 +28,10 @@ ATTN_HD int score_tiles(int nb, bool causal) { return causal ? nb * (nb + 1) / 2
 struct ScoreTile {
     int bh, qb, kb;
 };
-// Consecutive workgroups go to the 8 XCDs in turn; where the count allows, each XCD gets a contiguous run of tiles.  Tiles in regions of 4 x 4, which share
-// their operands in the XCD's L2.
+// Regions of 4 x 4 tiles (full calls: where the count allows) read the fewest rows.
 ATTN_HD ScoreTile score_tile(int block, int nb, int bhs, bool causal) {
     const int per_head = score_tiles(nb, causal), total = per_head * bhs;
-    int t = block;
-    if ((total & 7) == 0) t = (t >> 3) + (t & 7) * (total >> 3);
+    const int t = xcd_run(block, total);
     ScoreTile s;
     s.bh = t / per_head;
     const int tile = t - s.bh * per_head;

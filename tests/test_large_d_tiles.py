@@ -50,6 +50,11 @@ def test_score_tiles(lib, nb, causal):
         # nothing that the causal rule hides is launched: one such workgroup holds a CU's LDS and those behind it wait
         assert not causal or (kb <= qb).all()
         assert n == bhs * (nb * (nb + 1) // 2 if causal else nb * nb)
+        # workgroups go to the 8 XCDs in turn: each has a contiguous run of the heads' tiles, as many as any other or one less
+        first = [out[x::8] for x in range(min(8, n))]
+        assert np.array_equal(np.concatenate(first), np.concatenate([out[x::8] for x in range(8)])) and max(map(len, first)) - min(map(len, first)) <= 1
+        heads = np.concatenate(first)[:, 0]
+        assert (np.diff(heads) >= 0).all()
 
 
 @pytest.mark.parametrize("count", [1, 3])
