@@ -763,16 +763,17 @@ static hipError_t set_lds(const void* fn, int bytes) {
 
 constexpr int gemm_lds(bool rows) { return 3 * gemm_stage(rows); }  // three stages of an A and a B tile (72 or 75 KB: two workgroups per CU)
 // Whether `tiles` product tiles of 256 x 256 fill the chip: with one for every other CU they are faster than 256 x 128, of which a CU holds
-// two, except where the causal rule makes them short (backward) or leaves one launch of them uneven (forward, whose tiles are a third as
-// many).  us of the forward / backward, tiles of 256 x 128 -> 256 x 256, d = 512:
-//   full    h8 n4096 346 / 716 -> 313 / 672   h8 n1000 46 / 62 -> 49 / 59   h1 n4096 98 / 102 -> 107 / 114   h16 n128 28 / 36 -> 29 / 37
-//   causal  h8 n4096 208 / 426 -> 214 / 420   h16 n1880 109 / 233 -> 108 / 227   h2 n4096 115 / 158 -> 123 / 142   h8 n1000 45 / 54 -> 47 / 57
-// d = 1024: h16 n577 58 / 106 -> 53 / 108, h8 n2000 causal 106 / 223 -> 105 / 219, h1 n3000 causal 90 / 110 -> 95 / 108
-// (d = 1024 has twice the tiles at a length, so causal ones may be half as long; the backward: h7 n1571 240 -> 198, h12 n1200 199 -> 159,
-// h5 n1300 125 -> 101, h16 n1000 131 -> 129)
+// two; under the causal rule, whose tiles differ in length, they have to be more than the CUs, and longer than one row block (backward).  us of the
+// forward / backward, tiles of 256 x 128 -> 256 x 256:
+//   full    d = 512  h8 n4096 346 / 716 -> 313 / 672   h8 n1000 46 / 62 -> 49 / 59   h1 n4096 98 / 102 -> 107 / 114   h16 n128 28 / 36 -> 29 / 37
+//   causal, forward (tiles)    d = 512  h8 n2040 (128, below) 0.95 as fast   h28 n1780 (392) 1.05   h16 n4090 (512) 1.12   d = 1024  h8 n4090 (512) 1.10
+//   causal, backward (tiles)   d = 256  h8 n2040 (192, below) 82 -> 85   h22 n3060 (792) 440 -> 419
+//     d = 512  h4 n2550 (240, below) 100 -> 100   h2 n3060 (144, below) 86 -> 95   h12 n1270 (360) 88 -> 85   h8 n2550 (480) 166 -> 156   h133 n250 (798, one block) 97 -> 102
+//     d = 1024  h2 n2040 (192, below) 87 -> 91   h10 n1000 (480) 104 -> 98   h4 n2040 (384) 111 -> 105   h6 n3060 (864) 321 -> 313
 inline bool wide_products(const LargeDParams& p, unsigned tiles, bool backward) {
     if (p.d < kWide) return false;
-    return backward ? tiles > 128 && !(p.causal && p.npad * (p.d / 512) < 2048) : tiles > (p.causal ? 256u : 128u);
+    if (!p.causal) return tiles > 128;
+    return backward ? tiles > 320 && p.npad > kWide : tiles > 256;
 }
 template <bool BACKWARD>
 static void run_gemm(const LargeDParams& p, const GradArgs& g, hipStream_t stream) {

@@ -14,6 +14,10 @@ RULES = [
     synth.Workload("wide_products_d512", 81, 1, 24, 520, 512, "bf16"),
     # the same under the causal rule (270 and 810 tiles): tiles of one to nine row blocks, the last with 2 rows
     synth.Workload("wide_products_d512_causal", 82, 1, 15, 2050, 512, "bf16", causal=True),
+    # d = 1024 under the causal rule, backward tiles of 256 x 256 in four column blocks (360 and 480), the last row block with 6 rows; heads
+    # that the 8 XCDs do and do not divide
+    synth.Workload("wide_backward_d1024_causal", 84, 1, 6, 1030, 1024, "bf16", causal=True),
+    synth.Workload("wide_backward_d1024_causal_8", 85, 1, 8, 1030, 1024, "bf16", causal=True),
     # 256 x 128 forward (72 tiles), 256 x 256 backward (216), four column tiles
     synth.Workload("wide_backward_d1024", 83, 1, 9, 300, 1024, "bf16"),
 ]
@@ -22,6 +26,31 @@ RULES = [
 @pytest.mark.parametrize("w", RULES, ids=lambda w: w.name)
 def test_large_calls_of_odd_length(w):
     check_at_full_size(w, w.index)
+
+
+@pytest.mark.parametrize("causal,heads,n", [(False, 15, 700), (True, 24, 1030), (True, 25, 1030)])
+def test_four_phases_at_d_256_with_wide_products(causal, heads, n):
+    """One column tile, 135, 360 and 375 tiles of 256 x 256, against float64.  Bound: P, dS, O and the results are rounded to bf16 (2^-9 each),
+    sums in fp32: the norm of the difference over that of the result stays below 2^-7."""
+    import torch
+    from paper_2410_09397_amd import attn
+    print("case four phases d256", causal, heads, n, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + heads)
+    Q, K, V, dO = (torch.randn((1, heads, n, 256), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    O, LSE = attn.attn_fwd(Q, K, V, 1 / 16, causal=causal)
+    grads = attn.attn_bwd(Q, K, V, O, dO, LSE, 1 / 16, causal=causal, tiling=attn.ATTN_BWD_FOUR_PHASE)
+    for h in range(heads):
+        q, k, v, g = (t[0, h].double() for t in (Q, K, V, dO))
+        s = q @ k.T / 16
+        if causal:
+            s = s.masked_fill(torch.ones(n, n, device="cuda", dtype=torch.bool).triu(1), float("-inf"))
+        P = torch.softmax(s, 1)
+        dP = g @ v.T
+        dS = P * (dP - (P * dP).sum(1, keepdim=True)) / 16
+        for name, x, ref in zip(("dQ", "dK", "dV"), grads, (dS @ k, dS.T @ q, P.T @ g)):
+            err = float((x[0, h].double() - ref).norm() / ref.norm())
+            assert err <= 2.0 ** -7, (name, h, err)
 
 
 @pytest.mark.parametrize("kind", ["full", "causal", "mask"])
