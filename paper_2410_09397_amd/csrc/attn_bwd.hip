@@ -13,6 +13,7 @@
 
 #include "attn_common.hpp"
 #include "attn_internal.hpp"
+#include "attn_rules.hpp"
 
 namespace attn {
 
@@ -903,15 +904,6 @@ inline bool side_by_side(long grid, int d, bool uneven) {
     return grid <= 256L * both_per_cu(d) * (!uneven ? 1 : d == 64 ? 6 : 4);
 }
 
-// Whether a short call runs in one launch alone (bwd_short_kernel): every key block forms the row sums of the queries it sees again and keeps
-// them in LDS, instead of a launch in front that forms each once (3 to 4 us, and 2 us of the host).  The price grows with the rows and with
-// the blocks that share a CU, so the line lies at 256 rows (d = 64: 448) and one block per CU (d = 64: three).  Not under a block mask, whose
-// order of blocks needs the launch in front anyway.  us of the backward, two launches -> one:
-//   d64  h2 n300 11.3 -> 9.1   h8 n333 causal 11.4 -> 10.2   b4 h16 n333 causal 14.5 -> 13.7   h16 n500 (beyond) 12.3 -> 12.4
-//   d128 b4 h5 n250 causal 13.5 -> 12.5   b4 h32 n100 (beyond) 13.5 -> 15.2     d256 b4 h16 n66 16.7 -> 12.7   b2 h23 n97 causal 17.8 -> 14.2
-constexpr int kOwnRows = 448;
-inline bool own_rows(int n, int d, long grid, bool masked) { return !masked && n <= (d == 64 ? kOwnRows : 256) && grid <= (d == 64 ? 768 : 256); }
-
 // Whether blocks of 64 queries and of 64 keys get eight waves instead of four (two groups that take a block's tiles in turn and add up at
 // the end; all the LDS of a CU at d = 128).  A block of four waves that has a CU to itself waits out every latency of its chain (1.3 us a
 // tile at d = 128); two of them on a CU take 2 us for a tile each, and eight waves as long for two tiles of one block.  So the line lies where every block has
@@ -961,7 +953,7 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     }
     const dim3 block((unsigned)(groups * kThreads));
     hipError_t e = hipSuccess;
-    if (both && split && own_rows(p.n, D, both_grid, csr_ptr != nullptr)) {
+    if (both && split && own_rows(p.causal != 0, p.n, D, both_grid, csr_ptr != nullptr)) {
         void (*fn)(FusedParams) = bwd_short_kernel<D, 1>;
         if constexpr (D == 64) {
             if (eight) fn = bwd_short_kernel<D, 2>;
