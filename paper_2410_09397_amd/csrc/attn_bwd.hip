@@ -904,22 +904,6 @@ inline bool side_by_side(long grid, int d, bool uneven) {
     return grid <= 256L * both_per_cu(d) * (!uneven ? 1 : d == 64 ? 6 : 4);
 }
 
-// Whether blocks of 64 queries and of 64 keys get eight waves instead of four (two groups that take a block's tiles in turn and add up at
-// the end; all the LDS of a CU at d = 128).  A block of four waves that has a CU to itself waits out every latency of its chain (1.3 us a
-// tile at d = 128); two of them on a CU take 2 us for a tile each, and eight waves as long for two tiles of one block.  So the line lies where every block has
-// a CU; under the causal rule, whose blocks differ in length, at one and a half.  Not for a few tiles, which the end of the block
-// costs more.  The rule does not look at the mask (see few_blocks) nor at whether one launch or two are made: the sums of a block keep their order.
-// `mask_form`: dQ and dK / dV share the chip; else (the weight gradient) dQ is alone.  us of the backward, four waves -> eight:
-//   full     d128 h11 n700 24.0 -> 21.6   h4 n2048 48.9 -> 41.6   h1 n8000 163 -> 127   h10 n1024 (beyond) 32 -> 44   d64 h4 n1500 27.3 -> 22.0
-//   causal   d128 h16 n700 21.9 -> 21.0   h2 n4000 72.5 -> 61.9   h14 n1024 (beyond) 29.2 -> 30.0   d64 h12 n1000 20.3 -> 18.6   h24 n600 (beyond) 16.0 -> 17.4
-//   weight gradient   full d128 h16 n1024 54.8 -> 52.8, h5 n2412 85 -> 77, d64 h12 n1500 (beyond) 56 -> 64   causal d64 h16 n1200 44.6 -> 41.8, d128 h2 n9251 275 -> 237
-// dQ alone under the causal rule: of 1500 and more queries up to two blocks for each CU, there being no masked call whose shorter lists lose by it (see eight_waves):
-//   causal   d64 h20 n1500 54.9 -> 53.9, h6 n5000 118 -> 107, h30 n1024 (beyond) 44.8 -> 45.3   d128 h16 n1900 85.6 -> 82.3, h4 n8192 268 -> 243, h22 n1900 (660 blocks, beyond) 98 -> 105
-inline bool eight_waves_bwd(const FusedParams& p, int bh) {
-    const long blocks = (long)((p.n + 63) / 64) * bh * (p.mask_form ? 2 : 1);
-    return p.n > 256 && blocks <= (!p.causal ? 256 : p.mask_form || p.n < 1500 ? 384 : 512);
-}
-
 // ------------------------------------------------------------------------------ launchers
 void launch_delta(const FusedParams& p, int d, hipStream_t stream) {
     const long lanes = (long)p.batch * p.heads * p.n * (d / 8 < 64 ? d / 8 : 64);
@@ -938,7 +922,7 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     const bool split = few_blocks(blocks128 * bh, dq_per_cu(D), p.causal && !p.mask_form);
     const long both_grid = (long)bh * (split ? 2 * (csr_ptr ? 2 * blocks128 : (p.n + 63) / 64) : 3 * blocks128);
     const bool both = p.may_join && !onepass && !dq_only && !dkdv_only && side_by_side(both_grid, D, p.causal || csr_ptr);
-    const bool eight = D <= 128 && split && eight_waves_bwd(p, bh);
+    const bool eight = D <= 128 && split && eight_waves_bwd(p.causal != 0, p.mask_form, p.n, bh);
     const int groups = eight ? 2 : 1;
     const int q_lds = groups * (split ? 5 : 4) * (64 * D * 2);  // two stages of K, V; blocks of 64 queries: and their O rows
     void (*dq_fn)(FusedParams) = split ? bwd_dq_split_kernel<D> : bwd_dq_kernel<D, 1>;
