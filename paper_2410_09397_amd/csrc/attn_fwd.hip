@@ -9,6 +9,41 @@
 
 namespace attn {
 
+// The Q rows of a wave, 32 from q0 on, as operands: through `lds`, which only this wave uses (read straight from memory every load takes
+// 16 bytes from each of 64 places), as O leaves through LDS in whole rows (fwd_finish; 8-byte pieces of 32 rows before).  us, straight -> through LDS:
+// d = 64 b4 h16 n2048 84.9 -> 82.6   d = 128 b2 h16 n1024 causal 19.9 -> 18.7, h11 n700 14.2 -> 13.3, b2 h32 n8192 causal 1086 -> 1075   d = 256 h8 n1000 29.1 -> 27.2
+// In the kernels of short calls a wave that the end of the sequence cuts reads its rows straight from memory after all, and at d = 64 and 256 writes its O
+// so: that is little to read, and under the causal rule, where the last block is the longest, the way through LDS was its whole price.  us of the forward,
+// causal, all through LDS -> those straight: d = 64 h46 n337 7.7 -> 7.5, h26 n580 9.9 -> 9.6   d = 128 h12 n721 14.3 -> 14.2, h6 n200 7.4 -> 7.2 (O straight too: 14.3)
+// d = 256 b2 h29 n284 22.7 -> 21.1, h26 n580 31.7 -> 30.4.  Not with 128 queries at d = 64, where two ways need 12 bytes of scratch, nor at d = 128, where they
+// gain nothing (h34 n2982 full 171 -> 176), nor with eight waves (d = 64 h16 n1024 11.1 -> 11.3).  Rows past n are 0, or there repeat the last row; nothing of theirs is stored.
+template <int D, int SPLIT>
+constexpr bool kCutRowsStraight = D == 256 || SPLIT == 2;
+template <int D, int SPLIT>
+constexpr bool kCutResultsStraight = kCutRowsStraight<D, SPLIT> && D != 128;
+template <int D, int SPLIT>
+__device__ __forceinline__ void load_queries(const FusedParams& p, long base, int q0, char* lds, const FragOffsets<D>& offsets, int lane,
+                                             bf16x8 (&qf)[D / 16]) {
+    const long ld = p.stride_n;
+    if (!kCutRowsStraight<D, SPLIT> || q0 + 32 <= p.n) {
+        TileLoader<D, 32, 1> rows;
+        rows.init(lane, ld);
+        if constexpr (kCutRowsStraight<D, SPLIT>) rows.load(p.Q + base + (long)q0 * ld, lds);
+        else rows.load(p.Q + base, ld, q0, p.n, lds, lane);
+        wait_direct_loads();
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) qf[ks] = offsets.frag(lds, 0, 0, ks);
+    } else {
+        const int q = q0 + (lane & 31), h = lane >> 5;
+        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {
+            qf[ks] = zero;
+            if (q < p.n) qf[ks] = *reinterpret_cast<const bf16x8*>(p.Q + base + (long)q * ld + 16 * ks + 8 * h);
+        }
+    }
+}
+
 // The end of a query block: O / l and LSE of wave (wq, wk)'s 32 queries, from w0 on.  SPLIT > 1: SPLIT waves hold a part of the keys each; of the
 // 4 MT groups of four registers of O each writes MG, from MG wk on, and hands the others theirs through LDS, whose stages are
 // free (every wave is past the last barrier of the loop).
@@ -72,6 +107,18 @@ __device__ __forceinline__ void fwd_finish(const FusedParams& p, char* smem, lon
     const float inv = l > 0.f ? 1.f / l : 0.f;
     if (h == 0 && wk == 0 && q < p.n)
         p.LSEout[(long)bh * p.n + q] = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : -__builtin_inff();
+    if constexpr (kCutResultsStraight<D, SPLIT>)
+        if (w0 + 32 > p.n) {  // (see load_queries)
+            if (q < p.n) {
+                __bf16* row = p.Oout + base + (long)q * p.stride_n;
+#pragma unroll
+                for (int g = 0; g < MG; ++g)
+                    *reinterpret_cast<u32x2*>(row + 8 * (MG * wk + g) + 4 * h) =
+                        u32x2{pack_bf16(o[g / 4][4 * (g % 4) + 0] * inv, o[g / 4][4 * (g % 4) + 1] * inv),
+                              pack_bf16(o[g / 4][4 * (g % 4) + 2] * inv, o[g / 4][4 * (g % 4) + 3] * inv)};
+            }
+            return;
+        }
     // (a wave's own rows and columns: nothing to wait for but its own writes; behind the slots of the other parts)
     typedef RowStage<8 * MG> Rows;
     constexpr int kWaves = 4 * (SPLIT > 1 ? SPLIT / 2 : 1);
@@ -140,24 +187,15 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
         loader.load(p.K + base, ld, j0, p.n, s, tid);
         loader.load(p.V + base, ld, j0, p.n, s + 2 * kTileBytes, tid);
     };
-    // The Q rows of a wave come through a piece of the second stage that only it reads (straight from memory as operands, every load takes
-    // 16 bytes from each of 64 places), and O leaves through LDS in whole rows (8-byte pieces of 32 rows before); the latency of
-    // the first tile overlaps.  Rows past n repeat the last row; nothing of theirs is stored.  us, before -> now: d = 64 b4 h16 n2048
-    // 84.9 -> 82.6   d = 128 b2 h16 n1024 causal 19.9 -> 18.7, h11 n700 14.2 -> 13.3, b2 h32 n8192 causal 1086 -> 1075   d = 256 h8 n1000 29.1 -> 27.2
+    // the latency of the first tile overlaps that of the Q rows, which come through a piece of the second stage that only this wave reads
     int j0_next = n_it > 0 ? tile_start(0) : 0;
     if (n_it > 0) fetch(j0_next, 0);
 
     const int q = i0 + 32 * wq + l32;
-    TileLoader<D, 32, 1> rows;
-    rows.init(lane, ld);
-    char* q_rows = smem + (w < 2 ? 1 : 3) * kTileBytes + (w & 1) * (32 * D * 2);
-    rows.load(p.Q + base, ld, i0 + 32 * wq, p.n, q_rows, lane);
     FragOffsets<D> lane_offsets;
     lane_offsets.init(lane);
-    wait_direct_loads();
     bf16x8 qf[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = lane_offsets.frag(q_rows, 0, 0, ks);
+    load_queries<D, SPLIT>(p, base, i0 + 32 * wq, smem + (w < 2 ? 1 : 3) * kTileBytes + (w & 1) * (32 * D * 2), lane_offsets, lane, qf);
 
     f32x16 o[MT];
 #pragma unroll
@@ -383,23 +421,17 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
     // [K stage 0][K stage 1][V stage 0][V stage 1]: every fetch of a fragment is a register plus an immediate of 16 bits
     auto fetch_k = [&](int j0, int stage) { loader.load(p.K + base, ld, j0, p.n, smem + stage * kTileBytes, tid); };
     auto fetch_v = [&](int j0, int stage) { loader.load(p.V + base, ld, j0, p.n, smem + (2 + stage) * kTileBytes, tid); };
-    // the first tiles are requested before the resident Q rows, so that the latencies overlap; those come through the places of V (see fwd_block)
+    // the first tiles are requested before the resident Q rows, so that the latencies overlap; those come through the places of V
     auto start_of = [&](int t) { return t < n_it ? tile_start(t) : 0; };
     int j[3] = {start_of(0), start_of(1), start_of(2)};  // of tiles t, t + 1, t + 2
     if (n_it > 0) fetch_k(j[0], 0);
     if (n_it > 1) fetch_k(j[1], 1);
 
     const int q = i0 + 32 * wq + l32;
-    TileLoader<D, 32, 1> rows;
-    rows.init(lane, ld);
-    char* q_rows = smem + 2 * kTileBytes + w * (32 * D * 2);
-    rows.load(p.Q + base, ld, i0 + 32 * wq, p.n, q_rows, lane);
     FragOffsets<D> lane_offsets;
     lane_offsets.init(lane);
-    wait_direct_loads();
     bf16x8 qf[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = lane_offsets.frag(q_rows, 0, 0, ks);
+    load_queries<D, SPLIT>(p, base, i0 + 32 * wq, smem + 2 * kTileBytes + w * (32 * D * 2), lane_offsets, lane, qf);
 
     f32x16 o[MT];
 #pragma unroll
