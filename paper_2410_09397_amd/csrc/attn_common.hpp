@@ -352,6 +352,14 @@ struct TileLoader {
     }
 };
 
+// Between writes to LDS and reads of the same bytes by other lanes of the wave.  The hardware takes the LDS operations of a wave in order; the compiler is
+// told here that lanes meet (by addresses alone, which differ per lane, it could move a read in front of a write).  No instruction.
+__device__ __forceinline__ void wave_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A wave's result of 32 rows x W columns of bf16 on its way to memory through LDS: accumulators hold four consecutive columns of a
 // row per lane, and stored as they are every instruction writes 8 bytes to each of 32 rows.  From here it leaves in whole rows,
 // 16 bytes per lane.  (Rows 2 W + 16 bytes apart: 16 lanes that write one column group together touch every bank once.)
@@ -367,12 +375,14 @@ struct RowStage {
     static __device__ __forceinline__ void store(const char* at, __bf16* dst, long ld, int rows, int lane, int wave = 0) {
         constexpr int kRows = 64 * WAVES / kLanes;
         const int c = lane % kLanes;
+        if constexpr (WAVES == 1) wave_exchange();  // (several waves: behind their barrier)
 #pragma unroll
         for (int r = 0; r < ROWS; r += kRows) {
             const int row = r + (64 * wave + lane) / kLanes;
             if (row < rows && (kRows <= ROWS || row < ROWS))
                 *reinterpret_cast<u32x4*>(dst + (long)row * ld + 8 * c) = *reinterpret_cast<const u32x4*>(at + row * kPitch + 16 * c);
         }
+        if constexpr (WAVES == 1) wave_exchange();  // (the next rows may come through the same place)
     }
 };
 

@@ -224,12 +224,14 @@ __global__ void __launch_bounds__(kWideThreads, 2) ld_scores_kernel(LargeDParams
         int row_lane = lane;  // formed here, not carried in registers through the products
         asm volatile("" : "+v"(row_lane));
         const int cc = row_lane & 7;
+        wave_exchange();
 #pragma unroll
         for (int r = 0; r < 32; r += 8) {
             const int row = r + (row_lane >> 3);
             const long off = ((long)bh * p.npad + q0 + 128 * wm + 32 * tm + row) * p.npad + k0 + 64 * wn + 8 * cc;
             *reinterpret_cast<u32x4*>(M + off) = *reinterpret_cast<const u32x4*>(mine + tile_off<64>(row, cc));
         }
+        wave_exchange();
     };
 
     const float* lds_lse = reinterpret_cast<const float*>(smem + kWideLds) + 128 * wm + l32;
