@@ -1097,13 +1097,18 @@ hipError_t launch_waves(const GenericParams& p, dim3 grid, hipStream_t stream) {
 }
 
 // Whether the key owners form the row sums themselves or read those of stream_rows_kernel.  Read, a step copies two tensors instead of
-// three, so that a third or a fourth workgroup fits a CU's LDS (fp32 beyond d = 96: eight waves instead of four) and a third of its LDS
-// reads go; the price is the launch in front, 2 to 3 us with the host's share.  So the line is one of work, pairs times padded columns,
-// and narrow fp32 heads with at most one workgroup per CU gain nothing.  The sums have the same bits either way, so a masked call, whose
-// lists the host does not know, keeps its one launch; but not where the wave count goes with it.  us of the backward, one launch -> two:
+// three and a third of its LDS reads go; in fp32 a third or a fourth workgroup fits a CU's LDS as well (beyond d = 96: eight waves instead of four), in
+// bf16 the registers hold the number at two.  The price is the launch in front, 2 to 3 us with the host's share.  So the line is one of work, pairs times
+// padded columns, and narrow fp32 heads with at most one workgroup per CU gain nothing.  The sums have the same bits either way, so a masked call, whose
+// lists the host does not know, keeps its one launch; but not where the wave count goes with it: fp32 beyond d = 96 goes by the pairs of the call without a
+// mask, whose bits it has to have.  us of the backward, one launch -> two:
 //   fp32  d32 h32 n1100 201 -> 185   d64 h8 n1100 causal 62 -> 52   d77 h6 n700 82 -> 66   d80 h12 n777 causal 60.8 -> 58   d80 h9 n900 causal 60.5 -> 59.4
+//         of 2e8 to 3.2e8 causal, 31 calls: 1.02 to 1.19 times as fast (d40 h6 n1100 42.6 -> 41.3, d96 h20 n500 59 -> 53); full, 27 calls: 1.0 to 1.22, but with
+//         3850 to 4030 rows, two full rounds of eight waves either way, 0.96 to 0.99 (d77 h6 n672 54.5 -> 56.8)
 //         d128 h16 n1024 429 -> 308, h13 n300 46 -> 41   (below the lines) d64 h3 n900 causal 24.3 -> 27.7, d128 h8 n390 causal 31.3 -> 30.7
+//         masked, share of the other blocks kept: d128 h16 n1024 0.05 93 -> 66, 0.3 205 -> 146, h4 n1024 0.3 68 -> 56, 0.15 55 -> 50, the diagonal alone 26.5 -> 29.0
 //   bf16  d56 h8 n1100 49 -> 44   d96 h8 n1100 60 -> 53, h2 n1300 23.9 -> 23.6   d120 h8 n1100 110 -> 91   d192 h8 n1100 168 -> 125
+//         of 3e8 to 4.3e8 up to d = 96, 29 calls: 0.99 to 1.1, but d96 b2 h15 n475 causal 27.6 -> 28.9
 //         (below) d96 h20 n512 causal 21.9 -> 22.4   d120 h13 n300 causal 18.7 -> 18.9   d160 h5 n512 causal 17.6 -> 18.1
 inline bool own_rows(bool f32, int width, const GenericParams& p) {
     const double rows = (double)p.batch * p.heads * p.n, work = rows * p.n * width * (p.causal ? 0.5 : 1.0);
