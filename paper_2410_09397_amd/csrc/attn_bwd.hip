@@ -4,7 +4,9 @@
 //             forms delta = rowsum(dO o O) (second matrix form of p, App. B.4) for those queries
 //   dK, dV  : one workgroup owns a block of 64 keys and streams query tiles
 //   calls of few blocks run both kinds of blocks side by side in one launch (bwd_both_kernel), with delta from a small
-//   launch in front (bwd_rows_kernel); delta_kernel serves the large-d path
+//   launch in front (bwd_rows_kernel), short ones alone, with delta formed in every block (bwd_short_kernel); blocks that
+//   have a CU to themselves get eight waves, two groups that take the tiles in turn (bwd_*_eight_kernel); the rules are in
+//   attn_rules.hpp and attn_common.hpp.  delta_kernel serves the large-d path
 // Per tile pair this is the inner body of the paper's large-cache phase-2 algorithm (App. D):
 // q = dO h^T, A = S A_2^T, f = exp(A) / l, p = f o q - diag(v) f, followed by the three
 // products that use f and p.  The resident operand is the owned block, so dK/dV (resp. dQ)
@@ -876,7 +878,8 @@ __global__ void __launch_bounds__(2 * kThreads, 2) bwd_both_eight_kernel(FusedPa
     else dkdv_block<D, 2>(pk, smem, bh, rank >> 1);
 }
 
-// The whole backward of a short call in one launch: every block forms the row sums it needs (see own_rows).
+// The whole backward of a short call in one launch: every block forms the row sums it needs (see own_rows; the query blocks leave theirs in the
+// workspace as they do for bwd_dkdv_kernel, though nothing reads them here).
 template <int D, int NG>
 __global__ void __launch_bounds__(NG * kThreads, D <= 128 ? 2 : 1) bwd_short_kernel(FusedParams p) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -946,7 +949,7 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
         e = allow_lds(fn, lds);
         if (e != hipSuccess) return e;
         FusedParams ps = p;
-        if (p.causal) ps.resident = causal_resident((int)both_grid, eight ? 1 : both_per_cu(D));
+        if (p.causal) ps.resident = causal_resident((int)both_grid, D == 64 && !eight ? both_per_cu(D) : 1);
         hipLaunchKernelGGL(fn, dim3((unsigned)both_grid), block, lds, stream, ps);
         return hipGetLastError();
     }
