@@ -12,25 +12,35 @@ namespace attn {
 // The Q rows of a wave, 32 from q0 on, as operands: through `lds`, which only this wave uses (read straight from memory every load takes
 // 16 bytes from each of 64 places), as O leaves through LDS in whole rows (fwd_finish; 8-byte pieces of 32 rows before).  us, straight -> through LDS:
 // d = 64 b4 h16 n2048 84.9 -> 82.6   d = 128 b2 h16 n1024 causal 19.9 -> 18.7, h11 n700 14.2 -> 13.3, b2 h32 n8192 causal 1086 -> 1075   d = 256 h8 n1000 29.1 -> 27.2
-// In the kernels of short calls a wave that the end of the sequence cuts reads its rows straight from memory after all, and at d = 64 and 256 writes its O
-// so: that is little to read, and under the causal rule, where the last block is the longest, the way through LDS was its whole price.  us of the forward,
-// causal, all through LDS -> those straight: d = 64 h46 n337 7.7 -> 7.5, h26 n580 9.9 -> 9.6   d = 128 h12 n721 14.3 -> 14.2, h6 n200 7.4 -> 7.2 (O straight too: 14.3)
-// d = 256 b2 h29 n284 22.7 -> 21.1, h26 n580 31.7 -> 30.4.  Not with 128 queries at d = 64, where two ways need 12 bytes of scratch, nor at d = 128, where they
-// gain nothing (h34 n2982 full 171 -> 176), nor with eight waves (d = 64 h16 n1024 11.1 -> 11.3).  Rows past n are 0, or there repeat the last row; nothing of theirs is stored.
+// The way through LDS is 0.3 us in front of the first tile and behind the last, which a causal call of few blocks shows where its last block, the longest, has
+// few rows to read and write.  So in the kernels of short calls
+//   d = 64 (64 queries) and 256: a wave that the end of the sequence cuts reads its rows straight from memory and writes its O so (kCutRowsStraight; rows past
+//     n are 0 then, else they repeat the last row; nothing of theirs is stored).  us, causal, all through LDS -> those straight: d = 64 h46 n337 7.7 -> 7.5,
+//     h26 n580 9.9 -> 9.6 (full h64 n512 9.6 -> 9.7)   d = 256 b2 h29 n284 22.7 -> 21.1, h26 n580 31.7 -> 30.4.  With 128 queries at d = 64 the two ways need 12 bytes of scratch.
+//   d = 128 (64 queries): the Q rows are requested in front of the first tile, not behind it, and read while it is on its way (kQueriesFirst).  us, behind -> in
+//     front: causal h46 n337 10.2 -> 10.0, h58 n284 9.4 -> 9.1, h12 n721 14.3 -> 14.2, h16 n1900 29.6 -> 29.5; full h6 n200 7.4 -> 7.3, h30 n460 14.3 -> 14.5.  (Cut rows straight
+//     there: h16 n1900 30.5 -> 30.7; with 128 queries h34 n2982 full 171 -> 176.)
 template <int D, int SPLIT>
-constexpr bool kCutRowsStraight = D == 256 || SPLIT == 2;
+constexpr bool kCutRowsStraight = D == 256 || (D == 64 && SPLIT == 2);
 template <int D, int SPLIT>
-constexpr bool kCutResultsStraight = kCutRowsStraight<D, SPLIT> && D != 128;
-template <int D, int SPLIT>
+constexpr bool kQueriesFirst = D == 128 && SPLIT == 2;
+// first_tile: requests the copies of the first tile (kCopies of them, or none); called here if kQueriesFirst
+template <int D, int SPLIT, int kCopies, typename FirstTile>
 __device__ __forceinline__ void load_queries(const FusedParams& p, long base, int q0, char* lds, const FragOffsets<D>& offsets, int lane,
-                                             bf16x8 (&qf)[D / 16]) {
+                                             bf16x8 (&qf)[D / 16], FirstTile first_tile) {
     const long ld = p.stride_n;
     if (!kCutRowsStraight<D, SPLIT> || q0 + 32 <= p.n) {
         TileLoader<D, 32, 1> rows;
         rows.init(lane, ld);
         if constexpr (kCutRowsStraight<D, SPLIT>) rows.load(p.Q + base + (long)q0 * ld, lds);
         else rows.load(p.Q + base, ld, q0, p.n, lds, lane);
-        wait_direct_loads();
+        if constexpr (kQueriesFirst<D, SPLIT>) {
+            first_tile();
+            // (a block without a tile has no use for its queries; what is still on its way to LDS is waited for before the next barrier)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kCopies) : "memory");
+        } else {
+            wait_direct_loads();
+        }
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks) qf[ks] = offsets.frag(lds, 0, 0, ks);
     } else {
@@ -107,7 +117,7 @@ __device__ __forceinline__ void fwd_finish(const FusedParams& p, char* smem, lon
     const float inv = l > 0.f ? 1.f / l : 0.f;
     if (h == 0 && wk == 0 && q < p.n)
         p.LSEout[(long)bh * p.n + q] = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : -__builtin_inff();
-    if constexpr (kCutResultsStraight<D, SPLIT>)
+    if constexpr (kCutRowsStraight<D, SPLIT>)
         if (w0 + 32 > p.n) {  // (see load_queries)
             if (q < p.n) {
                 __bf16* row = p.Oout + base + (long)q * p.stride_n;
@@ -187,15 +197,19 @@ __device__ __forceinline__ void fwd_block(const FusedParams p, char* smem) {
         loader.load(p.K + base, ld, j0, p.n, s, tid);
         loader.load(p.V + base, ld, j0, p.n, s + 2 * kTileBytes, tid);
     };
-    // the latency of the first tile overlaps that of the Q rows, which come through a piece of the second stage that only this wave reads
+    // the Q rows come through a piece of the second stage that only this wave reads; their latency and that of the first tile overlap
     int j0_next = n_it > 0 ? tile_start(0) : 0;
-    if (n_it > 0) fetch(j0_next, 0);
+    auto first_tile = [&] {
+        if (n_it > 0) fetch(j0_next, 0);
+    };
+    if constexpr (!kQueriesFirst<D, SPLIT>) first_tile();
 
     const int q = i0 + 32 * wq + l32;
     FragOffsets<D> lane_offsets;
     lane_offsets.init(lane);
     bf16x8 qf[KS];
-    load_queries<D, SPLIT>(p, base, i0 + 32 * wq, smem + (w < 2 ? 1 : 3) * kTileBytes + (w & 1) * (32 * D * 2), lane_offsets, lane, qf);
+    load_queries<D, SPLIT, 2 * TileLoader<D, BC>::kInst>(p, base, i0 + 32 * wq, smem + (w < 2 ? 1 : 3) * kTileBytes + (w & 1) * (32 * D * 2), lane_offsets, lane, qf,
+                                                         first_tile);
 
     f32x16 o[MT];
 #pragma unroll
@@ -431,7 +445,7 @@ __device__ __forceinline__ void fwd_pipe(const FusedParams p, char* smem) {
     FragOffsets<D> lane_offsets;
     lane_offsets.init(lane);
     bf16x8 qf[KS];
-    load_queries<D, SPLIT>(p, base, i0 + 32 * wq, smem + 2 * kTileBytes + w * (32 * D * 2), lane_offsets, lane, qf);
+    load_queries<D, SPLIT, 0>(p, base, i0 + 32 * wq, smem + 2 * kTileBytes + w * (32 * D * 2), lane_offsets, lane, qf, [] {});
 
     f32x16 o[MT];
 #pragma unroll
