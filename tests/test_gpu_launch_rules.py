@@ -80,15 +80,51 @@ def test_blocks_of_eight_waves_at_the_edges_of_their_tiles(d, kind):
             check(w.name, name, to_np(g), r, "bf16")
 
 
-# fp32 arithmetic with the row sums formed in front (past the lines of work that the launch draws, under the causal rule too, where a call counts
-# for half), at lengths that end inside a tile and at padded head dimensions; 16-byte and 4-byte rows in fp32
-ROWS_IN_FRONT = [("f32", 33, 8, 901), ("f32", 80, 4, 1031), ("f32", 77, 4, 1031), ("f32", 128, 6, 517), ("f32", 115, 14, 401),
-                 ("bf16", 40, 10, 1001), ("bf16", 96, 6, 1031), ("bf16", 120, 4, 901), ("bf16", 136, 4, 805), ("bf16", 192, 4, 750)]
+# fp32 arithmetic with the row sums formed in front (past the lines of work that the launch draws), at lengths that end inside a tile and at
+# padded head dimensions; 16-byte and 4-byte rows in fp32
+ROWS_IN_FRONT = [("f32", 33, 4, 901), ("f32", 80, 2, 1031), ("f32", 77, 2, 1031), ("f32", 128, 3, 517), ("f32", 115, 7, 401),
+                 ("bf16", 40, 5, 1001), ("bf16", 96, 3, 1031), ("bf16", 120, 2, 901), ("bf16", 136, 2, 805), ("bf16", 192, 2, 750)]
+
+
+@pytest.mark.parametrize("dtype,d,heads,n", ROWS_IN_FRONT)
+def test_row_sums_in_front_against_the_oracle_and_the_masked_call(dtype, d, heads, n):
+    """Against the oracle, and bit for bit against the call with a mask that keeps every block: up to d = 96 (fp32) and everywhere in bf16 that
+    one forms the row sums inside.  Then the same with a NaN and an infinite key under the causal rule, whose rows are redone."""
+    import numpy as np
+    import torch
+    from paper_2410_09397_amd import attn
+    width = -(-d // 32) * 32
+    assert heads * n * n * width >= (1e8 if dtype == "f32" and d > 96 else 2e8 if dtype == "f32" or d > 96 else 3e8)
+    w = synth.Workload("rows_in_front_%s_d%d" % (dtype, d), 95, 1, heads, n, d, dtype)
+    inp = synth.make_inputs(w)
+    ref = oracle_reference(w, inp)
+    Q, K, V, dO = (to_dev(inp[t], dtype) for t in ("Q", "K", "V", "dO"))
+    O, LSE = to_dev(ref["O_in"], dtype), to_dev(ref["LSE_in"], "f32")
+    grads = attn.attn_bwd(Q, K, V, O, dO, LSE, w.scale)
+    for name, g, r in zip(("dQ", "dK", "dV"), grads, ref["iso"]):
+        check(w.name, name, to_np(g), r, dtype)
+    nblk = -(-n // 32)
+    full, lower = np.ones((nblk, nblk), np.uint8), np.tril(np.ones((nblk, nblk), np.uint8))
+    for g, m in zip(grads, attn.attn_bwd_blocksparse(Q, K, V, O, dO, LSE, w.scale, attn.BlockMask(full, 32, n))):
+        assert torch.equal(g, m)
+    K[0, 0, n - 40, 1], V[0, heads - 1, n // 2, d - 1] = float("nan"), float("inf")
+    O, LSE = attn.attn_fwd(Q, K, V, w.scale, causal=True)
+    causal = attn.attn_bwd(Q, K, V, O, dO, LSE, w.scale, causal=True)
+    masked = attn.attn_bwd_blocksparse(Q, K, V, O, dO, LSE, w.scale, attn.BlockMask(lower, 32, n), causal=True)
+    seen = torch.isfinite(causal[0][0, 0, : n - 40])
+    assert seen.all()  # the queries before the NaN key do not see it
+    for g, m in zip(causal[1:], masked[1:]):  # (redone rows of dQ add the keys of a list of blocks of 32 in another order)
+        assert torch.equal(torch.isnan(g), torch.isnan(m)) and torch.equal(g.nan_to_num(0.0), m.nan_to_num(0.0))
+
+
+# the same at twice the work, past the lines under the causal rule too, where a call counts for half
+CAUSAL_ROWS_IN_FRONT = [("f32", 33, 8, 901), ("f32", 80, 4, 1031), ("f32", 77, 4, 1031), ("f32", 128, 6, 517), ("f32", 115, 14, 401),
+                        ("bf16", 40, 10, 1001), ("bf16", 96, 6, 1031), ("bf16", 120, 4, 901), ("bf16", 136, 4, 805), ("bf16", 192, 4, 750)]
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("dtype,d,heads,n", ROWS_IN_FRONT)
-def test_row_sums_in_front_against_the_oracle_and_the_masked_call(dtype, d, heads, n, causal):
+@pytest.mark.parametrize("dtype,d,heads,n", CAUSAL_ROWS_IN_FRONT)
+def test_row_sums_in_front_of_causal_calls_and_of_keys_that_are_not_finite(dtype, d, heads, n, causal):
     """Against the oracle, and bit for bit against the call with a mask that keeps every block (causal: every one below the diagonal): up to d = 96
     (fp32) and everywhere in bf16 that one forms the row sums inside.  Then the same with a NaN and an infinite key, whose rows are redone."""
     import numpy as np
@@ -96,7 +132,7 @@ def test_row_sums_in_front_against_the_oracle_and_the_masked_call(dtype, d, head
     from paper_2410_09397_amd import attn
     work = heads * n * n * (-(-d // 32) * 32) * (0.5 if causal else 1.0)
     assert work >= (1e8 if dtype == "f32" and d > 96 else 2e8 if dtype == "f32" or d > 96 else 3e8) and heads * n > 2048
-    w = synth.Workload("rows_in_front_%s_d%d%s" % (dtype, d, "_causal" if causal else ""), 95, 1, heads, n, d, dtype, causal=causal)
+    w = synth.Workload("rows_in_front_twice_%s_d%d%s" % (dtype, d, "_causal" if causal else ""), 95, 1, heads, n, d, dtype, causal=causal)
     print("case", w.name, flush=True)
     inp = synth.make_inputs(w)
     ref = oracle_reference(w, inp)
