@@ -20,6 +20,8 @@
  *   - Every tensor pointer is DEVICE memory owned by the caller.  Q, K, V, O, dO, dQ, dK, dV are
  *     [batch, heads, n, d] with element strides (stride_b, stride_h, stride_n, 1), the same for
  *     all of them; LSE is contiguous [batch, heads, n] float.  Outputs are overwritten.
+ *     Gradients do not overlap what their call reads, but for one: with ATTN_BF16, d in {64, 128, 256, 512, 1024} and ATTN_BWD_AUTO one
+ *     of dQ, dK and dV may have the memory of O, whose rows are read before they are written.
  *   - All work is enqueued on `stream` (a hipStream_t passed as void*, NULL = default stream);
  *     calls return without synchronising.  The library allocates no device memory and keeps no
  *     state between calls (attn_bwd_noalloc alone keeps the device address of its scratch array,

@@ -940,7 +940,9 @@ static hipError_t launch_bwd(const FusedParams& p, const int32_t* csr_ptr, const
     }
     const dim3 block((unsigned)(groups * kThreads));
     hipError_t e = hipSuccess;
-    if (both && split && own_rows(p.causal != 0, p.n, D, both_grid, csr_ptr != nullptr)) {
+    // (a gradient that takes the place of O: key blocks of the short kernel would read O beside the blocks that write it)
+    const bool o_stays = p.O != p.dQ && p.O != p.dK && p.O != p.dV;
+    if (both && split && o_stays && own_rows(p.causal != 0, p.n, D, both_grid, csr_ptr != nullptr)) {
         void (*fn)(FusedParams) = bwd_short_kernel<D, 1>;
         if constexpr (D == 64) {
             if (eight) fn = bwd_short_kernel<D, 2>;

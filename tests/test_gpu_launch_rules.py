@@ -157,3 +157,25 @@ def test_row_sums_in_front_of_causal_calls_and_of_keys_that_are_not_finite(dtype
         assert torch.isfinite(grads[0][0, 0, : n - 40]).all()  # the queries before the NaN key do not see it
     for g, m in zip(grads[1:], masked[1:]):  # (redone rows of dQ add the keys of a list of blocks of 32 in another order)
         assert torch.equal(torch.isnan(g), torch.isnan(m)) and torch.equal(g.nan_to_num(0.0), m.nan_to_num(0.0))
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,heads,n", [(64, 3, 333), (64, 5, 200), (128, 3, 250), (256, 4, 97), (512, 2, 130)])
+def test_a_gradient_in_the_place_of_o(d, heads, n, causal):
+    """The memory of O may be that of a gradient: the same bits as with four buffers.  (Calls that otherwise run in one launch, whose key blocks
+    read O while others write gradients, and one of the four phases.)"""
+    import torch
+    from paper_2410_09397_amd import attn
+    print("case gradient in the place of O", d, heads, n, causal, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    Q, K, V, dO = (torch.randn((1, heads, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    O, LSE = attn.attn_fwd(Q, K, V, d ** -0.5, causal=causal)
+    ref = attn.attn_bwd(Q, K, V, O, dO, LSE, d ** -0.5, causal=causal)
+    for which in range(3):
+        o = O.clone()
+        out = [torch.empty_like(O) for _ in range(3)]
+        out[which] = o
+        attn.attn_bwd(Q, K, V, o, dO, LSE, d ** -0.5, causal=causal, out=tuple(out))
+        for x, y in zip(out, ref):
+            assert torch.equal(x, y)
